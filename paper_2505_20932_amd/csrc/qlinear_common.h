@@ -261,6 +261,11 @@ cwac_status launch_fast_conv(FwdParams p, int out_kind, bool int_only, int shape
 // Same kernel with the statistics epilogue; additionally requires n % 4 == 0, ld_full % 4 == 0
 // and a 16-byte aligned y_full.  p.partial receives ceil(m / 256) row groups.  waves: 8 (0) or 4.
 cwac_status launch_fast_stats(FwdParams p, int waves, hipStream_t st);
+// Small-problem kernel (qlinear_splitk.hip): any m, n and k % 16 == 0 with fast_pitch_ok(ldx, ldw); every output kind
+// but kOutStats, p.code_table set for kOutTable.
+cwac_status launch_splitk(const FwdParams &p, int out_kind, bool int_only, hipStream_t st);
+// The tile it takes, 0 where the tile kernels are faster.
+int splitk_tile(int64_t m, int n, int k);
 constexpr int kFastTile = 256;
 constexpr int kFastKStep = 128;
 

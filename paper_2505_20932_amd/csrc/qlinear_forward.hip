@@ -252,10 +252,19 @@ static int choose_forward(int64_t m, int n, int k, int64_t ldx, int64_t ldw, int
   return fast ? CWAC_KERNEL_DIRECT_LDS : tile;
 }
 
+// Small problems: where the automatic choice is the 64 x 64 tile, the kernel that splits K over the wavefronts of a
+// workgroup takes the layer if its own rule (splitk_tile) says it is the faster one.  (Its name towards callers is that of
+// the tile kernel it stands in for; CWAC_KERNEL_GENERIC_64 forces that one.)
+static bool splitk_ok(int64_t m, int n, int k, int64_t ldx, int64_t ldw) {
+  return fast_pitch_ok(ldx, ldw) && splitk_tile(m, n, k) != 0;
+}
+
 static cwac_status dispatch_forward(const FwdParams &p, int out_kind, bool int_only, const Tune &tune,
                                     hipStream_t st) {
   const int choice = choose_forward(p.m, p.n, p.k, p.ldx, p.ldw, out_kind, tune);
   if (choice == CWAC_KERNEL_DIRECT_LDS) return launch_fast(p, out_kind, int_only, tune, st);
+  if (choice == 64 && tune.kernel == CWAC_KERNEL_AUTO && splitk_ok(p.m, p.n, p.k, p.ldx, p.ldw))
+    return launch_splitk(p, out_kind, int_only, st);
   if (choice == 256) return launch_tile<256, 256, 128, 2, 2>(p, out_kind, int_only, st);
   if (choice == 128) return launch_tile<128, 128, 128, 2, 2>(p, out_kind, int_only, st);
   return launch_tile<64, 64, 128, 2, 2>(p, out_kind, int_only, st);
@@ -340,7 +349,8 @@ extern "C" cwac_status qlinear_cwac_forward_table_ex(const int8_t *x_q, int64_t 
       (ldo % 16) != 0 || !aligned(table, 4))
     return CWAC_E_ALIGN;
   // Where the plain forward would take the direct-to-LDS kernel in one of its two large tiles, the table
-  // is applied in that kernel's epilogue; elsewhere the forward is followed by a lookup pass in place.
+  // is applied in that kernel's epilogue, and likewise in the small-problem kernel's; elsewhere the forward is followed
+  // by a lookup pass in place.
   const int64_t t256 = ceil_div(m, 256) * ceil_div(n, 256), t_half = ceil_div(m, 128) * ceil_div(n, 256);
   const bool fused_ok = m >= kFastTile && n >= kFastTile && (k % 64) == 0 && fast_pitch_ok(ldx, ldw);
   bool fused = fused_ok && !fast_prefers_quarter_tile(m, n);
@@ -348,12 +358,6 @@ extern "C" cwac_status qlinear_cwac_forward_table_ex(const int8_t *x_q, int64_t 
   // the caller's override: the direct-to-LDS kernel means the fused form where its shape constraints
   // hold, a generic tile means two passes
   if (tune.kernel != CWAC_KERNEL_AUTO) fused = fused_ok && tune.kernel == CWAC_KERNEL_DIRECT_LDS;
-  if (!fused) {
-    const cwac_status st = qlinear_cwac_forward_ex(x_q, ldx, w_q, ldw, m, n, k, qp, mult, offset, nullptr, nullptr,
-                                                   CWAC_OUT_INT8, out, ldo, tuning, stream);
-    if (st != CWAC_OK) return st;
-    return vit_table_lookup(out, ldo, table, out, ldo, m, n, stream);
-  }
   FwdParams p = {};
   p.x = x_q; p.w = w_q; p.ldx = ldx; p.ldw = ldw; p.ldo = ldo;
   p.m = m; p.n = n; p.k = k;
@@ -362,6 +366,15 @@ extern "C" cwac_status qlinear_cwac_forward_table_ex(const int8_t *x_q, int64_t 
   p.lo = (float)(qp->qmin - qp->z_r);
   p.hi = (float)(qp->qmax - qp->z_r);
   p.code_table = table;
+  if (!fused) {
+    if (tune.kernel == CWAC_KERNEL_AUTO && splitk_ok(m, n, k, ldx, ldw) &&
+        choose_forward(m, n, k, ldx, ldw, CWAC_OUT_INT8, tune) == 64)
+      return launch_splitk(p, kOutTable, true, as_stream(stream));
+    const cwac_status st = qlinear_cwac_forward_ex(x_q, ldx, w_q, ldw, m, n, k, qp, mult, offset, nullptr, nullptr,
+                                                   CWAC_OUT_INT8, out, ldo, tuning, stream);
+    if (st != CWAC_OK) return st;
+    return vit_table_lookup(out, ldo, table, out, ldo, m, n, stream);
+  }
   return launch_fast_table(p, tune.shape, tune.persist_workgroups, tune.persist_loaders, as_stream(stream));
 }
 
