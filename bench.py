@@ -604,7 +604,7 @@ def weight_only_int4(P, synth, torch, cfg: int, dev: str, steps: int, cpu_rows: 
                    "its weights from HBM",
         "roofline": {"bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(gbs / HBM_PEAK_GBS, 4), "traffic": None,
-                     "kernel": "w4a16_small_m_kernel (fp16 out, fused CWAC epilogue)",
+                     "kernel": "w4a16_stream_kernel (fp16 out, fused CWAC epilogue)",
                      "bytes_per_pass": small_bytes}}
     del reps
     if cpu_rows > 0:
@@ -1519,7 +1519,7 @@ def small_batch_sweep(P, synth, torch, dev: str):
     wbytes = n * k // 2 + n * (k // 128) * 4
     out.append({"n": n, "k": k, "weight_bytes": wbytes, "copies": 2,
                 "us": {f"m={sm}": {"auto": round(us, 1), "auto_gbs": round(wbytes / us / 1e3, 1)}}})
-    return {"small_batch_sweep": "w4a16_small_m_kernel, microseconds per launch from a HIP graph, weights from HBM; "
+    return {"small_batch_sweep": "w4a16_stream_kernel, microseconds per launch from a HIP graph, weights from HBM; "
                                  "columns: the dispatcher's choice, then <wavefronts per workgroup>w_d<ring depth> (up to 32 tokens) or "
                                  "the tiled kernel with tile<tokens per tile> (above)",
             "layers": out}

@@ -592,7 +592,7 @@ typedef struct cwac_tuning {
   int32_t w4_small_waves; /* ... its weight-streaming kernel (small batches): 0 | 4 | 8 wavefronts per workgroup */
   int32_t persist_workgroups; /* CWAC_SHAPE_256_PERSIST: 0 = one workgroup per compute unit; n > 0 = at most n
                                  (each then walks more tiles; leaves compute units to concurrent work) */
-  int32_t w4_small_depth; /* ... and its ring depth: 0 | 2 | 3 | 4 groups of 128 input channels in flight per
+  int32_t w4_small_depth; /* ... and its ring depth: 0 | 2 | 3 | 4 units of 64 input channels in flight per
                              wavefront (a depth whose rings do not fit the LDS is lowered to one that does) */
   int32_t persist_loaders; /* CWAC_SHAPE_256_PERSIST: how many of the eight wavefronts issue the panel loads:
                               0 (= 4 from k = 4096, else 8) | 4 | 8 */

@@ -21,11 +21,11 @@
 //   * Epilogue in registers: acc * mult[n] + fbias[n] (two fp32 operations), conversion to
 //     binary16, transposition through a wave-private LDS slab, whole 128-byte line stores.
 // The same kernel with 128-token tiles (two token blocks per wavefront) serves batches whose
-// 128-token tiles fit the chip in one round; small batches (a decoding step, and up to 256
-// tokens while passes of 32 rows are estimated to be cheaper) take the weight-streaming kernel
-// further down.
+// 128-token tiles fit the chip in one round; small batches (a decoding step, and up to several hundred tokens
+// while its estimate is the lower one) take the weight-streaming kernel further down.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
 
 #include "qlinear_common.h"
 
@@ -517,221 +517,311 @@ cwac_status launch_w4(const W4Params &p, hipStream_t st) {
 }
 
 // ------------------------------------------------------------------------------------------
-// Small batches (32 tokens per launch: the decode step of an LLM).  The layer is then bound by the
-// stream of 4-bit weights, not by the matrix cores: one workgroup of NW (4 or 8) wavefronts owns 32
-// output channels (one row of 1 KiB blocks of the packed layout) over the whole of K, each wavefront
-// a contiguous share of the groups.  Neither operand passes through registers on its way in: every
-// wavefront owns a ring of D slots in LDS - per group 2 KiB of codes, the 32 scale / zero-point
-// words and the group's block of activations (MP rows x 256 bytes, MP = m rounded up to 8, 16 or
-// 32) - that global_load_lds fills D groups ahead of the arithmetic.  The activations are fetched
-// four rows per instruction (whole 256-byte row pieces: a lane-per-row register load would touch 32
-// cache lines per instruction, which bounded the kernel by the L1's tag rate), with the chunk
-// position XOR (row & 15) applied on the global-address side so that the MFMA operand reads
-// (lane = token row) are free of bank conflicts.  Rows beyond m repeat row m - 1 (their results are
-// not stored).  Codes are expanded in registers and meet the activations in one 32 x 32 MFMA tile
-// per 16 input channels.  The wavefronts' partial tiles are added in wavefront order through LDS
-// (deterministic), then the epilogue of the tiled kernel.  No workspace, no atomics.
+// Small batches (decoding steps, a few users).  The layer is bound by the stream of 4-bit weights and by the
+// activations that every workgroup re-reads from the L2, not by the matrix cores.  A workgroup owns NB blocks of 32
+// output channels and up to MP tokens (MB = ceil(MP / 32) MFMA columns) over the whole of K; its NW wavefronts
+// split K, each a contiguous share of the units of 64 input channels.  Neither operand passes through registers on its
+// way in: every wavefront owns a ring of D slots in LDS - per unit NB KiB of codes, the scale / zero-point words and the
+// unit's 128-byte pieces of MP activation rows - that direct-to-LDS loads fill D units ahead of the arithmetic, with
+// no barrier before the sums meet.  The activations come eight rows per instruction (whole 128-byte lines; a
+// lane-per-row register load would touch a line per lane), the chunk position XORed with bits 1-3 of the row on
+// the global side so that the MFMA operand reads are free of bank conflicts.  Rows beyond m lie behind the
+// descriptor's extent and cost no memory traffic (their results are not stored).  Codes are expanded in registers, once
+// for all MB columns.  The partial tiles are added in wavefront order through LDS (deterministic), by all threads,
+// then the epilogue of the tiled kernel.  No workspace, no atomics.
 // ------------------------------------------------------------------------------------------
-constexpr int kSmallM = 32;
-constexpr int kHalfTileUpTo = 256;  // 128-token tiles in a launch up to which they are taken (one per compute unit)
-constexpr int kSmallPasses = 8;  // at most this many launches of 32 rows each
-// Whether ceil(m / 32) passes of the weight-streaming kernel beat one launch of the tiled kernel with
-// 128-token tiles.  Fitted to measurements on 4096 .. 12288 channels x 4096 .. 11008 input channels
-// (microseconds): a pass costs 5.5 + packed bytes / 2.6 MB, a single round of 128-token tiles 3 + 0.0127 k.
-inline bool small_passes_pay(int64_t m, int n, int k) {
-  if (m > kSmallPasses * kSmallM) return false;
-  const double passes = (double)((m + kSmallM - 1) / kSmallM);
-  const double pass_us = 5.5 + (double)n * (double)k * 0.5 / 2.6e6;
-  return m <= kSmallM || passes * pass_us < 3.0 + 0.0127 * (double)k;
-}
+// 128-token tiles in a launch up to which the tiled kernel takes them (one per compute unit)
+constexpr int kHalfTileUpTo = 256;
 
-template <int NW, int MP, int D_>
+template <int NB_, int MP_, int NW_, int D_>
 struct StreamCfg {
-  static constexpr int D = D_;                     // ring slots per wavefront
-  static constexpr int X_OFF = 2048 + 256;         // codes, then 64 lanes x 4 bytes of scale words, then activations
-  static constexpr int SLOT = X_OFF + MP * 256;
-  static constexpr int RING = D * SLOT;
-  static constexpr int LX = MP / 4, LW = 3, L = LX + LW;  // load instructions per group
-  static constexpr int PART = (NW - 1) * 16 * 64 * 4;  // partial tiles of wavefronts 1 .. NW - 1 (over the rings)
-  static constexpr int LDS = NW * RING > PART ? NW * RING : PART;
-  static_assert(LDS <= 160 * 1024, "LDS budget of one compute unit");
-  static_assert(D >= 2 && D <= 4 && (D - 1) * L < 64, "waits below are written for up to three groups in flight");
+  static constexpr int NB = NB_, MP = MP_, NW = NW_, D = D_;
+  static constexpr int MB = (MP + 31) / 32;
+  static constexpr int SZ_OFF = NB * 1024;              // behind the codes: 64 lanes x 4 bytes of scale words
+  static constexpr int X_OFF = SZ_OFF + 256;
+  static constexpr int SLOT = X_OFF + MP * 128;
+  static constexpr int RING = D * SLOT;                 // of one wavefront; its partial tiles go over it
+  static constexpr int L = NB + 1 + MP / 8;             // load instructions per unit
+  static constexpr int PART = NB * MB * 4096;
+  static constexpr int WAVE_BYTES = RING > PART ? RING : PART;
+  static constexpr int LDS = NW * WAVE_BYTES;
+  static constexpr bool FITS = LDS <= 160 * 1024 && D * L < 64;
+  static_assert(MP % 8 == 0 && (NB == 1 || NB == 2), "whole loads; one scale load per unit");
 };
 
-template <int OUT_KIND, int NW, int MP, int D_>
-__global__ __launch_bounds__(64 * NW) void w4a16_small_m_kernel(const W4Params p) {
-  using S = StreamCfg<NW, MP, D_>;
-  constexpr int D = S::D, L = S::L;
+// 64 lanes x 16 bytes from desc + offset (per lane) + k0 to 1 KiB of LDS (outside the kernel template: the host pass drops
+// the stub of a template that passes dependent arguments to this builtin)
+__device__ __forceinline__ void load_x_to_lds(__amdgpu_buffer_rsrc_t desc, int8_t *dst, int offset, int k0) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(desc, CWAC_LDS_PTR(dst), 16, offset, k0, 0, 0);
+}
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+template <int OUT_KIND, class S>
+__global__ __launch_bounds__(64 * S::NW) void w4a16_stream_kernel(const W4Params p) {
+  constexpr int NB = S::NB, MB = S::MB, MP = S::MP, NW = S::NW, D = S::D;
   extern __shared__ __attribute__((aligned(16))) int8_t smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, half = lane >> 5;
-  const int nb = blockIdx.x, n0 = nb * 32;
-  const int groups = p.k / kGroup, kb64 = p.k / 64;
-  const int g_begin = wave * groups / NW, g_end = (wave + 1) * groups / NW;
-  const bool row_ok = l32 < p.m;
-  int8_t *ring = smem + wave * S::RING;
+  int tile_m, tile_n;
+  tile_of_block(blockIdx.x, p.tiles_m, p.tiles_n, tile_m, tile_n);
+  const int64_t bm0 = (int64_t)tile_m * MP;
+  const int rows = p.m - bm0 < MP ? (int)(p.m - bm0) : MP;
+  int n0 = tile_n * (32 * NB);
+  if (n0 > p.n - 32 * NB) n0 = p.n - 32 * NB;  // channel edge: shifted inwards (n % 32 == 0; the same values twice)
+  const int kb64 = p.k / 64;
+  const int u_begin = wave * kb64 / NW, mine = (wave + 1) * kb64 / NW - u_begin;
+  int8_t *ring = smem + wave * S::WAVE_BYTES;
 
-  const char *wrow = reinterpret_cast<const char *>(p.wp) + (int64_t)nb * kb64 * 1024 + lane * 16;
-  const uint32_t *szp = p.sz + n0 + l32;
-  // activation loads: instruction t covers rows 4 t .. 4 t + 3 of the block, lane i = (row i / 16,
-  // chunk position i % 16), which receives the row's chunk (i % 16) ^ (row & 15)
-  uint32_t xoff[S::LX];
+  const char *wrow = reinterpret_cast<const char *>(p.wp) + ((int64_t)(n0 >> 5) * kb64 + u_begin) * 1024 + lane * 16;
+  const uint32_t *szp = p.sz + n0 + (NB == 2 ? lane : l32);
+  const __amdgpu_buffer_rsrc_t xd = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<char *>(p.x + bm0 * p.ldx_bytes), 0, (int)((int64_t)(rows - 1) * p.ldx_bytes + 2 * p.k), 0x00020000);
+  const int lr = lane >> 3, pc = lane & 7;
+  int xo[MP / 8];
 #pragma unroll
-  for (int t = 0; t < S::LX; ++t) {
-    const int row = 4 * t + (lane >> 4);
-    const int src_row = row < (int)p.m ? row : (int)p.m - 1;
-    xoff[t] = (uint32_t)src_row * (uint32_t)p.ldx_bytes + (uint32_t)(((lane & 15) ^ (row & 15)) << 4);
-  }
-  // group g -> slot: two 1 KiB blocks of codes, one scale word per lane (the upper half-wave repeats
-  // the lower one's 32 words), MP / 4 blocks of four activation rows
-  auto issue = [&](int g, int slot_i) {
+  for (int t = 0; t < MP / 8; ++t) xo[t] = (8 * t + lr) * (int)p.ldx_bytes + ((pc ^ (lr >> 1) ^ ((t & 1) << 2)) << 4);
+  auto issue = [&](int i, int slot_i) {  // this wavefront's unit i
     int8_t *slot = ring + slot_i * S::SLOT;
-    __builtin_amdgcn_global_load_lds(CWAC_GLOBAL_PTR(wrow + (int64_t)(2 * g) * 1024), CWAC_LDS_PTR(slot), 16, 0, 0);
-    __builtin_amdgcn_global_load_lds(CWAC_GLOBAL_PTR(wrow + (int64_t)(2 * g + 1) * 1024), CWAC_LDS_PTR(slot + 1024),
-                                     16, 0, 0);
-    __builtin_amdgcn_global_load_lds(CWAC_GLOBAL_PTR(szp + (int64_t)g * p.n), CWAC_LDS_PTR(slot + 2048), 4, 0, 0);
-    const char *xg = p.x + (int64_t)g * 256;
 #pragma unroll
-    for (int t = 0; t < S::LX; ++t)
-      __builtin_amdgcn_global_load_lds(CWAC_GLOBAL_PTR(xg + xoff[t]), CWAC_LDS_PTR(slot + S::X_OFF + t * 1024), 16, 0,
-                                       0);
+    for (int a = 0; a < NB; ++a)
+      __builtin_amdgcn_global_load_lds(CWAC_GLOBAL_PTR(wrow + ((int64_t)a * kb64 + i) * 1024), CWAC_LDS_PTR(slot + a * 1024),
+                                       16, 0, 0);
+    __builtin_amdgcn_global_load_lds(CWAC_GLOBAL_PTR(szp + (int64_t)((u_begin + i) >> 1) * p.n),
+                                     CWAC_LDS_PTR(slot + S::SZ_OFF), 4, 0, 0);
+#pragma unroll
+    for (int t = 0; t < MP / 8; ++t) load_x_to_lds(xd, slot + S::X_OFF + t * 1024, xo[t], (u_begin + i) * 128);
   };
-  // MFMA operand of k-step kk: row l32 (clamped into the block), chunk 2 kk + half
-  const int xrow = l32 < MP ? l32 : MP - 1;
-  const int xrd = S::X_OFF + xrow * 256, xsw = xrow & 15;
-  // two accumulators (even / odd k-steps): consecutive MFMAs do not wait for each other
-  v16f acc, acc1;
+  // two accumulators per tile where a wavefront has one tile only: consecutive MFMAs do not wait for each other
+  constexpr int ACCS = NB * MB == 1 ? 2 : 1;
+  v16f acc[ACCS][NB][MB];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) acc[i] = acc1[i] = 0.0f;
+  for (int c = 0; c < ACCS; ++c)
+#pragma unroll
+    for (int a = 0; a < NB; ++a)
+#pragma unroll
+      for (int b = 0; b < MB; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[c][a][b][i] = 0.0f;
   const ExpandConst ec = expand_const();
 
-  // Memory operations return in order, so "at most N outstanding" means everything older than the
-  // newest N has arrived: with r groups issued behind group g, group g is complete at r * L.
+  struct Unit {
+    u4 c[NB];
+    uint32_t sz[NB];
+    h8 x[4][MB];
+  };
+  auto read = [&](int slot_i, Unit &u) {
+    const int8_t *slot = ring + slot_i * S::SLOT;
+#pragma unroll
+    for (int a = 0; a < NB; ++a) {
+      u.c[a] = *reinterpret_cast<const u4 *>(slot + a * 1024 + lane * 16);
+      u.sz[a] = *reinterpret_cast<const uint32_t *>(slot + S::SZ_OFF + (a * 32 + l32) * 4);
+    }
+#pragma unroll
+    for (int b = 0; b < MB; ++b) {
+      const int row = b * 32 + l32 < MP ? b * 32 + l32 : MP - 1;
+      const int8_t *base = slot + S::X_OFF + row * 128;
+      const int sw = (row >> 1) & 7;
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) u.x[kk][b] = *reinterpret_cast<const h8 *>(base + (((2 * kk + half) ^ sw) << 4));
+    }
+  };
+  auto multiply = [&](const Unit &u) {
+#pragma unroll
+    for (int a = 0; a < NB; ++a) {
+      const GroupConst gc = group_const(u.sz[a]);
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        const h8 w = expand8(u.c[a][kk], gc, ec);
+#pragma unroll
+        for (int b = 0; b < MB; ++b)
+          acc[kk % ACCS][a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(w, u.x[kk][b], acc[kk % ACCS][a][b], 0, 0, 0);
+      }
+    }
+  };
+
+  // Memory operations return in order: with r units issued behind a unit, it is complete at r * L outstanding.
+#pragma unroll
+  for (int d = 0; d < D; ++d)
+    if (d < mine) issue(d, d);
   int slot_i = 0;
 #pragma unroll 1
-  for (int i = 0; i < D; ++i)
-    if (g_begin + i < g_end) issue(g_begin + i, i);
-#pragma unroll 1
-  for (int g = g_begin; g < g_end; ++g) {
-    const int behind = g_end - 1 - g < D - 1 ? g_end - 1 - g : D - 1;
-    if (behind >= 3)
-      __builtin_amdgcn_s_waitcnt(wait_imm(3 * L, 15));
-    else if (behind == 2)
-      __builtin_amdgcn_s_waitcnt(wait_imm(2 * L, 15));
-    else if (behind == 1)
-      __builtin_amdgcn_s_waitcnt(wait_imm(L, 15));
-    else
-      __builtin_amdgcn_s_waitcnt(wait_imm(0, 15));
+  for (int i = 0; i + D < mine; ++i) {
+    __builtin_amdgcn_s_waitcnt(wait_imm((D - 1) * S::L, 15));
     asm volatile("" ::: "memory");  // the slot reads stay below the wait
     __builtin_amdgcn_sched_barrier(0);
-    const int8_t *slot = ring + slot_i * S::SLOT;
-    const u4 c0 = *reinterpret_cast<const u4 *>(slot + lane * 16);
-    const u4 c1 = *reinterpret_cast<const u4 *>(slot + 1024 + lane * 16);
-    const uint32_t sz = *reinterpret_cast<const uint32_t *>(slot + 2048 + l32 * 4);
-    h8 x[8];
-#pragma unroll
-    for (int kk = 0; kk < 8; ++kk)
-      x[kk] = *reinterpret_cast<const h8 *>(slot + xrd + (((2 * kk + half) ^ xsw) << 4));
-    if (g + D < g_end) {
-      // the slot's contents are in registers before the next group may land in it
-      __builtin_amdgcn_s_waitcnt(wait_imm(63, 0));
-      asm volatile("" ::: "memory");
-      __builtin_amdgcn_sched_barrier(0);
-      issue(g + D, slot_i);
-    }
+    Unit u;
+    read(slot_i, u);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(wait_imm(63, 0));  // in registers before the next unit may land in the slot
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    issue(i + D, slot_i);
+    multiply(u);
     slot_i = slot_i + 1 == D ? 0 : slot_i + 1;
-    const GroupConst gc = group_const(sz);
-#pragma unroll
-    for (int kk = 0; kk < 8; kk += 2) {
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(expand8(kk < 4 ? c0[kk & 3] : c1[kk & 3], gc, ec), x[kk], acc, 0, 0,
-                                                   0);
-      acc1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(expand8(kk + 1 < 4 ? c0[(kk + 1) & 3] : c1[(kk + 1) & 3], gc, ec),
-                                                    x[kk + 1], acc1, 0, 0, 0);
-    }
   }
-#pragma unroll
-  for (int i = 0; i < 16; ++i) acc[i] += acc1[i];
+  auto last = [&](auto tag) {  // the last D units: nothing more to issue
+    constexpr int behind = decltype(tag)::value;
+    if (behind >= D || behind >= mine) return;
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(wait_imm(behind < D ? behind * S::L : 0, 15));
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    Unit u;
+    read(slot_i, u);
+    multiply(u);
+    slot_i = slot_i + 1 == D ? 0 : slot_i + 1;
+  };
+  static_assert(D <= 8, "one call per slot");
+  last(std::integral_constant<int, 7>{});
+  last(std::integral_constant<int, 6>{});
+  last(std::integral_constant<int, 5>{});
+  last(std::integral_constant<int, 4>{});
+  last(std::integral_constant<int, 3>{});
+  last(std::integral_constant<int, 2>{});
+  last(std::integral_constant<int, 1>{});
+  last(std::integral_constant<int, 0>{});
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
 
-  // partial tiles over the rings, once every wavefront has left its ring
-  float *s_part = reinterpret_cast<float *>(smem);
-  __syncthreads();
-  if (wave > 0) {
+  // partial tiles over this wavefront's own ring: [tile][q][lane] x 4 channels (accumulator elements 4q .. 4q + 3)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) s_part[((wave - 1) * 16 + i) * 64 + lane] = acc[i];
-  }
-  __syncthreads();
-  if (wave != 0) return;
-#pragma unroll 1
-  for (int w = 0; w < NW - 1; ++w)
+  for (int a = 0; a < NB; ++a)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] += s_part[(w * 16 + i) * 64 + lane];
-  if (!row_ok) return;
+    for (int b = 0; b < MB; ++b)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        v4f t;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          t[r] = acc[0][a][b][4 * q + r];
+          if (ACCS == 2) t[r] += acc[ACCS - 1][a][b][4 * q + r];
+        }
+        reinterpret_cast<v4f *>(ring)[((a * MB + b) * 4 + q) * 64 + lane] = t;
+      }
+  __syncthreads();
+  // thread -> (token, four channels): consecutive threads take consecutive channels of a token
+  constexpr int CG = NB * 8, GROUPS = MB * 32 * CG;
   constexpr int ESZ = OUT_KIND == CWAC_OUT_FP16 ? 2 : 4;
-  char *orow = p.out + ((int64_t)l32 * p.ldo + n0) * ESZ;
+  for (int g = tid; g < GROUPS; g += 64 * NW) {
+    const int cg = g % CG, row = g / CG;
+    if (row >= rows) break;
+    const int tile = (cg >> 3) * MB + (row >> 5);
+    const int8_t *part = smem + (((tile * 4 + ((cg & 7) >> 1)) * 64 + (cg & 1) * 32 + (row & 31)) * 16);
+    v4f sum = *reinterpret_cast<const v4f *>(part);
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int ch = 8 * q + 4 * half;  // channel inside the block: accumulator elements 4q .. 4q + 3
+    for (int w = 1; w < NW; ++w) sum += *reinterpret_cast<const v4f *>(part + w * S::WAVE_BYTES);
+    const int ch = n0 + 4 * cg;
     float u[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const float v = acc[4 * q + r] * (p.mult ? p.mult[n0 + ch + r] : 1.0f);
-      u[r] = v + (p.fbias ? p.fbias[n0 + ch + r] : 0.0f);
+      const float v = sum[r] * (p.mult ? p.mult[ch + r] : 1.0f);
+      u[r] = v + (p.fbias ? p.fbias[ch + r] : 0.0f);
     }
+    char *o = p.out + ((bm0 + row) * p.ldo + ch) * ESZ;
     if (OUT_KIND == CWAC_OUT_FP16) {
       const h2 lo = {(_Float16)u[0], (_Float16)u[1]}, hi = {(_Float16)u[2], (_Float16)u[3]};
-      *reinterpret_cast<uint2 *>(orow + ch * 2) =
-          make_uint2(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi));
+      *reinterpret_cast<uint2 *>(o) = make_uint2(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi));
     } else {
-      *reinterpret_cast<float4 *>(orow + ch * 4) = make_float4(u[0], u[1], u[2], u[3]);
+      *reinterpret_cast<float4 *>(o) = make_float4(u[0], u[1], u[2], u[3]);
     }
   }
 }
 
-template <int OUT_KIND, int NW, int MP, int D>
-cwac_status launch_w4_small_cfg(const W4Params &p, hipStream_t st) {
-  static const hipError_t attr =
-      hipFuncSetAttribute(reinterpret_cast<const void *>(&w4a16_small_m_kernel<OUT_KIND, NW, MP, D>),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, StreamCfg<NW, MP, D>::LDS);
-  if (attr != hipSuccess) return CWAC_E_LAUNCH;
-  w4a16_small_m_kernel<OUT_KIND, NW, MP, D><<<dim3((unsigned)(p.n / 32)), 64 * NW, StreamCfg<NW, MP, D>::LDS, st>>>(p);
-  return launch_status();
+template <int NB, int MP, int NW, int D>
+cwac_status launch_w4_stream_cfg(W4Params p, int out_kind, hipStream_t st) {
+  using S = StreamCfg<NB, MP, NW, D>;
+  if constexpr (!S::FITS) {  // a depth whose rings do not fit is lowered to one that does
+    return launch_w4_stream_cfg<NB, MP, NW, D - 1>(p, out_kind, st);
+  } else {
+    p.tiles_m = (int)ceil_div(p.m, MP);
+    p.tiles_n = (int)ceil_div(p.n, 32 * NB);
+    const int64_t blocks = (int64_t)p.tiles_m * p.tiles_n;
+    if (blocks > 0x7fffffff) return CWAC_E_LAUNCH;
+    const dim3 grid((unsigned)blocks);
+    if (out_kind == CWAC_OUT_FP16) {
+      static const hipError_t attr = hipFuncSetAttribute(
+          reinterpret_cast<const void *>(&w4a16_stream_kernel<CWAC_OUT_FP16, S>), hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS);
+      if (attr != hipSuccess) return CWAC_E_LAUNCH;
+      w4a16_stream_kernel<CWAC_OUT_FP16, S><<<grid, 64 * NW, S::LDS, st>>>(p);
+    } else {
+      static const hipError_t attr = hipFuncSetAttribute(
+          reinterpret_cast<const void *>(&w4a16_stream_kernel<CWAC_OUT_FP32, S>), hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS);
+      if (attr != hipSuccess) return CWAC_E_LAUNCH;
+      w4a16_stream_kernel<CWAC_OUT_FP32, S><<<grid, 64 * NW, S::LDS, st>>>(p);
+    }
+    return launch_status();
+  }
 }
 
-template <int OUT_KIND>
-cwac_status launch_w4_small(const W4Params &p, int waves, int depth, hipStream_t st) {
-  // Four wavefronts per workgroup where the layer has at least as many channel blocks as the chip
-  // has compute units, eight with fewer blocks (waves, depth: the caller's overrides,
-  // cwac_tuning.w4_small_waves / w4_small_depth).  The ring depth trades bytes in flight per
-  // wavefront against resident wavefronts per compute unit (the rings are what fills its LDS):
-  // two slots - four workgroups of four wavefronts per compute unit at up to 8 rows - measured
-  // best on every layer shape, since what a wavefront waits for most is its first group.  A
-  // combination whose rings do not fit the LDS takes the nearest one that does.
-  int nw = waves ? waves : (p.n / 32 >= 256 ? 4 : 8);
-  const int mp = p.m <= 8 ? 8 : (p.m <= 16 ? 16 : 32);
-  if (mp == 32) nw = 4;  // 32-row activation blocks leave room for the rings of four wavefronts only
-  int d = depth ? depth : 2;
-  if (mp == 32 && d > 3) d = 3;
-  if (mp == 16 && nw == 8 && d > 3) d = 3;
-#define CWAC_W4_SMALL(NW, MP, D) \
-  if (nw == NW && mp == MP && d == D) return launch_w4_small_cfg<OUT_KIND, NW, MP, D>(p, st)
-  CWAC_W4_SMALL(4, 8, 2);
-  CWAC_W4_SMALL(4, 8, 3);
-  CWAC_W4_SMALL(4, 8, 4);
-  CWAC_W4_SMALL(8, 8, 2);
-  CWAC_W4_SMALL(8, 8, 3);
-  CWAC_W4_SMALL(8, 8, 4);
-  CWAC_W4_SMALL(4, 16, 2);
-  CWAC_W4_SMALL(4, 16, 3);
-  CWAC_W4_SMALL(4, 16, 4);
-  CWAC_W4_SMALL(8, 16, 2);
-  CWAC_W4_SMALL(8, 16, 3);
-  CWAC_W4_SMALL(4, 32, 2);
-  CWAC_W4_SMALL(4, 32, 3);
-#undef CWAC_W4_SMALL
+// Tile of the weight-streaming kernel by size; waves / depth: the caller's overrides (cwac_tuning.w4_small_waves /
+// w4_small_depth), which keep to 32 channels and at most 32 tokens per workgroup.
+struct StreamChoice {
+  int cfg = 0;          // launch_w4_stream's case
+  double cost = 1e30;   // estimated microseconds
+};
+// A workgroup's time is its share of the operand stream; a round of one workgroup per compute unit takes
+// c * k / 4096 microseconds, and 2 go to launch and epilogue.  c as measured (weights cold, n = 4096 .. 12288,
+// k = 4096 and 11008).  What the tiles trade: fewer tokens per workgroup read the weights more often, fewer channels
+// the activations, and each halves when its factor doubles, until there is less than a round of workgroups.
+inline StreamChoice stream_choice(int64_t m, int n, int k) {
+  struct Tile {
+    int nb, mp;
+    double c;
+  };
+  constexpr Tile tiles[] = {{1, 16, 4.2}, {1, 32, 5.0}, {2, 32, 8.5}, {1, 64, 8.0}, {2, 64, 12.3}, {2, 128, 21.5}};
+  StreamChoice best;
+  if (m <= 8) {
+    best.cfg = 1;
+    best.cost = 0.0;
+    return best;
+  }
+  for (int i = 0; i < 6; ++i) {
+    const int64_t wgs = ceil_div(m, tiles[i].mp) * ceil_div(n, 32 * tiles[i].nb);
+    const double cost = 2.0 + (double)ceil_div(wgs, 256) * tiles[i].c * (double)k / 4096.0;
+    if (cost < best.cost) {
+      best.cost = cost;
+      best.cfg = i + 2;
+    }
+  }
+  return best;
+}
+// Whether the weight-streaming kernel beats the tiled one, whose first round of 128-token tiles costs 3 + 0.0127 k: a
+// tile walks all of k by itself.  Measured, tiled -> streaming: 128 x 4096 x 4096 55 -> 10.0, 400 x 4096 x 4096 55.5 ->
+// 24.1, 256 x 4096 x 11008 119 -> 34.1, 200 x 12288 x 4096 56.7 -> 41.3; level at 400 x 12288 x 4096 (68.9 / 68.5).
+inline bool stream_pays(int64_t m, int n, int k, const StreamChoice &c) {
+  return ceil_div(m, 128) * ceil_div(n, 256) <= 256 && c.cost < 3.0 + 0.0127 * (double)k;
+}
+
+template <int NW>
+cwac_status launch_w4_stream_forced(const W4Params &p, int depth, int out_kind, hipStream_t st) {
+#define CWAC_W4_DEPTH(MP)                                                           \
+  return depth == 3   ? launch_w4_stream_cfg<1, MP, NW, 3>(p, out_kind, st)         \
+         : depth == 4 ? launch_w4_stream_cfg<1, MP, NW, 4>(p, out_kind, st)         \
+                      : launch_w4_stream_cfg<1, MP, NW, 2>(p, out_kind, st)
+  if (p.m <= 8) CWAC_W4_DEPTH(8);
+  if (p.m <= 16) CWAC_W4_DEPTH(16);
+  CWAC_W4_DEPTH(32);
+#undef CWAC_W4_DEPTH
+}
+
+cwac_status launch_w4_stream(const W4Params &p, int cfg, int waves, int depth, int out_kind, hipStream_t st) {
+  if (waves || depth)
+    return waves == 4 ? launch_w4_stream_forced<4>(p, depth, out_kind, st) : launch_w4_stream_forced<8>(p, depth, out_kind, st);
+  // Wavefronts and ring depth as measured best: eight wavefronts where their rings fit the LDS (two per SIMD, so that
+  // one's LDS reads run under the other's MFMAs), two slots each (three: within 3 %; four of 8 rows: 4 % slower).
+  switch (cfg) {
+    case 1: return launch_w4_stream_cfg<1, 8, 8, 2>(p, out_kind, st);
+    case 2: return launch_w4_stream_cfg<1, 16, 8, 3>(p, out_kind, st);
+    case 3: return launch_w4_stream_cfg<1, 32, 8, 2>(p, out_kind, st);
+    case 4: return launch_w4_stream_cfg<2, 32, 8, 2>(p, out_kind, st);
+    case 5: return launch_w4_stream_cfg<1, 64, 8, 2>(p, out_kind, st);
+    case 6: return launch_w4_stream_cfg<2, 64, 4, 2>(p, out_kind, st);
+    case 7: return launch_w4_stream_cfg<2, 128, 4, 2>(p, out_kind, st);
+  }
   return CWAC_E_MODE;
 }
-
 
 int grid_for(int64_t items) {
   const int64_t b = ceil_div(items, kThreads);
@@ -791,7 +881,7 @@ cwac_status cwac_fold_weight_only(const float *alpha, const float *beta, const f
 cwac_status qlinear_w4a16_cwac_forward_ex(const uint16_t *x, int64_t ldx, const void *packed_w,
                                           const uint32_t *packed_sz, int64_t m, int32_t n, int32_t k,
                                           const float *mult, const float *fbias, int32_t out_kind, void *out,
-                                          int64_t ldo, const cwac_tuning *tuning, void *stream) {
+                                          int64_t ldo, const cwac_tuning *tuning, void *stream_handle) {
   if (!x || !packed_w || !packed_sz || !out) return CWAC_E_NULL;
   if (out_kind != CWAC_OUT_FP16 && out_kind != CWAC_OUT_FP32) return CWAC_E_MODE;
   const int w4_tile = tuning ? tuning->w4_tile : 0, small_waves = tuning ? tuning->w4_small_waves : 0;
@@ -822,23 +912,10 @@ cwac_status qlinear_w4a16_cwac_forward_ex(const uint16_t *x, int64_t ldx, const 
   p.ldo = ldo;
   p.tiles_n = (int)ceil_div(n, 256);
   // The caller's override (results agree to the rounding of the fp32 sums): w4_tile = 256 keeps the
-  // 256-token tiles at every batch size, 128 the 128-token tiles.
-  if (w4_tile == 0 && small_passes_pay(m, n, k)) {
-    // passes of the weight-streaming kernel over blocks of 32 rows: the packed weights of a layer
-    // stay in the last-level cache between passes, and a row of 128- or 256-token tiles would leave
-    // most of the chip idle at these sizes (each tile as long as its K loop)
-    for (int64_t r0 = 0; r0 < m; r0 += kSmallM) {
-      W4Params q = p;
-      q.x = p.x + r0 * p.ldx_bytes;
-      q.out = p.out + r0 * ldo * esz;
-      q.m = m - r0 < kSmallM ? m - r0 : kSmallM;
-      const cwac_status s = out_kind == CWAC_OUT_FP16
-                                ? launch_w4_small<CWAC_OUT_FP16>(q, small_waves, small_depth, as_stream(stream))
-                                : launch_w4_small<CWAC_OUT_FP32>(q, small_waves, small_depth, as_stream(stream));
-      if (s != CWAC_OK) return s;
-    }
-    return CWAC_OK;
-  }
+  // 256-token tiles at every batch size, 128 the 128-token tiles.  Otherwise the weight-streaming kernel where it pays.
+  const StreamChoice stream = stream_choice(m, n, k);
+  if (w4_tile == 0 && stream_pays(m, n, k, stream))
+    return launch_w4_stream(p, stream.cfg, small_waves, small_depth, out_kind, as_stream(stream_handle));
   // 128-token tiles while they fit the chip in one round (one tile per compute unit): a half tile
   // takes about two thirds of a full tile's time (the weight expansion is per channel block, not
   // per token, so it spends more vector work per MFMA), which pays exactly while the full tiles
@@ -846,19 +923,19 @@ cwac_status qlinear_w4a16_cwac_forward_ex(const uint16_t *x, int64_t ldx, const 
   const bool half = w4_tile == 128 || (w4_tile == 0 && ceil_div(m, 128) * p.tiles_n <= kHalfTileUpTo);
   if (half) {
     p.tiles_m = (int)ceil_div(m, 128);
-    return out_kind == CWAC_OUT_FP16 ? launch_w4<CWAC_OUT_FP16, 2>(p, as_stream(stream))
-                                     : launch_w4<CWAC_OUT_FP32, 2>(p, as_stream(stream));
+    return out_kind == CWAC_OUT_FP16 ? launch_w4<CWAC_OUT_FP16, 2>(p, as_stream(stream_handle))
+                                     : launch_w4<CWAC_OUT_FP32, 2>(p, as_stream(stream_handle));
   }
   // large batches: the tile of 512 channels x 128 tokens (no wavefront expands another one's weights)
   if (w4_tile == 512 || (w4_tile == 0 && n >= 512)) {
     p.tiles_m = (int)ceil_div(m, 128);
     p.tiles_n = (int)ceil_div(n, 512);
-    return out_kind == CWAC_OUT_FP16 ? launch_w4<CWAC_OUT_FP16, 4, 1>(p, as_stream(stream))
-                                     : launch_w4<CWAC_OUT_FP32, 4, 1>(p, as_stream(stream));
+    return out_kind == CWAC_OUT_FP16 ? launch_w4<CWAC_OUT_FP16, 4, 1>(p, as_stream(stream_handle))
+                                     : launch_w4<CWAC_OUT_FP32, 4, 1>(p, as_stream(stream_handle));
   }
   p.tiles_m = (int)ceil_div(m, 256);
-  return out_kind == CWAC_OUT_FP16 ? launch_w4<CWAC_OUT_FP16, 4>(p, as_stream(stream))
-                                   : launch_w4<CWAC_OUT_FP32, 4>(p, as_stream(stream));
+  return out_kind == CWAC_OUT_FP16 ? launch_w4<CWAC_OUT_FP16, 4>(p, as_stream(stream_handle))
+                                   : launch_w4<CWAC_OUT_FP32, 4>(p, as_stream(stream_handle));
 }
 
 cwac_status qlinear_w4a16_cwac_forward(const uint16_t *x, int64_t ldx, const void *packed_w,
