@@ -16,6 +16,8 @@
 //   * rows past the last token or channel lie behind the descriptor's extent: such lanes touch no memory;
 //   * the partial tiles meet in LDS once, and the whole epilogue runs on the sums, four consecutive channels
 //     per thread.
+#include <type_traits>
+
 #include "qlinear_common.h"
 
 namespace cwac {
@@ -116,16 +118,10 @@ __global__ __launch_bounds__(64 * W) void qlinear_splitk_kernel(const FwdParams 
       for (int b = 0; b < TM; ++b) acc[a][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fw[a], fx[b], acc[a][b], 0, 0, 0);
   };
 
-  // ---- K: a contiguous range of whole units per wavefront, D units in flight.  Loads past this wavefront's last unit
-  // fetch that unit again (a cached line, never multiplied), so the wait count is a constant.
+  // ---- K: a contiguous range of whole units per wavefront, D units in flight
   const int units = p.k / C::UK;
   const int mine = units / W + (wave < units % W ? 1 : 0);
   const int k_first = (wave * (units / W) + (wave < units % W ? wave : units % W)) * C::UK;
-  const int k_last = k_first + (mine - 1) * C::UK;
-  auto k_of = [&](int i) {
-    const int k0 = k_first + i * C::UK;
-    return k0 < k_last ? k0 : k_last;
-  };
   // epilogue parameters: the round trip runs under the K loop
   int r_off = 0, r_tab = 0;
   float r_mult = 0.0f, r_fb = 0.0f, r_rs = 1.0f;
@@ -144,28 +140,45 @@ __global__ __launch_bounds__(64 * W) void qlinear_splitk_kernel(const FwdParams 
     if (!INT_ONLY && OUT_KIND != CWAC_OUT_INT32 && p.sx_row && tid < rows_m) r_rs = p.sx_row[bm0 + tid];
     if (OUT_KIND == kOutTable && tid < 64) r_tab = reinterpret_cast<const int32_t *>(p.code_table)[tid];
   }
-  if (mine > 0) {
-    // (the parameter loads above are older than the panel loads and have landed when a unit has)
+  // (The parameter loads above are older than the panel loads and have landed when a unit has.)  Memory operations
+  // return in order: with r units issued behind a unit, it is complete at r * LPU outstanding.
 #pragma unroll
-    for (int d = 0; d < D; ++d) issue(d, k_of(d));
-    int d = 0;
+  for (int d = 0; d < D; ++d)
+    if (d < mine) issue(d, k_first + d * C::UK);
+  int d = 0;
 #pragma unroll 1
-    for (int i = 0; i < mine; ++i) {
-      wait_loads<(D - 1) * C::LPU>();
-      v4i fw0[TN], fx0[TM], fw1[TN], fx1[TM];
-      read(d, 0, fw0, fx0);
-      read(d, 1, fw1, fx1);
-      __builtin_amdgcn_sched_barrier(0);
-      __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (3 << 14));  // lgkmcnt(0): the unit is in registers, its place is free
-      asm volatile("" ::: "memory");
-      __builtin_amdgcn_sched_barrier(0);
-      issue(d, k_of(i + D));
-      mma(fw0, fx0);
-      mma(fw1, fx1);
-      d = d + 1 == D ? 0 : d + 1;
-    }
-    wait_loads<0>();  // the ring is about to be overwritten
+  for (int i = 0; i + D < mine; ++i) {
+    wait_loads<(D - 1) * C::LPU>();
+    v4i fw0[TN], fx0[TM], fw1[TN], fx1[TM];
+    read(d, 0, fw0, fx0);
+    read(d, 1, fw1, fx1);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (3 << 14));  // lgkmcnt(0): the unit is in registers, its place is free
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    issue(d, k_first + (i + D) * C::UK);
+    mma(fw0, fx0);
+    mma(fw1, fx1);
+    d = d + 1 == D ? 0 : d + 1;
   }
+  auto last = [&](auto tag) {  // the last D units: nothing more to issue
+    constexpr int behind = decltype(tag)::value;
+    if (behind >= D || behind >= mine) return;
+    wait_loads<(behind < D ? behind * C::LPU : 0)>();
+    v4i fw0[TN], fx0[TM], fw1[TN], fx1[TM];
+    read(d, 0, fw0, fx0);
+    read(d, 1, fw1, fx1);
+    mma(fw0, fx0);
+    mma(fw1, fx1);
+    d = d + 1 == D ? 0 : d + 1;
+  };
+  static_assert(D <= 4, "one call per slot");
+  last(std::integral_constant<int, 3>{});
+  last(std::integral_constant<int, 2>{});
+  last(std::integral_constant<int, 1>{});
+  last(std::integral_constant<int, 0>{});
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
   // the last K % 128 bytes, 64 at a time, straight to registers: lanes whose 16 bytes lie beyond K read past the
   // extent (zeros)
   if (wave == W - 1) {
