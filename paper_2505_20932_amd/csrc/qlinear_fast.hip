@@ -1331,13 +1331,35 @@ cwac_status launch_cfg(FwdParams p, int out_kind, bool int_only, hipStream_t st)
   return launch_one<BM, WM, BK, NSTAGE, NCHUNK, CWAC_OUT_INT32, false, CONV, BN, TA>(p, grid, st);
 }
 
-template <int BM, int WM, int BK, int NSTAGE>
+template <int BM, int WM, int BK, int NSTAGE, int NCHUNK = 2, int BN = 256, int TA = 0>
 cwac_status launch_table_cfg(FwdParams p, hipStream_t st) {
   p.tiles_m = (int)ceil_div(p.m, BM);
-  p.tiles_n = (int)ceil_div(p.n, 256);
+  p.tiles_n = (int)ceil_div(p.n, BN);
   const int64_t blocks = (int64_t)p.tiles_m * p.tiles_n;
   if (blocks > 0x7fffffff) return CWAC_E_LAUNCH;
-  return launch_one<BM, WM, BK, NSTAGE, 2, kOutTable, true>(p, dim3((unsigned)blocks), st);
+  return launch_one<BM, WM, BK, NSTAGE, NCHUNK, kOutTable, true, false, BN, TA>(p, dim3((unsigned)blocks), st);
+}
+
+// K step and ring depth of the 128 x 128 tile (four wavefronts of 64 x 64; `kstep`: K or the channels of a filter tap).
+// Measured, microseconds at m x n x k, int8 output unless noted:
+//   0: 64-byte steps, three stages, three workgroups per compute unit: where steps of 128 do not divide K, and for
+//      4-byte outputs in more than two rounds of tiles (their stores weigh as much as the K loop: 12608 x 3072 x 768 fp32
+//      52.8 / 54.6 with 1).
+//   1: 128-byte steps, two stages, two workgroups per compute unit: half the barriers.  4616 x 768 x 768 9.0 -> 8.1,
+//      7252 x 512 x 512 7.1 -> 6.5, 2000 x 3072 x 768 11.8 -> 10.0.
+//   2: 128-byte steps, three stages, one workgroup per compute unit: one round of tiles and a long K, where nothing
+//      else covers a stage's round trip.  4616 x 768 x 3072 19.6 -> 16.1, 1000 x 4096 x 4096 30.7 -> 23.2,
+//      7252 x 512 x 2048 14.6 -> 12.8 (14.4 with 1), 6272 x 256 x 1024 8.5 -> 8.6 (8.4 with 1).
+int quarter_ring(int64_t m, int n, int k, int kstep, bool wide) {
+  const int64_t tiles = ceil_div(m, 128) * ceil_div(n, 128);
+  if ((kstep % 128) != 0 || (wide && tiles > 512)) return 0;
+  return tiles <= 256 && k >= 1536 ? 2 : 1;
+}
+
+// The 128-token x 256-channel tile on one workgroup per compute unit with 128-byte steps and three stages: one round of
+// tiles and a long K.  2048 x 4096 x 4096 42.9 -> 35.1, 500 x 11008 x 4096 39.8 -> 33.2, 2000 x 4096 x 11008 fp32 105.8 -> 88.7.
+bool half_deep(int64_t m, int n, int k) {
+  return (k % 128) == 0 && k >= 3072 && ceil_div(m, 128) * ceil_div(n, 256) <= 256;
 }
 
 }  // namespace
@@ -1345,10 +1367,17 @@ cwac_status launch_table_cfg(FwdParams p, hipStream_t st) {
 cwac_status launch_fast_table(FwdParams p, int shape, int max_workgroups, int loaders, hipStream_t st) {
   p.vec_store = aligned(p.out, 16) && (p.ldo % 16) == 0;
   // the tiles of the plain int8 forward of a layer with n >= 256, by the same rule: the persistent
-  // 256 x 256 tile, the same tile with one workgroup per tile, or the 128-token pair
+  // 256 x 256 tile, the same tile with one workgroup per tile, or a tile of 128 tokens
   if (shape == CWAC_SHAPE_AUTO) shape = fast_linear_shape(p.m, p.n, p.k, 1);
-  if ((p.k % 128) != 0 || shape == CWAC_SHAPE_128_128) shape = CWAC_SHAPE_128_PAIR;
-  if (shape == CWAC_SHAPE_128_PAIR) return launch_table_cfg<128, 2, 64, 3>(p, st);
+  if (shape == CWAC_SHAPE_128_128) {
+    const int ring = quarter_ring(p.m, p.n, p.k, p.k, false);
+    if (ring == 2) return launch_table_cfg<128, 2, 128, 3, 4, 128, 2>(p, st);
+    if (ring == 1) return launch_table_cfg<128, 2, 128, 2, 2, 128, 2>(p, st);
+    return launch_table_cfg<128, 2, 64, 3, 2, 128, 2>(p, st);
+  }
+  if ((p.k % 128) != 0) shape = CWAC_SHAPE_128_PAIR;
+  if (shape == CWAC_SHAPE_128_PAIR)
+    return half_deep(p.m, p.n, p.k) ? launch_table_cfg<128, 2, 128, 3>(p, st) : launch_table_cfg<128, 2, 64, 3>(p, st);
   if (shape == CWAC_SHAPE_256_PERSIST) return launch_persist(p, kOutTable, true, max_workgroups, loaders, st);
   return launch_table_cfg<256, 4, 128, 2>(p, st);
 }
@@ -1397,9 +1426,16 @@ cwac_status launch_fast(FwdParams p, int out_kind, bool int_only, const Tune &tu
   // the 128-token tile, two workgroups of four wavefronts per compute unit, _128_128 the quarter tile.
   const int out_bytes = (out_kind == CWAC_OUT_INT8 || out_kind == kOutFixed) ? 1 : 4;
   if (shape == CWAC_SHAPE_AUTO) shape = fast_linear_shape(p.m, p.n, p.k, out_bytes);
-  if (shape == CWAC_SHAPE_128_128) return launch_cfg<128, 2, 64, 3, 2, false, 128, 2>(p, out_kind, int_only, st);
+  if (shape == CWAC_SHAPE_128_128) {
+    const int ring = quarter_ring(p.m, p.n, p.k, p.k, out_bytes > 1);
+    if (ring == 2) return launch_cfg<128, 2, 128, 3, 4, false, 128, 2>(p, out_kind, int_only, st);
+    if (ring == 1) return launch_cfg<128, 2, 128, 2, 2, false, 128, 2>(p, out_kind, int_only, st);
+    return launch_cfg<128, 2, 64, 3, 2, false, 128, 2>(p, out_kind, int_only, st);
+  }
   if ((p.k % 128) != 0) shape = CWAC_SHAPE_128_PAIR;  // K a multiple of 64 only: the tile that steps K by 64
-  if (shape == CWAC_SHAPE_128_PAIR) return launch_cfg<128, 2, 64, 3, 2>(p, out_kind, int_only, st);
+  if (shape == CWAC_SHAPE_128_PAIR)
+    return half_deep(p.m, p.n, p.k) ? launch_cfg<128, 2, 128, 3, 2>(p, out_kind, int_only, st)
+                                    : launch_cfg<128, 2, 64, 3, 2>(p, out_kind, int_only, st);
   if (shape == CWAC_SHAPE_256_4W_K64) return launch_cfg<256, 2, 64, 4, 2>(p, out_kind, int_only, st);
   if (shape == CWAC_SHAPE_256_8W) return launch_cfg<256, 4, 128, 2, 2>(p, out_kind, int_only, st);
   if (shape == CWAC_SHAPE_256_4W_K128) return launch_cfg<256, 2, 128, 2, 2>(p, out_kind, int_only, st);
@@ -1411,7 +1447,9 @@ int fast_linear_shape(int64_t m, int n, int k, int out_bytes) {
   // The automatic tile shape of a linear layer with n >= 256, from measurements on the ViT / Swin / LLM
   // layer shapes (K 512 .. 11008, 196 .. 3072 tiles of 256 x 256).
   //  * Few tiles and a long K loop: 128 x 128 tiles (fast_prefers_quarter_tile).
-  //  * Less than a round of 256 x 256 tiles: the 128-token tile where the one-tile cost model prefers it.
+  //  * Less than a round of 256 x 256 tiles: 128 x 256 tiles where they are one round and K is long (half_deep), else
+  //    the persistent tile from half a round on (3152 x 3072 x 768, 156 tiles: 14.3 us, 128 x 128 tiles 15.2; 12608 x 768 x
+  //    3072 fp32, 150 tiles: 39.4 / 45.7), else 128 x 128 tiles (2000 x 3072 x 768, 96 tiles: 13.6 / 10.0).
   //  * Otherwise the persistent 256 x 256 tile (which splits the tiles of a thin last round in two).
   //    With 4-byte outputs and a short K loop the tile's store burst weighs as much as its K loop:
   //    when, on top, the last round leaves a good part of the chip idle, the 128 x 128 tile (three
@@ -1419,7 +1457,10 @@ int fast_linear_shape(int64_t m, int n, int k, int out_bytes) {
   if (fast_prefers_quarter_tile(m, n)) return CWAC_SHAPE_128_128;
   if ((k % 128) != 0) return CWAC_SHAPE_128_PAIR;
   const int64_t t256 = ceil_div(m, 256) * ceil_div(n, 256);
-  if (t256 < 160) return fast_prefers_half_tile(m, n, k, out_bytes) ? CWAC_SHAPE_128_PAIR : CWAC_SHAPE_256_PERSIST;
+  if (t256 < 160) {
+    if (half_deep(m, n, k)) return CWAC_SHAPE_128_PAIR;
+    return t256 >= 128 ? CWAC_SHAPE_256_PERSIST : CWAC_SHAPE_128_128;
+  }
   const double fill = (double)t256 / (double)(256 * ceil_div(t256, 256));  // busy share of the rounds
   if (out_bytes > 1 && k <= 1024 && fill < 0.85) return CWAC_SHAPE_128_128;
   return CWAC_SHAPE_256_PERSIST;
@@ -1440,7 +1481,12 @@ cwac_status launch_fast_conv(FwdParams p, int out_kind, bool int_only, int shape
   // `shape` (cwac_tuning, same results): _256_8W | _128_PAIR | _128_128; the four-wavefront forms of
   // the 256-token tile are not instantiated for the convolution and leave the choice automatic
   if (shape == CWAC_SHAPE_128_128 || (shape == CWAC_SHAPE_AUTO && fast_prefers_quarter_tile(p.m, p.n)))
+  {
+    const int ring = quarter_ring(p.m, p.n, p.k, p.cv_cin, esz > 1);
+    if (ring == 2) return launch_cfg<128, 2, 128, 3, 4, true, 128, 2>(p, out_kind, int_only, st);
+    if (ring == 1) return launch_cfg<128, 2, 128, 2, 2, true, 128, 2>(p, out_kind, int_only, st);
     return launch_cfg<128, 2, 64, 3, 2, true, 128, 2>(p, out_kind, int_only, st);
+  }
   bool half = !full_ok || fast_prefers_half_tile(p.m, p.n, p.k, (int)esz) ||
               ceil_div(p.m, 256) * ceil_div(p.n, 256) < 160;
   if (shape == CWAC_SHAPE_128_PAIR) half = true;

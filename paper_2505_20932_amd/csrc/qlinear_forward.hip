@@ -235,11 +235,9 @@ static int choose_forward(int64_t m, int n, int k, int64_t ldx, int64_t ldw, int
   // the large-problem kernel: K a multiple of 128, or of 64 (then only its 128-token tile, which
   // steps K by 64); 64 <= N < 256: its 256 x 128 or 256 x 64 tile; pitches its 32-bit lane offsets hold
   const bool fast_ok = m >= kFastTile && n >= 64 && (k % 64) == 0 && fast_pitch_ok(ldx, ldw);
-  // it wants most compute units busy: 160 full tiles, or 256 half tiles
-  const int out_bytes = (out_kind == CWAC_OUT_INT8 || out_kind == kOutFixed) ? 1 : 4;
-  bool fast = fast_ok && n >= kFastTile && (k % kFastKStep) == 0 &&
-              (t256 >= 160 || fast_prefers_half_tile(m, n, k, out_bytes));
-  if (fast_ok && n >= kFastTile && (k % kFastKStep) != 0) fast = ceil_div(m, 128) * ceil_div(n, 256) >= 160;
+  // it wants most compute units busy: 160 tiles of 128 x 256 (3152 x 3072 x 768, 300 of them: 24.8 us with the
+  // register-staged kernel, 14.3 with this one; 12608 x 768 x 768 fp32, 297: 34.0 / 19.5)
+  bool fast = fast_ok && n >= kFastTile && ceil_div(m, 128) * ceil_div(n, 256) >= 160;
   if (fast_ok && n < kFastTile) fast = ceil_div(m, 256) * ceil_div(n, n < 128 ? 64 : 128) >= 160;
   if (fast_ok && n >= kFastTile && fast_prefers_quarter_tile(m, n)) fast = true;
   // the caller's override (results are identical)
@@ -348,16 +346,11 @@ extern "C" cwac_status qlinear_cwac_forward_table_ex(const int8_t *x_q, int64_t 
   if (!aligned(x_q, 16) || !aligned(w_q, 16) || (ldx % 16) != 0 || (ldw % 16) != 0 || !aligned(out, 16) ||
       (ldo % 16) != 0 || !aligned(table, 4))
     return CWAC_E_ALIGN;
-  // Where the plain forward would take the direct-to-LDS kernel in one of its two large tiles, the table
-  // is applied in that kernel's epilogue, and likewise in the small-problem kernel's; elsewhere the forward is followed
-  // by a lookup pass in place.
-  const int64_t t256 = ceil_div(m, 256) * ceil_div(n, 256), t_half = ceil_div(m, 128) * ceil_div(n, 256);
-  const bool fused_ok = m >= kFastTile && n >= kFastTile && (k % 64) == 0 && fast_pitch_ok(ldx, ldw);
-  bool fused = fused_ok && !fast_prefers_quarter_tile(m, n);
-  if (fused) fused = (k % kFastKStep) == 0 ? (t256 >= 160 || fast_prefers_half_tile(m, n, k, 1)) : t_half >= 160;
-  // the caller's override: the direct-to-LDS kernel means the fused form where its shape constraints
-  // hold, a generic tile means two passes
-  if (tune.kernel != CWAC_KERNEL_AUTO) fused = fused_ok && tune.kernel == CWAC_KERNEL_DIRECT_LDS;
+  // Where the plain forward would take the direct-to-LDS kernel, the table is applied in that kernel's
+  // epilogue (layers of 256 channels and more), and likewise in the small-problem kernel's; elsewhere - and where the caller
+  // forces a register-staged tile - the forward is followed by a lookup pass in place.
+  const int choice = choose_forward(m, n, k, ldx, ldw, CWAC_OUT_INT8, tune);
+  const bool fused = n >= kFastTile && choice == CWAC_KERNEL_DIRECT_LDS;
   FwdParams p = {};
   p.x = x_q; p.w = w_q; p.ldx = ldx; p.ldw = ldw; p.ldo = ldo;
   p.m = m; p.n = n; p.k = k;
@@ -367,8 +360,7 @@ extern "C" cwac_status qlinear_cwac_forward_table_ex(const int8_t *x_q, int64_t 
   p.hi = (float)(qp->qmax - qp->z_r);
   p.code_table = table;
   if (!fused) {
-    if (tune.kernel == CWAC_KERNEL_AUTO && splitk_ok(m, n, k, ldx, ldw) &&
-        choose_forward(m, n, k, ldx, ldw, CWAC_OUT_INT8, tune) == 64)
+    if (choice == 64 && tune.kernel == CWAC_KERNEL_AUTO && splitk_ok(m, n, k, ldx, ldw))
       return launch_splitk(p, kOutTable, true, as_stream(stream));
     const cwac_status st = qlinear_cwac_forward_ex(x_q, ldx, w_q, ldw, m, n, k, qp, mult, offset, nullptr, nullptr,
                                                    CWAC_OUT_INT8, out, ldo, tuning, stream);

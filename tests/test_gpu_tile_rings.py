@@ -1,0 +1,62 @@
+"""GPU parity of the direct-to-LDS kernel's 128-token tiles with 128-byte K steps (two and three stages, one and several
+rounds of the ring, ragged edges), of their code-table epilogue and of their implicit-GEMM form, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2505_20932_amd as P
+from tuning import tuning_of
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+
+
+# 128 x 128: K < 1536 two stages, else three; 128 x 256: K >= 3072 three stages of 128 bytes; K % 128 == 64: 64-byte steps
+@pytest.mark.parametrize("m,n,k,pipe", [(256, 256, 128, "q"), (300, 272, 256, "q"), (257, 400, 1408, "q"), (256, 256, 1536, "q"),
+                                        (385, 272, 1664, "q"), (300, 304, 1792, "q"), (300, 272, 192, "q"), (300, 272, 3072, "duo"),
+                                        (257, 528, 3200, "duo"), (384, 256, 3328, "duo"), (300, 272, 2944, "duo")])
+def test_ring_bit_exact(orc, m, n, k, pipe):
+    print(f"ring {m} x {n} x {k} {pipe}", flush=True)
+    rng = np.random.default_rng(m + 7 * n + 13 * k)
+    xq = rng.integers(-128, 128, (m, k), dtype=np.int8)
+    wq = rng.integers(-127, 128, (n, k), dtype=np.int8)
+    acc = orc.gemm_i8(xq, wq)
+    mult = (np.abs(rng.standard_normal(n)) * 3e-4 + 1e-5).astype(np.float32)
+    off = rng.integers(-5000, 5000, n).astype(np.int32)
+    fb = rng.standard_normal(n).astype(np.float32)
+    sxr = (np.abs(rng.standard_normal(m)) * 0.5 + 0.5).astype(np.float32)
+    table = rng.permutation(np.arange(-128, 128)).astype(np.int8)
+    tun = tuning_of("fast", pipe=pipe)
+    for zr in (4, -7):
+        code = orc.folded_forward(acc, off, mult, zr)
+        qp, qpt = P.make_qparams(z_r=zr), P.make_qparams(P.CWAC_EPI_FP_BIAS, True, 1.0, 0, 1.0, zr)
+        o8 = torch.empty(m, n, dtype=torch.int8, device=DEV)
+        P.qlinear_cwac_forward(dev(xq), dev(wq), qp, dev(mult), dev(off), None, None, P.CWAC_OUT_INT8, o8, tuning=tun)
+        np.testing.assert_array_equal(o8.cpu().numpy(), code)
+        P.qlinear_cwac_forward(dev(xq), dev(wq), qpt, dev(mult), dev(off), dev(fb), dev(sxr), P.CWAC_OUT_INT8, o8, tuning=tun)
+        np.testing.assert_array_equal(o8.cpu().numpy(), orc.folded_forward(acc, off, mult, zr, fb, sxr))
+        P.qlinear_cwac_forward_table(dev(xq), dev(wq), qp, dev(mult), dev(off), dev(table), o8, tuning=tun)
+        np.testing.assert_array_equal(o8.cpu().numpy(), table[code.astype(np.int32) + 128])
+    o32 = torch.empty(m, n, dtype=torch.float32, device=DEV)
+    P.qlinear_cwac_forward(dev(xq), dev(wq), None, dev(mult), dev(off), dev(fb), dev(sxr), P.CWAC_OUT_FP32, o32, tuning=tun)
+    np.testing.assert_array_equal(o32.cpu().numpy(), orc.folded_forward(acc, off, mult, 0, fb, sxr, want_f32=True)[1])
+
+
+@pytest.mark.parametrize("shape", [(2, 14, 13, 128, 256, 3, 3, 1, 1), (5, 8, 9, 256, 272, 3, 3, 1, 1), (3, 17, 17, 128, 256, 2, 2, 2, 0)])
+def test_conv_ring_bit_exact(orc, shape):
+    b, h, w, c, n, kh, kw, stride, pad = shape
+    print(f"conv ring {shape}", flush=True)
+    rng = np.random.default_rng(sum(shape))
+    xq = rng.integers(-128, 128, (b, h, w, c), dtype=np.int8)
+    wq = rng.integers(-127, 128, (n, kh, kw, c), dtype=np.int8)
+    acc = orc.conv2d_i8(xq, wq, stride, pad, 9)
+    mult = (np.abs(rng.standard_normal(n)) * 3e-4 + 1e-5).astype(np.float32)
+    off = rng.integers(-5000, 5000, n).astype(np.int32)
+    out = torch.empty(acc.shape[0], n, dtype=torch.int8, device=DEV)
+    P.qconv2d_cwac_forward(dev(xq), dev(wq), stride, pad, P.make_qparams(z_x=9, z_r=3), dev(mult), dev(off), None,
+                           P.CWAC_OUT_INT8, out, tuning=tuning_of("fast", pipe="q"))
+    np.testing.assert_array_equal(out.cpu().numpy(), orc.folded_forward(acc, off, mult, 3))
