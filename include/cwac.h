@@ -270,6 +270,7 @@ cwac_status qlinear_cwac_forward(const int8_t *x_q, int64_t ldx, const int8_t *w
  * byte read from LDS in the epilogue of large layers and no pass over the tensor; small layers run
  * the forward and then a lookup pass in place.  Arguments as qlinear_cwac_forward, plus
  *   table  device int8 [256], 4-byte aligned
+ *   qp     folded for that epilogue: act_per_token and mode CWAC_EPI_FP_BIAS return CWAC_E_MODE at every size
  *   n % 16 == 0; out 16-byte aligned, ldo % 16 == 0 */
 cwac_status qlinear_cwac_forward_table(const int8_t *x_q, int64_t ldx, const int8_t *w_q, int64_t ldw,
                                        int64_t m, int32_t n, int32_t k, const cwac_qparams *qp,

@@ -337,7 +337,9 @@ extern "C" cwac_status qlinear_cwac_forward_table_ex(const int8_t *x_q, int64_t 
   if (!x_q || !w_q || !out || !qp || !mult || !table) return CWAC_E_NULL;
   Tune tune;
   if (!tune_from(tuning, tune)) return CWAC_E_MODE;
-  if (qp->act_per_token) return CWAC_E_MODE;  // the integer-offset epilogue has no per-row scales
+  // the integer-offset epilogue has no per-row scales and no fp32 bias: a qp that was folded with either is refused here,
+  // before a kernel is chosen, so that the answer does not depend on the layer's size
+  if (qp->act_per_token || qp->mode == CWAC_EPI_FP_BIAS) return CWAC_E_MODE;
   if (m < 1 || m > ((int64_t)1 << 40) || n < 16 || (n % 16) != 0 || k < 16 || k > 32768 || (k % 16) != 0)
     return CWAC_E_SHAPE;
   if (ldx < k || ldw < k || ldo < n) return CWAC_E_SHAPE;

@@ -314,3 +314,16 @@ def test_argument_errors_of_the_block_glue_entry_points(lib):
     bp = binding.vit_block_params()
     assert lib.vit_encoder_w8a8_forward(C.byref(bp), 0, a, a, a, 1 << 30, null) == -2   # no blocks
     assert lib.vit_encoder_w8a8_forward(C.byref(bp), 1, a, a, a, 1 << 30, null) == -1   # empty parameter block
+
+
+@pytest.mark.parametrize("m,n,k", [(1, 16, 16), (197, 3072, 768), (2000, 3072, 768), (16384, 4096, 4096)])
+def test_code_table_forward_refuses_an_fp_bias_fold_at_every_size(lib, m, n, k):
+    """The table rides in the integer-offset epilogue, which has no fp32 bias: a qp folded with one is an error whichever
+    kernel the sizes pick (split-K, 128 x 128 tiles, persistent tiles; forced register-staged tiles: two passes)."""
+    a, null = C.c_void_p(4096), None
+    qp = binding.make_qparams(mode=binding.CWAC_EPI_FP_BIAS)
+    f = lib.qlinear_cwac_forward_table_ex
+    for kernel in (binding.CWAC_KERNEL_AUTO, binding.CWAC_KERNEL_DIRECT_LDS, binding.CWAC_KERNEL_GENERIC_64):
+        t = binding.make_tuning(kernel=kernel)
+        assert f(a, k, a, k, m, n, k, C.byref(qp), a, null, a, a, n, C.byref(t), null) == -4
+    assert lib.qlinear_cwac_forward_table(a, k, a, k, m, n, k, C.byref(qp), a, null, a, a, n, null) == -4
