@@ -28,6 +28,7 @@
 #include <type_traits>
 
 #include "qlinear_common.h"
+#include "w4_rules.h"
 
 namespace cwac {
 namespace {
@@ -530,9 +531,6 @@ cwac_status launch_w4(const W4Params &p, hipStream_t st) {
 // for all MB columns.  The partial tiles are added in wavefront order through LDS (deterministic), by all threads,
 // then the epilogue of the tiled kernel.  No workspace, no atomics.
 // ------------------------------------------------------------------------------------------
-// 128-token tiles in a launch up to which the tiled kernel takes them (one per compute unit)
-constexpr int kHalfTileUpTo = 256;
-
 template <int NB_, int MP_, int NW_, int D_>
 struct StreamCfg {
   static constexpr int NB = NB_, MP = MP_, NW = NW_, D = D_;
@@ -755,45 +753,8 @@ cwac_status launch_w4_stream_cfg(W4Params p, int out_kind, hipStream_t st) {
   }
 }
 
-// Tile of the weight-streaming kernel by size; waves / depth: the caller's overrides (cwac_tuning.w4_small_waves /
-// w4_small_depth), which keep to 32 channels and at most 32 tokens per workgroup.
-struct StreamChoice {
-  int cfg = 0;          // launch_w4_stream's case
-  double cost = 1e30;   // estimated microseconds
-};
-// A workgroup's time is its share of the operand stream; a round of one workgroup per compute unit takes
-// c * k / 4096 microseconds, and 2 go to launch and epilogue.  c as measured (weights cold, n = 4096 .. 12288,
-// k = 4096 and 11008).  What the tiles trade: fewer tokens per workgroup read the weights more often, fewer channels
-// the activations, and each halves when its factor doubles, until there is less than a round of workgroups.
-inline StreamChoice stream_choice(int64_t m, int n, int k) {
-  struct Tile {
-    int nb, mp;
-    double c;
-  };
-  constexpr Tile tiles[] = {{1, 16, 4.2}, {1, 32, 5.0}, {2, 32, 8.5}, {1, 64, 8.0}, {2, 64, 12.3}, {2, 128, 21.5}};
-  StreamChoice best;
-  if (m <= 8) {
-    best.cfg = 1;
-    best.cost = 0.0;
-    return best;
-  }
-  for (int i = 0; i < 6; ++i) {
-    const int64_t wgs = ceil_div(m, tiles[i].mp) * ceil_div(n, 32 * tiles[i].nb);
-    const double cost = 2.0 + (double)ceil_div(wgs, 256) * tiles[i].c * (double)k / 4096.0;
-    if (cost < best.cost) {
-      best.cost = cost;
-      best.cfg = i + 2;
-    }
-  }
-  return best;
-}
-// Whether the weight-streaming kernel beats the tiled one, whose first round of 128-token tiles costs 3 + 0.0127 k: a
-// tile walks all of k by itself.  Measured, tiled -> streaming: 128 x 4096 x 4096 55 -> 10.0, 400 x 4096 x 4096 55.5 ->
-// 24.1, 256 x 4096 x 11008 119 -> 34.1, 200 x 12288 x 4096 56.7 -> 41.3; level at 400 x 12288 x 4096 (68.9 / 68.5).
-inline bool stream_pays(int64_t m, int n, int k, const StreamChoice &c) {
-  return ceil_div(m, 128) * ceil_div(n, 256) <= 256 && c.cost < 3.0 + 0.0127 * (double)k;
-}
-
+// waves / depth: the caller's overrides (cwac_tuning.w4_small_waves / w4_small_depth), which keep to 32 channels and at most
+// 32 tokens per workgroup.
 template <int NW>
 cwac_status launch_w4_stream_forced(const W4Params &p, int depth, int out_kind, hipStream_t st) {
 #define CWAC_W4_DEPTH(MP)                                                           \
@@ -806,20 +767,24 @@ cwac_status launch_w4_stream_forced(const W4Params &p, int depth, int out_kind, 
 #undef CWAC_W4_DEPTH
 }
 
-cwac_status launch_w4_stream(const W4Params &p, int cfg, int waves, int depth, int out_kind, hipStream_t st) {
+template <int I>
+cwac_status launch_w4_stream_tile(const W4Params &p, int out_kind, hipStream_t st) {
+  return launch_w4_stream_cfg<kW4Stream[I].nb, kW4Stream[I].mp, kW4Stream[I].nw, kW4Stream[I].depth>(p, out_kind, st);
+}
+
+cwac_status launch_w4_stream(const W4Params &p, int tile, int waves, int depth, int out_kind, hipStream_t st) {
   if (waves || depth)
     return waves == 4 ? launch_w4_stream_forced<4>(p, depth, out_kind, st) : launch_w4_stream_forced<8>(p, depth, out_kind, st);
-  // Wavefronts and ring depth as measured best: eight wavefronts where their rings fit the LDS (two per SIMD, so that
-  // one's LDS reads run under the other's MFMAs), two slots each (three: within 3 %; four of 8 rows: 4 % slower).
-  switch (cfg) {
-    case 1: return launch_w4_stream_cfg<1, 8, 8, 2>(p, out_kind, st);
-    case 2: return launch_w4_stream_cfg<1, 16, 8, 3>(p, out_kind, st);
-    case 3: return launch_w4_stream_cfg<1, 32, 8, 2>(p, out_kind, st);
-    case 4: return launch_w4_stream_cfg<2, 32, 8, 2>(p, out_kind, st);
-    case 5: return launch_w4_stream_cfg<1, 64, 8, 2>(p, out_kind, st);
-    case 6: return launch_w4_stream_cfg<2, 64, 4, 2>(p, out_kind, st);
-    case 7: return launch_w4_stream_cfg<2, 128, 4, 2>(p, out_kind, st);
+  switch (tile) {
+    case 0: return launch_w4_stream_tile<0>(p, out_kind, st);
+    case 1: return launch_w4_stream_tile<1>(p, out_kind, st);
+    case 2: return launch_w4_stream_tile<2>(p, out_kind, st);
+    case 3: return launch_w4_stream_tile<3>(p, out_kind, st);
+    case 4: return launch_w4_stream_tile<4>(p, out_kind, st);
+    case 5: return launch_w4_stream_tile<5>(p, out_kind, st);
+    case 6: return launch_w4_stream_tile<6>(p, out_kind, st);
   }
+  static_assert(kW4StreamTiles == 7, "one case per tile");
   return CWAC_E_MODE;
 }
 
@@ -913,14 +878,14 @@ cwac_status qlinear_w4a16_cwac_forward_ex(const uint16_t *x, int64_t ldx, const 
   p.tiles_n = (int)ceil_div(n, 256);
   // The caller's override (results agree to the rounding of the fp32 sums): w4_tile = 256 keeps the
   // 256-token tiles at every batch size, 128 the 128-token tiles.  Otherwise the weight-streaming kernel where it pays.
-  const StreamChoice stream = stream_choice(m, n, k);
-  if (w4_tile == 0 && stream_pays(m, n, k, stream))
-    return launch_w4_stream(p, stream.cfg, small_waves, small_depth, out_kind, as_stream(stream_handle));
+  const W4StreamChoice stream = w4_stream_choice(m, n, k);
+  if (w4_tile == 0 && w4_stream_pays(m, n, k, stream))
+    return launch_w4_stream(p, stream.tile, small_waves, small_depth, out_kind, as_stream(stream_handle));
   // 128-token tiles while they fit the chip in one round (one tile per compute unit): a half tile
   // takes about two thirds of a full tile's time (the weight expansion is per channel block, not
   // per token, so it spends more vector work per MFMA), which pays exactly while the full tiles
   // would leave compute units idle
-  const bool half = w4_tile == 128 || (w4_tile == 0 && ceil_div(m, 128) * p.tiles_n <= kHalfTileUpTo);
+  const bool half = w4_tile == 128 || (w4_tile == 0 && ceil_div(m, 128) * p.tiles_n <= kW4HalfTileUpTo);
   if (half) {
     p.tiles_m = (int)ceil_div(m, 128);
     return out_kind == CWAC_OUT_FP16 ? launch_w4<CWAC_OUT_FP16, 2>(p, as_stream(stream_handle))

@@ -1,0 +1,50 @@
+"""The library's HIP-free dispatch rules (paper_2505_20932_amd/csrc/*_rules.h), compiled with g++ for the CPU tests."""
+import ctypes as C
+import os
+import subprocess
+import tempfile
+
+_ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+_CSRC = os.path.join(_ROOT, "paper_2505_20932_amd", "csrc")
+
+_SHIM = r"""
+#include "w4_rules.h"
+using namespace cwac;
+// the weight-streaming kernel's tile for the layer, -1 where the tiled kernel takes it
+extern "C" int w4_tile(long long m, int n, int k) {
+  const W4StreamChoice c = w4_stream_choice(m, n, k);
+  return w4_stream_pays(m, n, k, c) ? c.tile : -1;
+}
+extern "C" int w4_tiles() { return kW4StreamTiles; }
+extern "C" void w4_shape(int tile, int *out) {
+  const W4StreamTile &t = kW4Stream[tile];
+  out[0] = t.nb, out[1] = t.mp, out[2] = t.nw, out[3] = t.depth;
+}
+"""
+_lib = None
+
+
+def lib():
+    global _lib
+    if _lib is None:
+        with tempfile.TemporaryDirectory() as d:
+            src, so = os.path.join(d, "rules.cpp"), os.path.join(d, "rules.so")
+            with open(src, "w") as f:
+                f.write(_SHIM)
+            subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", _CSRC, src, "-o", so],
+                           check=True)
+            _lib = C.CDLL(so)
+        _lib.w4_tile.argtypes = [C.c_longlong, C.c_int, C.c_int]
+        _lib.w4_shape.argtypes = [C.c_int, C.POINTER(C.c_int)]
+    return _lib
+
+
+def w4_tile(m, n, k):
+    return lib().w4_tile(m, n, k)
+
+
+def w4_shape(tile):
+    """(blocks of 32 channels, tokens, wavefronts, ring depth) of the weight-streaming kernel's tile."""
+    out = (C.c_int * 4)()
+    lib().w4_shape(tile, out)
+    return tuple(out)
