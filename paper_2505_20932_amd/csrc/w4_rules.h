@@ -10,31 +10,35 @@ namespace cwac {
 // units of 64 input channels.  Wavefronts and ring depth as measured best: eight wavefronts where their rings fit the
 // LDS (two per SIMD, so that one's LDS reads run under the other's MFMAs), two slots each (three: within 3 %; four of 8
 // rows: 4 % slower).  us: a round of one workgroup per compute unit at k = 4096, measured with cold weights at
-// n = 4096 .. 12288 and k = 4096 and 11008; taken to grow with k.
+// n = 4096 .. 12288 and k = 4096 and 11008; the choice among the tiles takes it to grow with k.  short_us, long_us: a round
+// costs short_us + long_us k / 4096 (launches of 1 to 16 rounds, k = 128 .. 4096, n = 512 .. 131072; rms 6 to 8 %): what a
+// workgroup does besides its K loop weighs as much as the loop where k is a few hundred.
 struct W4StreamTile {
   int nb, mp, nw, depth;
-  double us;
+  double us, short_us, long_us;
 };
-constexpr W4StreamTile kW4Stream[] = {{1, 8, 8, 2, 4.2},  {1, 16, 8, 3, 4.2}, {1, 32, 8, 2, 5.0},  {2, 32, 8, 2, 8.5},
-                                      {1, 64, 8, 2, 8.0}, {2, 64, 4, 2, 12.3}, {2, 128, 4, 2, 21.5}};
+constexpr W4StreamTile kW4Stream[] = {{1, 8, 8, 2, 4.2, 0.5, 2.7},  {1, 16, 8, 3, 4.2, 0.7, 3.2},  {1, 32, 8, 2, 5.0, 1.6, 4.5},
+                                      {2, 32, 8, 2, 8.5, 2.5, 6.8}, {1, 64, 8, 2, 8.0, 2.1, 7.3},  {2, 64, 4, 2, 12.3, 2.9, 10.2},
+                                      {2, 128, 4, 2, 21.5, 5.1, 17.0}};
 constexpr int kW4StreamTiles = (int)(sizeof(kW4Stream) / sizeof(kW4Stream[0]));
 
-struct W4StreamChoice {
-  int tile = 0;         // index into kW4Stream
-  double cost = 1e30;   // estimated microseconds
-};
+// rounds of one workgroup per compute unit
+inline double w4_stream_rounds(const W4StreamTile &t, int64_t m, int n) {
+  const int64_t wgs = ((m + t.mp - 1) / t.mp) * (((int64_t)n + 32 * t.nb - 1) / (32 * t.nb));
+  return (double)((wgs + 255) / 256);
+}
 
-// What the tiles trade: fewer tokens per workgroup read the weights more often, fewer channels the activations, and each
-// halves when its factor doubles, until there is less than a round of workgroups.  2 us go to launch and epilogue.
-inline W4StreamChoice w4_stream_choice(int64_t m, int n, int k) {
-  W4StreamChoice best;
-  for (int i = m <= 8 ? 0 : 1; i < (m <= 8 ? 1 : kW4StreamTiles); ++i) {
-    const W4StreamTile &t = kW4Stream[i];
-    const int64_t wgs = ((m + t.mp - 1) / t.mp) * (((int64_t)n + 32 * t.nb - 1) / (32 * t.nb));
-    const double cost = 2.0 + (double)((wgs + 255) / 256) * t.us * (double)k / 4096.0;
-    if (cost < best.cost) {
-      best.cost = cost;
-      best.tile = i;
+// The tile (index into kW4Stream).  What the tiles trade: fewer tokens per workgroup read the weights more often, fewer
+// channels the activations, and each halves when its factor doubles, until there is less than a round of workgroups.
+inline int w4_stream_tile(int64_t m, int n, int k) {
+  if (m <= 8) return 0;
+  int best = 1;
+  double cost = 1e30;
+  for (int i = 1; i < kW4StreamTiles; ++i) {
+    const double c = w4_stream_rounds(kW4Stream[i], m, n) * kW4Stream[i].us * (double)k / 4096.0;
+    if (c < cost) {
+      cost = c;
+      best = i;
     }
   }
   return best;
@@ -43,15 +47,23 @@ inline W4StreamChoice w4_stream_choice(int64_t m, int n, int k) {
 // 128-token tiles of the tiled kernel in a launch up to which it takes them (one per compute unit)
 constexpr int64_t kW4HalfTileUpTo = 256;
 
-// Whether the weight-streaming kernel takes the layer.  Up to 32 tokens always: the layer is its weight stream, and a tile
-// of the tiled kernel would compute 128 token rows for them.  Tiled -> streaming, 1 / 16 / 32 tokens: 131072 x 4096
-// 99 / 104 / 104 us -> 58 / 76 / 91, 151936 x 4096 173 / 177 / 178 -> 64 / 88 / 108.  Above 32, against the tiled kernel's first round of 128-token
-// tiles, which costs 3 + 0.0127 k: a tile walks all of k by itself.  Measured, tiled -> streaming: 128 x 4096 x 4096
-// 55 -> 10.0, 400 x 4096 x 4096 55.5 -> 24.1, 256 x 4096 x 11008 119 -> 34.1, 200 x 12288 x 4096 56.7 -> 41.3; level at
-// 400 x 12288 x 4096 (68.9 / 68.5).
-inline bool w4_stream_pays(int64_t m, int n, int k, const W4StreamChoice &c) {
+// Whether the weight-streaming kernel takes the layer, with the tile above.  Up to 32 tokens always: the layer is its weight
+// stream, and a tile of the tiled kernel would compute 128 token rows for them.  Tiled -> streaming, 1 / 16 / 32 tokens:
+// 131072 x 4096 99 / 104 / 104 us -> 58 / 76 / 91, 151936 x 4096 173 / 177 / 178 -> 64 / 88 / 108.
+// Above 32, against one round of the tiled kernel's 128-token tiles: each walks all of k by itself, but a wide layer with a
+// short k needs one round where the streaming kernel needs several.  Both estimates were fitted to 900 launches; the tiled
+// one is taken 5 % low, since the tiled kernel loses less where the two are close.  Measured, tiled -> streaming:
+// 128 x 4096 x 4096 55 -> 10.0, 400 x 4096 x 4096 55.5 -> 24.1, 256 x 4096 x 11008 119 -> 34.1, 200 x 12288 x 4096
+// 56.7 -> 41.3; level at 400 x 12288 x 4096 (68.9 / 68.5); behind at 200 x 24576 x 128 (7.3 / 16.8), 384 x 12288 x 384
+// (10.8 / 20.3) and 128 x 32768 x 768 (16.4 / 19.5).
+inline bool w4_stream_pays(int64_t m, int n, int k, int tile) {
   if (m <= 32) return true;
-  return ((m + 127) / 128) * (((int64_t)n + 255) / 256) <= kW4HalfTileUpTo && c.cost < 3.0 + 0.0127 * (double)k;
+  if (((m + 127) / 128) * (((int64_t)n + 255) / 256) > kW4HalfTileUpTo) return false;
+  const W4StreamTile &t = kW4Stream[tile];
+  const double dk = (double)k, dn = (double)n;
+  const double stream = 1.0 + w4_stream_rounds(t, m, n) * (t.short_us + t.long_us * dk / 4096.0);
+  const double tiled = 3.7 + 0.0125 * dk + 0.44e-6 * (double)m * dn + 6.0e-8 * dn * dk;
+  return stream < 0.95 * tiled;
 }
 
 }  // namespace cwac

@@ -878,9 +878,9 @@ cwac_status qlinear_w4a16_cwac_forward_ex(const uint16_t *x, int64_t ldx, const 
   p.tiles_n = (int)ceil_div(n, 256);
   // The caller's override (results agree to the rounding of the fp32 sums): w4_tile = 256 keeps the
   // 256-token tiles at every batch size, 128 the 128-token tiles.  Otherwise the weight-streaming kernel where it pays.
-  const W4StreamChoice stream = w4_stream_choice(m, n, k);
-  if (w4_tile == 0 && w4_stream_pays(m, n, k, stream))
-    return launch_w4_stream(p, stream.tile, small_waves, small_depth, out_kind, as_stream(stream_handle));
+  const int stream_tile = w4_stream_tile(m, n, k);
+  if (w4_tile == 0 && w4_stream_pays(m, n, k, stream_tile))
+    return launch_w4_stream(p, stream_tile, small_waves, small_depth, out_kind, as_stream(stream_handle));
   // 128-token tiles while they fit the chip in one round (one tile per compute unit): a half tile
   // takes about two thirds of a full tile's time (the weight expansion is per channel block, not
   // per token, so it spends more vector work per MFMA), which pays exactly while the full tiles

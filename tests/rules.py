@@ -12,8 +12,8 @@ _SHIM = r"""
 using namespace cwac;
 // the weight-streaming kernel's tile for the layer, -1 where the tiled kernel takes it
 extern "C" int w4_tile(long long m, int n, int k) {
-  const W4StreamChoice c = w4_stream_choice(m, n, k);
-  return w4_stream_pays(m, n, k, c) ? c.tile : -1;
+  const int tile = w4_stream_tile(m, n, k);
+  return w4_stream_pays(m, n, k, tile) ? tile : -1;
 }
 extern "C" int w4_tiles() { return kW4StreamTiles; }
 extern "C" void w4_shape(int tile, int *out) {
