@@ -1,0 +1,69 @@
+// Which tile of the direct-to-LDS int8 kernel takes a layer.  Host arithmetic on sizes only, no HIP: the launchers and a CPU
+// test share it.
+#pragma once
+
+#include <stdint.h>
+
+#include "cwac.h"
+
+namespace cwac {
+
+inline int64_t tiles_of(int64_t m, int n, int bm, int bn) { return ((m + bm - 1) / bm) * (((int64_t)n + bn - 1) / bn); }
+
+// True where it takes 128 x 128 tiles (layers with few tiles and a long K loop).
+inline bool fast_prefers_quarter_tile(int64_t m, int n) {
+  // Layers with too few 128 x 256 tiles to occupy the chip: a tile's duration is the K loop of one
+  // wavefront, so 128 x 128 tiles of four 64 x 64 wavefronts (half the MFMAs per wavefront and K step,
+  // twice the tiles) finish sooner.  Thresholds from measurements on LLM layer shapes at 256-2048
+  // tokens and ResNet-50 stage 5: ahead from 96 such tiles on, until 160 half tiles exist.
+  const int64_t t_half = tiles_of(m, n, 128, 256), t_q = tiles_of(m, n, 128, 128);
+  return n >= 128 && t_half < 160 && t_q >= 96;
+}
+
+// K step and ring depth of the 128 x 128 tile (four wavefronts of 64 x 64; `kstep`: K or the channels of a filter tap).
+// Measured, microseconds at m x n x k, int8 output unless noted:
+//   0: 64-byte steps, three stages, three workgroups per compute unit: where steps of 128 do not divide K, and for
+//      4-byte outputs in more than two rounds of tiles (their stores weigh as much as the K loop: 12608 x 3072 x 768 fp32
+//      52.8 / 54.6 with 1).
+//   1: 128-byte steps, two stages, two workgroups per compute unit: half the barriers.  4616 x 768 x 768 9.0 -> 8.1,
+//      7252 x 512 x 512 7.1 -> 6.5, 2000 x 3072 x 768 11.8 -> 10.0.
+//   2: 128-byte steps, three stages, one workgroup per compute unit: one round of tiles and a long K, where nothing
+//      else covers a stage's round trip.  4616 x 768 x 3072 19.6 -> 16.1, 1000 x 4096 x 4096 30.7 -> 23.2,
+//      7252 x 512 x 2048 14.6 -> 12.8 (14.4 with 1), 6272 x 256 x 1024 8.5 -> 8.6 (8.4 with 1).
+inline int quarter_ring(int64_t m, int n, int k, int kstep, bool wide) {
+  const int64_t tiles = tiles_of(m, n, 128, 128);
+  if ((kstep % 128) != 0 || (wide && tiles > 512)) return 0;
+  return tiles <= 256 && k >= 1536 ? 2 : 1;
+}
+
+// The 128-token x 256-channel tile on one workgroup per compute unit with 128-byte steps and three stages: one round of
+// tiles and a long K.  2048 x 4096 x 4096 42.9 -> 35.1, 500 x 11008 x 4096 39.8 -> 33.2, 2000 x 4096 x 11008 fp32 105.8 -> 88.7.
+inline bool half_deep(int64_t m, int n, int k) {
+  return (k % 128) == 0 && k >= 3072 && tiles_of(m, n, 128, 256) <= 256;
+}
+
+// The tile shape (CWAC_SHAPE_*) it picks by itself for a linear layer with n >= 256.
+inline int fast_linear_shape(int64_t m, int n, int k, int out_bytes) {
+  // The automatic tile shape of a linear layer with n >= 256, from measurements on the ViT / Swin / LLM
+  // layer shapes (K 512 .. 11008, 196 .. 3072 tiles of 256 x 256).
+  //  * Few tiles and a long K loop: 128 x 128 tiles (fast_prefers_quarter_tile).
+  //  * Less than a round of 256 x 256 tiles: 128 x 256 tiles where they are one round and K is long (half_deep), else
+  //    the persistent tile from half a round on (3152 x 3072 x 768, 156 tiles: 14.3 us, 128 x 128 tiles 15.2; 12608 x 768 x
+  //    3072 fp32, 150 tiles: 39.4 / 45.7), else 128 x 128 tiles (2000 x 3072 x 768, 96 tiles: 13.6 / 10.0).
+  //  * Otherwise the persistent 256 x 256 tile (which splits the tiles of a thin last round in two).
+  //    With 4-byte outputs and a short K loop the tile's store burst weighs as much as its K loop:
+  //    when, on top, the last round leaves a good part of the chip idle, the 128 x 128 tile (three
+  //    workgroups per compute unit, four times as many tiles, stores spread out) finishes sooner.
+  if (fast_prefers_quarter_tile(m, n)) return CWAC_SHAPE_128_128;
+  if ((k % 128) != 0) return CWAC_SHAPE_128_PAIR;
+  const int64_t t256 = tiles_of(m, n, 256, 256);
+  if (t256 < 160) {
+    if (half_deep(m, n, k)) return CWAC_SHAPE_128_PAIR;
+    return t256 >= 128 ? CWAC_SHAPE_256_PERSIST : CWAC_SHAPE_128_128;
+  }
+  const double fill = (double)t256 / (double)(256 * ((t256 + 255) / 256));  // busy share of the rounds
+  if (out_bytes > 1 && k <= 1024 && fill < 0.85) return CWAC_SHAPE_128_128;
+  return CWAC_SHAPE_256_PERSIST;
+}
+
+}  // namespace cwac

@@ -8,6 +8,7 @@ _ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 _CSRC = os.path.join(_ROOT, "paper_2505_20932_amd", "csrc")
 
 _SHIM = r"""
+#include "fast_rules.h"
 #include "w4_rules.h"
 using namespace cwac;
 // the weight-streaming kernel's tile for the layer, -1 where the tiled kernel takes it
@@ -15,6 +16,8 @@ extern "C" int w4_tile(long long m, int n, int k) {
   const int tile = w4_stream_tile(m, n, k);
   return w4_stream_pays(m, n, k, tile) ? tile : -1;
 }
+// the direct-to-LDS kernel's tile shape for a linear layer of n >= 256 channels
+extern "C" int fast_shape(long long m, int n, int k, int out_bytes) { return fast_linear_shape(m, n, k, out_bytes); }
 extern "C" int w4_tiles() { return kW4StreamTiles; }
 extern "C" void w4_shape(int tile, int *out) {
   const W4StreamTile &t = kW4Stream[tile];
@@ -31,16 +34,22 @@ def lib():
             src, so = os.path.join(d, "rules.cpp"), os.path.join(d, "rules.so")
             with open(src, "w") as f:
                 f.write(_SHIM)
-            subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", _CSRC, src, "-o", so],
+            subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", _CSRC, "-I", os.path.join(_ROOT, "include"), src, "-o", so],
                            check=True)
             _lib = C.CDLL(so)
         _lib.w4_tile.argtypes = [C.c_longlong, C.c_int, C.c_int]
+        _lib.fast_shape.argtypes = [C.c_longlong, C.c_int, C.c_int, C.c_int]
         _lib.w4_shape.argtypes = [C.c_int, C.POINTER(C.c_int)]
     return _lib
 
 
 def w4_tile(m, n, k):
     return lib().w4_tile(m, n, k)
+
+
+def fast_shape(m, n, k, out_bytes):
+    """CWAC_SHAPE_* the direct-to-LDS kernel picks for a linear layer of at least 256 channels."""
+    return lib().fast_shape(m, n, k, out_bytes)
 
 
 def w4_shape(tile):
