@@ -48,8 +48,11 @@ inline int fast_linear_shape(int64_t m, int n, int k, int out_bytes) {
   // layer shapes (K 512 .. 11008, 196 .. 3072 tiles of 256 x 256).
   //  * Few tiles and a long K loop: 128 x 128 tiles (fast_prefers_quarter_tile).
   //  * Less than a round of 256 x 256 tiles: 128 x 256 tiles where they are one round and K is long (half_deep), else
-  //    the persistent tile from half a round on (3152 x 3072 x 768, 156 tiles: 14.3 us, 128 x 128 tiles 15.2; 12608 x 768 x
-  //    3072 fp32, 150 tiles: 39.4 / 45.7), else 128 x 128 tiles (2000 x 3072 x 768, 96 tiles: 13.6 / 10.0).
+  //    128 x 128 tiles where those are at most two rounds, two workgroups to a compute unit (2000 x 3072 x 768, 384 of
+  //    them: 10.0 us, persistent tile 13.6; 1979 x 3952 x 1280, 496: 16.2 / 21.1; 16337 x 448 x 1664, 512: 18.2 / 23.4), or
+  //    where K is too short for a tile's loop to matter (8031 x 816 x 128: 9.2 / 12.6; 3106 x 2656 x 128: 8.2 / 9.1; level
+  //    at K = 384), else the persistent tile (3152 x 3072 x 768, 600 of them: 14.3, 128 x 128 tiles 15.2; 12608 x 768 x
+  //    3072 fp32, 594: 39.4 / 45.7).
   //  * Otherwise the persistent 256 x 256 tile (which splits the tiles of a thin last round in two).
   //    With 4-byte outputs and a short K loop the tile's store burst weighs as much as its K loop:
   //    when, on top, the last round leaves a good part of the chip idle, the 128 x 128 tile (three
@@ -59,7 +62,7 @@ inline int fast_linear_shape(int64_t m, int n, int k, int out_bytes) {
   const int64_t t256 = tiles_of(m, n, 256, 256);
   if (t256 < 160) {
     if (half_deep(m, n, k)) return CWAC_SHAPE_128_PAIR;
-    return t256 >= 128 ? CWAC_SHAPE_256_PERSIST : CWAC_SHAPE_128_128;
+    return tiles_of(m, n, 128, 128) <= 512 || k <= 256 ? CWAC_SHAPE_128_128 : CWAC_SHAPE_256_PERSIST;
   }
   const double fill = (double)t256 / (double)(256 * ((t256 + 255) / 256));  // busy share of the rounds
   if (out_bytes > 1 && k <= 1024 && fill < 0.85) return CWAC_SHAPE_128_128;

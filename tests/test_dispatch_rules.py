@@ -2,6 +2,7 @@
 import pytest
 
 import rules
+from paper_2505_20932_amd import binding as B
 
 WIDE = (65536, 65568, 98304, 128256, 131072, 151936, 262144)
 
@@ -30,3 +31,14 @@ MEASURED = [(384, 12288, 128, 7.0, 16.3), (200, 24576, 128, 7.3, 16.8), (100, 49
 def test_weight_only_mid_batch_takes_the_kernel_that_measured_faster(m, n, k, tiled, streaming):
     """A wide layer with a short K is one round of the tiled kernel and several of the streaming one's."""
     assert (rules.w4_tile(m, n, k) >= 0) == (streaming < tiled)
+
+
+# microseconds measured with cold weights: the persistent 256 x 256 tile, 128 x 128 tiles
+@pytest.mark.parametrize("m,n,k,out_bytes,persistent,quarter",
+                         [(1979, 3952, 1280, 1, 21.1, 16.2), (16337, 448, 1664, 1, 23.4, 18.2), (3193, 2416, 384, 1, 12.7, 9.2),
+                          (1310, 5600, 384, 4, 13.6, 10.4), (1863, 4064, 128, 1, 9.5, 6.8), (8031, 816, 128, 4, 12.6, 9.2),
+                          (7107, 1072, 128, 1, 9.2, 6.4), (3106, 2656, 128, 1, 9.1, 8.2), (1517, 6256, 128, 4, 13.8, 11.8),
+                          (2000, 3072, 768, 1, 13.6, 10.0), (3152, 3072, 768, 1, 14.3, 15.2), (12608, 768, 3072, 4, 39.4, 45.7)])
+def test_half_a_round_of_large_tiles_takes_the_tile_that_measured_faster(m, n, k, out_bytes, persistent, quarter):
+    want = B.CWAC_SHAPE_128_128 if quarter < persistent else B.CWAC_SHAPE_256_PERSIST
+    assert rules.fast_shape(m, n, k, out_bytes) == want
