@@ -4,6 +4,7 @@
 
 #include "cwac_internal.h"
 #include "fast_rules.h"
+#include "splitk_rules.h"
 
 namespace cwac {
 
@@ -261,8 +262,6 @@ cwac_status launch_fast_stats(FwdParams p, int waves, hipStream_t st);
 // Small-problem kernel (qlinear_splitk.hip): any m, n and k % 16 == 0 with fast_pitch_ok(ldx, ldw); every output kind
 // but kOutStats, p.code_table set for kOutTable.
 cwac_status launch_splitk(const FwdParams &p, int out_kind, bool int_only, hipStream_t st);
-// The tile it takes, 0 where the tile kernels are faster.
-int splitk_tile(int64_t m, int n, int k);
 constexpr int kFastTile = 256;
 constexpr int kFastKStep = 128;
 

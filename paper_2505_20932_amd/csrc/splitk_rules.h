@@ -1,0 +1,41 @@
+// Which tile of the small-problem int8 kernel (qlinear_splitk.hip) takes a layer.  Host arithmetic on sizes only, no HIP: the
+// launcher and a CPU test share it.
+#pragma once
+
+#include <stdint.h>
+
+#include "fast_rules.h"
+
+namespace cwac {
+
+// Its tiles: 16 tn channels x 16 tm tokens, K split over w wavefronts with rings of d units of 128 bytes of K.
+struct SplitkTile {
+  int tn, tm, w, d;
+};
+constexpr SplitkTile kSplitk[] = {{0, 0, 0, 0}, {1, 1, 4, 4}, {2, 1, 4, 3}, {2, 2, 4, 2}, {4, 4, 4, 2}};
+
+// The tile (index into kSplitk), 0 where the tile kernels are faster.
+inline int splitk_tile(int64_t m, int n, int k) {
+  // Measured against the 64 x 64 tile kernel and among 15 tiles / wavefront counts / ring depths, weights cold
+  // (microseconds at m x n x k, tile kernel -> this one):
+  //   m <= 16: 16 x 16 tiles.  16 x 4096 x 4096 29.2 -> 6.7, 16 x 12288 x 4096 30.6 -> 13.1 (3.9 TB/s),
+  //     16 x 4096 x 11008 70.0 -> 12.7.
+  if (m <= 16) return 1;
+  const int64_t t32 = tiles_of(m, n, 32, 32), t64 = tiles_of(m, n, 64, 64);
+  //   17 .. 32 tokens of a layer whose 32 x 32 tiles would leave compute units idle: 32 channels x 16 tokens.
+  //     32 x 4096 x 4096 29.1 -> 7.2 (32 x 32 tiles: 9.0); 32 x 11008 x 4096 16.5 against 15.4 with 32 x 32 tiles.
+  if (m <= 32 && t32 <= 192) return 2;
+  //   64 x 64 tiles halve the operand traffic of 32 x 32 ones, but only one workgroup fits a compute unit: where
+  //     they fill one round and K is long.  200 x 4096 x 4096 28.8 -> 13.0 (18.2 with 32 x 32 tiles),
+  //     200 x 4096 x 11008 67.9 -> 24.8 (40.9), 64 x 12288 x 4096 30.5 -> 17.3 (18.9); but 394 x 768 x 3072 (84 tiles)
+  //     9.6 against 7.5, 1576 x 768 x 3072 (300 tiles) 17.8 against 15.8, 197 x 3072 x 768 6.9 against 6.7.
+  if (t32 > 512 && t64 <= 256 && k >= 1024) return 4;
+  //   32 x 32 tiles: 197 x 768 x 768 5.7 -> 3.5, 197 x 768 x 3072 16.7 -> 5.0, 197 x 1152 x 384 4.5 -> 3.2.  The tile
+  //     kernel's time grows with K, this one's with the rounds of tiles: level at 2.3 rounds for K = 768
+  //     (788 x 768: 6.7 / 6.8) and 4.4 for K = 1536 (3000 x 384: 10.9 / 10.7); ahead at 4.7 rounds for K = 3072
+  //     (1576 x 768: 15.8 / 18.0) and 6 for 4096 (128 x 12288: 30.0 / 31.6), behind at 9.4 (200 x 11008: 41.0 / 33.4).
+  const double rounds = (double)t32 / 256.0, most = 1.0 + (double)k / 480.0;
+  return rounds <= (most < 6.0 ? most : 6.0) ? 3 : 0;
+}
+
+}  // namespace cwac

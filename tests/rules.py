@@ -9,6 +9,7 @@ _CSRC = os.path.join(_ROOT, "paper_2505_20932_amd", "csrc")
 
 _SHIM = r"""
 #include "fast_rules.h"
+#include "splitk_rules.h"
 #include "w4_rules.h"
 using namespace cwac;
 // the weight-streaming kernel's tile for the layer, -1 where the tiled kernel takes it
@@ -18,6 +19,12 @@ extern "C" int w4_tile(long long m, int n, int k) {
 }
 // the direct-to-LDS kernel's tile shape for a linear layer of n >= 256 channels
 extern "C" int fast_shape(long long m, int n, int k, int out_bytes) { return fast_linear_shape(m, n, k, out_bytes); }
+// the small-problem kernel's tile, 0 where the tile kernels take the layer
+extern "C" int split_tile(long long m, int n, int k) { return splitk_tile(m, n, k); }
+extern "C" void split_shape(int tile, int *out) {
+  const SplitkTile &t = kSplitk[tile];
+  out[0] = t.tn, out[1] = t.tm, out[2] = t.w, out[3] = t.d;
+}
 extern "C" int w4_tiles() { return kW4StreamTiles; }
 extern "C" void w4_shape(int tile, int *out) {
   const W4StreamTile &t = kW4Stream[tile];
@@ -38,6 +45,8 @@ def lib():
                            check=True)
             _lib = C.CDLL(so)
         _lib.w4_tile.argtypes = [C.c_longlong, C.c_int, C.c_int]
+        _lib.split_tile.argtypes = [C.c_longlong, C.c_int, C.c_int]
+        _lib.split_shape.argtypes = [C.c_int, C.POINTER(C.c_int)]
         _lib.fast_shape.argtypes = [C.c_longlong, C.c_int, C.c_int, C.c_int]
         _lib.w4_shape.argtypes = [C.c_int, C.POINTER(C.c_int)]
     return _lib
@@ -50,6 +59,17 @@ def w4_tile(m, n, k):
 def fast_shape(m, n, k, out_bytes):
     """CWAC_SHAPE_* the direct-to-LDS kernel picks for a linear layer of at least 256 channels."""
     return lib().fast_shape(m, n, k, out_bytes)
+
+
+def split_tile(m, n, k):
+    return lib().split_tile(m, n, k)
+
+
+def split_shape(tile):
+    """(16-channel blocks, 16-token blocks, wavefronts, ring depth) of the small-problem kernel's tile."""
+    out = (C.c_int * 4)()
+    lib().split_shape(tile, out)
+    return tuple(out)
 
 
 def w4_shape(tile):
