@@ -34,8 +34,11 @@ inline int splitk_tile(int64_t m, int n, int k) {
   //     kernel's time grows with K, this one's with the rounds of tiles: level at 2.3 rounds for K = 768
   //     (788 x 768: 6.7 / 6.8) and 4.4 for K = 1536 (3000 x 384: 10.9 / 10.7); ahead at 4.7 rounds for K = 3072
   //     (1576 x 768: 15.8 / 18.0) and 6 for 4096 (128 x 12288: 30.0 / 31.6), behind at 9.4 (200 x 11008: 41.0 / 33.4).
-  const double rounds = (double)t32 / 256.0, most = 1.0 + (double)k / 480.0;
-  return rounds <= (most < 6.0 ? most : 6.0) ? 3 : 0;
+  //     Rows that are no whole number of 64-byte pieces cost the direct-to-LDS loads more than the tile kernel's: four
+  //     rounds there (350 x 3040 x 1776, 4.1 rounds: 11.8 / 12.9; 547 x 2352 x 3472, 5.2: 20.1 / 23.4; 286 x 5120 x 8944,
+  //     5.6: 62.5 / 72.4; 1712 at 3.9 rounds: 0.89 of the tile kernel's time).
+  const double rounds = (double)t32 / 256.0, most = 1.0 + (double)k / 480.0, cap = (k % 64) != 0 ? 4.0 : 6.0;
+  return rounds <= (most < cap ? most : cap) ? 3 : 0;
 }
 
 }  // namespace cwac

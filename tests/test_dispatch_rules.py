@@ -42,3 +42,12 @@ def test_weight_only_mid_batch_takes_the_kernel_that_measured_faster(m, n, k, ti
 def test_half_a_round_of_large_tiles_takes_the_tile_that_measured_faster(m, n, k, out_bytes, persistent, quarter):
     want = B.CWAC_SHAPE_128_128 if quarter < persistent else B.CWAC_SHAPE_256_PERSIST
     assert rules.fast_shape(m, n, k, out_bytes) == want
+
+
+# microseconds measured with cold weights: the 64 x 64 tile kernel, the split-K kernel with its tile
+@pytest.mark.parametrize("m,n,k,tile,split", [(350, 3040, 1776, 11.8, 12.9), (547, 2352, 3472, 20.1, 23.4), (481, 2912, 3280, 20.2, 23.0),
+                                              (286, 5120, 8944, 62.5, 72.4), (2655, 544, 9504, 49.2, 57.9), (1348, 832, 4720, 25.5, 27.5),
+                                              (296, 4096, 2000, 13.5, 14.6), (197, 768, 768, 5.7, 3.5), (197, 768, 3072, 16.7, 5.0),
+                                              (1576, 768, 3072, 18.0, 15.8), (16, 4096, 4096, 29.2, 6.7), (200, 11008, 4096, 33.4, 41.0)])
+def test_small_layers_take_the_kernel_that_measured_faster(m, n, k, tile, split):
+    assert (rules.split_tile(m, n, k) != 0) == (split < tile)
