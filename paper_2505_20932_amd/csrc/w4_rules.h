@@ -19,8 +19,11 @@ struct W4StreamTile {
 };
 constexpr W4StreamTile kW4Stream[] = {{1, 8, 8, 2, 4.2, 0.5, 2.7},  {1, 16, 8, 3, 4.2, 0.7, 3.2},  {1, 32, 8, 2, 5.0, 1.6, 4.5},
                                       {2, 32, 8, 2, 8.5, 2.5, 6.8}, {1, 64, 8, 2, 8.0, 2.1, 7.3},  {2, 64, 4, 2, 12.3, 2.9, 10.2},
-                                      {2, 128, 4, 2, 21.5, 5.1, 17.0}};
+                                      {2, 128, 4, 2, 21.5, 5.1, 17.0},
+                                      // the first two with four wavefronts (chosen by w4_stream_tile, not by cost)
+                                      {1, 8, 4, 2, 4.2, 0.5, 2.7},  {1, 16, 4, 2, 4.2, 0.7, 3.2}};
 constexpr int kW4StreamTiles = (int)(sizeof(kW4Stream) / sizeof(kW4Stream[0]));
+constexpr int kW4StreamByCost = 7;  // the tiles that the estimate chooses among
 
 // rounds of one workgroup per compute unit
 inline double w4_stream_rounds(const W4StreamTile &t, int64_t m, int n) {
@@ -31,10 +34,14 @@ inline double w4_stream_rounds(const W4StreamTile &t, int64_t m, int n) {
 // The tile (index into kW4Stream).  What the tiles trade: fewer tokens per workgroup read the weights more often, fewer
 // channels the activations, and each halves when its factor doubles, until there is less than a round of workgroups.
 inline int w4_stream_tile(int64_t m, int n, int k) {
+  // Up to 16 tokens, more than a round of workgroups and at most two units of K for each of eight wavefronts: four of them.
+  // Eight / four, us: 16 x 24576 x 128 5.1 / 3.8, 16 x 131072 x 512 22.9 / 14.0, 1 x 131072 x 1024 23.7 / 19.2,
+  // 8 x 12288 x 1024 4.8 / 4.7; level at 8 x 8192 x 1024 (4.0 / 4.0), behind at 1 x 49152 x 2048 (14.1 / 15.1).
+  if (m <= 16 && n > 8192 && k <= 1024) return m <= 8 ? kW4StreamByCost : kW4StreamByCost + 1;
   if (m <= 8) return 0;
   int best = 1;
   double cost = 1e30;
-  for (int i = 1; i < kW4StreamTiles; ++i) {
+  for (int i = 1; i < kW4StreamByCost; ++i) {
     const double c = w4_stream_rounds(kW4Stream[i], m, n) * kW4Stream[i].us * (double)k / 4096.0;
     if (c < cost) {
       cost = c;

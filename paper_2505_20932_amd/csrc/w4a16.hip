@@ -783,8 +783,10 @@ cwac_status launch_w4_stream(const W4Params &p, int tile, int waves, int depth, 
     case 4: return launch_w4_stream_tile<4>(p, out_kind, st);
     case 5: return launch_w4_stream_tile<5>(p, out_kind, st);
     case 6: return launch_w4_stream_tile<6>(p, out_kind, st);
+    case 7: return launch_w4_stream_tile<7>(p, out_kind, st);
+    case 8: return launch_w4_stream_tile<8>(p, out_kind, st);
   }
-  static_assert(kW4StreamTiles == 7, "one case per tile");
+  static_assert(kW4StreamTiles == 9, "one case per tile");
   return CWAC_E_MODE;
 }
 

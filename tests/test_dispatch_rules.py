@@ -51,3 +51,11 @@ def test_half_a_round_of_large_tiles_takes_the_tile_that_measured_faster(m, n, k
                                               (1576, 768, 3072, 18.0, 15.8), (16, 4096, 4096, 29.2, 6.7), (200, 11008, 4096, 33.4, 41.0)])
 def test_small_layers_take_the_kernel_that_measured_faster(m, n, k, tile, split):
     assert (rules.split_tile(m, n, k) != 0) == (split < tile)
+
+
+# microseconds measured with cold weights: eight and four wavefronts to a workgroup of the weight-streaming kernel
+@pytest.mark.parametrize("m,n,k,eight,four", [(16, 24576, 128, 5.1, 3.8), (16, 24576, 256, 5.4, 4.0), (12, 131072, 512, 22.8, 13.8),
+                                              (16, 131072, 1024, 30.9, 22.1), (1, 131072, 256, 15.1, 9.8), (8, 131072, 1024, 23.8, 20.2),
+                                              (8, 4096, 2048, 4.5, 4.8), (1, 49152, 2048, 14.1, 15.1), (1, 8192, 4096, 6.7, 8.1)])
+def test_weight_only_decode_of_a_short_k_takes_the_wavefronts_that_measured_faster(m, n, k, eight, four):
+    assert (rules.w4_shape(rules.w4_tile(m, n, k))[2] == 4) == (four < eight)
