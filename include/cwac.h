@@ -567,6 +567,8 @@ enum {
   CWAC_KERNEL_DIRECT_LDS = 1,    /* the direct-to-LDS kernel wherever its constraints hold (m >= 256,
                                     n >= 64, k % 64 == 0, ldx and ldw <= 2^24; convolution: c_in % 64
                                     == 0, image below 2 GiB); otherwise the automatic choice */
+  CWAC_KERNEL_SPLIT_K = 2,       /* the small-problem kernel, K split over a workgroup's wavefronts (linear layers and
+                                    pointwise convolutions, ldx and ldw <= 2^24); otherwise the automatic choice */
   CWAC_KERNEL_GENERIC_64 = 64,   /* the register-staged kernel with 64 x 64, 128 x 128 or 256 x 256 */
   CWAC_KERNEL_GENERIC_128 = 128, /* output tiles (any shape)                                       */
   CWAC_KERNEL_GENERIC_256 = 256
@@ -600,8 +602,8 @@ typedef struct cwac_tuning {
 } cwac_tuning;
 
 /* Which kernel qlinear_cwac_forward(_ex) would run for these sizes and this tuning (host
- * arithmetic only; nothing is launched, no pointer is involved): CWAC_KERNEL_DIRECT_LDS or
- * CWAC_KERNEL_GENERIC_64 / _128 / _256; a negative cwac_status for sizes the forward rejects. */
+ * arithmetic only; nothing is launched, no pointer is involved): CWAC_KERNEL_DIRECT_LDS,
+ * CWAC_KERNEL_SPLIT_K or CWAC_KERNEL_GENERIC_64 / _128 / _256; a negative cwac_status for sizes the forward rejects. */
 int32_t cwac_forward_kernel_for(int64_t m, int32_t n, int32_t k, int64_t ldx, int64_t ldw,
                                 int32_t out_kind, const cwac_tuning *tuning);
 

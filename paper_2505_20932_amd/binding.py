@@ -19,7 +19,7 @@ CWAC_EPI_INT_OFFSET, CWAC_EPI_FP_BIAS = 0, 1
 CWAC_OUT_INT8, CWAC_OUT_FP32, CWAC_OUT_INT32, CWAC_OUT_FP16 = 0, 1, 2, 3
 CWAC_W4_GROUP = 128
 # cwac_tuning.kernel / .shape
-CWAC_KERNEL_AUTO, CWAC_KERNEL_DIRECT_LDS = 0, 1
+CWAC_KERNEL_AUTO, CWAC_KERNEL_DIRECT_LDS, CWAC_KERNEL_SPLIT_K = 0, 1, 2
 CWAC_KERNEL_GENERIC_64, CWAC_KERNEL_GENERIC_128, CWAC_KERNEL_GENERIC_256 = 64, 128, 256
 (CWAC_SHAPE_AUTO, CWAC_SHAPE_256_8W, CWAC_SHAPE_256_4W_K128, CWAC_SHAPE_256_4W_K64, CWAC_SHAPE_128_PAIR,
  CWAC_SHAPE_128_128, CWAC_SHAPE_256_PERSIST) = range(7)

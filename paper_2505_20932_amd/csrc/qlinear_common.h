@@ -224,8 +224,8 @@ struct Tune {
 inline bool tune_from(const cwac_tuning *t, Tune &o) {
   o = Tune{};
   if (!t) return true;
-  if (t->kernel != CWAC_KERNEL_AUTO && t->kernel != CWAC_KERNEL_DIRECT_LDS && t->kernel != CWAC_KERNEL_GENERIC_64 &&
-      t->kernel != CWAC_KERNEL_GENERIC_128 && t->kernel != CWAC_KERNEL_GENERIC_256)
+  if (t->kernel != CWAC_KERNEL_AUTO && t->kernel != CWAC_KERNEL_DIRECT_LDS && t->kernel != CWAC_KERNEL_SPLIT_K &&
+      t->kernel != CWAC_KERNEL_GENERIC_64 && t->kernel != CWAC_KERNEL_GENERIC_128 && t->kernel != CWAC_KERNEL_GENERIC_256)
     return false;
   if (t->shape < CWAC_SHAPE_AUTO || t->shape > CWAC_SHAPE_256_PERSIST) return false;
   if (t->stats_waves != 0 && t->stats_waves != 4 && t->stats_waves != 8) return false;

@@ -221,9 +221,9 @@ __global__ __launch_bounds__(256) void row0_kernel(const FwdParams p, float *__r
 
 using namespace cwac;
 
-// Kernel and tile choice shared by the forward entry points: CWAC_KERNEL_DIRECT_LDS or the generic
+// Kernel and tile choice shared by the forward entry points: CWAC_KERNEL_DIRECT_LDS, CWAC_KERNEL_SPLIT_K or the generic
 // kernel's tile (CWAC_KERNEL_GENERIC_*).  Host arithmetic on sizes only.
-static int choose_forward(int64_t m, int n, int k, int64_t ldx, int64_t ldw, int out_kind, const Tune &tune) {
+static int choose_forward(int64_t m, int n, int k, int64_t ldx, int64_t ldw, const Tune &tune) {
   // Tile choice: the largest tile that still gives the 256 compute units at least
   // two workgroups each; small problems fall back to small tiles.
   const int64_t t256 = ceil_div(m, 256) * ceil_div(n, 256);
@@ -240,29 +240,26 @@ static int choose_forward(int64_t m, int n, int k, int64_t ldx, int64_t ldw, int
   bool fast = fast_ok && n >= kFastTile && ceil_div(m, 128) * ceil_div(n, 256) >= 160;
   if (fast_ok && n < kFastTile) fast = ceil_div(m, 256) * ceil_div(n, n < 128 ? 64 : 128) >= 160;
   if (fast_ok && n >= kFastTile && fast_prefers_quarter_tile(m, n)) fast = true;
+  // small problems: where the choice is the 64 x 64 tile, the kernel that splits K over the wavefronts of a workgroup takes
+  // the layer if its own rule (splitk_tile) says it is the faster one
+  const bool split_ok = fast_pitch_ok(ldx, ldw);
+  const bool split = split_ok && tile == 64 && splitk_tile(m, n, k) != 0;
   // the caller's override (results are identical)
   if (tune.kernel == CWAC_KERNEL_DIRECT_LDS) {
     fast = fast_ok;
+  } else if (tune.kernel == CWAC_KERNEL_SPLIT_K) {
+    if (split_ok && tiles_of(m, n, 32, 32) <= 0x7fffffff) return CWAC_KERNEL_SPLIT_K;
   } else if (tune.kernel != CWAC_KERNEL_AUTO) {
-    tile = tune.kernel;
-    fast = false;
+    return tune.kernel;
   }
-  return fast ? CWAC_KERNEL_DIRECT_LDS : tile;
-}
-
-// Small problems: where the automatic choice is the 64 x 64 tile, the kernel that splits K over the wavefronts of a
-// workgroup takes the layer if its own rule (splitk_tile) says it is the faster one.  (Its name towards callers is that of
-// the tile kernel it stands in for; CWAC_KERNEL_GENERIC_64 forces that one.)
-static bool splitk_ok(int64_t m, int n, int k, int64_t ldx, int64_t ldw) {
-  return fast_pitch_ok(ldx, ldw) && splitk_tile(m, n, k) != 0;
+  return fast ? CWAC_KERNEL_DIRECT_LDS : split ? CWAC_KERNEL_SPLIT_K : tile;
 }
 
 static cwac_status dispatch_forward(const FwdParams &p, int out_kind, bool int_only, const Tune &tune,
                                     hipStream_t st) {
-  const int choice = choose_forward(p.m, p.n, p.k, p.ldx, p.ldw, out_kind, tune);
+  const int choice = choose_forward(p.m, p.n, p.k, p.ldx, p.ldw, tune);
   if (choice == CWAC_KERNEL_DIRECT_LDS) return launch_fast(p, out_kind, int_only, tune, st);
-  if (choice == 64 && tune.kernel == CWAC_KERNEL_AUTO && splitk_ok(p.m, p.n, p.k, p.ldx, p.ldw))
-    return launch_splitk(p, out_kind, int_only, st);
+  if (choice == CWAC_KERNEL_SPLIT_K) return launch_splitk(p, out_kind, int_only, st);
   if (choice == 256) return launch_tile<256, 256, 128, 2, 2>(p, out_kind, int_only, st);
   if (choice == 128) return launch_tile<128, 128, 128, 2, 2>(p, out_kind, int_only, st);
   return launch_tile<64, 64, 128, 2, 2>(p, out_kind, int_only, st);
@@ -274,7 +271,7 @@ extern "C" int32_t cwac_forward_kernel_for(int64_t m, int32_t n, int32_t k, int6
   if (!tune_from(tuning, tune)) return CWAC_E_MODE;
   if (out_kind != CWAC_OUT_INT8 && out_kind != CWAC_OUT_FP32 && out_kind != CWAC_OUT_INT32) return CWAC_E_MODE;
   if (m < 1 || n < 1 || k < 16 || k > 32768 || (k % 16) != 0 || ldx < k || ldw < k) return CWAC_E_SHAPE;
-  return choose_forward(m, n, k, ldx, ldw, out_kind, tune);
+  return choose_forward(m, n, k, ldx, ldw, tune);
 }
 
 extern "C" cwac_status qlinear_cwac_forward_ex(const int8_t *x_q, int64_t ldx, const int8_t *w_q,
@@ -351,7 +348,7 @@ extern "C" cwac_status qlinear_cwac_forward_table_ex(const int8_t *x_q, int64_t 
   // Where the plain forward would take the direct-to-LDS kernel, the table is applied in that kernel's
   // epilogue (layers of 256 channels and more), and likewise in the small-problem kernel's; elsewhere - and where the caller
   // forces a register-staged tile - the forward is followed by a lookup pass in place.
-  const int choice = choose_forward(m, n, k, ldx, ldw, CWAC_OUT_INT8, tune);
+  const int choice = choose_forward(m, n, k, ldx, ldw, tune);
   const bool fused = n >= kFastTile && choice == CWAC_KERNEL_DIRECT_LDS;
   FwdParams p = {};
   p.x = x_q; p.w = w_q; p.ldx = ldx; p.ldw = ldw; p.ldo = ldo;
@@ -362,8 +359,7 @@ extern "C" cwac_status qlinear_cwac_forward_table_ex(const int8_t *x_q, int64_t 
   p.hi = (float)(qp->qmax - qp->z_r);
   p.code_table = table;
   if (!fused) {
-    if (choice == 64 && tune.kernel == CWAC_KERNEL_AUTO && splitk_ok(m, n, k, ldx, ldw))
-      return launch_splitk(p, kOutTable, true, as_stream(stream));
+    if (choice == CWAC_KERNEL_SPLIT_K) return launch_splitk(p, kOutTable, true, as_stream(stream));
     const cwac_status st = qlinear_cwac_forward_ex(x_q, ldx, w_q, ldw, m, n, k, qp, mult, offset, nullptr, nullptr,
                                                    CWAC_OUT_INT8, out, ldo, tuning, stream);
     if (st != CWAC_OK) return st;
@@ -446,7 +442,7 @@ extern "C" cwac_status qconv2d_cwac_forward_ex(const int8_t *x_q, const int8_t *
   if (fast_ok && c_out >= 256 && fast_prefers_quarter_tile(m, c_out)) fast = true;
   if (tune.kernel == CWAC_KERNEL_DIRECT_LDS) {  // the caller's override, as for the linear layer
     fast = fast_ok;
-  } else if (tune.kernel != CWAC_KERNEL_AUTO) {
+  } else if (tune.kernel != CWAC_KERNEL_AUTO && tune.kernel != CWAC_KERNEL_SPLIT_K) {
     tile = tune.kernel;
     fast = false;
   }

@@ -281,7 +281,8 @@ cwac_status launch_splitk_tile(const FwdParams &p, int out_kind, bool int_only, 
 }  // namespace
 
 cwac_status launch_splitk(const FwdParams &p, int out_kind, bool int_only, hipStream_t st) {
-  switch (splitk_tile(p.m, p.n, p.k)) {
+  const int tile = splitk_tile(p.m, p.n, p.k);
+  switch (tile ? tile : 3) {  // forced where the rule leaves the layer to the tile kernels: 32 x 32 tiles
     case 1: return launch_splitk_tile<1>(p, out_kind, int_only, st);
     case 2: return launch_splitk_tile<2>(p, out_kind, int_only, st);
     case 3: return launch_splitk_tile<3>(p, out_kind, int_only, st);

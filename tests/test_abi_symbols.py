@@ -327,3 +327,19 @@ def test_code_table_forward_refuses_an_fp_bias_fold_at_every_size(lib, m, n, k):
         t = binding.make_tuning(kernel=kernel)
         assert f(a, k, a, k, m, n, k, C.byref(qp), a, null, a, a, n, C.byref(t), null) == -4
     assert lib.qlinear_cwac_forward_table(a, k, a, k, m, n, k, C.byref(qp), a, null, a, a, n, null) == -4
+
+
+def test_kernel_query_names_the_small_problem_kernel(lib):
+    """cwac_forward_kernel_for answers with the kernel that runs, so that forcing the answer changes nothing."""
+    ask, tun = binding.cwac_forward_kernel_for, binding.make_tuning
+    split, g64, big = binding.CWAC_KERNEL_SPLIT_K, binding.CWAC_KERNEL_GENERIC_64, (1 << 24) + 16
+    for m, n, k in ((1, 4096, 4096), (16, 12288, 4096), (32, 1152, 384), (197, 768, 3072), (200, 4096, 4096)):
+        assert ask(m, n, k, k, k) == split
+        assert ask(m, n, k, k, k, tuning=tun(kernel=split)) == split
+        assert ask(m, n, k, k, k, tuning=tun(kernel=g64)) == g64
+        assert ask(m, n, k, big, k) == ask(m, n, k, k, big) == g64                          # pitches beyond its 32-bit offsets
+        assert ask(m, n, k, big, k, tuning=tun(kernel=split)) == g64                        # ... forced, too
+    assert ask(200, 11008, 4096, 4096, 4096) == g64                                         # the tile kernel is ahead
+    assert ask(200, 11008, 4096, 4096, 4096, tuning=tun(kernel=split)) == split
+    assert ask(16384, 4096, 4096, 4096, 4096, tuning=tun(kernel=split)) == split
+    assert ask(16384, 4096, 4096, big, 4096, tuning=tun(kernel=split)) == binding.CWAC_KERNEL_GENERIC_256

@@ -70,3 +70,29 @@ def test_small_problem_bit_exact(orc, m, n, k):
         if n % 16 == 0 and ldo % 16 == 0:
             eq(run(torch.int8, lambda o: P.qlinear_cwac_forward_table(x, w, qp, dev(mult), dev(off), dev(table), o)),
                table[code.astype(np.int32) + 128])
+
+
+@pytest.mark.parametrize("m,n,k", [(300, 272, 192), (257, 3000, 144), (1000, 65, 640)])
+def test_forced_on_larger_layers_and_pointwise_convolutions(orc, m, n, k):
+    """cwac_tuning.kernel = CWAC_KERNEL_SPLIT_K beyond the kernel's own rule: 32 x 32 tiles, the same codes."""
+    print(f"forced split-K {m} x {n} x {k}", flush=True)
+    rng = np.random.default_rng(m + n + k)
+    xq = rng.integers(-128, 128, (m, k), dtype=np.int8)
+    wq = rng.integers(-127, 128, (n, k), dtype=np.int8)
+    mult = (np.abs(rng.standard_normal(n)) * 3e-4 + 1e-5).astype(np.float32)
+    off = rng.integers(-5000, 5000, n).astype(np.int32)
+    want = orc.folded_forward(orc.gemm_i8(xq, wq), off, mult, 5)
+    tun, out = P.make_tuning(kernel=P.binding.CWAC_KERNEL_SPLIT_K), torch.zeros(m, n, dtype=torch.int8, device=DEV)
+    P.qlinear_cwac_forward(dev(xq), dev(wq), P.make_qparams(z_r=5), dev(mult), dev(off), None, None, P.CWAC_OUT_INT8, out, tuning=tun)
+    np.testing.assert_array_equal(out.cpu().numpy(), want)
+    out.zero_()
+    P.qconv2d_cwac_forward(dev(xq).view(1, 1, m, k), dev(wq).view(n, 1, 1, k), 1, 0, P.make_qparams(z_r=5), dev(mult), dev(off),
+                           None, P.CWAC_OUT_INT8, out, tuning=tun)
+    np.testing.assert_array_equal(out.cpu().numpy(), want)
+    # a filter with taps has no split-K form: the automatic choice runs
+    w4 = rng.integers(-127, 128, (n, 1, 3, 16), dtype=np.int8)
+    x4 = rng.integers(-128, 128, (1, 5, 40, 16), dtype=np.int8)
+    acc = orc.conv2d_i8(x4, w4, 1, 0, 0)
+    o4 = torch.zeros(acc.shape[0], n, dtype=torch.int8, device=DEV)
+    P.qconv2d_cwac_forward(dev(x4), dev(w4), 1, 0, P.make_qparams(z_r=5), dev(mult), dev(off), None, P.CWAC_OUT_INT8, o4, tuning=tun)
+    np.testing.assert_array_equal(o4.cpu().numpy(), orc.folded_forward(acc, off, mult, 5))
