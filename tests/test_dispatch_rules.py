@@ -2,6 +2,8 @@
 import pytest
 
 import rules
+from test_gpu_small_problem import MAIN_LOOP as SPLIT_MAIN_LOOP
+from test_gpu_w4_mid_batch import MAIN_LOOP as W4_MAIN_LOOP
 from paper_2505_20932_amd import binding as B
 
 WIDE = (65536, 65568, 98304, 128256, 131072, 151936, 262144)
@@ -59,3 +61,41 @@ def test_small_layers_take_the_kernel_that_measured_faster(m, n, k, tile, split)
                                               (8, 4096, 2048, 4.5, 4.8), (1, 49152, 2048, 14.1, 15.1), (1, 8192, 4096, 6.7, 8.1)])
 def test_weight_only_decode_of_a_short_k_takes_the_wavefronts_that_measured_faster(m, n, k, eight, four):
     assert (rules.w4_shape(rules.w4_tile(m, n, k))[2] == 4) == (four < eight)
+
+
+def shares(units, wavefronts):
+    return {units // wavefronts, -(-units // wavefronts)}
+
+
+def test_gpu_shapes_run_the_main_loop_of_every_split_k_tile():
+    """The ring-refill loop runs for the units of a wavefront beyond its ring; the GPU test's shapes give every tile two
+    such units or more, and every remainder behind the last whole unit (none, one and two 64-byte steps)."""
+    loops, tails = {}, {}
+    for m, n, k in SPLIT_MAIN_LOOP:
+        tile = rules.split_tile(m, n, k)
+        assert tile > 0 and B.cwac_forward_kernel_for(m, n, k, k, k) == B.CWAC_KERNEL_SPLIT_K, (m, n, k)
+        _, _, waves, depth = rules.split_shape(tile)
+        loops.setdefault(tile, []).append(min(shares(k // 128, waves)) - depth)
+        tails.setdefault(tile, set()).add(-(-(k % 128) // 64))
+    assert set(loops) == {1, 2, 3, 4}
+    assert all(min(v) >= 2 for v in loops.values()), loops
+    assert all(tails[t] == {0, 1, 2} for t in loops), tails
+    assert any(rules.split_tile(m, n, k) == 4 and n % 16 == 0 for m, n, k in SPLIT_MAIN_LOOP)    # its code-table epilogue
+
+
+def test_gpu_shapes_run_the_main_loop_of_every_weight_streaming_tile():
+    loops = {}
+    for m, n, k in W4_MAIN_LOOP:
+        tile = rules.w4_tile(m, n, k)
+        assert tile >= 0, (m, n, k)
+        _, _, waves, depth = rules.w4_shape(tile)
+        share = shares(k // 64, waves)
+        loops.setdefault(tile, []).append((min(share) - depth, len(share)))
+    assert set(loops) == set(range(rules.lib().w4_tiles()))
+    assert all(max(v)[0] >= 2 for v in loops.values()), loops
+    assert all(max(c for _, c in v) == 2 for v in loops.values()), loops      # wavefronts with shares of unequal length
+
+
+def test_random_shapes_lie_on_both_sides_of_the_weight_streaming_kernels_limit():
+    for m, n, k in ((256, 4096, 128), (512, 2048, 256), (1632, 640, 256)):
+        assert rules.w4_tile(m, n, k) >= 0 and rules.w4_tile(m + 1, n, k) == -1

@@ -131,10 +131,11 @@ def _w4_shapes():
               for _ in range(10)]
     shapes += [(int(rng.integers(1, 33)), 32 * int(rng.integers(8, 21)), 128 * int(rng.integers(1, 12)))
                for _ in range(6)]            # decode-sized batches: the weight-streaming kernel
-    # several passes of the weight-streaming kernel (7 and 5 passes, a last pass of 8 rows / 1 row), and shapes just
-    # past the point where its estimated cost exceeds a tile's K loop
+    # several token blocks of the weight-streaming kernel, and shapes on both sides of the point where its estimated cost
+    # exceeds that of a round of the tiled kernel
     return shapes + [(32, 256, 128), (33, 256, 128), (1, 288, 1408), (200, 256, 4096), (129, 288, 3072),
-                     (130, 256, 1536), (256, 256, 2560)]
+                     (130, 256, 1536), (256, 256, 2560), (256, 4096, 128), (257, 4096, 128), (512, 2048, 256), (513, 2048, 256),
+                     (1632, 640, 256), (1633, 640, 256)]
 
 
 @pytest.mark.parametrize("m,n,k", _w4_shapes())

@@ -1,6 +1,7 @@
 """GPU parity of the kernel that splits K over a workgroup's wavefronts (few tokens or few tiles), against the oracle,
 bit for bit: every tile it has at its edges (rows, channels, K remainders of 128 and of 64 bytes, fewer K units
-than wavefronts), every epilogue, padded pitches and an output that does not admit vector stores."""
+than wavefronts, K of several rounds of the ring), every epilogue, padded pitches and an output that does not admit
+vector stores."""
 import numpy as np
 import pytest
 import torch
@@ -14,6 +15,10 @@ DEV = "cuda:0"
 SHAPES = [(1, 1, 16), (1, 17, 48), (16, 33, 64), (15, 50, 112), (7, 16, 144), (16, 100, 640), (3, 31, 1008), (16, 64, 4096),
           (17, 31, 16), (32, 33, 128), (31, 100, 784), (20, 4096, 256), (33, 32, 96), (50, 65, 192), (65, 130, 656),
           (197, 96, 384), (197, 161, 768), (129, 4090, 1040), (255, 2049, 1024)]
+# per tile: a wavefront's share of K is several rounds of its ring (4, 3, 2 and 2 units of 128 bytes), with nothing, one or two
+# 64-byte steps behind the last whole unit; 80 and 2064 channels run the code-table epilogue
+MAIN_LOOP = [(16, 80, 4096), (9, 50, 4240), (13, 33, 4208), (20, 65, 4240), (31, 80, 4096), (17, 33, 3184), (65, 66, 3152),
+             (197, 96, 3136), (197, 80, 3072), (129, 4090, 2064), (255, 2064, 3184), (200, 4096, 2048)]
 
 
 def dev(a):
@@ -27,7 +32,7 @@ def padded(a, pad):
     return dev(full)[:, :a.shape[1]]
 
 
-@pytest.mark.parametrize("m,n,k", SHAPES)
+@pytest.mark.parametrize("m,n,k", SHAPES + MAIN_LOOP)
 def test_small_problem_bit_exact(orc, m, n, k):
     print(f"small problem {m} x {n} x {k}", flush=True)
     rng = np.random.default_rng(m * 7919 + n * 31 + k)

@@ -1,6 +1,6 @@
-"""GPU parity of the weight-streaming INT4 kernel on batches of more than eight tokens: each of its tiles (channels x
-tokens) at its ragged edges - a last token block of one row, an odd number of 32-channel blocks, fewer K units than
-wavefronts - on operands whose every partial sum is exactly representable, against the oracle bit for bit."""
+"""GPU parity of the weight-streaming INT4 kernel: each of its tiles (channels x tokens) at its ragged edges - a last token
+block of one row, an odd number of 32-channel blocks, fewer K units than wavefronts - and with K of several rounds of
+its ring, on operands whose every partial sum is exactly representable, against the oracle bit for bit."""
 import numpy as np
 import pytest
 import torch
@@ -10,13 +10,23 @@ from test_gpu_w4a16 import _exact_case, _forward, _pack, w4  # noqa: F401
 pytestmark = pytest.mark.gpu
 
 
-# the sizes reach, in this order, the tiles 32 channels x 16, 32 and 64 tokens, 64 channels x 32, 64 and 128 tokens
-@pytest.mark.parametrize("m,n,k", [(9, 288, 128), (17, 4096, 384), (33, 4096, 256), (45, 4128, 128), (64, 4096, 128),
-                                   (65, 4096, 640), (100, 4096, 128), (32, 12288, 128), (31, 11040, 256), (45, 11040, 128),
-                                   (64, 11008, 256), (100, 11040, 128), (128, 11008, 384), (257, 4096, 256)])
+# short K: the tiles' edges
+SHORT = [(9, 288, 128), (17, 4096, 384), (33, 4096, 256), (45, 4128, 128), (64, 4096, 128),
+         (65, 4096, 640), (100, 4096, 128), (32, 12288, 128), (31, 11040, 256), (45, 11040, 128),
+         (64, 11008, 256), (100, 11040, 128), (128, 11008, 384), (257, 4096, 256)]
+# per tile: a wavefront's share of K is more units of 64 channels than its ring has slots, by at least one round of the ring
+# (two where the tile is for a K of up to 1024), with shares of unequal length
+MAIN_LOOP = [(5, 288, 4224), (13, 288, 4224), (16, 4096, 3200), (33, 4096, 2176), (31, 11040, 2176), (65, 4096, 2176),
+             (45, 11040, 1152), (64, 11008, 1408), (128, 11008, 1152), (257, 4096, 1408), (5, 8224, 896), (8, 8224, 1024),
+             (13, 8224, 896), (16, 8256, 1024)]
+
+
+@pytest.mark.parametrize("m,n,k", SHORT + MAIN_LOOP)
 def test_mid_batch_exact_operands(w4, m, n, k):  # noqa: F811
     print(f"w4a16 mid batch {m} x {n} x {k}", flush=True)
     x16, codes, scales, zeros = _exact_case(700 + m + n + k, m, n, k)
+    if k > 2048:
+        scales[:] = np.float16(0.5)
     acc, _ = w4.product(x16, w4.dequant(codes, scales, zeros))
     acc32 = acc.astype(np.float32)
     assert np.array_equal(acc32.astype(np.float64), acc)

@@ -175,8 +175,8 @@ def test_forward_exact_operands(w4, m, n, k):
 @pytest.mark.parametrize("n,k", [(256, 128), (320, 384), (512, 1024), (288, 640)])
 @pytest.mark.parametrize("m", [1, 5, 17, 32])
 def test_small_batch_exact_operands(w4, m, n, k):
-    """Batches of at most 32 tokens take the weight-streaming kernel (one workgroup per 32 channels,
-    K split over its four wavefronts - here 1, 3, 8 and 5 groups); `tile` and `half` force the tiled kernel
+    """Batches of at most 32 tokens take the weight-streaming kernel (workgroups of 32 channels, K split over their eight
+    wavefronts - here 2, 6, 16 and 10 units of 64 channels); `tile` and `half` force the tiled kernel
     with 256- and 128-token tiles.
     Exact operands: both give the oracle's bits."""
     print(f"w4a16 small batch {m} x {n} x {k}", flush=True)
@@ -210,9 +210,9 @@ def test_small_batch_exact_operands(w4, m, n, k):
                                    (3, 256, 9088), (8, 256, 2048), (9, 256, 1536), (16, 288, 3072), (13, 256, 4224)])
 def test_small_batch_every_wave_count(w4, m, n, k, waves, depth):
     """The weight-streaming kernel with 4 and 8 wavefronts per workgroup and every ring depth, for each padded row
-    count (8, 16, 32; by default rings of 4, 3 and 3 groups per wavefront): wavefronts without a group (K = 128), with fewer groups than ring
-    slots, with exactly a ring, and with several rounds of the ring plus a ragged rest (33 and 71 groups).  Exact
-    operands: the oracle's bits."""
+    count (8, 16, 32; forced wavefronts take rings of 2 units of 64 channels unless a depth is forced, too): wavefronts
+    without a unit (K = 128), with fewer units than ring slots, with exactly a ring, and with several rounds of the ring plus a
+    ragged rest (66 and 142 units).  Exact operands: the oracle's bits."""
     print(f"w4a16 small batch {m} x {n} x {k}, {waves} wavefronts, depth {depth}", flush=True)
     x16, codes, scales, zeros = _exact_case(900 + m + n + k, m, n, k)
     if k > 2048:
