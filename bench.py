@@ -1440,9 +1440,9 @@ def forward_shapes(P, synth, torch, dev: str, cfgs, reps: int = 20):
 
 
 def small_batch_sweep(P, synth, torch, dev: str):
-    """The weight-only layer at decode-sized batches (its own JSON line): every distinct layer shape of
-    workload 5 at 1, 8, 16 and 32 tokens, the dispatcher's choice and every (wavefronts, ring depth) of the
-    weight-streaming kernel; enough copies of the packed weights cycle that each launch reads them from HBM
+    """The weight-only layer at small batches (its own JSON line): every distinct layer shape of workload 5 at 1 to 512
+    tokens, the dispatcher's choice beside every (wavefronts, ring depth) of the weight-streaming kernel (up to 32
+    tokens) or the tiled kernel (above); enough copies of the packed weights cycle that each launch reads them from HBM
     (more than 400 MB per shape); three passes over the copies replayed from a HIP graph."""
     layers = setup_weight_only(P, synth, torch, 5, dev)
     for L in layers:
@@ -1463,8 +1463,8 @@ def small_batch_sweep(P, synth, torch, dev: str):
             o = torch.empty(sm, L.n, dtype=torch.float16, device=dev)
             row = {}
             # up to 32 rows: every (wavefronts, ring depth) of the weight-streaming kernel; above: the dispatcher's
-            # choice (passes of that kernel up to 128 rows, 128-token tiles while they fit one round) against the
-            # tiled kernel with 128- and 256-token tiles
+            # choice (that kernel while its estimate is the lower one, else the tiled kernel) against the tiled
+            # kernel with 128- and 256-token tiles
             choices = (((0, 0, 0), (4, 2, 0), (4, 3, 0), (4, 4, 0), (8, 2, 0), (8, 3, 0), (8, 4, 0)) if sm <= 32 else
                        ((0, 0, 0), (0, 0, 128), (0, 0, 256)))
             for waves, depth, tile in choices:
@@ -1519,9 +1519,9 @@ def small_batch_sweep(P, synth, torch, dev: str):
     wbytes = n * k // 2 + n * (k // 128) * 4
     out.append({"n": n, "k": k, "weight_bytes": wbytes, "copies": 2,
                 "us": {f"m={sm}": {"auto": round(us, 1), "auto_gbs": round(wbytes / us / 1e3, 1)}}})
-    return {"small_batch_sweep": "w4a16_stream_kernel, microseconds per launch from a HIP graph, weights from HBM; "
-                                 "columns: the dispatcher's choice, then <wavefronts per workgroup>w_d<ring depth> (up to 32 tokens) or "
-                                 "the tiled kernel with tile<tokens per tile> (above)",
+    return {"small_batch_sweep": "weight-only layer, microseconds per launch from a HIP graph, weights from HBM; "
+                                 "columns: the dispatcher's choice, then <wavefronts per workgroup>w_d<ring depth> of w4a16_stream_kernel "
+                                 "(up to 32 tokens) or the tiled kernel with tile<tokens per tile> (above)",
             "layers": out}
 
 

@@ -267,7 +267,8 @@ cwac_status qlinear_cwac_forward(const int8_t *x_q, int64_t ldx, const int8_t *w
 /* qlinear_cwac_forward (CWAC_OUT_INT8, integer-offset epilogue of Eq. 10: no fbias, no per-row scales)
  * followed by a 256-entry code table: out = table[r_q + 128].  An activation function between two
  * int8 layers acts on one code at a time (vit_gelu_table builds the GELU's table), so it costs a
- * byte read from LDS in the epilogue of large layers and no pass over the tensor; small layers run
+ * byte read from LDS in the epilogue and no pass over the tensor where the layer takes the
+ * direct-to-LDS kernel (n >= 256) or the split-K one; layers that take a register-staged tile run
  * the forward and then a lookup pass in place.  Arguments as qlinear_cwac_forward, plus
  *   table  device int8 [256], 4-byte aligned
  *   qp     folded for that epilogue: act_per_token and mode CWAC_EPI_FP_BIAS return CWAC_E_MODE at every size
@@ -578,8 +579,11 @@ enum {
   CWAC_SHAPE_256_8W = 1,      /* 256 tokens x 256 channels, eight wavefronts, K steps of 128 (k % 128 == 0) */
   CWAC_SHAPE_256_4W_K128 = 2, /* the same tile, four wavefronts, K steps of 128, two stages */
   CWAC_SHAPE_256_4W_K64 = 3,  /* four wavefronts, K steps of 64, four stages */
-  CWAC_SHAPE_128_PAIR = 4,    /* 128 tokens x 256 channels, two workgroups per compute unit */
-  CWAC_SHAPE_128_128 = 5,     /* 128 x 128, four wavefronts of 64 x 64 */
+  CWAC_SHAPE_128_PAIR = 4,    /* 128 tokens x 256 channels, two workgroups per compute unit (K steps of 64); where its
+                                 tiles are at most one per compute unit, k >= 3072 and k % 128 == 0: one workgroup per
+                                 compute unit with three stages of 128 */
+  CWAC_SHAPE_128_128 = 5,     /* 128 x 128, four wavefronts of 64 x 64; K steps of 64 or 128 and two or three stages by
+                                 the number of tiles, k and the output's width */
   CWAC_SHAPE_256_PERSIST = 6  /* CWAC_SHAPE_256_8W's tile on persistent workgroups, one per compute unit, the
                                  next tile's first loads in flight under a tile's epilogue (linear layers, every
                                  epilogue but the fused statistics; convolutions take CWAC_SHAPE_256_8W) */
@@ -592,7 +596,8 @@ typedef struct cwac_tuning {
   int32_t w4_tile;        /* qlinear_w4a16_cwac_forward_ex: 0 | 256 | 128: the tiled kernel with that many
                              tokens per tile (256 channels wide) at every batch size; 512: its tile of 512
                              channels x 128 tokens (needs n >= 512, else CWAC_E_MODE) */
-  int32_t w4_small_waves; /* ... its weight-streaming kernel (small batches): 0 | 4 | 8 wavefronts per workgroup */
+  int32_t w4_small_waves; /* ... its weight-streaming kernel, where that runs: 0 | 4 | 8 wavefronts per workgroup; with
+                             this or the next field given, workgroups keep to 32 channels x at most 32 tokens */
   int32_t persist_workgroups; /* CWAC_SHAPE_256_PERSIST: 0 = one workgroup per compute unit; n > 0 = at most n
                                  (each then walks more tiles; leaves compute units to concurrent work) */
   int32_t w4_small_depth; /* ... and its ring depth: 0 | 2 | 3 | 4 units of 64 input channels in flight per

@@ -250,7 +250,7 @@ cwac_status launch_fast(FwdParams p, int out_kind, bool int_only, const Tune &tu
 // The integer-offset int8 forward with p.code_table applied to every output code (kOutTable); shapes as
 // launch_fast with n >= 256.
 cwac_status launch_fast_table(FwdParams p, int shape, int max_workgroups, int loaders, hipStream_t st);
-// True where that kernel would take its 128-token tile shape (two workgroups per compute unit).
+// True where the convolution takes the 128-token tile shape (two workgroups per compute unit).
 bool fast_prefers_half_tile(int64_t m, int n, int k, int out_bytes);
 // The same kernel as an implicit-GEMM convolution (p.cv_* set, p.ldx unused).  fast_conv_ok: its shape
 // constraints (m >= 256, n >= 64, c_in % 64 == 0, image below 2 GiB).
