@@ -10,7 +10,8 @@
 //   quantizer  code = clip(rne(fma(y, 1 / s, z)), -128, 127)                            (Eq. 1)
 //   attention  S = (K - z)(Q - z)^T exactly (integers below 2^24 in the fp32 MFMA accumulators);
 //              P = 1024 p = exp2(fma(S, s^2 / sqrt(d) * log2 e, 10 - that * max S));  O = (sum_j RN16(P_j) (V_j - z)) * s / sum_j P_j,
-//              keys taken in groups of 96 with the running maximum (earlier partial sums rescaled)
+//              keys taken in groups of 64 with a running maximum (earlier partial sums rescaled when it rises by more
+//              than a factor of 32 in the weights)
 //   GELU table entry(c) = clip(rne(GELU(s_in (c - z_in)) / s_out + z_out)) evaluated in fp64 (erf form)
 #include <hip/hip_runtime.h>
 
@@ -227,24 +228,33 @@ __global__ __launch_bounds__(256) void table_lookup_kernel(const int8_t *in, int
 }
 
 // ------------------------------------------------------------------------------------------
-// Multi-head self-attention, head width D = 64 or 32, up to 224 tokens: one workgroup per (image, head),
-// one wavefront per 32 queries.  K (as (code - z) in binary16, row-major, rows of 2 D + 16 bytes) and V
-// (transposed, rows of 64 NT + 8 bytes) of the head sit in LDS; both row strides make the operand reads
-// conflict-free.  S^T = K Q^T: 32 x 32 x 16 MFMA tiles with keys along M, so a lane owns one
-// query (its N index) and, with its partner lane ^ 32, all of that query's scores - the softmax
-// is a reduction over the lane's own registers plus one exchange.  Registers 8u .. 8u + 7 of score
-// tile t are, in order, the B operand of k-step (t, u) of O^T = V^T P^T; the A operand gathers
-// the same keys, 32 t + 16 u + 8 (e >> 2) + 4 half + (e & 3), from the transposed V with two
-// 8-byte reads.  Scores are exact integers; p is scaled by 1024 before its conversion to binary16
-// so that no term that matters falls into the subnormal range.
+// Multi-head self-attention, head width D = 64 or 32.  One wavefront owns 32 queries; K (as (code - z) in
+// binary16, row-major, rows of 2 D + 16 bytes) and V (transposed, rows of 64 NT + 16 bytes) of 32 NT keys
+// sit in LDS.  S^T = K Q^T: 32 x 32 x 16 MFMA tiles with keys along M, so a lane owns one query (its N
+// index) and, with its partner lane ^ 32, all of that query's scores - the softmax is a reduction over the
+// lane's own registers plus one exchange.  Registers 8u .. 8u + 7 of score tile t are, in order, the B operand
+// of k-step (t, u) of O^T = V^T P^T; they hold keys 32 t + 16 u + 8 (e >> 2) + 4 half + (e & 3), so V^T is
+// stored with the four quads of every 16 keys in the order 0, 2, 1, 3 and the A operand is one 16-byte read.
+// Scores are exact integers; p is scaled by 1024 before its conversion to binary16 so that no term that
+// matters falls into the subnormal range.
+//
+// What bounds it: the vector ALU - per score one fused multiply-add, one exponential, one addition, half a
+// maximum and half a conversion - as long as enough wavefronts are resident to cover the loads of a head and
+// the chain scores -> maximum -> exponentials -> second product.  Hence at most 128 registers (two workgroups
+// of seven wavefronts to a compute unit), score tiles in pairs, a bias read a pair ahead, and a fill that moves
+// 4 keys x D / 8 channels per thread: V is transposed in registers (8-byte LDS writes instead of 2-byte ones).
+// Against one workgroup to a compute unit, 2-byte transposing writes and 224-query blocks of long sequences:
+// 128 images x 12 heads x 197 tokens 44.4 -> 34.8 us, 8 x 12 x 577 32.1 -> 20.9, 148 x 16 x 49 with a bias
+// 9.8 -> 8.6, one image 7.2 -> 6.5.  Chunks of 64 or 192 keys, three, five or seven wavefronts and shorter
+// chunks for 197 tokens were 5 to 150 % slower.
 // ------------------------------------------------------------------------------------------
 constexpr int kHeadDim = 64;     // widest head; 32 is the other width
 constexpr int kMaxTokens = 4096; // longest sequence
 // bytes per K row in LDS: the head's binary16 values + 16 (conflict-free 16-byte operand reads for both widths)
 constexpr int k_stride(int d) { return 2 * d + 16; }
-// bytes per V^T row in LDS: 2 * 32 * NT of keys + 8; in words twice an odd number, so the 8-byte operand
-// reads of 32 consecutive rows cover all 64 banks once
-constexpr int v_stride(int nt) { return 64 * nt + 8; }
+// bytes per V^T row in LDS: 2 * 32 * NT of keys + 16; four times an odd number of words, so the 16-byte operand
+// reads of 16 consecutive rows cover all 64 banks once
+constexpr int v_stride(int nt) { return 64 * nt + 16; }
 
 struct AttnParams {
   const int8_t *r;
@@ -252,7 +262,7 @@ struct AttnParams {
   float s;
   int z;
   int tokens, heads;
-  int64_t pairs;  // batch * heads
+  uint32_t pairs;  // batch * heads
   const uint16_t *bias;  // binary16 [heads][tokens][ldb] added to the logits, or NULL
   int64_t ldb;
   float s_a;
@@ -261,18 +271,104 @@ struct AttnParams {
   int64_t lda;
 };
 
-// Scores, softmax weights and the second product for CNT key tiles starting at tile t0, with the
-// running maximum `mx`, the running (lane-local) sum of weights and the output accumulators
-// rescaled when a later group raises the maximum (the usual streaming form of the softmax: the
-// result is the same up to fp32 rounding, and only CNT score tiles are live at a time).
-// With LONG the tiles in LDS are one chunk of a longer sequence: tile t0 + t holds keys from
-// key0 + 32 (t0 + t) on, and a tile may lie wholly beyond the last token (its scores are masked and its
-// bias is not read).
-template <int CNT, int D, int VS, bool BIAS, bool LONG = false>
+// One thread's share of a chunk of keys: units of 4 keys x D / 8 channels, 64 per 32 keys.
+template <int NT, int NW, int D>
+struct AttnFill {
+  static constexpr int kUnits = 64 * NT, kThreads = 64 * NW, kPer = (kUnits + kThreads - 1) / kThreads;
+  static constexpr int kWords = D / 32;  // words of codes per key and unit
+  uint32_t k[kPer][4][kWords], v[kPer][4][kWords];
+
+  // Keys from key0 on; keys beyond the last token repeat it (their scores are masked, their weights zero).
+  __device__ __forceinline__ void load(const int8_t *base, int64_t ld, int c, int key0, int tokens, int tid) {
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      const int i = tid + j * kThreads;
+      if (kUnits % kThreads != 0 && i >= kUnits) break;
+      const int quad = i >> 3, col = (i & 7) * (D / 8);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        int key = key0 + 4 * quad + r;
+        key = key < tokens ? key : tokens - 1;
+        const int8_t *at = base + (uint32_t)(key * (int)ld + col);
+        if constexpr (kWords == 2) {
+          const uint2 kw = *reinterpret_cast<const uint2 *>(at + c), vw = *reinterpret_cast<const uint2 *>(at + 2 * c);
+          k[j][r][0] = kw.x, k[j][r][1] = kw.y, v[j][r][0] = vw.x, v[j][r][1] = vw.y;
+        } else {
+          k[j][r][0] = *reinterpret_cast<const uint32_t *>(at + c);
+          v[j][r][0] = *reinterpret_cast<const uint32_t *>(at + 2 * c);
+        }
+      }
+    }
+  }
+
+  __device__ __forceinline__ void store(int8_t *s_k, int8_t *s_v, h2 zbias, int tid) const {
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      const int i = tid + j * kThreads;
+      if (kUnits % kThreads != 0 && i >= kUnits) break;
+      const int quad = i >> 3, col = (i & 7) * (D / 8);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        int8_t *at = s_k + (4 * quad + r) * k_stride(D) + 2 * col;
+        if constexpr (kWords == 2) {
+          *reinterpret_cast<h8 *>(at) = codes_to_h8(make_uint2(k[j][r][0], k[j][r][1]), zbias);
+        } else {
+          h2 lo, hi;
+          codes_to_h4(k[j][r][0], zbias, lo, hi);
+          *reinterpret_cast<h4 *>(at) = h4{lo[0], lo[1], hi[0], hi[1]};
+        }
+      }
+      // quads 0, 1, 2, 3 of 16 keys go to positions 0, 2, 1, 3
+      int8_t *vt = s_v + col * v_stride(NT) + (quad >> 2) * 32 + ((quad & 1) << 4) + ((quad & 2) << 2);
+#pragma unroll
+      for (int w = 0; w < kWords; ++w)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          // channel 4 w + b of keys 0, 1 and of keys 2, 3: the byte under 0x64 with its sign bit flipped is 1024 + (code + 128)
+          const uint32_t sel = 0x0c000c00u | ((4u + b) << 16) | (uint32_t)b;
+          const uint32_t p01 = __builtin_amdgcn_perm(v[j][1][w], v[j][0][w], sel) ^ 0x64806480u;
+          const uint32_t p23 = __builtin_amdgcn_perm(v[j][3][w], v[j][2][w], sel) ^ 0x64806480u;
+          const h2 a = __builtin_bit_cast(h2, p01) - zbias, d = __builtin_bit_cast(h2, p23) - zbias;
+          *reinterpret_cast<h4 *>(vt + (4 * w + b) * v_stride(NT)) = h4{a[0], a[1], d[0], d[1]};
+        }
+    }
+  }
+};
+
+// Running state of one query: maximum of the logits the weights refer to (as the exponent offset
+// 10 - max), lane-local sum of the weights and the output accumulators.
+template <int D>
+struct AttnState {
+  float mx, eoff, sum;
+  v16f oc[D / 32];
+};
+
+// A raised maximum rescales what has been summed only if it grew by more than this many powers of two: the
+// weights then stay below 1024 * 2^kLazy = 32768, inside binary16.
+constexpr float kLazy = 5.0f;
+
+// A query's bias for a pair of key tiles, read one pair ahead (so the loads travel under the pair before).
+// Rows are padded to whole key tiles; a second tile beyond the last one reads the last one again.
+struct AttnBias {
+  uint2 w[2][4];
+  __device__ __forceinline__ void load(const uint16_t *row, int key0, int tokens, int half) {
+    const int last = (tokens - 1) & ~31;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int key = key0 + 32 * t < last ? key0 + 32 * t : last;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) w[t][g] = *reinterpret_cast<const uint2 *>(row + key + 8 * g + 4 * half);
+    }
+  }
+};
+
+// Scores, softmax weights and the second product for CNT key tiles from LDS tile t0 on, whose first key is
+// key0 + 32 t0 of the sequence.  HALF: only the first 16 keys of the (single) tile can be real.
+template <int CNT, int D, int VS, bool BIAS, bool HALF = false>
 __device__ __forceinline__ void attention_key_group(int t0, bool first, const int8_t *s_k, const int8_t *s_v,
-                                                    const h8 (&fq)[D / 16], const uint16_t *bias_row, int tokens,
-                                                    float lscale, int l32, int half,
-                                                    float &mx, float &sum, v16f (&oc)[D / 32], int key0 = 0) {
+                                                    const h8 (&fq)[D / 16], const AttnBias &bias, int left,
+                                                    float lscale, int l32, int half, AttnState<D> &st) {
+  constexpr int R = HALF ? 8 : 16;  // score registers of a tile that can hold real keys
   v16f sc[CNT];
 #pragma unroll
   for (int t = 0; t < CNT; ++t) {
@@ -287,71 +383,93 @@ __device__ __forceinline__ void attention_key_group(int t0, bool first, const in
   // register 4 g + r of tile t is key 32 t + 8 g + 4 half + r of this lane's query
   if (BIAS) {
     // with a bias the scores become logits in the log2 domain first: x = S * lscale + bias * log2(e)
-    // (the bias rows are padded to whole key tiles, so the loads of padded keys stay inside them)
 #pragma unroll
     for (int t = 0; t < CNT; ++t)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        if (LONG && key0 + 32 * (t0 + t) >= tokens) continue;  // uniform: the tile is masked below
-        const uint2 bw = *reinterpret_cast<const uint2 *>(bias_row + key0 + 32 * (t0 + t) + 8 * g + 4 * half);
-        const h2 b01 = __builtin_bit_cast(h2, bw.x), b23 = __builtin_bit_cast(h2, bw.y);
+      for (int g = 0; g < R / 4; ++g) {
+        const h2 b01 = __builtin_bit_cast(h2, bias.w[t][g].x), b23 = __builtin_bit_cast(h2, bias.w[t][g].y);
         const float bf[4] = {(float)b01[0], (float)b01[1], (float)b23[0], (float)b23[1]};
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          sc[t][4 * g + r] = __builtin_fmaf(sc[t][4 * g + r], lscale, bf[r] * 1.44269504088896340736f);
+          sc[t][4 * g + r] = __builtin_fmaf(bf[r], 1.44269504088896340736f, sc[t][4 * g + r] * lscale);
       }
   }
   const float dscale = BIAS ? 1.0f : lscale;  // what turns a score difference into a log2 difference
-  float gmx = -INFINITY;
+  float gmx = -1e30f;  // finite, so that a group whose keys are all masked by the bias has zero weights
 #pragma unroll
   for (int t = 0; t < CNT; ++t) {
-    if (key0 + 32 * (t0 + t) + 32 > tokens) {  // only the last tiles can hold padded keys (uniform branch)
+    if (32 * t + 2 * R > left) {  // only the last tile can hold padded keys (uniform branch)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int key = key0 + 32 * (t0 + t) + 8 * (i >> 2) + 4 * half + (i & 3);
-        if (key >= tokens) sc[t][i] = -INFINITY;
-      }
+      for (int i = 0; i < R; ++i)
+        if (8 * (i >> 2) + (i & 3) >= left - 32 * t - 4 * half) sc[t][i] = -INFINITY;
     }
 #pragma unroll
-    for (int i = 0; i < 16; ++i) gmx = fmaxf(gmx, sc[t][i]);
+    for (int i = 0; i < R; ++i) gmx = fmaxf(gmx, sc[t][i]);
   }
-  gmx = fmaxf(gmx, __shfl_xor(gmx, 32, 64));  // a group's first tile holds at least one real key: finite
+  {
+    const uint32_t mine = __builtin_bit_cast(uint32_t, gmx);
+    const auto both = __builtin_amdgcn_permlane32_swap(mine, mine, false, false);
+    const uint32_t low = both[0], high = both[1];
+    gmx = fmaxf(__builtin_bit_cast(float, low), __builtin_bit_cast(float, high));
+  }
+  // 1024 p = exp2(S * lscale + (10 - mx * lscale)), one fused multiply-add per exponent
   if (first) {
-    mx = gmx;
-  } else if (gmx > mx) {  // the same decision in both lanes of a query
-    const float corr = __builtin_amdgcn_exp2f((mx - gmx) * dscale);
-    sum *= corr;
+    st.mx = gmx;
+    st.eoff = __builtin_fmaf(-gmx, dscale, 10.0f);
+  } else if ((gmx - st.mx) * dscale > kLazy) {  // the same decision in both lanes of a query
+    const float eoff = __builtin_fmaf(-gmx, dscale, 10.0f);
+    const float corr = __builtin_amdgcn_exp2f(eoff - st.eoff);  // of the offsets as they are used
+    st.sum *= corr;
 #pragma unroll
     for (int a = 0; a < D / 32; ++a)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) oc[a][i] *= corr;
-    mx = gmx;
+      for (int i = 0; i < 16; ++i) st.oc[a][i] *= corr;
+    st.mx = gmx;
+    st.eoff = eoff;
   }
-  // 1024 p = exp2(S * lscale + (10 - mx * lscale)), one fused multiply-add per exponent;
-  // exp2(-inf) = 0 for masked keys
-  const float eoff = 10.0f - mx * dscale;
+  const float eoff = st.eoff;
 #pragma unroll
   for (int t = 0; t < CNT; ++t)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      sc[t][i] = __builtin_amdgcn_exp2f(BIAS ? sc[t][i] + eoff : __builtin_fmaf(sc[t][i], lscale, eoff));
-      sum += sc[t][i];
-    }
-#pragma unroll
-  for (int t = 0; t < CNT; ++t)
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
+    for (int u = 0; u < R / 8; ++u) {
       h8 fp;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) fp[e] = (_Float16)sc[t][8 * u + e];
+      for (int e = 0; e < 8; ++e) {
+        const float x = sc[t][8 * u + e];
+        const float w = __builtin_amdgcn_exp2f(BIAS ? x + eoff : __builtin_fmaf(x, lscale, eoff));  // exp2(-inf) = 0
+        st.sum += w;
+        fp[e] = (_Float16)w;
+      }
 #pragma unroll
       for (int a = 0; a < D / 32; ++a) {
-        const int8_t *vb = s_v + (32 * a + l32) * VS + (32 * (t0 + t) + 16 * u + 4 * half) * 2;
-        const h4 lo = *reinterpret_cast<const h4 *>(vb), hi = *reinterpret_cast<const h4 *>(vb + 16);
-        const h8 fv = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-        oc[a] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fv, fp, oc[a], 0, 0, 0);
+        const h8 fv = *reinterpret_cast<const h8 *>(s_v + (32 * a + l32) * VS + (32 * (t0 + t) + 16 * u + 8 * half) * 2);
+        st.oc[a] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fv, fp, st.oc[a], 0, 0, 0);
       }
     }
+}
+
+// The NT tiles of a chunk in LDS, in pairs, from key key0 of the sequence on.  A sequence that does not come
+// in CHUNKS has more than 32 (NT - 1) keys.  `bias` holds the first pair's on entry and, on exit, the next chunk's.
+template <int NT, int D, bool BIAS, bool CHUNKS>
+__device__ __forceinline__ void attention_chunk(int key0, int tokens, const int8_t *s_k, const int8_t *s_v,
+                                                const h8 (&fq)[D / 16], const uint16_t *bias_row, AttnBias &bias,
+                                                float lscale, int l32, int half, AttnState<D> &st) {
+  constexpr int VS = v_stride(NT);
+#pragma unroll
+  for (int t0 = 0; t0 < NT; t0 += 2) {
+    const int rest = tokens - key0 - 32 * t0;
+    const bool f = key0 == 0 && t0 == 0;
+    if (CHUNKS && rest <= 0) break;  // uniform over the wavefront
+    const AttnBias now = bias;
+    if (BIAS && (CHUNKS || t0 + 2 < NT)) bias.load(bias_row, key0 + 32 * t0 + 64, tokens, half);
+    if (t0 + 1 < NT && (!CHUNKS || rest > 32))
+      attention_key_group<2, D, VS, BIAS>(t0, f, s_k, s_v, fq, now, rest, lscale, l32, half, st);
+    else if (rest > 16)
+      attention_key_group<1, D, VS, BIAS>(t0, f, s_k, s_v, fq, now, rest, lscale, l32, half, st);
+    else
+      attention_key_group<1, D, VS, BIAS, true>(t0, f, s_k, s_v, fq, now, rest, lscale, l32, half, st);
+    __builtin_amdgcn_sched_barrier(0);  // one group's score tiles live at a time
+  }
 }
 
 // Normalizes, quantizes and stores one query's output row.  O^T: register 4 g + r of tile a is channel
@@ -360,17 +478,22 @@ template <int D>
 __device__ __forceinline__ void attention_store_row(const AttnParams &p, float sum, const v16f (&oc)[D / 32], int8_t *orow,
                                                     int half, bool store) {
   sum += __shfl_xor(sum, 32, 64);
-  const float onorm = p.s * (1.0f / sum);  // sum and the accumulators both carry the factor 1024
-  const float zf = (float)p.z_a, inv_sa = 1.0f / p.s_a;
+  // sum and the accumulators both carry the factor 1024; the code is rne(O * s / (sum * s_a) + z_a)
+  const float onorm = p.s / (sum * p.s_a), zf = (float)p.z_a;
 #pragma unroll
   for (int a = 0; a < D / 32; ++a) {
     uint32_t packed[4];
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-      uint32_t w = 0;
+      // the rounding as an addition: what is clamped to whole bounds first rounds to the same code
+      uint32_t w[4];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) w |= (uint32_t)(quant_code(oc[a][4 * g + r] * onorm, inv_sa, zf) & 0xff) << (8 * r);
-      packed[g] = w;
+      for (int r = 0; r < 4; ++r) {
+        const float v = __builtin_amdgcn_fmed3f(__builtin_fmaf(oc[a][4 * g + r], onorm, zf), -128.0f, 127.0f);
+        w[r] = __builtin_bit_cast(uint32_t, v + 12582912.0f);
+      }
+      const uint32_t lo = __builtin_amdgcn_perm(w[1], w[0], 0x0c0c0400u), hi = __builtin_amdgcn_perm(w[3], w[2], 0x04000c0cu);
+      packed[g] = lo | hi;
     }
     // lower half-wave holds channels 8g .. 8g+3, upper 8g+4 .. 8g+7: after the two swaps the lower
     // lane owns channels 0 .. 15 of this 32-channel tile and the upper lane 16 .. 31
@@ -381,207 +504,105 @@ __device__ __forceinline__ void attention_store_row(const AttnParams &p, float s
   }
 }
 
-constexpr int kKeyGroup = 3;  // key tiles per group: 48 score registers live, two workgroups per compute unit
-
 // G heads per workgroup (short sequences: a head of two wavefronts alone would leave the compute unit to
-// workgroup turnover); the wavefronts of a head work only on that head's slice of LDS.
-template <int NT, int D, int G, bool BIAS>
-__global__ __launch_bounds__(64 * NT * G) void attention_int8_kernel(const AttnParams p) {
+// workgroup turnover), NW wavefronts (32 queries each) per head; the wavefronts of a head work only on that
+// head's slice of LDS.  CHUNKS: the sequence passes through LDS in chunks of 32 NT keys, the next chunk's
+// codes travelling in registers; otherwise it fits one.  gridDim.y counts blocks of 32 NW queries.
+template <int NT, int NW, int D, int G, bool BIAS, bool CHUNKS>
+__global__ __launch_bounds__(64 * NW * G, D == 64 && BIAS ? 2 : (CHUNKS || (BIAS && NT > 6) ? 3 : 4)) void attention_int8_kernel(const AttnParams p) {
   constexpr int TP = 32 * NT;
   __shared__ __attribute__((aligned(16))) int8_t s_k_all[G * TP * k_stride(D)];
   __shared__ __attribute__((aligned(16))) int8_t s_v_all[G * D * v_stride(NT)];
-  const int slot = threadIdx.x / (64 * NT);  // which of the workgroup's heads
+  // which of the workgroup's heads: the same for a whole wavefront, so everything derived from it is scalar
+  const int slot = G == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / (64 * NW));
   int8_t *s_k = s_k_all + slot * (TP * k_stride(D));
   int8_t *s_v = s_v_all + slot * (D * v_stride(NT));
-  const int tid = threadIdx.x % (64 * NT), lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x - slot * (64 * NW), lane = tid & 63, wave = tid >> 6;
   const int l32 = lane & 31, half = lane >> 5;
   // (image, head) pairs beyond the last repeat it and store nothing (every wavefront reaches the barrier)
-  int64_t pair = (int64_t)blockIdx.x * G + slot;
+  uint32_t pair = blockIdx.x * G + slot;  // at most 2^31 pairs
   const bool live = pair < p.pairs;
   if (!live) pair = p.pairs - 1;
-  const int head = (int)(pair % p.heads);
-  const int64_t row0 = (pair / p.heads) * p.tokens;
+  const uint32_t image = pair / (uint32_t)p.heads;
+  const int head = (int)(pair - image * p.heads);
+  const int64_t row0 = (int64_t)image * p.tokens;
   const int c = p.heads * D;
   const int8_t *qbase = p.r + row0 * p.ld + head * D;
 
   const _Float16 zb = (_Float16)(float)(1152 + p.z);
   const h2 zbias = {zb, zb};
-  // K and V of the head -> LDS as (code - z) in binary16; rows beyond the last token are zero
-  constexpr int CH = D / 8;  // 8-channel chunks per row
-  constexpr int IT = CH / 2;  // chunks per thread: TP * CH / (64 * NT)
-  // all of the thread's loads go out before the first conversion (one round trip to memory, not IT + 1);
-  // a key beyond the last token reads as the zero point, i.e. as (code - z) = 0
-  const uint32_t zword = 0x01010101u * (uint32_t)(p.z & 0xff);
-  uint2 kraw[IT], vraw[IT];
-#pragma unroll
-  for (int j = 0; j < IT; ++j) {
-    const int i = tid + j * (64 * NT);
-    const int key = i / CH, ch = i % CH;
-    kraw[j] = vraw[j] = make_uint2(zword, zword);
-    if (key < p.tokens) {
-      kraw[j] = *reinterpret_cast<const uint2 *>(qbase + key * p.ld + c + 8 * ch);
-      vraw[j] = *reinterpret_cast<const uint2 *>(qbase + key * p.ld + 2 * c + 8 * ch);
-    }
-  }
+  // all of the thread's loads go out before the first conversion (one round trip to memory)
+  AttnFill<NT, NW, D> fill;
+  fill.load(qbase, p.ld, c, 0, p.tokens, tid);
   // this lane's query row as B operands (rows beyond the last token repeat it; never stored)
-  const int q = wave * 32 + l32;
+  const int q0 = (int)blockIdx.y * (32 * NW) + wave * 32, q = q0 + l32;
   const int qrow = q < p.tokens ? q : p.tokens - 1;
-  uint2 qraw[D / 16];
-#pragma unroll
-  for (int s = 0; s < D / 16; ++s)
-    qraw[s] = *reinterpret_cast<const uint2 *>(qbase + qrow * p.ld + 16 * s + 8 * half);
-#pragma unroll
-  for (int j = 0; j < IT; ++j) {
-    const int i = tid + j * (64 * NT);
-    const int key = i / CH, ch = i % CH;
-    const h8 kv = codes_to_h8(kraw[j], zbias), vv = codes_to_h8(vraw[j], zbias);
-    *reinterpret_cast<h8 *>(s_k + key * k_stride(D) + ch * 16) = kv;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) *reinterpret_cast<_Float16 *>(s_v + (8 * ch + e) * v_stride(NT) + key * 2) = vv[e];
-  }
+  const bool wave_live = q0 < p.tokens;  // otherwise it only helps to fill LDS
+  // this lane's row of the bias: [head][query][key], rows padded to whole key tiles
+  const uint16_t *bias_row = BIAS ? p.bias + ((int64_t)head * p.tokens + qrow) * p.ldb : nullptr;
+  AttnBias bias;
+  if (BIAS) bias.load(bias_row, 0, p.tokens, half);
   h8 fq[D / 16];
+  {
+    uint2 qraw[D / 16];
 #pragma unroll
-  for (int s = 0; s < D / 16; ++s) fq[s] = codes_to_h8(qraw[s], zbias);
-  __syncthreads();
+    for (int s = 0; s < D / 16; ++s)
+      qraw[s] = *reinterpret_cast<const uint2 *>(qbase + (uint32_t)(qrow * (int)p.ld + 16 * s + 8 * half));
+    fill.store(s_k, s_v, zbias, tid);
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s) fq[s] = codes_to_h8(qraw[s], zbias);
+  }
 
   // s^2 / sqrt(D) * log2(e)
   const float lscale = p.s * p.s * (D == 64 ? 0.125f : 0.17677669529663687f) * 1.44269504088896340736f;
-  // this lane's row of the bias: [head][query][key], rows padded to whole key tiles
-  const uint16_t *bias_row = BIAS ? p.bias + ((int64_t)head * p.tokens + qrow) * p.ldb : nullptr;
-  float mx = 0.0f, sum = 0.0f;
-  v16f oc[D / 32];
+  AttnState<D> st;
+  st.mx = 0.0f, st.eoff = 0.0f, st.sum = 0.0f;
 #pragma unroll
   for (int a = 0; a < D / 32; ++a)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) oc[a][i] = 0.0f;
-#pragma unroll
-  for (int g = 0; g < NT / kKeyGroup; ++g) {
-    attention_key_group<kKeyGroup, D, v_stride(NT), BIAS>(g * kKeyGroup, g == 0, s_k, s_v, fq, bias_row, p.tokens, lscale, l32, half, mx, sum, oc);
-    __builtin_amdgcn_sched_barrier(0);  // one group's score tiles live at a time
-  }
-  if constexpr (NT % kKeyGroup != 0)
-    attention_key_group<NT % kKeyGroup, D, v_stride(NT), BIAS>(NT / kKeyGroup * kKeyGroup, NT < kKeyGroup, s_k, s_v, fq,
-                                                               bias_row, p.tokens, lscale, l32,
-                                        half, mx, sum, oc);
+    for (int i = 0; i < 16; ++i) st.oc[a][i] = 0.0f;
 
-  attention_store_row<D>(p, sum, oc, p.a + (row0 + qrow) * p.lda + head * D, half, q < p.tokens && live);
-}
-
-template <int NT, int D>
-cwac_status launch_attention(const AttnParams &p, int batch, hipStream_t st) {
-  constexpr int G = NT == 1 ? 4 : (NT == 2 ? 2 : 1);  // 256 threads per workgroup for short sequences
-  const int64_t blocks = ceil_div((int64_t)batch * p.heads, G);
-  if (p.bias)
-    attention_int8_kernel<NT, D, G, true><<<dim3((unsigned)blocks), 64 * NT * G, 0, st>>>(p);
-  else
-    attention_int8_kernel<NT, D, G, false><<<dim3((unsigned)blocks), 64 * NT * G, 0, st>>>(p);
-  return launch_status();
-}
-
-// Sequences of more than 224 tokens: one workgroup per (image, head, block of 224 queries); the keys and
-// values pass through LDS in chunks of 224, the running maximum, sum and accumulators carried from chunk
-// to chunk exactly as from key group to key group.
-constexpr int kChunkTiles = 7, kChunk = 32 * kChunkTiles;
-template <int D, bool BIAS>
-__global__ __launch_bounds__(64 * kChunkTiles) void attention_long_kernel(const AttnParams p) {
-  constexpr int NT = kChunkTiles;
-  __shared__ __attribute__((aligned(16))) int8_t s_k[kChunk * k_stride(D)];
-  __shared__ __attribute__((aligned(16))) int8_t s_v[D * v_stride(NT)];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int l32 = lane & 31, half = lane >> 5;
-  const int64_t pair = blockIdx.x;
-  const int head = (int)(pair % p.heads);
-  const int64_t row0 = (pair / p.heads) * p.tokens;
-  const int c = p.heads * D;
-  const int8_t *qbase = p.r + row0 * p.ld + head * D;
-  const _Float16 zb = (_Float16)(float)(1152 + p.z);
-  const h2 zbias = {zb, zb};
-
-  const int q0 = blockIdx.y * kChunk + wave * 32;  // this wavefront's first query
-  const bool wave_live = q0 < p.tokens;            // otherwise it only helps to fill LDS
-  const int q = q0 + l32;
-  const int qrow = q < p.tokens ? q : p.tokens - 1;
-  h8 fq[D / 16];
-#pragma unroll
-  for (int s = 0; s < D / 16; ++s) {
-    fq[s] = codes_to_h8(*reinterpret_cast<const uint2 *>(qbase + (int64_t)qrow * p.ld + 16 * s + 8 * half), zbias);
-  }
-  const float lscale = p.s * p.s * (D == 64 ? 0.125f : 0.17677669529663687f) * 1.44269504088896340736f;
-  const uint16_t *bias_row = BIAS ? p.bias + ((int64_t)head * p.tokens + qrow) * p.ldb : nullptr;
-  float mx = 0.0f, sum = 0.0f;
-  v16f oc[D / 32];
-#pragma unroll
-  for (int a = 0; a < D / 32; ++a)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) oc[a][i] = 0.0f;
-
-  constexpr int CH = D / 8;
-  for (int key0 = 0; key0 < p.tokens; key0 += kChunk) {
-    // the chunk's loads first (one round trip), then the conversions; keys beyond the last token read as the
-    // zero point, i.e. as (code - z) = 0
-    static_assert(kChunk * CH % (64 * NT) == 0, "whole chunks per thread");
-    constexpr int IT = kChunk * CH / (64 * NT);
-    const uint32_t zword = 0x01010101u * (uint32_t)(p.z & 0xff);
-    uint2 kraw[IT], vraw[IT];
-#pragma unroll
-    for (int j = 0; j < IT; ++j) {
-      const int i = tid + j * (64 * NT);
-      const int kl = i / CH, ch = i % CH, key = key0 + kl;
-      kraw[j] = vraw[j] = make_uint2(zword, zword);
-      if (key < p.tokens) {
-        kraw[j] = *reinterpret_cast<const uint2 *>(qbase + (int64_t)key * p.ld + c + 8 * ch);
-        vraw[j] = *reinterpret_cast<const uint2 *>(qbase + (int64_t)key * p.ld + 2 * c + 8 * ch);
-      }
-    }
-    if (key0 > 0) __syncthreads();  // every wavefront is done with the previous chunk
-#pragma unroll
-    for (int j = 0; j < IT; ++j) {
-      const int i = tid + j * (64 * NT);
-      const int kl = i / CH, ch = i % CH;
-      const h8 kv = codes_to_h8(kraw[j], zbias), vv = codes_to_h8(vraw[j], zbias);
-      *reinterpret_cast<h8 *>(s_k + kl * k_stride(D) + ch * 16) = kv;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) *reinterpret_cast<_Float16 *>(s_v + (8 * ch + e) * v_stride(NT) + kl * 2) = vv[e];
-    }
-    __syncthreads();
-    if (wave_live) {
-#pragma unroll
-      for (int t0 = 0; t0 + kKeyGroup <= NT; t0 += kKeyGroup) {
-        if (key0 + 32 * t0 < p.tokens)
-          attention_key_group<kKeyGroup, D, v_stride(NT), BIAS, true>(t0, key0 + t0 == 0, s_k, s_v, fq, bias_row, p.tokens,
-                                                                     lscale, l32, half, mx, sum, oc, key0);
-      }
-      constexpr int TAIL = NT / kKeyGroup * kKeyGroup;
-      if (NT % kKeyGroup != 0 && key0 + 32 * TAIL < p.tokens)
-        attention_key_group<(NT % kKeyGroup ? NT % kKeyGroup : 1), D, v_stride(NT), BIAS, true>(
-            TAIL, false, s_k, s_v, fq, bias_row, p.tokens, lscale, l32, half, mx, sum, oc, key0);
+  __syncthreads();
+  if constexpr (!CHUNKS) {
+    if (wave_live) attention_chunk<NT, D, BIAS, false>(0, p.tokens, s_k, s_v, fq, bias_row, bias, lscale, l32, half, st);
+  } else {
+    for (int key0 = 0;; key0 += TP) {
+      const bool more = key0 + TP < p.tokens;  // uniform over the workgroup
+      if (more) fill.load(qbase, p.ld, c, key0 + TP, p.tokens, tid);
+      if (wave_live)
+        attention_chunk<NT, D, BIAS, true>(key0, p.tokens, s_k, s_v, fq, bias_row, bias, lscale, l32, half, st);
+      if (!more) break;
+      __syncthreads();  // every wavefront is done with this chunk
+      fill.store(s_k, s_v, zbias, tid);
+      __syncthreads();
     }
   }
   if (wave_live)
-    attention_store_row<D>(p, sum, oc, p.a + (row0 + qrow) * p.lda + head * D, half, q < p.tokens);
+    attention_store_row<D>(p, st.sum, st.oc, p.a + (row0 + qrow) * p.lda + head * D, half, q < p.tokens && live);
 }
 
-template <int D>
-cwac_status launch_attention_long(const AttnParams &p, int batch, hipStream_t st) {
-  const dim3 grid((unsigned)((int64_t)batch * p.heads), (unsigned)ceil_div(p.tokens, kChunk));
+template <int NT, int NW, int D, int G, bool CHUNKS>
+cwac_status launch_attention(const AttnParams &p, hipStream_t st) {
+  const dim3 grid((unsigned)ceil_div((int64_t)p.pairs, G), (unsigned)ceil_div(p.tokens, 32 * NW));
   if (p.bias)
-    attention_long_kernel<D, true><<<grid, 64 * kChunkTiles, 0, st>>>(p);
+    attention_int8_kernel<NT, NW, D, G, true, CHUNKS><<<grid, 64 * NW * G, 0, st>>>(p);
   else
-    attention_long_kernel<D, false><<<grid, 64 * kChunkTiles, 0, st>>>(p);
+    attention_int8_kernel<NT, NW, D, G, false, CHUNKS><<<grid, 64 * NW * G, 0, st>>>(p);
   return launch_status();
 }
 
 template <int D>
-cwac_status launch_attention_d(const AttnParams &p, int batch, hipStream_t st) {
-  if (p.tokens > kChunk) return launch_attention_long<D>(p, batch, st);
+cwac_status launch_attention_d(const AttnParams &p, hipStream_t st) {
   switch ((p.tokens + 31) / 32) {
-    case 1: return launch_attention<1, D>(p, batch, st);
-    case 2: return launch_attention<2, D>(p, batch, st);
-    case 3: return launch_attention<3, D>(p, batch, st);
-    case 4: return launch_attention<4, D>(p, batch, st);
-    case 5: return launch_attention<5, D>(p, batch, st);
-    case 6: return launch_attention<6, D>(p, batch, st);
-    default: return launch_attention<7, D>(p, batch, st);
+    // 256 threads per workgroup for short sequences
+    case 1: return launch_attention<1, 1, D, 4, false>(p, st);
+    case 2: return launch_attention<2, 2, D, 2, false>(p, st);
+    case 3: return launch_attention<3, 3, D, 1, false>(p, st);
+    case 4: return launch_attention<4, 4, D, 1, false>(p, st);
+    case 5: return launch_attention<5, 5, D, 1, false>(p, st);
+    case 6: return launch_attention<6, 6, D, 1, false>(p, st);
+    case 7: return launch_attention<7, 7, D, 1, false>(p, st);
+    default: return launch_attention<4, 4, D, 1, true>(p, st);
   }
 }
 
@@ -694,7 +715,7 @@ cwac_status vit_attention_int8(const int8_t *r_qkv, int64_t ld, float s, int32_t
   p.z = z;
   p.tokens = tokens;
   p.heads = heads;
-  p.pairs = (int64_t)batch * heads;
+  p.pairs = (uint32_t)batch * (uint32_t)heads;
   p.bias = bias;
   p.ldb = ldb;
   p.s_a = s_a;
@@ -702,7 +723,7 @@ cwac_status vit_attention_int8(const int8_t *r_qkv, int64_t ld, float s, int32_t
   p.a = a_q;
   p.lda = lda;
   hipStream_t st = as_stream(stream);
-  return head_dim == 64 ? launch_attention_d<64>(p, batch, st) : launch_attention_d<32>(p, batch, st);
+  return head_dim == 64 ? launch_attention_d<64>(p, st) : launch_attention_d<32>(p, st);
 }
 
 size_t vit_block_workspace(int32_t batch, int32_t tokens, int32_t heads, int32_t hidden) {

@@ -286,6 +286,54 @@ def test_attention_one_dominant_key_picks_its_value(tokens):
     np.testing.assert_array_equal(got, r[perm, 2 * c:])
 
 
+@pytest.mark.parametrize("batch,tokens,heads,head_dim", [
+    (1, 16, 5, 64), (3, 17, 3, 32), (1, 32, 1, 32), (5, 48, 1, 64), (1, 80, 2, 32), (1, 112, 2, 64), (1, 144, 3, 32),
+    (1, 160, 1, 64), (2, 176, 1, 32), (1, 208, 2, 64), (1, 209, 1, 64), (1, 256, 1, 64), (1, 257, 2, 32),
+    (1, 272, 1, 64), (1, 273, 1, 32), (1, 384, 1, 64), (1, 385, 2, 64)])
+@pytest.mark.parametrize("rising", [False, True])
+def test_attention_tile_edges_and_rising_maxima(batch, tokens, heads, head_dim, rising):
+    """The last key tile holding at most or more than 16 keys, one tile or two left in the last pair, heads that do
+    not fill a workgroup, chunks of a long sequence ending at or one past a tile.  `rising`: later keys score
+    higher, by steps above and below the bound that has earlier sums rescaled."""
+    print(f"attention {batch} x {tokens} tokens x {heads} heads of {head_dim}, rising {rising}", flush=True)
+    rng = np.random.default_rng(tokens * 3 + head_dim + rising)
+    c = head_dim * heads
+    r = np.clip(np.rint(rng.standard_normal((batch * tokens, 3 * c)) * 30 - 6), -128, 127).astype(np.int8)
+    s, z = np.float32(0.04), -6
+    if rising:                        # keys grow along the sequence and point the way the queries do
+        ramp = np.tile(np.linspace(0.0, 1.0, tokens), batch)[:, None]
+        r[:, :c] = np.clip(np.rint(25 + 5 * rng.standard_normal((batch * tokens, c))), -128, 127)
+        r[:, c:2 * c] = np.clip(np.rint(-20 + 60 * ramp + 5 * rng.standard_normal((batch * tokens, c))), -128, 127)
+    o, mag = blk.attention_codes(r, s, z, batch, tokens, heads)
+    s_a, z_a = _out_params(o)
+    full = torch.full((batch * tokens + 1, c), 99, dtype=torch.int8, device=DEV)
+    P.vit_attention_int8(_dev(r), float(s), z, batch, tokens, heads, s_a, z_a, full[:-1], head_dim=head_dim)
+    torch.cuda.synchronize()
+    assert (full[-1] == 99).all()
+    _, v = blk.quantize(o, np.float32(s_a), z_a)
+    delta = (2.0 ** -11 + 1024 * U32) * mag / s_a + 64 * U32 * (np.abs(v) + 128) + 1e-4
+    _codes_within(full[:-1].cpu().numpy(), v, delta)
+
+
+@pytest.mark.parametrize("tokens,low", [(49, -65504.0), (144, -np.inf), (197, -65504.0), (300, -np.inf)])
+def test_attention_bias_that_masks_whole_key_groups(tokens, low):
+    """A bias of the lowest binary16 value, or minus infinity, on every key but the last eleven: the groups of
+    keys before them have no weight, and no NaN."""
+    heads, d = 2, 32
+    rng = np.random.default_rng(tokens)
+    r = np.clip(np.rint(rng.standard_normal((tokens, 3 * heads * d)) * 30), -128, 127).astype(np.int8)
+    bias16 = np.zeros((heads, tokens, 32 * ((tokens + 31) // 32)), dtype=np.float16)
+    bias16[:, :, :tokens - 11] = low
+    s, z = np.float32(0.04), 0
+    o, mag = blk.attention_codes(r, s, z, 1, tokens, heads, bias16[:, :, :tokens].astype(np.float64))
+    s_a, z_a = _out_params(o)
+    a = torch.empty(tokens, heads * d, dtype=torch.int8, device=DEV)
+    P.vit_attention_int8(_dev(r), float(s), z, 1, tokens, heads, s_a, z_a, a, head_dim=d, bias=_dev(bias16))
+    torch.cuda.synchronize()
+    _, v = blk.quantize(o, np.float32(s_a), z_a)
+    _codes_within(a.cpu().numpy(), v, (2.0 ** -11 + 1024 * U32) * mag / s_a + 64 * U32 * (np.abs(v) + 128) + 1e-4)
+
+
 def test_attention_row_subset_of_a_batch_matches_single_image():
     """Images are independent: image 1 of a batch of 3 equals the same image alone."""
     tokens, heads = 60, 2
