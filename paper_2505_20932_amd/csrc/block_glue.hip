@@ -28,11 +28,30 @@ typedef _Float16 h4 __attribute__((ext_vector_type(4)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef int v4i __attribute__((ext_vector_type(4)));
 
-// sum over aligned groups of LPR lanes (the same value in every lane of a group)
+// sum over aligned groups of LPR lanes (the same value in every lane of a group), without LDS: neighbours, pairs,
+// quads and halves of 16 lanes by DPP, 16s and 32s by the half-wave exchanges
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+}
 template <int LPR>
 __device__ __forceinline__ float group_sum(float v) {
-#pragma unroll
-  for (int off = LPR / 2; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+  v += dpp<0xb1>(v);   // quad_perm 1,0,3,2
+  v += dpp<0x4e>(v);   // quad_perm 2,3,0,1
+  v += dpp<0x141>(v);  // row_half_mirror: the other quad of 8
+  v += dpp<0x140>(v);  // row_mirror: the other half of 16
+  if constexpr (LPR >= 32) {
+    const uint32_t mine = __builtin_bit_cast(uint32_t, v);
+    const auto both = __builtin_amdgcn_permlane16_swap(mine, mine, false, false);
+    const uint32_t a = both[0], b = both[1];
+    v = __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b);
+  }
+  if constexpr (LPR >= 64) {
+    const uint32_t mine = __builtin_bit_cast(uint32_t, v);
+    const auto both = __builtin_amdgcn_permlane32_swap(mine, mine, false, false);
+    const uint32_t a = both[0], b = both[1];
+    v = __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b);
+  }
   return v;
 }
 
@@ -52,18 +71,28 @@ __device__ __forceinline__ h8 codes_to_h8(uint2 c, h2 bias) {
   return h8{a[0], a[1], b[0], b[1], d[0], d[1], e[0], e[1]};
 }
 
-// Eq. 1 with the division by the scale as a fused multiply-add with its fp32 reciprocal (the
-// reciprocal's rounding instead of the division's: far inside what decides a code only at a tie).
-__device__ __forceinline__ int quant_code(float y, float inv_s, float zf) {
-  const float v = __builtin_fmaf(y, inv_s, zf);
-  return (int)__builtin_amdgcn_fmed3f(rintf(v), -128.0f, 127.0f);
+// Four values of Eq. 1 before rounding -> four codes in a word.  The rounding is an addition: what is clamped to
+// whole bounds first rounds to the same code.
+__device__ __forceinline__ uint32_t pack_codes(const float (&v)[4]) {
+  uint32_t w[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    w[i] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_fmed3f(v[i], -128.0f, 127.0f) + 12582912.0f);
+  return __builtin_amdgcn_perm(w[1], w[0], 0x0c0c0400u) | __builtin_amdgcn_perm(w[3], w[2], 0x04000c0cu);
 }
 
 // ------------------------------------------------------------------------------------------
-// Residual add + layer norm + quantizer: LPR (16, 32 or 64) lanes per token row, the row in
-// registers (NV vectors of 8 channels per lane: C <= 8 * LPR * NV; the host picks the pair that
-// leaves the fewest idle lanes, e.g. 32 x 3 for C = 768), two-pass mean / variance; LDS holds gamma and beta only.
-// HBM bytes per element: 2 (h) [+ 1 (codes) + 2 (h1)] + 1 (x_q).
+// Residual add + layer norm + quantizer: LPR lanes per token row, the row in registers (NV vectors of V channels
+// per lane), two-pass mean / variance with the sums taken over the lanes' registers by DPP and half-wave
+// exchanges (no LDS).  HBM bytes per element: 2 (h) [+ 1 (codes) + 2 (h1)] + 1 (x_q).
+//
+// Two forms.  Many rows: V = 8, LPR = 16, 32 or 64 - the host picks the pair with the fewest idle lanes, e.g.
+// 32 x 3 for C = 768 - bound by HBM and, close behind, by the ~16 vector instructions per element; gamma and
+// beta pass through LDS, staged while the row's loads are in flight.  Few rows (few wavefronts to a
+// compute unit): the serial chain of one row is what takes the time, so a wavefront takes one row with V = 4,
+// half the elements per lane, and reads gamma and beta straight into registers.
+// Residual + norm, microseconds, with shuffles through LDS, an integer rounding chain and a row loop / now: 25216 x 768
+// 20.4 / 18.5 (6.3 TB/s), 7252 x 512 6.1 / 5.5, 4616 x 768 6.5 / 5.4, 197 x 768 3.6 / 2.3.
 // ------------------------------------------------------------------------------------------
 struct LnParams {
   const _Float16 *h;
@@ -83,110 +112,188 @@ struct LnParams {
   int c;
 };
 
-// FULL: every lane's every vector is inside the row (C = 8 * LPR * NV): no masks.
-template <int LPR, int NV, bool FULL>
-__global__ __launch_bounds__(256) void residual_ln_quant_kernel(const LnParams p) {
+template <int V>
+struct LnVec;
+template <>
+struct LnVec<8> {
+  typedef h8 Half;
+  typedef uint2 Codes;
+  static __device__ __forceinline__ uint32_t word(const uint2 &c, int i) { return i ? c.y : c.x; }
+  static __device__ __forceinline__ uint2 pack(const uint32_t (&w)[2]) { return make_uint2(w[0], w[1]); }
+};
+template <>
+struct LnVec<4> {
+  typedef h4 Half;
+  typedef uint32_t Codes;
+  static __device__ __forceinline__ uint32_t word(const uint32_t &c, int) { return c; }
+  static __device__ __forceinline__ uint32_t pack(const uint32_t (&w)[1]) { return w[0]; }
+};
+
+// FULL: every lane's every vector is inside the row (C = V * LPR * NV): no masks.
+template <int LPR, int NV, int V, int THREADS, bool FULL>
+__global__ __launch_bounds__(THREADS) void residual_ln_quant_kernel(const LnParams p) {
+  constexpr bool kLds = V == 8;  // gamma and beta through LDS
   const int lane = threadIdx.x & (LPR - 1);  // position inside the row's group of LPR lanes
-  const int nvec = p.c >> 3;
-  // A lane group walks rows first, first + stride, ...; the loads of its next row are in flight while it
-  // reduces and quantizes the current one.  Groups past the end read the last row and store nothing: the
-  // shuffles then always run with every lane active, and the trip count is uniform over the workgroup
-  // (h_out may be h itself, so such a group must not store).
-  const int64_t stride = (int64_t)gridDim.x * (256 / LPR);
-  int64_t row = ((int64_t)blockIdx.x * 256 + threadIdx.x) / LPR;
-  const int64_t block_row0 = (int64_t)blockIdx.x * (256 / LPR);
-  struct Raw {
-    h8 hv[NV];
-    uint2 cw[NV];
-  };
-  auto load = [&](Raw &r, int64_t at) {
-    if (at > p.m - 1) at = p.m - 1;
+  const int nvec = p.c / V;
+  const int64_t row = ((int64_t)blockIdx.x * THREADS + threadIdx.x) / LPR;
+  // Groups past the last row read it again and store nothing (h_out may be h): the exchanges run with every lane.
+  const bool live = row < p.m;
+  const int64_t at = live ? row : p.m - 1;
+  typename LnVec<V>::Half hv[NV];
+  typename LnVec<V>::Codes cw[NV];
+  const _Float16 *hp = p.h + at * p.ldh;
+  const int8_t *rp = p.r + at * p.ldr;
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    const int v = (FULL || lane + LPR * j < nvec) ? lane + LPR * j : 0;
+    hv[j] = *reinterpret_cast<const typename LnVec<V>::Half *>(hp + V * v);
+  }
+  if (p.r) {
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
       const int v = (FULL || lane + LPR * j < nvec) ? lane + LPR * j : 0;
-      r.hv[j] = *reinterpret_cast<const h8 *>(p.h + at * p.ldh + 8 * v);
-      if (p.r) r.cw[j] = *reinterpret_cast<const uint2 *>(p.r + at * p.ldr + 8 * v);
+      cw[j] = *reinterpret_cast<const typename LnVec<V>::Codes *>(rp + V * v);
     }
-  };
-  // gamma and beta are the same for every row: staged once per workgroup in LDS (c <= 2048)
-  __shared__ __attribute__((aligned(16))) float s_gamma[2048], s_beta[2048];
+  }
+  // gamma and beta in LDS: the first and the second four channels of every vector side by side, so that the
+  // lanes of a 16-byte read cover all banks
+  __shared__ __attribute__((aligned(16))) float s_gb[kLds ? 4096 : 4];
+  float4 gr[kLds ? 1 : NV], br[kLds ? 1 : NV];
   if (p.x_q) {
-    for (int i = threadIdx.x; i < p.c; i += 256) {
-      s_gamma[i] = p.gamma[i];
-      s_beta[i] = p.beta[i];
+    if constexpr (kLds) {
+      for (int i = threadIdx.x; i < p.c / 4; i += THREADS) {
+        const int to = ((i & 1) << 10) + 4 * (i >> 1);
+        *reinterpret_cast<float4 *>(s_gb + to) = *reinterpret_cast<const float4 *>(p.gamma + 4 * i);
+        *reinterpret_cast<float4 *>(s_gb + 2048 + to) = *reinterpret_cast<const float4 *>(p.beta + 4 * i);
+      }
+      __syncthreads();
+    } else {
+#pragma unroll
+      for (int j = 0; j < NV; ++j) {
+        const int v = (FULL || lane + LPR * j < nvec) ? lane + LPR * j : 0;
+        gr[j] = *reinterpret_cast<const float4 *>(p.gamma + 4 * v);
+        br[j] = *reinterpret_cast<const float4 *>(p.beta + 4 * v);
+      }
     }
   }
-  __syncthreads();
+  float x[NV][V];
+  const float zr = (float)p.z_r + 128.0f;
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    const int v = lane + LPR * j;
+    const bool ok = FULL || v < nvec;
+#pragma unroll
+    for (int e = 0; e < V; ++e) x[j][e] = (float)hv[j][e];
+    if (p.r) {
+      typename LnVec<V>::Half ho;
+#pragma unroll
+      for (int e = 0; e < V; ++e) {
+        const uint32_t u = LnVec<V>::word(cw[j], e >> 2) ^ 0x80808080u;  // code + 128 in every byte
+        const float t = x[j][e] + p.s_r * ((float)((u >> (8 * (e & 3))) & 0xff) - zr);  // whole numbers: exact
+        ho[e] = (_Float16)t;
+        x[j][e] = (float)ho[e];
+      }
+      if (p.h_out && live && ok) *reinterpret_cast<typename LnVec<V>::Half *>(p.h_out + at * p.ldho + V * v) = ho;
+    }
+    if (!ok) {
+#pragma unroll
+      for (int e = 0; e < V; ++e) x[j][e] = 0.0f;
+    }
+  }
+  if (!p.x_q) return;
+  float s = 0.0f;
+#pragma unroll
+  for (int j = 0; j < NV; ++j)
+#pragma unroll
+    for (int e = 0; e < V; ++e) s += x[j][e];
+  const float mean = group_sum<LPR>(s) * p.inv_c;
+  float ss = 0.0f;
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    const bool ok = FULL || lane + LPR * j < nvec;
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+      const float d = ok ? x[j][e] - mean : 0.0f;
+      x[j][e] = d;
+      ss = __builtin_fmaf(d, d, ss);
+    }
+  }
+  const float var = group_sum<LPR>(ss) * p.inv_c;
+  const float rstd = __builtin_amdgcn_rsqf(var + p.eps);  // 1 ulp
   const float zf = (float)p.z_x, inv_s = p.inv_s_x;
-  Raw cur, nxt;
-  load(cur, row);
-  for (int64_t base = block_row0; base < p.m; base += stride, row += stride) {
-    const bool more = base + stride < p.m;  // uniform over the workgroup
-    if (more) load(nxt, row + stride);
-    const bool live = row < p.m;
-    const int64_t at = live ? row : p.m - 1;
-    float x[NV][8];
 #pragma unroll
-    for (int j = 0; j < NV; ++j) {
-      const int v = lane + LPR * j;
-      const bool ok = FULL || v < nvec;
+  for (int j = 0; j < NV; ++j) {
+    const int v = lane + LPR * j;
+    const int vs = (FULL || v < nvec) ? v : 0;
+    uint32_t w[V / 4];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) x[j][e] = ok ? (float)cur.hv[j][e] : 0.0f;
-      if (p.r) {
-        h8 ho;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const uint32_t w = e < 4 ? cur.cw[j].x : cur.cw[j].y;
-          const int code = (int)(int8_t)(w >> (8 * (e & 3)));
-          const float t = x[j][e] + p.s_r * (float)(code - p.z_r);
-          ho[e] = (_Float16)t;
-          x[j][e] = ok ? (float)ho[e] : 0.0f;
-        }
-        if (p.h_out && live && ok) *reinterpret_cast<h8 *>(p.h_out + at * p.ldho + 8 * v) = ho;
+    for (int q = 0; q < V / 4; ++q) {
+      float4 g4, b4;
+      if constexpr (kLds) {
+        g4 = *reinterpret_cast<const float4 *>(s_gb + 1024 * q + 4 * vs);
+        b4 = *reinterpret_cast<const float4 *>(s_gb + 2048 + 1024 * q + 4 * vs);
+      } else {
+        g4 = gr[j], b4 = br[j];
       }
+      const float g[4] = {g4.x, g4.y, g4.z, g4.w}, b[4] = {b4.x, b4.y, b4.z, b4.w};
+      float y[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) y[e] = __builtin_fmaf(__builtin_fmaf(x[j][4 * q + e] * rstd, g[e], b[e]), inv_s, zf);
+      w[q] = pack_codes(y);
     }
-    if (p.x_q) {
-      float s = 0.0f;
-#pragma unroll
-      for (int j = 0; j < NV; ++j)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) s += x[j][e];
-      const float mean = group_sum<LPR>(s) * p.inv_c;
-      float ss = 0.0f;
-#pragma unroll
-      for (int j = 0; j < NV; ++j) {
-        const bool ok = FULL || lane + LPR * j < nvec;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float d = ok ? x[j][e] - mean : 0.0f;
-          x[j][e] = d;
-          ss += d * d;
-        }
-      }
-      const float var = group_sum<LPR>(ss) * p.inv_c;
-      const float rstd = __builtin_amdgcn_rsqf(var + p.eps);  // 1 ulp
-#pragma unroll
-      for (int j = 0; j < NV; ++j) {
-        const int v = lane + LPR * j;
-        const int vs = (FULL || v < nvec) ? v : 0;
-        const float4 g0 = *reinterpret_cast<const float4 *>(s_gamma + 8 * vs),
-                     g1 = *reinterpret_cast<const float4 *>(s_gamma + 8 * vs + 4),
-                     b0 = *reinterpret_cast<const float4 *>(s_beta + 8 * vs),
-                     b1 = *reinterpret_cast<const float4 *>(s_beta + 8 * vs + 4);
-        const float g[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
-        const float b[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
-        uint32_t w[2] = {0u, 0u};
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float y = __builtin_fmaf(x[j][e] * rstd, g[e], b[e]);
-          const int code = quant_code(y, inv_s, zf);
-          w[e >> 2] |= (uint32_t)(code & 0xff) << (8 * (e & 3));
-        }
-        if (live && (FULL || v < nvec)) *reinterpret_cast<uint2 *>(p.x_q + at * p.ldxq + 8 * v) = make_uint2(w[0], w[1]);
-      }
-    }
-    if (more) cur = nxt;
+    if (live && (FULL || v < nvec)) *reinterpret_cast<typename LnVec<V>::Codes *>(p.x_q + at * p.ldxq + V * v) = LnVec<V>::pack(w);
   }
+}
+
+// At most kLnMaxRows rows per launch (64 threads each: a grid counts fewer than 2^32 threads).
+constexpr int64_t kLnMaxRows = (int64_t)1 << 25;
+
+cwac_status launch_ln(const LnParams &p, hipStream_t st) {
+  const int64_t m = p.m;
+  const int c = p.c;
+  // lanes per row and vectors of 8 channels per lane: the pair with the fewest idle vector slots, ties to the wider group
+  const int nvec = c / 8;
+  int lpr = 64, nv = (nvec + 63) / 64;
+  for (int cand = 32; cand >= 16; cand /= 2) {
+    const int cnv = (nvec + cand - 1) / cand;
+    if (cnv <= 4 && cnv * cand < nv * lpr) lpr = cand, nv = cnv;
+  }
+  // A wavefront per row (residual + norm, microseconds, row groups of 8 channels per lane / this): 197 x 768 3.0 / 2.3,
+  // 788 x 768 3.2 / 2.5, 2308 x 768 4.2 / 3.7, 197 x 1280 3.4 / 2.7; level at 3152 x 768 (4.4 / 4.3) and behind at
+  // 7252 x 256 (3.4 / 4.1) and 2000 x 2048 (6.0 / 6.4).  Also where it leaves no idle lane and the other would:
+  // 12608 x 1280 17.4 / 16.4.
+  if ((m <= 2304 && m * c <= 2400000) || (c % 256 == 0 && nvec != lpr * nv)) {
+    const dim3 grid((unsigned)m);
+#define CWAC_LN_CASE(N)                                                  \
+  case N:                                                                \
+    if (c == 256 * N)                                                    \
+      residual_ln_quant_kernel<64, N, 4, 64, true><<<grid, 64, 0, st>>>(p);  \
+    else                                                                 \
+      residual_ln_quant_kernel<64, N, 4, 64, false><<<grid, 64, 0, st>>>(p); \
+    break;
+    switch ((c + 255) / 256) {
+      CWAC_LN_CASE(1) CWAC_LN_CASE(2) CWAC_LN_CASE(3) CWAC_LN_CASE(4) CWAC_LN_CASE(5) CWAC_LN_CASE(6) CWAC_LN_CASE(7)
+      CWAC_LN_CASE(8)
+    }
+#undef CWAC_LN_CASE
+    return launch_status();
+  }
+  const dim3 grid((unsigned)ceil_div(m, 256 / lpr));
+#define CWAC_LN_CASE(L, N)                                                                     \
+  if (lpr == L && nv == N) {                                                                   \
+    if (nvec == L * N)                                                                         \
+      residual_ln_quant_kernel<L, N, 8, 256, true><<<grid, 256, 0, st>>>(p);                   \
+    else                                                                                       \
+      residual_ln_quant_kernel<L, N, 8, 256, false><<<grid, 256, 0, st>>>(p);                  \
+  }
+  // clang-format off
+  CWAC_LN_CASE(64, 1) else CWAC_LN_CASE(64, 2) else CWAC_LN_CASE(64, 3) else CWAC_LN_CASE(64, 4)
+  else CWAC_LN_CASE(32, 1) else CWAC_LN_CASE(32, 2) else CWAC_LN_CASE(32, 3) else CWAC_LN_CASE(32, 4)
+  else CWAC_LN_CASE(16, 1) else CWAC_LN_CASE(16, 2) else CWAC_LN_CASE(16, 3) else CWAC_LN_CASE(16, 4)
+  else return CWAC_E_SHAPE;
+  // clang-format on
+#undef CWAC_LN_CASE
+  return launch_status();
 }
 
 // ------------------------------------------------------------------------------------------
@@ -485,15 +592,10 @@ __device__ __forceinline__ void attention_store_row(const AttnParams &p, float s
     uint32_t packed[4];
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-      // the rounding as an addition: what is clamped to whole bounds first rounds to the same code
-      uint32_t w[4];
+      float v[4];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float v = __builtin_amdgcn_fmed3f(__builtin_fmaf(oc[a][4 * g + r], onorm, zf), -128.0f, 127.0f);
-        w[r] = __builtin_bit_cast(uint32_t, v + 12582912.0f);
-      }
-      const uint32_t lo = __builtin_amdgcn_perm(w[1], w[0], 0x0c0c0400u), hi = __builtin_amdgcn_perm(w[3], w[2], 0x04000c0cu);
-      packed[g] = lo | hi;
+      for (int r = 0; r < 4; ++r) v[r] = __builtin_fmaf(oc[a][4 * g + r], onorm, zf);
+      packed[g] = pack_codes(v);
     }
     // lower half-wave holds channels 8g .. 8g+3, upper 8g+4 .. 8g+7: after the two swaps the lower
     // lane owns channels 0 .. 15 of this 32-channel tile and the upper lane 16 .. 31
@@ -647,33 +749,17 @@ cwac_status vit_residual_ln_quant(const uint16_t *h, int64_t ldh, const int8_t *
   p.ldxq = ldxq;
   p.m = m;
   p.c = c;
-  // lanes per row and vectors per lane: the pair with the fewest idle vector slots, ties to the wider group
-  const int nvec = c / 8;
-  int lpr = 64, nv = (nvec + 63) / 64;
-  for (int cand = 32; cand >= 16; cand /= 2) {
-    const int cnv = (nvec + cand - 1) / cand;
-    if (cnv <= 4 && cnv * cand < nv * lpr) lpr = cand, nv = cnv;
+  for (int64_t row = 0; row < m; row += kLnMaxRows) {
+    LnParams q = p;
+    q.m = m - row < kLnMaxRows ? m - row : kLnMaxRows;
+    q.h += row * ldh;
+    if (r) q.r += row * ldr;
+    if (h_out) q.h_out += row * ldho;
+    if (x_q) q.x_q += row * ldxq;
+    const cwac_status st = launch_ln(q, as_stream(stream));
+    if (st != CWAC_OK) return st;
   }
-  // at most 8 workgroups per compute unit: beyond that a lane group walks several rows
-  int64_t blocks = ceil_div(m, 256 / lpr);
-  if (blocks > 2048) blocks = 2048;
-  const dim3 grid((unsigned)blocks);
-  hipStream_t st = as_stream(stream);
-#define CWAC_LN_CASE(L, N)                                                                     \
-  if (lpr == L && nv == N) {                                                                   \
-    if (nvec == L * N)                                                                         \
-      residual_ln_quant_kernel<L, N, true><<<grid, 256, 0, st>>>(p);                           \
-    else                                                                                       \
-      residual_ln_quant_kernel<L, N, false><<<grid, 256, 0, st>>>(p);                          \
-  }
-  // clang-format off
-  CWAC_LN_CASE(64, 1) else CWAC_LN_CASE(64, 2) else CWAC_LN_CASE(64, 3) else CWAC_LN_CASE(64, 4)
-  else CWAC_LN_CASE(32, 1) else CWAC_LN_CASE(32, 2) else CWAC_LN_CASE(32, 3) else CWAC_LN_CASE(32, 4)
-  else CWAC_LN_CASE(16, 1) else CWAC_LN_CASE(16, 2) else CWAC_LN_CASE(16, 3) else CWAC_LN_CASE(16, 4)
-  else return CWAC_E_SHAPE;
-  // clang-format on
-#undef CWAC_LN_CASE
-  return launch_status();
+  return CWAC_OK;
 }
 
 cwac_status vit_gelu_table(float s_in, int32_t z_in, float s_out, int32_t z_out, int8_t *table, void *stream) {

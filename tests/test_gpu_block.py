@@ -81,6 +81,25 @@ def test_residual_ln_quant(m, c, with_residual):
     assert pinned > 0.99
 
 
+@pytest.mark.parametrize("m,c", [(2304, 1040), (2308, 1040), (2305, 264), (700, 776), (2310, 1280), (2500, 1032),
+                                 (3000, 56), (2400, 136), (130, 1536), (1, 2048), (2401, 520), (2311, 2040)])
+def test_residual_ln_quant_row_and_group_forms(m, c):
+    """Either side of the bounds between a wavefront per row and groups of lanes, each number of vectors per lane,
+    rows that fill their lanes and rows that do not; in place."""
+    print(f"residual + layer norm + quantizer {m} x {c}", flush=True)
+    h, r, gamma, beta = _ln_case(m + c, m, c)
+    hp, xq = _dev(h), torch.full((m + 1, c), 77, dtype=torch.int8, device=DEV)
+    P.vit_residual_ln_quant(hp, _dev(r), 0.0625, -7, hp, _dev(gamma), _dev(beta), 1e-6, 0.03, 4, xq[:-1])
+    torch.cuda.synchronize()
+    assert (xq[-1] == 77).all()
+    want16, _ = blk.residual(h, r, 0.0625, -7)
+    got16 = hp.cpu().numpy()
+    # |h| < 64 and a multiple of 2^-24 at least where it matters, 0.0625 * integer: the fp32 sum can round, rarely
+    assert (got16 == want16).mean() > 0.999 and np.abs(got16.astype(float) - want16.astype(float)).max() < 0.04
+    _, v = blk.quantize(blk.layernorm(got16.astype(np.float64), gamma, beta, 1e-6), 0.03, 4)
+    assert _codes_within(xq[:-1].cpu().numpy(), v, 64 * U32 * (np.abs(v) + 128) + 1e-4) > 0.99
+
+
 def test_residual_only_and_quantizer_saturation():
     m, c = 6, 128
     h, r, gamma, beta = _ln_case(5, m, c)
