@@ -57,8 +57,10 @@ inline int fast_linear_shape(int64_t m, int n, int k, int out_bytes) {
   //    With 4-byte outputs and a short K loop the tile's store burst weighs as much as its K loop:
   //    when, on top, the last round leaves a good part of the chip idle, the 128 x 128 tile (three
   //    workgroups per compute unit, four times as many tiles, stores spread out) finishes sooner.
+  //  * 128 to 255 tokens: 128-token tiles, the only ones that the rows fill.
   if (fast_prefers_quarter_tile(m, n)) return CWAC_SHAPE_128_128;
   if ((k % 128) != 0) return CWAC_SHAPE_128_PAIR;
+  if (m < 256) return half_deep(m, n, k) ? CWAC_SHAPE_128_PAIR : CWAC_SHAPE_128_128;
   const int64_t t256 = tiles_of(m, n, 256, 256);
   if (t256 < 160) {
     if (half_deep(m, n, k)) return CWAC_SHAPE_128_PAIR;

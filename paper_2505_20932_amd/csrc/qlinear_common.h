@@ -248,7 +248,7 @@ inline bool fast_pitch_ok(int64_t ldx, int64_t ldw) { return ldx <= kFastMaxPitc
 // tile: n >= 256 and k % 128 == 0) and fast_pitch_ok(ldx, ldw).  tune.shape: CWAC_SHAPE_* (0 = by cost model).
 cwac_status launch_fast(FwdParams p, int out_kind, bool int_only, const Tune &tune, hipStream_t st);
 // The integer-offset int8 forward with p.code_table applied to every output code (kOutTable); shapes as
-// launch_fast with n >= 256.
+// launch_fast with n >= 256, and m >= 128.
 cwac_status launch_fast_table(FwdParams p, int shape, int max_workgroups, int loaders, hipStream_t st);
 // True where the convolution takes the 128-token tile shape (two workgroups per compute unit).
 bool fast_prefers_half_tile(int64_t m, int n, int k, int out_bytes);

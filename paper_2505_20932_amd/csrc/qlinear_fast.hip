@@ -22,7 +22,7 @@
 //     registers per lane, so that TWO workgroups share a compute unit and one's prologue and
 //     epilogue run under the other's main loop.
 //
-// Requires m >= 256, n >= 256, k % 128 == 0 (the 128-token shape: k % 64 == 0).  Edge tiles are shifted inwards to overlap their
+// Requires m >= 256, n >= 256, k % 128 == 0 (the 128-token shapes: m >= 128, k % 64 == 0).  Edge tiles are shifted inwards to overlap their
 // neighbours (identical values are written twice) instead of being predicated.
 #include <type_traits>
 
@@ -1346,7 +1346,9 @@ cwac_status launch_fast_table(FwdParams p, int shape, int max_workgroups, int lo
   p.vec_store = aligned(p.out, 16) && (p.ldo % 16) == 0;
   // the tiles of the plain int8 forward of a layer with n >= 256, by the same rule: the persistent
   // 256 x 256 tile, the same tile with one workgroup per tile, or a tile of 128 tokens
-  if (shape == CWAC_SHAPE_AUTO) shape = fast_linear_shape(p.m, p.n, p.k, 1);
+  // (fewer than 256 tokens: 128-token tiles)
+  if (shape == CWAC_SHAPE_AUTO || (p.m < 256 && shape != CWAC_SHAPE_128_PAIR && shape != CWAC_SHAPE_128_128))
+    shape = fast_linear_shape(p.m, p.n, p.k, 1);
   if (shape == CWAC_SHAPE_128_128) {
     const int ring = quarter_ring(p.m, p.n, p.k, p.k, false);
     if (ring == 2) return launch_table_cfg<128, 2, 128, 3, 4, 128, 2>(p, st);

@@ -240,10 +240,14 @@ static int choose_forward(int64_t m, int n, int k, int64_t ldx, int64_t ldw, con
   bool fast = fast_ok && n >= kFastTile && ceil_div(m, 128) * ceil_div(n, 256) >= 160;
   if (fast_ok && n < kFastTile) fast = ceil_div(m, 256) * ceil_div(n, n < 128 ? 64 : 128) >= 160;
   if (fast_ok && n >= kFastTile && fast_prefers_quarter_tile(m, n)) fast = true;
-  // small problems: where the choice is the 64 x 64 tile, the kernel that splits K over the wavefronts of a workgroup takes
+  // small problems: where the choice is the 64 x 64 tile, and for a decoding step of any width, the kernel that splits K over the wavefronts of a workgroup takes
   // the layer if its own rule (splitk_tile) says it is the faster one
   const bool split_ok = fast_pitch_ok(ldx, ldw);
-  const bool split = split_ok && tile == 64 && splitk_tile(m, n, k) != 0;
+  const bool split = split_ok && (tile == 64 || m <= 32) && splitk_tile(m, n, k) != 0;
+  // 80 to 95 tiles of 128 x 128 still pay against the 64 x 64 register-staged one (microseconds, 64 x 64 / 128 x 128:
+  // 788 x 1536 x 512 6.6 / 6.0, 256 x 5504 x 2048 13.2 / 11.7, 640 x 2048 x 512 6.6 / 6.3; fewer are not sure to:
+  // 700 x 1536 x 512, 72: 6.5 / 5.6, but 2000 x 512 x 512, 64: 6.0 / 6.5, 450 x 2304 x 768, 72: 7.2 / 7.3)
+  if (fast_ok && n >= kFastTile && !split && (k % 128) == 0 && tiles_of(m, n, 128, 128) >= 80) fast = true;
   // the caller's override (results are identical)
   if (tune.kernel == CWAC_KERNEL_DIRECT_LDS) {
     fast = fast_ok;
@@ -347,8 +351,18 @@ extern "C" cwac_status qlinear_cwac_forward_table_ex(const int8_t *x_q, int64_t 
     return CWAC_E_ALIGN;
   // Where the plain forward would take the direct-to-LDS kernel, the table is applied in that kernel's
   // epilogue (layers of 256 channels and more), and likewise in the small-problem kernel's; elsewhere - and where the caller
-  // forces a register-staged tile - the forward is followed by a lookup pass in place.
-  const int choice = choose_forward(m, n, k, ldx, ldw, tune);
+  // forces a register-staged tile - the forward is followed by a lookup pass in place.  That pass costs 2 to 2.5 us, so
+  // by itself a layer leaves the register-staged tiles earlier (microseconds, register-staged tile and lookup / split-K /
+  // direct-to-LDS): 394 x 1536 x 384 6.6 / 4.7 / 5.3, 197 x 5120 x 1280 11.7 / 8.8 / -, 591 x 1536 x 384 (3.6 rounds of 32 x 32
+  // tiles) 7.3 / 5.2 / 5.4, 788 x 1536 x 384 (4.7) 7.8 / 6.6 / 5.5, 592 x 2048 x 512 (4.8) 8.6 / 7.0 / 5.8.
+  int choice = choose_forward(m, n, k, ldx, ldw, tune);
+  if (tune.kernel == CWAC_KERNEL_AUTO && choice == CWAC_KERNEL_GENERIC_64 && fast_pitch_ok(ldx, ldw)) {
+    const int64_t t32 = tiles_of(m, n, 32, 32);
+    if (t32 > 1024 && m >= 128 && n >= kFastTile && (k % 64) == 0)
+      choice = CWAC_KERNEL_DIRECT_LDS;
+    else if (t32 <= 1536)
+      choice = CWAC_KERNEL_SPLIT_K;
+  }
   const bool fused = n >= kFastTile && choice == CWAC_KERNEL_DIRECT_LDS;
   FwdParams p = {};
   p.x = x_q; p.w = w_q; p.ldx = ldx; p.ldw = ldw; p.ldo = ldo;

@@ -37,7 +37,14 @@ inline int splitk_tile(int64_t m, int n, int k) {
   //     Rows that are no whole number of 64-byte pieces cost the direct-to-LDS loads more than the tile kernel's: four
   //     rounds there (350 x 3040 x 1776, 4.1 rounds: 11.8 / 12.9; 547 x 2352 x 3472, 5.2: 20.1 / 23.4; 286 x 5120 x 8944,
   //     5.6: 62.5 / 72.4; 1712 at 3.9 rounds: 0.89 of the tile kernel's time).
-  const double rounds = (double)t32 / 256.0, most = 1.0 + (double)k / 480.0, cap = (k % 64) != 0 ? 4.0 : 6.0;
+  //     Two workgroups fit a compute unit, so its time steps at two and four rounds: short of four it stays ahead from
+  //     K = 680 on, with a shorter K in proportion (256 x 3072 x 768, 3 rounds: 7.1 / 5.9; 300 x 2304 x 768, 2.8: 7.2 / 6.0;
+  //     788 x 1280 x 1280, 3.9: 9.9 / 8.2; 300 x 2048 x 512, 2.5: 5.9 / 5.3; 394 x 1152 x 384, 1.8: 4.7 / 3.6; level at
+  //     1024 x 768 x 768, 3 rounds, and 512 x 1536 x 384, 3).
+  const double rounds = (double)t32 / 256.0, four = (double)k / 170.0 < 4.0 ? (double)k / 170.0 : 4.0;
+  double most = 1.0 + (double)k / 480.0;
+  if (most < four) most = four;
+  const double cap = (k % 64) != 0 ? 4.0 : 6.0;
   return rounds <= (most < cap ? most : cap) ? 3 : 0;
 }
 

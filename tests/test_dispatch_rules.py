@@ -99,3 +99,14 @@ def test_gpu_shapes_run_the_main_loop_of_every_weight_streaming_tile():
 def test_random_shapes_lie_on_both_sides_of_the_weight_streaming_kernels_limit():
     for m, n, k in ((256, 4096, 128), (512, 2048, 256), (1632, 640, 256)):
         assert rules.w4_tile(m, n, k) >= 0 and rules.w4_tile(m + 1, n, k) == -1
+
+
+# microseconds measured with cold weights: the 64 x 64 tile kernel, the split-K kernel, 128 x 128 direct-to-LDS tiles
+@pytest.mark.parametrize("m,n,k,tile,split,lds", [(640, 2048, 512, 6.64, 7.5, 6.26), (788, 1536, 512, 6.58, 7.39, 5.99),
+                                                  (256, 3072, 768, 7.14, 5.92, 7.5), (788, 1280, 1280, 9.9, 8.2, 9.7),
+                                                  (256, 5504, 2048, 13.19, 12.3, 11.73), (577, 2048, 2048, 13.2, 11.2, 11.7),
+                                                  (2000, 512, 512, 6.0, 7.1, 6.5), (300, 2304, 768, 7.2, 6.0, 7.4),
+                                                  (450, 2304, 768, 7.2, 7.6, 7.3)])
+def test_layers_between_the_kernels_take_the_one_that_measured_fastest(m, n, k, tile, split, lds):
+    want = min((tile, B.CWAC_KERNEL_GENERIC_64), (split, B.CWAC_KERNEL_SPLIT_K), (lds, B.CWAC_KERNEL_DIRECT_LDS))[1]
+    assert B.cwac_forward_kernel_for(m, n, k, k, k) == want

@@ -60,3 +60,23 @@ def test_conv_ring_bit_exact(orc, shape):
     P.qconv2d_cwac_forward(dev(xq), dev(wq), stride, pad, P.make_qparams(z_x=9, z_r=3), dev(mult), dev(off), None,
                            P.CWAC_OUT_INT8, out, tuning=tuning_of("fast", pipe="q"))
     np.testing.assert_array_equal(out.cpu().numpy(), orc.folded_forward(acc, off, mult, 3))
+
+
+# layers whose plain forward takes a register-staged tile: the code table in the split-K kernel (up to four rounds of 32 x 32
+# tiles, or fewer than 128 tokens), in 128 x 128 tiles (beyond; one row of tiles, two that overlap in all rows but one, ragged
+# channels, both K steps and ring depths), and as a pass of its own (K no multiple of 64)
+@pytest.mark.parametrize("m,n,k", [(394, 1536, 384), (591, 1536, 384), (700, 1520, 384), (592, 2048, 512), (100, 11008, 48), (700, 1520, 400),
+                                   (128, 8208, 128), (129, 6672, 192), (255, 4144, 384), (128, 12288, 1536), (129, 6672, 3072)])
+def test_code_table_of_layers_between_the_kernels(orc, m, n, k):
+    print(f"code table {m} x {n} x {k}", flush=True)
+    rng = np.random.default_rng(m + n + k)
+    xq = rng.integers(-128, 128, (m, k), dtype=np.int8)
+    wq = rng.integers(-127, 128, (n, k), dtype=np.int8)
+    mult = (np.abs(rng.standard_normal(n)) * 3e-4 + 1e-5).astype(np.float32)
+    off = rng.integers(-5000, 5000, n).astype(np.int32)
+    table = rng.permutation(np.arange(-128, 128)).astype(np.int8)
+    full = torch.full((m, n + 16), 55, dtype=torch.int8, device=DEV)
+    P.qlinear_cwac_forward_table(dev(xq), dev(wq), P.make_qparams(z_r=5), dev(mult), dev(off), dev(table), full[:, :n])
+    code = orc.folded_forward(orc.gemm_i8(xq, wq), off, mult, 5)
+    np.testing.assert_array_equal(full[:, :n].cpu().numpy(), table[code.astype(np.int32) + 128])
+    assert (full[:, n:] == 55).all()
