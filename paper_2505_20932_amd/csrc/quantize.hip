@@ -83,17 +83,71 @@ __global__ __launch_bounds__(kThreads) void range_final_kernel(const float *__re
   }
 }
 
+// ---- x / s as IEEE division rounds it, without the division's scaling and fix-up steps ------------------------
+// With y = RN(1 / s), a first quotient x * y is within 1.5 units in the last place; one residual step
+// makes it a neighbour of x / s, the second one RN(x / s) (Markstein's theorem: the residuals are exact and no
+// quotient of two 24-bit numbers lies closer than 2^-48 to a midpoint).  The residuals must not underflow where the
+// quotient decides a code (|x / s| >= 1/4): scales inside [2^-90, 2^100]; others take the division itself.
+// Five instructions instead of eleven; measured with it in the row quantizer below.
+constexpr float kQuotMin = 8.0779356694631609e-28f, kQuotMax = 1.2676506002282294e30f;  // 2^-90, 2^100
+__device__ __forceinline__ float quotient(float x, float s, float y) {
+  float q = x * y;
+  q = __builtin_fmaf(__builtin_fmaf(-q, s, x), y, q);
+  return __builtin_fmaf(__builtin_fmaf(-q, s, x), y, q);
+}
+
+// Four whole numbers in [-128, 127], given as v + 1.5 * 2^23 (whose addition is the rounding), as bytes.
+__device__ __forceinline__ uint32_t pack_bytes(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
+  return __builtin_amdgcn_perm(b, a, 0x0c0c0400u) | __builtin_amdgcn_perm(d, c, 0x04000c0cu);
+}
+constexpr float kRound = 12582912.0f;
+
 // ---- Eq. 1, per-tensor parameters, b-bit codes in signed 8-bit storage ------
 // zu = unsigned zero-point, levels = 2^b - 1, half = 2^(b-1)
 struct ActQ {
   float s, zu, levels;
   int half;
+  // fast form: y = RN(1 / s), 0 where s is outside its range; |x| is first limited to 1024 s (far outside the clip), so
+  // that an infinity has a residual; a NaN takes the lower bound, as fmaxf and fminf have it
+  float y, limit;
 };
 __device__ __forceinline__ int act_code(float x, const ActQ &a) {
   float v = rintf(__fdiv_rn(x, a.s)) + a.zu;
   v = fmaxf(v, 0.0f);
   v = fminf(v, a.levels);
   return static_cast<int>(v) - a.half;
+}
+__device__ __forceinline__ uint32_t act_codes4(const float4 &v, const ActQ &a) {
+  const float x[4] = {v.x, v.y, v.z, v.w};
+  uint32_t w[4];
+  if (a.y != 0.0f) {  // uniform
+    const int z = (int)a.zu - a.half;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float q = quotient(__builtin_amdgcn_fmed3f(x[i], -a.limit, a.limit), a.s, a.y);
+      w[i] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_fmed3f(q, -a.zu, a.levels - a.zu) + kRound) + (uint32_t)z;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w[i] = (uint32_t)act_code(x[i], a);
+  }
+  return pack_bytes(w[0], w[1], w[2], w[3]);
+}
+
+// Rows without gaps: a thread's U loads (256 vectors apart, so that every access is a whole line) go out before
+// its first code.
+template <int U>
+__global__ __launch_bounds__(kThreads) void quantize_act_flat_kernel(const float4 *__restrict__ x, int64_t total, ActQ a,
+                                                                     uint32_t *__restrict__ q) {
+  for (int64_t at = (int64_t)blockIdx.x * (kThreads * U) + threadIdx.x; at < total; at += (int64_t)gridDim.x * (kThreads * U)) {
+    float4 v[U];
+#pragma unroll
+    for (int j = 0; j < U; ++j)
+      if (at + j * kThreads < total) v[j] = x[at + j * kThreads];
+#pragma unroll
+    for (int j = 0; j < U; ++j)
+      if (at + j * kThreads < total) q[at + j * kThreads] = act_codes4(v[j], a);
+  }
 }
 
 __global__ __launch_bounds__(kThreads) void quantize_act_vec_kernel(const float *__restrict__ x,
@@ -106,10 +160,7 @@ __global__ __launch_bounds__(kThreads) void quantize_act_vec_kernel(const float 
        i += (int64_t)gridDim.x * kThreads) {
     const int64_t r = i / kv;
     const int c = static_cast<int>(i - r * kv) * 4;
-    const float4 v = *reinterpret_cast<const float4 *>(x + r * ldx + c);
-    const uint32_t b0 = act_code(v.x, a) & 0xff, b1 = act_code(v.y, a) & 0xff,
-                   b2 = act_code(v.z, a) & 0xff, b3 = act_code(v.w, a) & 0xff;
-    *reinterpret_cast<uint32_t *>(q + r * ldq + c) = b0 | (b1 << 8) | (b2 << 16) | (b3 << 24);
+    *reinterpret_cast<uint32_t *>(q + r * ldq + c) = act_codes4(*reinterpret_cast<const float4 *>(x + r * ldx + c), a);
   }
 }
 
@@ -126,14 +177,87 @@ __global__ __launch_bounds__(kThreads) void quantize_act_kernel(const float *__r
   }
 }
 
-// ---- symmetric per-row quantizer: one workgroup per row ---------------------
+// ---- symmetric per-row quantizer ---------------------
 __device__ __forceinline__ int sym_code(float x, float s, float qmax) {
   float v = rintf(__fdiv_rn(x, s));
   v = fmaxf(v, -qmax);
   v = fminf(v, qmax);
   return static_cast<int>(v);
 }
+__device__ __forceinline__ float row_scale(float amax, float qmax) {
+  const float s = __fdiv_rn(amax, qmax), floor_s = FLT_MIN * 256.0f;
+  return s >= floor_s ? s : floor_s;
+}
+// Four codes of a row; y = RN(1 / s), or 0 where s is outside the range of the fast quotient (uniform).  A finite
+// scale means finite values (or NaN, which takes the lower bound).
+__device__ __forceinline__ uint32_t sym_codes4(const float4 &v, float s, float y, float qmax) {
+  const float x[4] = {v.x, v.y, v.z, v.w};
+  uint32_t w[4];
+  if (y != 0.0f) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      w[i] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_fmed3f(quotient(x[i], s, y), -qmax, qmax) + kRound);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w[i] = (uint32_t)sym_code(x[i], s, qmax);
+  }
+  return pack_bytes(w[0], w[1], w[2], w[3]);
+}
 
+typedef float f4 __attribute__((ext_vector_type(4)));
+template <bool STREAM>
+__device__ __forceinline__ float4 load4(const float *p) {
+  const f4 *at = reinterpret_cast<const f4 *>(p);
+  const f4 v = STREAM ? __builtin_nontemporal_load(at) : *at;
+  return make_float4(v[0], v[1], v[2], v[3]);
+}
+
+// The row in registers: WPR wavefronts per row, NV vectors of 4 per thread (k <= 256 WPR NV), so every value is read once.
+// Bound: HBM for many rows - 4 bytes in, 1 out per value -, one round trip for a few.  Microseconds, with
+// every row read twice and IEEE division / now: 16 x 4096 3.4 / 2.7, 16 x 11008 6.0 / 3.0, 2048 x 4096 9.1 / 6.5,
+// 16384 x 4096 71 / 53 (6.4 TB/s), 16384 x 11008 238 / 145 (6.2 TB/s), 3072 x 768 4.6 / 3.0.
+// STREAM: non-temporal loads.
+template <int WPR, int NV, int THREADS, bool STREAM>
+__global__ __launch_bounds__(THREADS) void quantize_rows_reg_kernel(const float *__restrict__ x, int64_t ldx, int rows, int k,
+                                                                    float qmax, float *__restrict__ scale,
+                                                                    int8_t *__restrict__ q, int64_t ldq) {
+  constexpr int RPB = THREADS / (64 * WPR);  // rows per workgroup
+  const int tid = WPR == 1 ? (int)(threadIdx.x & 63) : (int)threadIdx.x;
+  const int64_t row = (int64_t)blockIdx.x * RPB + (WPR == 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0);
+  if (WPR == 1 && row >= rows) return;  // whole wavefronts; no barrier below for WPR == 1
+  const float *xr = x + row * ldx;
+  int8_t *qr = q + row * ldq;
+  float4 v[NV];
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    const int c = 4 * (tid + j * (64 * WPR));
+    v[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (c < k) v[j] = load4<STREAM>(xr + c);
+  }
+  float amax = 0.0f;
+#pragma unroll
+  for (int j = 0; j < NV; ++j)
+    amax = fmaxf(fmaxf(amax, fabsf(v[j].x)), fmaxf(fabsf(v[j].y), fmaxf(fabsf(v[j].z), fabsf(v[j].w))));
+  amax = wave_max(amax);
+  if constexpr (WPR > 1) {
+    __shared__ float s_max[WPR];
+    if ((threadIdx.x & 63) == 0) s_max[threadIdx.x >> 6] = amax;
+    __syncthreads();
+    amax = s_max[0];
+#pragma unroll
+    for (int i = 1; i < WPR; ++i) amax = fmaxf(amax, s_max[i]);
+  }
+  const float s = row_scale(amax, qmax);
+  const float y = s >= kQuotMin && s <= kQuotMax ? __fdiv_rn(1.0f, s) : 0.0f;
+  if (tid == 0) scale[row] = s;
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    const int c = 4 * (tid + j * (64 * WPR));
+    if (c < k) *reinterpret_cast<uint32_t *>(qr + c) = sym_codes4(v[j], s, y, qmax);
+  }
+}
+
+// Any layout and length: one workgroup per row, the row read twice.
 __global__ __launch_bounds__(kThreads) void quantize_rows_sym_kernel(
     const float *__restrict__ x, int64_t ldx, int k, int vec_ok, float qmax,
     float *__restrict__ scale, int8_t *__restrict__ q, int64_t ldq) {
@@ -155,17 +279,12 @@ __global__ __launch_bounds__(kThreads) void quantize_rows_sym_kernel(
   __syncthreads();
   amax = s_max[0];
   for (int i = 1; i < kThreads / kWave; ++i) amax = fmaxf(amax, s_max[i]);
-  float s = __fdiv_rn(amax, qmax);
-  const float floor_s = FLT_MIN * 256.0f;
-  if (!(s >= floor_s)) s = floor_s;
+  const float s = row_scale(amax, qmax);
   if (threadIdx.x == 0) scale[row] = s;
   if (vec_ok) {
-    for (int c = threadIdx.x * 4; c < k; c += kThreads * 4) {
-      const float4 v = *reinterpret_cast<const float4 *>(xr + c);
-      const uint32_t b0 = sym_code(v.x, s, qmax) & 0xff, b1 = sym_code(v.y, s, qmax) & 0xff,
-                     b2 = sym_code(v.z, s, qmax) & 0xff, b3 = sym_code(v.w, s, qmax) & 0xff;
-      *reinterpret_cast<uint32_t *>(qr + c) = b0 | (b1 << 8) | (b2 << 16) | (b3 << 24);
-    }
+    const float y = s >= kQuotMin && s <= kQuotMax ? __fdiv_rn(1.0f, s) : 0.0f;
+    for (int c = threadIdx.x * 4; c < k; c += kThreads * 4)
+      *reinterpret_cast<uint32_t *>(qr + c) = sym_codes4(*reinterpret_cast<const float4 *>(xr + c), s, y, qmax);
   } else {
     for (int c = threadIdx.x; c < k; c += kThreads)
       qr[c] = static_cast<int8_t>(sym_code(xr[c], s, qmax));
@@ -195,6 +314,38 @@ __global__ __launch_bounds__(kThreads) void colsum_kernel(const int8_t *__restri
   }
   s = wave_sum(s);
   if (lane == 0) colsum[row] = s;
+}
+
+template <int WPR, int NV, int THREADS>
+cwac_status rows_reg(const float *x, int64_t ldx, int rows, int k, float qmax, float *scale, int8_t *q, int64_t ldq,
+                     hipStream_t st) {
+  const unsigned grid = (unsigned)ceil_div(rows, THREADS / (64 * WPR));
+  // Values that the last-level cache (256 MiB) cannot hold are streamed past it: 16384 x 11008 152 us against 145,
+  // 16384 x 4096 59 against 53; smaller ones may be there already: 4096 x 11008 (172 MiB) 32 against 39 streamed.
+  if constexpr (WPR > 1) {
+    if ((int64_t)rows * k * 4 >= ((int64_t)256 << 20)) {
+      quantize_rows_reg_kernel<WPR, NV, THREADS, true><<<grid, THREADS, 0, st>>>(x, ldx, rows, k, qmax, scale, q, ldq);
+      return launch_status();
+    }
+  }
+  quantize_rows_reg_kernel<WPR, NV, THREADS, false><<<grid, THREADS, 0, st>>>(x, ldx, rows, k, qmax, scale, q, ldq);
+  return launch_status();
+}
+
+// k % 4 == 0 and k <= 16384, rows and codes aligned for vectors of 4.
+cwac_status launch_rows_reg(const float *x, int64_t ldx, int rows, int k, float qmax, float *scale, int8_t *q, int64_t ldq,
+                            hipStream_t st) {
+  const int vecs = (k + 255) / 256;  // per lane, were the row one wavefront's
+  // A wavefront per row to k = 1024, four to 4096, sixteen beyond.  Four instead of sixteen: 16 x 11008 3.8 us against 3.0, 4096 x
+  // 11008 35.0 against 32.4, level at 5000 x 5120; sixteen instead of four: 512 x 4096 4.3 against 3.1.
+  if (vecs <= 1) return rows_reg<1, 1, 256>(x, ldx, rows, k, qmax, scale, q, ldq, st);
+  if (vecs <= 2) return rows_reg<1, 2, 256>(x, ldx, rows, k, qmax, scale, q, ldq, st);
+  if (vecs <= 4) return rows_reg<1, 4, 256>(x, ldx, rows, k, qmax, scale, q, ldq, st);
+  if (vecs <= 8) return rows_reg<4, 2, 256>(x, ldx, rows, k, qmax, scale, q, ldq, st);
+  if (vecs <= 16) return rows_reg<4, 4, 256>(x, ldx, rows, k, qmax, scale, q, ldq, st);
+  if (vecs <= 32) return rows_reg<16, 2, 1024>(x, ldx, rows, k, qmax, scale, q, ldq, st);
+  if (vecs <= 48) return rows_reg<16, 3, 1024>(x, ldx, rows, k, qmax, scale, q, ldq, st);
+  return rows_reg<16, 4, 1024>(x, ldx, rows, k, qmax, scale, q, ldq, st);
 }
 
 }  // namespace
@@ -257,8 +408,24 @@ extern "C" cwac_status cwac_quantize_act_bits(const float *x, int64_t ldx, int64
   a.zu = (float)(z + half);
   a.levels = (float)((1 << bits) - 1);
   a.half = half;
+  a.y = s >= kQuotMin && s <= kQuotMax ? 1.0f / s : 0.0f;
+  a.limit = a.y != 0.0f ? 1024.0f * s : 0.0f;
   const bool vec = (k % 4 == 0) && (ldx % 4 == 0) && (ldq % 4 == 0) && aligned(x, 16) &&
                    aligned(q, 4);
+  if (vec && ldx == k && ldq == k) {
+    const int64_t total = rows * (k / 4);
+    const float4 *xv = reinterpret_cast<const float4 *>(x);
+    uint32_t *qv = reinterpret_cast<uint32_t *>(q);
+    // one vector per thread while that is at most four workgroups of 256 to a compute unit (latency), else four
+    if (total <= 1024 * kThreads) {
+      quantize_act_flat_kernel<1><<<(unsigned)ceil_div(total, kThreads), kThreads, 0, as_stream(stream)>>>(xv, total, a, qv);
+    } else {
+      const int64_t blocks = ceil_div(total, 4 * kThreads);
+      quantize_act_flat_kernel<4><<<(unsigned)(blocks < (1 << 23) ? blocks : (1 << 23)), kThreads, 0, as_stream(stream)>>>(
+          xv, total, a, qv);
+    }
+    return launch_status();
+  }
   const int64_t work = vec ? rows * (k / 4) : rows * (int64_t)k;
   const int64_t want = ceil_div(work, kThreads);
   const int blocks = (int)(want < 65536 ? want : 65536);
@@ -287,8 +454,10 @@ extern "C" cwac_status cwac_quantize_rows_sym_bits(const float *x, int64_t ldx, 
   const int vec = (k % 4 == 0) && (ldx % 4 == 0) && (ldq % 4 == 0) && aligned(x, 16) &&
                   aligned(q, 4);
   const float qmax = (float)((1 << (bits - 1)) - 1);
-  quantize_rows_sym_kernel<<<(unsigned)rows, kThreads, 0, as_stream(stream)>>>(x, ldx, k, vec, qmax,
-                                                                                scale, q, ldq);
+  hipStream_t st = as_stream(stream);
+  if (vec && k <= 16384 && (k <= 4096 || rows <= (1 << 21)))  // a grid counts fewer than 2^32 threads
+    return launch_rows_reg(x, ldx, (int)rows, k, qmax, scale, q, ldq, st);
+  quantize_rows_sym_kernel<<<(unsigned)rows, kThreads, 0, st>>>(x, ldx, k, vec, qmax, scale, q, ldq);
   return launch_status();
 }
 
