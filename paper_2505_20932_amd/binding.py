@@ -1,7 +1,12 @@
-"""Thin ctypes binding of libcwac_hip.so: one Python function per C entry point,
+"""Thin binding of libcwac_hip.so: one Python function per C entry point,
 same names, argument marshalling only.  torch supplies device memory and the
 stream handle; every step of the path runs in the library's HIP kernels.  There
-is no fallback: a missing library or an error status raises."""
+is no fallback: a missing library or an error status raises.
+
+Calls go through ctypes.  The most frequent ones - quantizers and forwards, several
+per layer and token - are first offered to a small extension module
+(csrc/fast_calls.cpp) that makes the same call in a tenth of the host time; whatever
+does not fit it exactly, errors included, takes the ctypes form."""
 from __future__ import annotations
 
 import ctypes as C
@@ -74,15 +79,23 @@ class CwacError(RuntimeError):
 
 
 _lib = None
+_calls = None  # the extension module, bound to the library's entry points
+
+
+def _fast_calls():
+    if _calls is None:
+        lib()
+    return _calls
 
 
 def lib() -> C.CDLL:
     """Loads the HIP library built in-tree (see build.py); raises if it is absent."""
-    global _lib
+    global _lib, _calls
     if _lib is None:
-        if not os.path.exists(LIB_PATH):
-            raise CwacError(f"{LIB_PATH} is missing: build it with "
-                            "`python -m paper_2505_20932_amd.build` (no fallback path exists)")
+        for path in (LIB_PATH, os.path.join(_PKG, "_fast_calls.so")):
+            if not os.path.exists(path):
+                raise CwacError(f"{path} is missing: build it with "
+                                "`python -m paper_2505_20932_amd.build` (no fallback path exists)")
         l = C.CDLL(LIB_PATH)
         vp, i64, i32, f32, f64, sz = C.c_void_p, C.c_int64, C.c_int32, C.c_float, C.c_double, C.c_size_t
         qpp = C.POINTER(cwac_qparams)
@@ -147,7 +160,9 @@ def lib() -> C.CDLL:
         for name, (res, args) in sig.items():
             fn = getattr(l, name)
             fn.restype, fn.argtypes = res, args
-        _lib = l
+        from . import _fast_calls as calls
+        calls.bind(cwac_qparams, {name: C.cast(getattr(l, name), vp).value for name in sig})
+        _lib, _calls = l, calls
     return _lib
 
 
@@ -211,12 +226,16 @@ def cwac_qparams_from_range(mn: float, mx: float, bits: int = 8):
 
 
 def cwac_quantize_act(x: torch.Tensor, s: float, z: int, q: torch.Tensor, stream=None):
+    if (_calls or _fast_calls()).quantize_act(x, s, z, q, stream):
+        return
     assert x.dtype == torch.float32 and q.dtype == torch.int8 and x.shape == q.shape
     _check(lib().cwac_quantize_act(_ptr(x), _rowmajor(x), x.shape[0], x.shape[1], s, z, _ptr(q),
                                    _rowmajor(q), _stream(stream)), "cwac_quantize_act")
 
 
 def cwac_quantize_rows_sym(x: torch.Tensor, scale: torch.Tensor, q: torch.Tensor, stream=None):
+    if (_calls or _fast_calls()).quantize_rows_sym(x, scale, q, stream):
+        return
     assert x.dtype == torch.float32 and q.dtype == torch.int8 and scale.dtype == torch.float32
     assert x.shape == q.shape and scale.numel() == x.shape[0]
     _check(lib().cwac_quantize_rows_sym(_ptr(x), _rowmajor(x), x.shape[0], x.shape[1], _ptr(scale),
@@ -316,6 +335,8 @@ def qlinear_cwac_forward(x_q: torch.Tensor, w_q: torch.Tensor, qp: Optional[cwac
                          offset, fbias, s_x_row, out_kind: int, out: torch.Tensor, stream=None,
                          tuning: Optional[cwac_tuning] = None):
     """tuning given: qlinear_cwac_forward_ex (the forward calls below likewise)."""
+    if tuning is None and (_calls or _fast_calls()).forward(x_q, w_q, qp, mult, offset, fbias, s_x_row, out_kind, out, stream):
+        return
     assert x_q.dtype == torch.int8 and w_q.dtype == torch.int8
     assert out.dtype == _OUT_DTYPE[out_kind]
     m, k = x_q.shape
@@ -334,6 +355,8 @@ def qlinear_cwac_forward(x_q: torch.Tensor, w_q: torch.Tensor, qp: Optional[cwac
 def qlinear_cwac_forward_table(x_q: torch.Tensor, w_q: torch.Tensor, qp: cwac_qparams, mult, offset,
                                table: torch.Tensor, out: torch.Tensor, stream=None, tuning=None):
     """int8 forward (integer-offset epilogue) with out = table[code + 128]."""
+    if tuning is None and (_calls or _fast_calls()).forward_table(x_q, w_q, qp, mult, offset, table, out, stream):
+        return
     assert x_q.dtype == torch.int8 and w_q.dtype == torch.int8 and out.dtype == torch.int8
     assert table.dtype == torch.int8 and table.numel() == 256
     m, k = x_q.shape
@@ -398,6 +421,8 @@ def cwac_fold_fixed_point(alpha, beta, s_w, bias, colsum, qp: cwac_qparams, m0, 
 
 def qlinear_cwac_forward_fixed_point(x_q: torch.Tensor, w_q: torch.Tensor, qp: cwac_qparams, m0,
                                      shift, offset, out: torch.Tensor, stream=None, tuning=None):
+    if tuning is None and (_calls or _fast_calls()).forward_fixed_point(x_q, w_q, qp, m0, shift, offset, out, stream):
+        return
     assert x_q.dtype == torch.int8 and w_q.dtype == torch.int8 and out.dtype == torch.int8
     assert m0.dtype == torch.int32 and shift.dtype == torch.int32
     m, k = x_q.shape
@@ -418,6 +443,8 @@ def qconv2d_cwac_forward(x_q: torch.Tensor, w_q: torch.Tensor, stride: int, pad:
                          stream=None, tuning=None):
     """x_q int8 [B, H, W, C_in] (channels last), w_q int8 [C_out, KH, KW, C_in];
     out [B*OH*OW, C_out] int8 / float32 / int32 per out_kind."""
+    if tuning is None and (_calls or _fast_calls()).conv2d(x_q, w_q, stride, pad, qp, mult, offset, fbias, out_kind, out, stream):
+        return
     assert x_q.dtype == torch.int8 and w_q.dtype == torch.int8
     assert x_q.is_contiguous() and w_q.is_contiguous() and x_q.dim() == 4 and w_q.dim() == 4
     b, h, w, c_in = x_q.shape
@@ -470,6 +497,8 @@ def cwac_fold_weight_only(alpha, beta, bias, mult: torch.Tensor, fbias: torch.Te
 def qlinear_w4a16_cwac_forward(x: torch.Tensor, packed_w: torch.Tensor, packed_sz: torch.Tensor,
                                n: int, mult, fbias, out: torch.Tensor, stream=None, tuning=None):
     """x float16 [m, k]; out float16 (CWAC_OUT_FP16) or float32 (CWAC_OUT_FP32) [m, n]."""
+    if tuning is None and (_calls or _fast_calls()).w4a16(x, packed_w, packed_sz, n, mult, fbias, out, stream):
+        return
     assert x.dtype == torch.float16 and out.dtype in (torch.float16, torch.float32)
     m, k = x.shape
     assert out.shape == (m, n)

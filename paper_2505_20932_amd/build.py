@@ -1,4 +1,5 @@
-"""Builds libcwac_hip.so (the C-ABI library) in-tree with hipcc for gfx950."""
+"""Builds libcwac_hip.so (the C-ABI library) in-tree with hipcc for gfx950, and beside it the Python extension through which
+the binding makes its most frequent calls."""
 from __future__ import annotations
 
 import os
@@ -36,11 +37,30 @@ def _compile(src: str, extra=(), suffix: str = "") -> str:
     return obj
 
 
+FAST_CALLS = os.path.join(PKG, "_fast_calls.so")
+
+
+def _build_fast_calls() -> None:
+    """csrc/fast_calls.cpp: host code only, against the headers of Python and of the installed torch."""
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM",
+                    f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", os.path.join(ROOT, "include"),
+                    "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(root, "include/torch/csrc/api/include"),
+                    "-isystem", "/opt/rocm/include", "-isystem", sysconfig.get_paths()["include"],
+                    os.path.join(CSRC, "fast_calls.cpp"), "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10",
+                    "-lc10_hip", "-o", FAST_CALLS], check=True, stderr=subprocess.PIPE, text=True)
+
+
 def build_library(verbose: bool = True) -> str:
     os.makedirs(BUILD, exist_ok=True)
     try:
-        with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+        with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as ex:
+            calls = ex.submit(_build_fast_calls)
             objs = list(ex.map(_compile, SOURCES))
+            calls.result()
         subprocess.run([_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB],
                        check=True, stderr=subprocess.PIPE, text=True)
     except subprocess.CalledProcessError as e:
