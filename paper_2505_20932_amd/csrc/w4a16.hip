@@ -154,6 +154,7 @@ struct W4Params {
   char *out;
   int64_t ldo;
   int tiles_m, tiles_n;
+  int whole;  // tiled kernel: workgroups that take a whole tile
 };
 
 constexpr int kFwdThreads = 512;  // 8 wavefronts: 2 per SIMD
@@ -317,20 +318,14 @@ __device__ __forceinline__ void w4_epilogue(const W4Params &p, v16f (&acc)[kTA][
   }
 }
 
+// One tile: 32 TB WM tokens from bm0 on (bm0 < m) x 512 / WM channels from bn0 on.
 template <int OUT_KIND, int TB, int WM>
-__global__ __launch_bounds__(kFwdThreads) void w4a16_kernel(const W4Params p) {
+__device__ __forceinline__ void w4_tile(const W4Params &p, int64_t bm0, int bn0, int8_t *smem) {
   using Cfg = W4Cfg<TB, WM>;
   constexpr int BN = Cfg::BN;
   constexpr int kXLoads = Cfg::XLOADS, kStageBytes = Cfg::STAGE_BYTES, kParams = Cfg::PARAMS;
-  extern __shared__ __attribute__((aligned(16))) int8_t smem[];
   float *s_mult = reinterpret_cast<float *>(smem + kParams);
   float *s_fb = reinterpret_cast<float *>(smem + kParams + BN * 4);
-
-  int tile_m, tile_n;
-  tile_of_block(blockIdx.x, p.tiles_m, p.tiles_n, tile_m, tile_n);
-  const int64_t bm0 = (int64_t)tile_m * Cfg::BM;  // row edges: clamped loads, predicated stores
-  int bn0 = tile_n * BN;
-  if (bn0 > p.n - BN) bn0 = p.n - BN;  // channel edge: tile shifted inwards (n % 32 == 0)
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
@@ -505,15 +500,45 @@ __global__ __launch_bounds__(kFwdThreads) void w4a16_kernel(const W4Params p) {
   w4_epilogue<OUT_KIND, TB, WM>(p, acc, smem, s_mult, s_fb, bm0, bn0, wave_m, wave_n, lane);
 }
 
-template <int OUT_KIND, int TB, int WM = 2>
-cwac_status launch_w4(const W4Params &p, hipStream_t st) {
+// Workgroups below p.whole take a tile each.  The others, PIECES to a tile, take 32 TB WM / PIECES tokens of one each: the
+// tiles of a last round that would leave at least half of the compute units idle.  A piece expands the whole tile's
+// weights, so it lasts longer than its share: about two thirds (halves) and half (quarters) of a tile.
+template <int OUT_KIND, int TB, int WM, int PIECES>
+__global__ __launch_bounds__(kFwdThreads) void w4a16_kernel(const W4Params p) {
+  extern __shared__ __attribute__((aligned(16))) int8_t smem[];
+  constexpr int BM = W4Cfg<TB, WM>::BM, BN = W4Cfg<TB, WM>::BN;
+  int id = blockIdx.x, piece = 0;
+  if (PIECES > 1 && id >= p.whole) {
+    const int rest = p.tiles_m * p.tiles_n - p.whole, j = id - p.whole;
+    piece = j / rest;
+    id = p.whole + j - piece * rest;
+  }
+  int tile_m, tile_n;
+  tile_of_block(id, p.tiles_m, p.tiles_n, tile_m, tile_n);
+  int64_t bm0 = (int64_t)tile_m * BM;  // row edges: clamped loads, predicated stores
+  int bn0 = tile_n * BN;
+  if (bn0 > p.n - BN) bn0 = p.n - BN;  // channel edge: tile shifted inwards (n % 32 == 0)
+  if constexpr (PIECES > 1) {
+    if ((int)blockIdx.x >= p.whole) {
+      bm0 += piece * (BM / PIECES);
+      if (bm0 < p.m) w4_tile<OUT_KIND, TB / PIECES, WM>(p, bm0, bn0, smem);  // the last tile's later pieces can be empty
+      return;
+    }
+  }
+  w4_tile<OUT_KIND, TB, WM>(p, bm0, bn0, smem);
+}
+
+template <int OUT_KIND, int TB, int WM = 2, int PIECES = 1>
+cwac_status launch_w4(W4Params p, hipStream_t st) {
   static const hipError_t attr =
-      hipFuncSetAttribute(reinterpret_cast<const void *>(&w4a16_kernel<OUT_KIND, TB, WM>),
+      hipFuncSetAttribute(reinterpret_cast<const void *>(&w4a16_kernel<OUT_KIND, TB, WM, PIECES>),
                           hipFuncAttributeMaxDynamicSharedMemorySize, W4Cfg<TB, WM>::LDS);
   if (attr != hipSuccess) return CWAC_E_LAUNCH;
-  const int64_t blocks = (int64_t)p.tiles_m * p.tiles_n;
+  const int64_t tiles = (int64_t)p.tiles_m * p.tiles_n, rest = PIECES > 1 ? tiles % 256 : 0;
+  const int64_t blocks = tiles + rest * (PIECES - 1);
   if (blocks > 0x7fffffff) return CWAC_E_LAUNCH;
-  w4a16_kernel<OUT_KIND, TB, WM><<<dim3((unsigned)blocks), kFwdThreads, W4Cfg<TB, WM>::LDS, st>>>(p);
+  p.whole = (int)(tiles - rest);
+  w4a16_kernel<OUT_KIND, TB, WM, PIECES><<<dim3((unsigned)blocks), kFwdThreads, W4Cfg<TB, WM>::LDS, st>>>(p);
   return launch_status();
 }
 
@@ -897,6 +922,17 @@ cwac_status qlinear_w4a16_cwac_forward_ex(const uint16_t *x, int64_t ldx, const 
   if (w4_tile == 512 || (w4_tile == 0 && n >= 512)) {
     p.tiles_m = (int)ceil_div(m, 128);
     p.tiles_n = (int)ceil_div(n, 512);
+    const int64_t tiles = (int64_t)p.tiles_m * p.tiles_n, rest = tiles % 256;
+    // A thin last round in pieces (us, whole tiles / pieces): rest 8, 1400 x 12288 x 4096 190 / 164; rest 32, 3000 x 6144 x
+    // 2048 98 / 82; rest 64, 3000 x 12288 x 4096 298 / 273; rest 96, 2048 x 11008 x 4096 189 / 174; rest 128, 2048 x 12288 x 4096
+    // 200 / 189.  Quarters rather than halves to 64: rest 8 164 / 169, rest 64 273 / 276; level at 68.  More than 128
+    // tiles would need two rounds of halves, 2 x 2/3 of a tile.
+    if (tiles > 256 && rest > 0 && rest <= 64)
+      return out_kind == CWAC_OUT_FP16 ? launch_w4<CWAC_OUT_FP16, 4, 1, 4>(p, as_stream(stream_handle))
+                                       : launch_w4<CWAC_OUT_FP32, 4, 1, 4>(p, as_stream(stream_handle));
+    if (tiles > 256 && rest > 0 && rest <= 128)
+      return out_kind == CWAC_OUT_FP16 ? launch_w4<CWAC_OUT_FP16, 4, 1, 2>(p, as_stream(stream_handle))
+                                       : launch_w4<CWAC_OUT_FP32, 4, 1, 2>(p, as_stream(stream_handle));
     return out_kind == CWAC_OUT_FP16 ? launch_w4<CWAC_OUT_FP16, 4, 1>(p, as_stream(stream_handle))
                                      : launch_w4<CWAC_OUT_FP32, 4, 1>(p, as_stream(stream_handle));
   }
