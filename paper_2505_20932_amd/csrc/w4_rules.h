@@ -51,6 +51,16 @@ inline int w4_stream_tile(int64_t m, int n, int k) {
   return best;
 }
 
+// Whether up to 16 tokens run in tiles of 16 channels instead (w4a16_stream16_kernel).  With m x n, the channels that the fullest of
+// 256 compute units gets are what counts: fewer with 16-channel tiles up to n = 4096 (16 against 32) and from 8224 to 12288
+// (48 against 64).  Gain over the 32-channel tiles, k = 128 .. 8192: n <= 4096 11 to 56 %, 9216 .. 12288 with up to 8 tokens 0 to
+// 24 %; with up to 8 tokens and n = 4128 .. 8192, where both give 32, -3 to 22 % to k = 4096, -8 to 5 % beyond.  Wider layers
+// lose up to 33 %, and 9 to 16 tokens wider than 4096 up to 40 %: their activations are read by twice the workgroups.
+inline bool w4_stream16_pays(int64_t m, int n, int k) {
+  if (n <= 4096) return m <= 16;
+  return m <= 8 && n <= 12288 && (n > 8192 || k <= 4096);
+}
+
 // 128-token tiles of the tiled kernel in a launch up to which it takes them (one per compute unit)
 constexpr int64_t kW4HalfTileUpTo = 256;
 

@@ -580,6 +580,25 @@ __device__ __forceinline__ void load_x_to_lds(__amdgpu_buffer_rsrc_t desc, int8_
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 
+// The epilogue of four channels of one token.
+template <int OUT_KIND>
+__device__ __forceinline__ void w4_store4(const W4Params &p, int64_t row, int ch, const v4f &sum) {
+  constexpr int ESZ = OUT_KIND == CWAC_OUT_FP16 ? 2 : 4;
+  float u[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const float v = sum[r] * (p.mult ? p.mult[ch + r] : 1.0f);
+    u[r] = v + (p.fbias ? p.fbias[ch + r] : 0.0f);
+  }
+  char *o = p.out + (row * p.ldo + ch) * ESZ;
+  if (OUT_KIND == CWAC_OUT_FP16) {
+    const h2 lo = {(_Float16)u[0], (_Float16)u[1]}, hi = {(_Float16)u[2], (_Float16)u[3]};
+    *reinterpret_cast<uint2 *>(o) = make_uint2(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi));
+  } else {
+    *reinterpret_cast<float4 *>(o) = make_float4(u[0], u[1], u[2], u[3]);
+  }
+}
+
 template <int OUT_KIND, class S>
 __global__ __launch_bounds__(64 * S::NW) void w4a16_stream_kernel(const W4Params p) {
   constexpr int NB = S::NB, MB = S::MB, MP = S::MP, NW = S::NW, D = S::D;
@@ -726,7 +745,6 @@ __global__ __launch_bounds__(64 * S::NW) void w4a16_stream_kernel(const W4Params
   __syncthreads();
   // thread -> (token, four channels): consecutive threads take consecutive channels of a token
   constexpr int CG = NB * 8, GROUPS = MB * 32 * CG;
-  constexpr int ESZ = OUT_KIND == CWAC_OUT_FP16 ? 2 : 4;
   for (int g = tid; g < GROUPS; g += 64 * NW) {
     const int cg = g % CG, row = g / CG;
     if (row >= rows) break;
@@ -735,19 +753,143 @@ __global__ __launch_bounds__(64 * S::NW) void w4a16_stream_kernel(const W4Params
     v4f sum = *reinterpret_cast<const v4f *>(part);
 #pragma unroll
     for (int w = 1; w < NW; ++w) sum += *reinterpret_cast<const v4f *>(part + w * S::WAVE_BYTES);
-    const int ch = n0 + 4 * cg;
-    float u[4];
+    w4_store4<OUT_KIND>(p, bm0 + row, n0 + 4 * cg, sum);
+  }
+}
+
+// ------------------------------------------------------------------------------------------
+// Up to 16 tokens: the same scheme on tiles of 16 output channels.  What bounds a decoding step here is not the
+// weight stream but what a compute unit does with it - thirteen vector instructions per eight codes, waits and
+// LDS reads, about 0.4 us per unit of a wavefront -, so the channels have to be dealt out evenly: 32-channel tiles
+// leave half of the compute units idle at n = 4096 and give 64 channels to some and 32 to others at n = 12288.
+// A unit is one quantization group, 128 input channels x 16 output channels = 1 KiB of codes.  Lane (r, q) of the
+// 16 x 16 x 32 MFMA takes channel r and, in step t, dword t of the 16 bytes that the packed layout keeps for (channel,
+// input channels 64 (q >> 1) + 8 (q & 1) + 16 t ..): one load and one LDS read bring all four steps, and the activation
+// operand follows with chunk 8 (q >> 1) + (q & 1) + 2 t of the token's 256-byte piece.  One token, cold weights, us, 32-channel tiles /
+// these: 4096 x 4096 6.3 / 4.6, 4096 x 11008 12.0 / 8.1 (2.9 TB/s), 12288 x 4096 9.6 / 8.4 (3.2 TB/s), 2048 x 2048 4.3 / 3.3.  Rings of
+// three or four slots and four wavefronts: within 4 % where one workgroup sits on a compute unit, up to 40 % slower
+// where three do.
+// ------------------------------------------------------------------------------------------
+template <int MP_, int NW_, int D_>
+struct Stream16Cfg {
+  static constexpr int MP = MP_, NW = NW_, D = D_;
+  static constexpr int SZ_OFF = 1024, X_OFF = SZ_OFF + 256;
+  static constexpr int SLOT = X_OFF + MP * 256;
+  static constexpr int RING = D * SLOT;
+  static constexpr int L = 2 + MP / 4;  // load instructions per unit
+  static constexpr int WAVE_BYTES = RING;
+  static constexpr int LDS = NW * WAVE_BYTES;
+  static_assert((MP == 8 || MP == 16) && RING >= 1024 && LDS <= 160 * 1024 && D * L < 64, "LDS budget, 6-bit load counter");
+};
+
+template <int OUT_KIND, class S>
+__global__ __launch_bounds__(64 * S::NW) void w4a16_stream16_kernel(const W4Params p) {
+  constexpr int MP = S::MP, NW = S::NW, D = S::D;
+  extern __shared__ __attribute__((aligned(16))) int8_t smem[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, quad = lane >> 4;
+  const int n0 = blockIdx.x * 16;  // n % 32 == 0
+  const int rows = (int)p.m;
+  const int kb64 = p.k / 64, units = p.k / kGroup;
+  const int u_begin = wave * units / NW, mine = (wave + 1) * units / NW - u_begin;
+  int8_t *ring = smem + wave * S::WAVE_BYTES;
+
+  // quad q of the lanes: 64-channel block q >> 1, half q & 1
+  const char *wrow = reinterpret_cast<const char *>(p.wp) + ((int64_t)(n0 >> 5) * kb64 + 2 * u_begin + (quad >> 1)) * 1024 +
+                     ((quad & 1) * 32 + (n0 & 16) + l16) * 16;
+  const uint32_t *szp = p.sz + n0 + l16;
+  const __amdgpu_buffer_rsrc_t xd = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(p.x), 0,
+                                                                      (int)((int64_t)(rows - 1) * p.ldx_bytes + 2 * p.k), 0x00020000);
+  int xo[MP / 4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const float v = sum[r] * (p.mult ? p.mult[ch + r] : 1.0f);
-      u[r] = v + (p.fbias ? p.fbias[ch + r] : 0.0f);
+  for (int t = 0; t < MP / 4; ++t) {  // 4 rows of 256 bytes per load, the chunk position XORed with the row
+    const int row = 4 * t + quad;
+    xo[t] = row * (int)p.ldx_bytes + ((l16 ^ row) << 4);
+  }
+  auto issue = [&](int i, int slot_i) {
+    int8_t *slot = ring + slot_i * S::SLOT;
+    __builtin_amdgcn_global_load_lds(CWAC_GLOBAL_PTR(wrow + (int64_t)i * 2048), CWAC_LDS_PTR(slot), 16, 0, 0);
+    __builtin_amdgcn_global_load_lds(CWAC_GLOBAL_PTR(szp + (int64_t)(u_begin + i) * p.n), CWAC_LDS_PTR(slot + S::SZ_OFF), 4, 0, 0);
+#pragma unroll
+    for (int t = 0; t < MP / 4; ++t) load_x_to_lds(xd, slot + S::X_OFF + t * 1024, xo[t], (u_begin + i) * 256);
+  };
+  v4f acc[2] = {v4f{0.0f, 0.0f, 0.0f, 0.0f}, v4f{0.0f, 0.0f, 0.0f, 0.0f}};
+  const ExpandConst ec = expand_const();
+  struct Unit {
+    u4 c;
+    uint32_t sz;
+    h8 x[4];
+  };
+  const int xrow = l16 < MP ? l16 : MP - 1;
+  auto read = [&](int slot_i, Unit &u) {
+    const int8_t *slot = ring + slot_i * S::SLOT;
+    u.c = *reinterpret_cast<const u4 *>(slot + lane * 16);
+    u.sz = *reinterpret_cast<const uint32_t *>(slot + S::SZ_OFF + l16 * 4);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int chunk = 8 * (quad >> 1) + (quad & 1) + 2 * t;
+      u.x[t] = *reinterpret_cast<const h8 *>(slot + S::X_OFF + xrow * 256 + ((chunk ^ xrow) << 4));
     }
-    char *o = p.out + ((bm0 + row) * p.ldo + ch) * ESZ;
-    if (OUT_KIND == CWAC_OUT_FP16) {
-      const h2 lo = {(_Float16)u[0], (_Float16)u[1]}, hi = {(_Float16)u[2], (_Float16)u[3]};
-      *reinterpret_cast<uint2 *>(o) = make_uint2(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi));
-    } else {
-      *reinterpret_cast<float4 *>(o) = make_float4(u[0], u[1], u[2], u[3]);
+  };
+  auto multiply = [&](const Unit &u) {
+    const GroupConst gc = group_const(u.sz);
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      acc[t & 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(expand8(u.c[t], gc, ec), u.x[t], acc[t & 1], 0, 0, 0);
+  };
+
+  // Memory operations return in order: with r units issued behind a unit, it is complete at r * L outstanding.
+#pragma unroll
+  for (int d = 0; d < D; ++d)
+    if (d < mine) issue(d, d);
+  int slot_i = 0;
+#pragma unroll 1
+  for (int i = 0; i + D < mine; ++i) {
+    __builtin_amdgcn_s_waitcnt(wait_imm((D - 1) * S::L, 15));
+    asm volatile("" ::: "memory");  // the slot reads stay below the wait
+    __builtin_amdgcn_sched_barrier(0);
+    Unit u;
+    read(slot_i, u);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(wait_imm(63, 0));  // in registers before the next unit may land in the slot
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    issue(i + D, slot_i);
+    multiply(u);
+    slot_i = slot_i + 1 == D ? 0 : slot_i + 1;
+  }
+  auto last = [&](auto tag) {  // the last D units: nothing more to issue
+    constexpr int behind = decltype(tag)::value;
+    if (behind >= D || behind >= mine) return;
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(wait_imm(behind < D ? behind * S::L : 0, 15));
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    Unit u;
+    read(slot_i, u);
+    multiply(u);
+    slot_i = slot_i + 1 == D ? 0 : slot_i + 1;
+  };
+  static_assert(D <= 4, "one call per slot");
+  last(std::integral_constant<int, 3>{});
+  last(std::integral_constant<int, 2>{});
+  last(std::integral_constant<int, 1>{});
+  last(std::integral_constant<int, 0>{});
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+
+  // partial tile over this wavefront's own ring: slot `lane` holds channels 4 quad .. 4 quad + 3 of token l16
+  reinterpret_cast<v4f *>(ring)[lane] = acc[0] + acc[1];
+  __syncthreads();
+  if (tid < 64) {  // thread -> (token, four channels): consecutive threads take consecutive channels of a token
+    const int cg = tid & 3, row = tid >> 2;
+    if (row < rows) {
+      const int8_t *part = smem + (cg * 16 + row) * 16;
+      v4f sum = *reinterpret_cast<const v4f *>(part);
+#pragma unroll
+      for (int w = 1; w < NW; ++w) sum += *reinterpret_cast<const v4f *>(part + w * S::WAVE_BYTES);
+      w4_store4<OUT_KIND>(p, row, n0 + 4 * cg, sum);
     }
   }
 }
@@ -778,6 +920,24 @@ cwac_status launch_w4_stream_cfg(W4Params p, int out_kind, hipStream_t st) {
   }
 }
 
+template <int MP, int NW, int D>
+cwac_status launch_w4_stream16(const W4Params &p, int out_kind, hipStream_t st) {
+  using S = Stream16Cfg<MP, NW, D>;
+  const dim3 grid((unsigned)(p.n / 16));
+  if (out_kind == CWAC_OUT_FP16) {
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&w4a16_stream16_kernel<CWAC_OUT_FP16, S>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS);
+    if (attr != hipSuccess) return CWAC_E_LAUNCH;
+    w4a16_stream16_kernel<CWAC_OUT_FP16, S><<<grid, 64 * NW, S::LDS, st>>>(p);
+  } else {
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&w4a16_stream16_kernel<CWAC_OUT_FP32, S>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS);
+    if (attr != hipSuccess) return CWAC_E_LAUNCH;
+    w4a16_stream16_kernel<CWAC_OUT_FP32, S><<<grid, 64 * NW, S::LDS, st>>>(p);
+  }
+  return launch_status();
+}
+
 // waves / depth: the caller's overrides (cwac_tuning.w4_small_waves / w4_small_depth), which keep to 32 channels and at most
 // 32 tokens per workgroup.
 template <int NW>
@@ -800,6 +960,8 @@ cwac_status launch_w4_stream_tile(const W4Params &p, int out_kind, hipStream_t s
 cwac_status launch_w4_stream(const W4Params &p, int tile, int waves, int depth, int out_kind, hipStream_t st) {
   if (waves || depth)
     return waves == 4 ? launch_w4_stream_forced<4>(p, depth, out_kind, st) : launch_w4_stream_forced<8>(p, depth, out_kind, st);
+  if (w4_stream16_pays(p.m, p.n, p.k))
+    return p.m <= 8 ? launch_w4_stream16<8, 8, 2>(p, out_kind, st) : launch_w4_stream16<16, 8, 2>(p, out_kind, st);
   switch (tile) {
     case 0: return launch_w4_stream_tile<0>(p, out_kind, st);
     case 1: return launch_w4_stream_tile<1>(p, out_kind, st);

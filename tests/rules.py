@@ -17,6 +17,7 @@ extern "C" int w4_tile(long long m, int n, int k) {
   const int tile = w4_stream_tile(m, n, k);
   return w4_stream_pays(m, n, k, tile) ? tile : -1;
 }
+extern "C" int w4_tile16(long long m, int n, int k) { return w4_stream16_pays(m, n, k); }
 // the direct-to-LDS kernel's tile shape for a linear layer of n >= 256 channels
 extern "C" int fast_shape(long long m, int n, int k, int out_bytes) { return fast_linear_shape(m, n, k, out_bytes); }
 // the small-problem kernel's tile, 0 where the tile kernels take the layer
@@ -54,6 +55,11 @@ def lib():
 
 def w4_tile(m, n, k):
     return lib().w4_tile(m, n, k)
+
+
+def w4_tile16(m, n, k):
+    """Whether up to 16 tokens stream in tiles of 16 channels."""
+    return bool(lib().w4_tile16(C.c_longlong(m), n, k))
 
 
 def fast_shape(m, n, k, out_bytes):

@@ -110,3 +110,22 @@ def test_random_shapes_lie_on_both_sides_of_the_weight_streaming_kernels_limit()
 def test_layers_between_the_kernels_take_the_one_that_measured_fastest(m, n, k, tile, split, lds):
     want = min((tile, B.CWAC_KERNEL_GENERIC_64), (split, B.CWAC_KERNEL_SPLIT_K), (lds, B.CWAC_KERNEL_DIRECT_LDS))[1]
     assert B.cwac_forward_kernel_for(m, n, k, k, k) == want
+
+
+# microseconds measured with cold weights: tiles of 32 and of 16 channels of the weight-streaming kernel
+@pytest.mark.parametrize("m,n,k,wide,narrow", [(1, 4096, 11008, 12.0, 8.1), (16, 4096, 4096, 7.0, 5.6), (12, 256, 8192, 8.5, 5.6),
+                                               (8, 12288, 4096, 11.2, 9.2), (9, 12288, 4096, 10.9, 12.4), (16, 5120, 2048, 4.7, 5.7),
+                                               (8, 5120, 8192, 9.8, 10.7), (4, 6144, 512, 3.5, 3.3), (1, 24576, 1024, 5.8, 7.0),
+                                               (8, 14336, 256, 3.5, 4.3), (4, 11008, 4096, 9.8, 8.2)])
+def test_weight_only_decode_takes_the_tile_that_measured_faster(m, n, k, wide, narrow):
+    assert rules.w4_tile16(m, n, k) == (narrow < wide)
+
+
+def test_gpu_shapes_reach_both_tile_widths_of_a_decoding_step():
+    from test_gpu_w4_mid_batch import TILES16, WIDE_MAIN_LOOP
+    assert all(rules.w4_tile16(*s) for s in TILES16)
+    assert not any(rules.w4_tile16(*s) for s in WIDE_MAIN_LOOP)
+    assert {rules.w4_tile(*s) for s in WIDE_MAIN_LOOP} == {0, 1, 7}
+    # a wavefront's share of the groups exceeds its two slots by a round at least, in shares of two lengths
+    assert any(min(shares(k // 128, 8)) >= 3 and len(shares(k // 128, 8)) == 2 and m > 8 for m, n, k in TILES16)
+    assert any(min(shares(k // 128, 8)) >= 2 and len(shares(k // 128, 8)) == 2 and m <= 8 for m, n, k in TILES16)

@@ -21,7 +21,15 @@ MAIN_LOOP = [(5, 288, 4224), (13, 288, 4224), (16, 4096, 3200), (33, 4096, 2176)
              (13, 8224, 896), (16, 8256, 1024)]
 
 
-@pytest.mark.parametrize("m,n,k", SHORT + MAIN_LOOP)
+# tiles of 16 channels (up to 16 tokens): one and both row counts' edges, fewer groups than wavefronts, shares of unequal
+# length over several rounds of the ring, the last 16 channels of a 32-channel block
+TILES16 = [(1, 256, 128), (8, 288, 896), (9, 288, 1152), (16, 320, 3200), (3, 4096, 2176), (16, 4096, 1408), (7, 8224, 256),
+           (1, 12288, 384), (8, 4128, 4096)]
+# the 32-channel tiles of those token counts where the 16-channel ones do not take the layer
+WIDE_MAIN_LOOP = [(5, 12320, 4224), (13, 4128, 4224), (8, 12320, 1024)]
+
+
+@pytest.mark.parametrize("m,n,k", SHORT + MAIN_LOOP + TILES16 + WIDE_MAIN_LOOP)
 def test_mid_batch_exact_operands(w4, m, n, k):  # noqa: F811
     print(f"w4a16 mid batch {m} x {n} x {k}", flush=True)
     x16, codes, scales, zeros = _exact_case(700 + m + n + k, m, n, k)
