@@ -20,6 +20,14 @@ inline bool fast_prefers_quarter_tile(int64_t m, int n) {
   return n >= 128 && t_half < 160 && t_q >= 96;
 }
 
+// True where a convolution of at least 256 rows takes 128 x 128 tiles however few they are: with up to one tile per compute unit
+// a layer lasts as long as one tile's K loop, and that of the deep ring (quarter_ring: 2) is the faster one.  3 x 3, 64 x 64
+// register-staged tile / this, us: 392 x 256 x 2304 14.9 / 13.2, 3136 x 256 x 2304 15.4 / 13.3, 294 x 512 x 4608 26.0 / 21.0,
+// 2205 x 512 x 4608 27.3 / 21.6.
+inline bool conv_quarter_tile(int64_t m, int n, int k, int c_in) {
+  return (c_in % 128) == 0 && k >= 1536 && n >= 256 && tiles_of(m, n, 128, 128) <= 256;
+}
+
 // K step and ring depth of the 128 x 128 tile (four wavefronts of 64 x 64; `kstep`: K or the channels of a filter tap).
 // Measured, microseconds at m x n x k, int8 output unless noted:
 //   0: 64-byte steps, three stages, three workgroups per compute unit: where steps of 128 do not divide K, and for
@@ -29,7 +37,10 @@ inline bool fast_prefers_quarter_tile(int64_t m, int n) {
 //      7252 x 512 x 512 7.1 -> 6.5, 2000 x 3072 x 768 11.8 -> 10.0.
 //   2: 128-byte steps, three stages, one workgroup per compute unit: one round of tiles and a long K, where nothing
 //      else covers a stage's round trip.  4616 x 768 x 3072 19.6 -> 16.1, 1000 x 4096 x 4096 30.7 -> 23.2,
-//      7252 x 512 x 2048 14.6 -> 12.8 (14.4 with 1), 6272 x 256 x 1024 8.5 -> 8.6 (8.4 with 1).
+//      7252 x 512 x 2048 14.6 -> 12.8 (14.4 with 1), 6272 x 256 x 1024 8.5 -> 8.6 (8.4 with 1).  Eight wavefronts in two groups
+//      that share a stage's k-steps (on another machine, four / eight): 4616 x 768 x 3072 17.0 / 16.5, 7252 x 512 x 2048 14.2 / 13.7,
+//      512 x 4096 x 11008 39.2 / 36.2, 3 x 3 convolutions 6272 x 256 x 2304 13.9 / 13.2, 6272 x 512 x 4608 24.9 / 23.0.  The time is
+//      about 6 us + 0.35 us per stage; four stages 0 to 2 % slower; with two stages (1) eight wavefronts 4 to 40 % slower.
 inline int quarter_ring(int64_t m, int n, int k, int kstep, bool wide) {
   const int64_t tiles = tiles_of(m, n, 128, 128);
   if ((kstep % 128) != 0 || (wide && tiles > 512)) return 0;

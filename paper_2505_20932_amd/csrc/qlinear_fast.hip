@@ -63,14 +63,15 @@ constexpr int s_waitcnt_imm(int vmcnt, int lgkmcnt) {
   return (vmcnt & 15) | (7 << 4) | ((lgkmcnt & 15) << 8) | (((vmcnt >> 4) & 3) << 14);
 }
 
-template <int BM_, int WM_, int BK, int NSTAGE, int NCHUNK, int BN_ = 256, int TA_ = 0>
+template <int BM_, int WM_, int BK, int NSTAGE, int NCHUNK, int BN_ = 256, int TA_ = 0, int KS_ = 1>
 struct FastCfg {
   static constexpr int BM = BM_, BN = BN_;
   static constexpr int TA = TA_ ? TA_ : (BN >= 128 ? 4 : BN / 32);  // 32-channel MFMA tiles per wavefront
   static constexpr int WM = WM_, WN = BN / (32 * TA);  // wavefronts along m and n
-  static constexpr int NWAVES = WN * WM, NT = 64 * NWAVES;
+  static constexpr int KS = KS_;                       // groups of wavefronts that share the k-steps of a stage
+  static constexpr int NWAVES = WN * WM * KS, NT = 64 * NWAVES;
   static constexpr int TB = BM / (32 * WM);      // 32-token MFMA tiles per wavefront
-  static constexpr int KK = BK / 32;  // MFMA k-steps per stage
+  static constexpr int KK = BK / 32 / KS;  // MFMA k-steps per stage and wavefront
   static constexpr int X_BYTES = BM * BK, W_BYTES = BN * BK, STAGE = X_BYTES + W_BYTES;
   static constexpr int RING = NSTAGE * STAGE;
   static constexpr int PARAM_BYTES = 4 * 256 * 4;  // offset, mult, fbias [256 channels], row scale [256 rows]
@@ -457,11 +458,15 @@ __device__ __forceinline__ void stats_epilogue(const FwdParams &p, v16i (&acc)[4
   }
 }
 
+// KS = 2 (the 128 x 128 tile, one workgroup to a compute unit): two groups of four wavefronts hold the same 64 x 64 sub-tiles and
+// take two of a stage's four k-steps each, so that every SIMD has a second wavefront to issue from while the first
+// one waits at its fragments, loads and barrier; operand reads and loads stay what they are.  The int32 halves
+// meet in LDS (exact), and either group finishes 32 of its wavefronts' 64 tokens.
 template <int BM, int WM, int BK, int NSTAGE, int NCHUNK, int OUT_KIND, bool INT_ONLY, bool CONV = false,
-          int BN = 256, int TA_ = 0>
-__global__ __launch_bounds__((FastCfg<BM, WM, BK, NSTAGE, NCHUNK, BN, TA_>::NT), (BM / (32 * WM)) == 2 ? 2 : 1) void qlinear_fast_kernel(
+          int BN = 256, int TA_ = 0, int KS = 1>
+__global__ __launch_bounds__((FastCfg<BM, WM, BK, NSTAGE, NCHUNK, BN, TA_, KS>::NT), (BM / (32 * WM)) == 2 ? 2 : 1) void qlinear_fast_kernel(
     const FwdParams p) {
-  using C = FastCfg<BM, WM, BK, NSTAGE, NCHUNK, BN, TA_>;
+  using C = FastCfg<BM, WM, BK, NSTAGE, NCHUNK, BN, TA_, KS>;
   constexpr int TB = C::TB, TA = C::TA;
   static_assert(OUT_KIND != kOutStats ||
                     (BM == 256 && BN == 256 && C::RING >= 131072 && C::STATS_LDS_BYTES <= 160 * 1024),
@@ -483,7 +488,8 @@ __global__ __launch_bounds__((FastCfg<BM, WM, BK, NSTAGE, NCHUNK, BN, TA_>::NT),
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
-  const int wave_m = wave % WM, wave_n = wave / WM;
+  const int group = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(wave / (C::NWAVES / KS));
+  const int wave_t = wave - group * (C::NWAVES / KS), wave_m = wave_t % WM, wave_n = wave_t / WM;
   const int l32 = lane & 31, half = lane >> 5;
   CWAC_STAMP(0);
 
@@ -605,7 +611,8 @@ __global__ __launch_bounds__((FastCfg<BM, WM, BK, NSTAGE, NCHUNK, BN, TA_>::NT),
   };
 
   // ---- LDS -> MFMA operand fragments (rows of a 32-row MFMA tile start at multiples of 16)
-  const int swz_l = C::swz(l32);
+  static_assert(KS == 1 || (KS == 2 && C::KK == 2 && BK == 128), "a group's k-steps differ in bits that its number does not touch");
+  const int swz_l = C::swz(l32) ^ (group * 2 * C::KK);  // k-step kk of group g is step KK g + kk of the stage
   const int x_off = (wave_m * 32 * TB + l32) * BK;
   const int w_off = C::X_BYTES + (wave_n * (32 * TA) + l32) * BK;
   auto read_frags = [&](int buf, int kk, v4i(&fw)[TA], v4i(&fx)[TB]) {
@@ -684,7 +691,8 @@ __global__ __launch_bounds__((FastCfg<BM, WM, BK, NSTAGE, NCHUNK, BN, TA_>::NT),
   for (int a = 0; a < TA; ++a)
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-      const v4i o = *reinterpret_cast<const v4i *>(s_off + wave_n * (32 * TA) + a * 32 + 8 * g + 4 * half);
+      v4i o = *reinterpret_cast<const v4i *>(s_off + wave_n * (32 * TA) + a * 32 + 8 * g + 4 * half);
+      if (KS > 1 && group) o = v4i{0, 0, 0, 0};  // the offset enters the sum once
 #pragma unroll
       for (int b = 0; b < TB; ++b)
 #pragma unroll
@@ -760,20 +768,58 @@ __global__ __launch_bounds__((FastCfg<BM, WM, BK, NSTAGE, NCHUNK, BN, TA_>::NT),
     stats_epilogue<TB, WM>(p, acc, smem, s_mult, s_fb, s_rs, s_pq, s_pf, bm0, bn0, tile_m, wave_m, wave_n,
                            wave_s, lane);
   } else {
+    // the tile's rows as the epilogue sees them: of all of a wavefront's tokens, or (KS == 2) of its group's half
+    constexpr int EB = TB / KS, EM = WM * KS;
+    v16i part[TA][EB];
+    auto &res = [&]() -> v16i(&)[TA][EB] {
+      if constexpr (KS == 1)
+        return acc;
+      else
+        return part;
+    }();
+    const int e_wave_m = KS == 1 ? wave_m : wave_m * KS + group;
+    if constexpr (KS == 2) {
+      // the ring is free: every wavefront fetched its last fragments before the last stage's barrier
+      static_assert(TB == 2 && C::NWAVES * TA * 4096 <= C::RING, "the exchanged halves lie over the ring");
+      v4i *give = reinterpret_cast<v4i *>(smem) + (group * (C::NWAVES / KS) + wave_t) * (TA * 256) + lane;
+      const v4i *take = reinterpret_cast<const v4i *>(smem) + ((1 - group) * (C::NWAVES / KS) + wave_t) * (TA * 256) + lane;
+#pragma unroll
+      for (int a = 0; a < TA; ++a)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          v4i t;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            t[r] = group ? acc[a][0][4 * g + r] : acc[a][TB - 1][4 * g + r];
+            part[a][0][4 * g + r] = group ? acc[a][TB - 1][4 * g + r] : acc[a][0][4 * g + r];
+          }
+          give[(a * 4 + g) * 64] = t;
+        }
+      __syncthreads();
+#pragma unroll
+      for (int a = 0; a < TA; ++a)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const v4i t = take[(a * 4 + g) * 64];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) part[a][0][4 * g + r] += t[r];
+        }
+      __syncthreads();  // the slabs of the epilogue go over the halves
+    }
     // whole-line stores need 16-byte aligned rows and tile origin (p.vec_store: base and row pitch)
     constexpr int ESZ = (OUT_KIND == CWAC_OUT_INT8 || OUT_KIND == kOutFixed || OUT_KIND == kOutTable) ? 1 : 4;
     const int vs = p.vec_store && (((bn0 * ESZ) & 15) == 0);
     if (vs) {
       if constexpr (OUT_KIND == CWAC_OUT_INT8 || OUT_KIND == kOutTable) {
         if (p.zr & 1)
-          fast_epilogue<OUT_KIND, INT_ONLY, true, TB, WM, TA, 2>(p, acc, smem, s_mult, s_fb, s_rs, bm0, bn0, wave_m, wave_n, lane);
+          fast_epilogue<OUT_KIND, INT_ONLY, true, EB, EM, TA, 2>(p, res, smem, s_mult, s_fb, s_rs, bm0, bn0, e_wave_m, wave_n, lane);
         else
-          fast_epilogue<OUT_KIND, INT_ONLY, true, TB, WM, TA, 1>(p, acc, smem, s_mult, s_fb, s_rs, bm0, bn0, wave_m, wave_n, lane);
+          fast_epilogue<OUT_KIND, INT_ONLY, true, EB, EM, TA, 1>(p, res, smem, s_mult, s_fb, s_rs, bm0, bn0, e_wave_m, wave_n, lane);
       } else {
-        fast_epilogue<OUT_KIND, INT_ONLY, true, TB, WM, TA>(p, acc, smem, s_mult, s_fb, s_rs, bm0, bn0, wave_m, wave_n, lane);
+        fast_epilogue<OUT_KIND, INT_ONLY, true, EB, EM, TA>(p, res, smem, s_mult, s_fb, s_rs, bm0, bn0, e_wave_m, wave_n, lane);
       }
     } else
-      fast_epilogue<OUT_KIND, INT_ONLY, false, TB, WM, TA>(p, acc, smem, s_mult, s_fb, s_rs, bm0, bn0, wave_m, wave_n, lane);
+      fast_epilogue<OUT_KIND, INT_ONLY, false, EB, EM, TA>(p, res, smem, s_mult, s_fb, s_rs, bm0, bn0, e_wave_m, wave_n, lane);
   }
   CWAC_STAMP(3);
 #ifdef CWAC_V_STAMP
@@ -1300,19 +1346,19 @@ cwac_status launch_persist(FwdParams p, int out_kind, bool int_only, int max_wor
 }
 
 template <int BM, int WM, int BK, int NSTAGE, int NCHUNK, int OUT_KIND, bool INT_ONLY, bool CONV = false,
-          int BN = 256, int TA = 0>
+          int BN = 256, int TA = 0, int KS = 1>
 cwac_status launch_one(const FwdParams &p, dim3 grid, hipStream_t st) {
-  using C = FastCfg<BM, WM, BK, NSTAGE, NCHUNK, BN, TA>;
+  using C = FastCfg<BM, WM, BK, NSTAGE, NCHUNK, BN, TA, KS>;
   constexpr int LDS = OUT_KIND == kOutStats ? C::STATS_LDS_BYTES : C::LDS_BYTES;
   static const hipError_t attr = hipFuncSetAttribute(
-      reinterpret_cast<const void *>(&qlinear_fast_kernel<BM, WM, BK, NSTAGE, NCHUNK, OUT_KIND, INT_ONLY, CONV, BN, TA>),
+      reinterpret_cast<const void *>(&qlinear_fast_kernel<BM, WM, BK, NSTAGE, NCHUNK, OUT_KIND, INT_ONLY, CONV, BN, TA, KS>),
       hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
   if (attr != hipSuccess) return CWAC_E_LAUNCH;
-  qlinear_fast_kernel<BM, WM, BK, NSTAGE, NCHUNK, OUT_KIND, INT_ONLY, CONV, BN, TA><<<grid, C::NT, LDS, st>>>(p);
+  qlinear_fast_kernel<BM, WM, BK, NSTAGE, NCHUNK, OUT_KIND, INT_ONLY, CONV, BN, TA, KS><<<grid, C::NT, LDS, st>>>(p);
   return launch_status();
 }
 
-template <int BM, int WM, int BK, int NSTAGE, int NCHUNK, bool CONV = false, int BN = 256, int TA = 0>
+template <int BM, int WM, int BK, int NSTAGE, int NCHUNK, bool CONV = false, int BN = 256, int TA = 0, int KS = 1>
 cwac_status launch_cfg(FwdParams p, int out_kind, bool int_only, hipStream_t st) {
   p.tiles_m = (int)ceil_div(p.m, BM);
   p.tiles_n = (int)ceil_div(p.n, BN);
@@ -1321,23 +1367,23 @@ cwac_status launch_cfg(FwdParams p, int out_kind, bool int_only, hipStream_t st)
   const dim3 grid((unsigned)blocks);
   if constexpr (!CONV) {
     if (out_kind == kOutFixed)
-      return launch_one<BM, WM, BK, NSTAGE, NCHUNK, kOutFixed, true, false, BN, TA>(p, grid, st);
+      return launch_one<BM, WM, BK, NSTAGE, NCHUNK, kOutFixed, true, false, BN, TA, KS>(p, grid, st);
   }
   if (out_kind == CWAC_OUT_INT8)
-    return int_only ? launch_one<BM, WM, BK, NSTAGE, NCHUNK, CWAC_OUT_INT8, true, CONV, BN, TA>(p, grid, st)
-                    : launch_one<BM, WM, BK, NSTAGE, NCHUNK, CWAC_OUT_INT8, false, CONV, BN, TA>(p, grid, st);
+    return int_only ? launch_one<BM, WM, BK, NSTAGE, NCHUNK, CWAC_OUT_INT8, true, CONV, BN, TA, KS>(p, grid, st)
+                    : launch_one<BM, WM, BK, NSTAGE, NCHUNK, CWAC_OUT_INT8, false, CONV, BN, TA, KS>(p, grid, st);
   if (out_kind == CWAC_OUT_FP32)
-    return launch_one<BM, WM, BK, NSTAGE, NCHUNK, CWAC_OUT_FP32, false, CONV, BN, TA>(p, grid, st);
-  return launch_one<BM, WM, BK, NSTAGE, NCHUNK, CWAC_OUT_INT32, false, CONV, BN, TA>(p, grid, st);
+    return launch_one<BM, WM, BK, NSTAGE, NCHUNK, CWAC_OUT_FP32, false, CONV, BN, TA, KS>(p, grid, st);
+  return launch_one<BM, WM, BK, NSTAGE, NCHUNK, CWAC_OUT_INT32, false, CONV, BN, TA, KS>(p, grid, st);
 }
 
-template <int BM, int WM, int BK, int NSTAGE, int NCHUNK = 2, int BN = 256, int TA = 0>
+template <int BM, int WM, int BK, int NSTAGE, int NCHUNK = 2, int BN = 256, int TA = 0, int KS = 1>
 cwac_status launch_table_cfg(FwdParams p, hipStream_t st) {
   p.tiles_m = (int)ceil_div(p.m, BM);
   p.tiles_n = (int)ceil_div(p.n, BN);
   const int64_t blocks = (int64_t)p.tiles_m * p.tiles_n;
   if (blocks > 0x7fffffff) return CWAC_E_LAUNCH;
-  return launch_one<BM, WM, BK, NSTAGE, NCHUNK, kOutTable, true, false, BN, TA>(p, dim3((unsigned)blocks), st);
+  return launch_one<BM, WM, BK, NSTAGE, NCHUNK, kOutTable, true, false, BN, TA, KS>(p, dim3((unsigned)blocks), st);
 }
 
 }  // namespace
@@ -1351,7 +1397,7 @@ cwac_status launch_fast_table(FwdParams p, int shape, int max_workgroups, int lo
     shape = fast_linear_shape(p.m, p.n, p.k, 1);
   if (shape == CWAC_SHAPE_128_128) {
     const int ring = quarter_ring(p.m, p.n, p.k, p.k, false);
-    if (ring == 2) return launch_table_cfg<128, 2, 128, 3, 4, 128, 2>(p, st);
+    if (ring == 2) return launch_table_cfg<128, 2, 128, 3, 2, 128, 2, 2>(p, st);
     if (ring == 1) return launch_table_cfg<128, 2, 128, 2, 2, 128, 2>(p, st);
     return launch_table_cfg<128, 2, 64, 3, 2, 128, 2>(p, st);
   }
@@ -1399,7 +1445,7 @@ cwac_status launch_fast(FwdParams p, int out_kind, bool int_only, const Tune &tu
   if (shape == CWAC_SHAPE_AUTO) shape = fast_linear_shape(p.m, p.n, p.k, out_bytes);
   if (shape == CWAC_SHAPE_128_128) {
     const int ring = quarter_ring(p.m, p.n, p.k, p.k, out_bytes > 1);
-    if (ring == 2) return launch_cfg<128, 2, 128, 3, 4, false, 128, 2>(p, out_kind, int_only, st);
+    if (ring == 2) return launch_cfg<128, 2, 128, 3, 2, false, 128, 2, 2>(p, out_kind, int_only, st);
     if (ring == 1) return launch_cfg<128, 2, 128, 2, 2, false, 128, 2>(p, out_kind, int_only, st);
     return launch_cfg<128, 2, 64, 3, 2, false, 128, 2>(p, out_kind, int_only, st);
   }
@@ -1428,10 +1474,10 @@ cwac_status launch_fast_conv(FwdParams p, int out_kind, bool int_only, int shape
   const bool full_ok = (p.cv_cin % 128) == 0;
   // `shape` (cwac_tuning, same results): _256_8W | _128_PAIR | _128_128; the four-wavefront forms of
   // the 256-token tile are not instantiated for the convolution and leave the choice automatic
-  if (shape == CWAC_SHAPE_128_128 || (shape == CWAC_SHAPE_AUTO && fast_prefers_quarter_tile(p.m, p.n)))
-  {
+  if (shape == CWAC_SHAPE_128_128 || (shape == CWAC_SHAPE_AUTO && (fast_prefers_quarter_tile(p.m, p.n) ||
+                                                                   conv_quarter_tile(p.m, p.n, p.k, p.cv_cin)))) {
     const int ring = quarter_ring(p.m, p.n, p.k, p.cv_cin, esz > 1);
-    if (ring == 2) return launch_cfg<128, 2, 128, 3, 4, true, 128, 2>(p, out_kind, int_only, st);
+    if (ring == 2) return launch_cfg<128, 2, 128, 3, 2, true, 128, 2, 2>(p, out_kind, int_only, st);
     if (ring == 1) return launch_cfg<128, 2, 128, 2, 2, true, 128, 2>(p, out_kind, int_only, st);
     return launch_cfg<128, 2, 64, 3, 2, true, 128, 2>(p, out_kind, int_only, st);
   }

@@ -453,7 +453,7 @@ extern "C" cwac_status qconv2d_cwac_forward_ex(const int8_t *x_q, const int8_t *
   const bool fast_ok = fast_conv_ok(p, image_bytes);
   bool fast = fast_ok && (c_out >= 256 ? ceil_div(m, 128) * ceil_div(c_out, 256)
                                       : ceil_div(m, 256) * ceil_div(c_out, c_out < 128 ? 64 : 128)) >= 64;
-  if (fast_ok && c_out >= 256 && fast_prefers_quarter_tile(m, c_out)) fast = true;
+  if (fast_ok && c_out >= 256 && (fast_prefers_quarter_tile(m, c_out) || conv_quarter_tile(m, c_out, (int)k, c_in))) fast = true;
   if (tune.kernel == CWAC_KERNEL_DIRECT_LDS) {  // the caller's override, as for the linear layer
     fast = fast_ok;
   } else if (tune.kernel != CWAC_KERNEL_AUTO && tune.kernel != CWAC_KERNEL_SPLIT_K) {

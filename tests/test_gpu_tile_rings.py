@@ -46,6 +46,35 @@ def test_ring_bit_exact(orc, m, n, k, pipe):
     np.testing.assert_array_equal(o32.cpu().numpy(), orc.folded_forward(acc, off, mult, 0, fb, sxr, want_f32=True)[1])
 
 
+# convolutions of few 128 x 128 tiles and a long K by the library's own choice, and beside its bounds (K, c_in % 128, rows)
+@pytest.mark.parametrize("shape", [(2, 14, 13, 256, 256, 3, 3, 1, 1), (7, 7, 7, 512, 272, 3, 3, 1, 1), (2, 12, 11, 128, 256, 3, 4, 1, 1),
+                                   (3, 10, 10, 192, 256, 3, 3, 1, 1), (1, 14, 14, 256, 256, 3, 3, 1, 1), (2, 14, 13, 128, 256, 3, 3, 1, 1)])
+@pytest.mark.parametrize("kind", ["int8", "fp32", "int32"])
+def test_conv_of_few_tiles_bit_exact(orc, shape, kind):
+    b, h, w, c, n, kh, kw, stride, pad = shape
+    print(f"conv of few tiles {shape} {kind}", flush=True)
+    rng = np.random.default_rng(sum(shape))
+    xq = rng.integers(-128, 128, (b, h, w, c), dtype=np.int8)
+    wq = rng.integers(-127, 128, (n, kh, kw, c), dtype=np.int8)
+    acc = orc.conv2d_i8(xq, wq, stride, pad, -3)
+    mult = (np.abs(rng.standard_normal(n)) * 3e-4 + 1e-5).astype(np.float32)
+    off = rng.integers(-5000, 5000, n).astype(np.int32)
+    fb = rng.standard_normal(n).astype(np.float32)
+    qp = P.make_qparams(z_x=-3, z_r=5)
+    if kind == "int8":
+        out = torch.empty(acc.shape[0], n, dtype=torch.int8, device=DEV)
+        P.qconv2d_cwac_forward(dev(xq), dev(wq), stride, pad, qp, dev(mult), dev(off), None, P.CWAC_OUT_INT8, out)
+        np.testing.assert_array_equal(out.cpu().numpy(), orc.folded_forward(acc, off, mult, 5))
+    elif kind == "fp32":
+        out = torch.empty(acc.shape[0], n, dtype=torch.float32, device=DEV)
+        P.qconv2d_cwac_forward(dev(xq), dev(wq), stride, pad, qp, dev(mult), dev(off), dev(fb), P.CWAC_OUT_FP32, out)
+        np.testing.assert_array_equal(out.cpu().numpy(), orc.folded_forward(acc, off, mult, 0, fb, None, want_f32=True)[1])
+    else:
+        out = torch.empty(acc.shape[0], n, dtype=torch.int32, device=DEV)
+        P.qconv2d_cwac_forward(dev(xq), dev(wq), stride, pad, qp, None, dev(off), None, P.CWAC_OUT_INT32, out)
+        np.testing.assert_array_equal(out.cpu().numpy(), acc + off)
+
+
 @pytest.mark.parametrize("shape", [(2, 14, 13, 128, 256, 3, 3, 1, 1), (5, 8, 9, 256, 272, 3, 3, 1, 1), (3, 17, 17, 128, 256, 2, 2, 2, 0)])
 def test_conv_ring_bit_exact(orc, shape):
     b, h, w, c, n, kh, kw, stride, pad = shape
