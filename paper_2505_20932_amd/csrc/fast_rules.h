@@ -65,9 +65,12 @@ inline int fast_linear_shape(int64_t m, int n, int k, int out_bytes) {
   //    at K = 384), else the persistent tile (3152 x 3072 x 768, 600 of them: 14.3, 128 x 128 tiles 15.2; 12608 x 768 x
   //    3072 fp32, 594: 39.4 / 45.7).
   //  * Otherwise the persistent 256 x 256 tile (which splits the tiles of a thin last round in two).
-  //    With 4-byte outputs and a short K loop the tile's store burst weighs as much as its K loop:
-  //    when, on top, the last round leaves a good part of the chip idle, the 128 x 128 tile (three
-  //    workgroups per compute unit, four times as many tiles, stores spread out) finishes sooner.
+  //    With 4-byte outputs and a short K loop the tile's store burst weighs as much as its K loop: there the 128 x 128
+  //    tile (three workgroups per compute unit, four times as many tiles, stores spread out) finishes sooner.  fp32, 2 x 54
+  //    layers from 160 to 2364 tiles, persistent / 128 x 128: K = 384 and 512 1.00 to 1.25 (12608 x 2304 x 384 34.5 / 31.5, 25216 x
+  //    1152 x 512 39.9 / 32.0) but for one of 198 tiles (0.94); K = 768 1.00 to 1.26 to four rounds (12608 x 2304: 44.7 / 39.2),
+  //    0.96 to 1.01 beyond; K = 1024 to two rounds 0.98 to 1.18, beyond them 0.86 to 1.05 unless the last round leaves a
+  //    good part of the chip idle (33000 x 1152: 68.8 / 60.5); K = 1536 0.77 to 1.02.
   //  * 128 to 255 tokens: 128-token tiles, the only ones that the rows fill.
   if (fast_prefers_quarter_tile(m, n)) return CWAC_SHAPE_128_128;
   if ((k % 128) != 0) return CWAC_SHAPE_128_PAIR;
@@ -78,7 +81,7 @@ inline int fast_linear_shape(int64_t m, int n, int k, int out_bytes) {
     return tiles_of(m, n, 128, 128) <= 512 || k <= 256 ? CWAC_SHAPE_128_128 : CWAC_SHAPE_256_PERSIST;
   }
   const double fill = (double)t256 / (double)(256 * ((t256 + 255) / 256));  // busy share of the rounds
-  if (out_bytes > 1 && k <= 1024 && fill < 0.85) return CWAC_SHAPE_128_128;
+  if (out_bytes > 1 && k <= 1024 && (fill < 0.85 || k <= 640 || t256 <= (k <= 768 ? 1024 : 512))) return CWAC_SHAPE_128_128;
   return CWAC_SHAPE_256_PERSIST;
 }
 
