@@ -25,6 +25,7 @@ namespace {
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef int v4i __attribute__((ext_vector_type(4)));
 
@@ -683,6 +684,104 @@ __global__ __launch_bounds__(64 * NW * G, D == 64 && BIAS ? 2 : (CHUNKS || (BIAS
     attention_store_row<D>(p, st.sum, st.oc, p.a + (row0 + qrow) * p.lda + head * D, half, q < p.tokens && live);
 }
 
+// Few heads (an image or two): a workgroup per (image, head, block of 32 queries) whose eight wavefronts split the keys.  What
+// takes the time there is the chain of one wavefront through all key tiles on a few compute units; here a wavefront
+// takes tiles wave, wave + 8, ... - one at 197 tokens - with K and V of a tile in its own slice of LDS, and the eight
+// partial results meet once: each wavefront rescales to the largest maximum and all threads add up, in wavefront
+// order, normalize and store.  us, a workgroup per 224 queries (128 of a long sequence) of a head / this: one image of 12 heads and 197
+// tokens 6.6 / 5.0, of 577 tokens 12.9 / 8.4, of 16 heads and 257 tokens 7.9 / 5.9, window of 16 x 32 and 144 tokens 5.5 / 4.2.
+constexpr int kSplitWaves = 8;
+template <int D, bool BIAS>
+__global__ __launch_bounds__(64 * kSplitWaves) void attention_split_kernel(const AttnParams p) {
+  constexpr int NW = kSplitWaves, KB = 32 * k_stride(D), SLICE = KB + D * v_stride(1);
+  static_assert(SLICE >= D * 128, "a wavefront's partial outputs lie over its slice");
+  __shared__ __attribute__((aligned(16))) int8_t s_mem[NW * SLICE];
+  __shared__ float s_eoff[NW][32], s_sum[NW][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int l32 = lane & 31, half = lane >> 5;
+  int8_t *s_k = s_mem + wave * SLICE, *s_v = s_k + KB;
+  const uint32_t pair = blockIdx.x, image = pair / (uint32_t)p.heads;
+  const int head = (int)(pair - image * p.heads);
+  const int64_t row0 = (int64_t)image * p.tokens;
+  const int c = p.heads * D;
+  const int8_t *qbase = p.r + row0 * p.ld + head * D;
+  const _Float16 zb = (_Float16)(float)(1152 + p.z);
+  const h2 zbias = {zb, zb};
+  const int q = (int)blockIdx.y * 32 + l32, qrow = q < p.tokens ? q : p.tokens - 1;
+  const uint16_t *bias_row = BIAS ? p.bias + ((int64_t)head * p.tokens + qrow) * p.ldb : nullptr;
+  const int tiles = (p.tokens + 31) / 32;
+  AttnFill<1, 1, D> fill;
+  AttnBias bias;
+  if (wave < tiles) {
+    fill.load(qbase, p.ld, c, 32 * wave, p.tokens, lane);
+    if (BIAS) bias.load(bias_row, 32 * wave, p.tokens, half);
+  }
+  uint2 qraw[D / 16];
+  h8 fq[D / 16];
+#pragma unroll
+  for (int s = 0; s < D / 16; ++s)
+    qraw[s] = *reinterpret_cast<const uint2 *>(qbase + (uint32_t)(qrow * (int)p.ld + 16 * s + 8 * half));
+#pragma unroll
+  for (int s = 0; s < D / 16; ++s) fq[s] = codes_to_h8(qraw[s], zbias);
+  const float lscale = p.s * p.s * (D == 64 ? 0.125f : 0.17677669529663687f) * 1.44269504088896340736f;
+  AttnState<D> st;
+  st.mx = 0.0f, st.eoff = INFINITY, st.sum = 0.0f;  // no keys: rescaled by exp2(-inf)
+#pragma unroll
+  for (int a = 0; a < D / 32; ++a)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) st.oc[a][i] = 0.0f;
+  const int rounds = (tiles + NW - 1) / NW;
+  for (int i = 0; i < rounds; ++i) {  // uniform over the workgroup
+    const int tile = wave + NW * i;
+    if (tile < tiles) fill.store(s_k, s_v, zbias, lane);
+    __syncthreads();
+    const AttnBias now = bias;
+    if (tile + NW < tiles) {
+      fill.load(qbase, p.ld, c, 32 * (tile + NW), p.tokens, lane);
+      if (BIAS) bias.load(bias_row, 32 * (tile + NW), p.tokens, half);
+    }
+    if (tile < tiles)
+      attention_key_group<1, D, v_stride(1), BIAS>(0, i == 0, s_k, s_v, fq, now, p.tokens - 32 * tile, lscale, l32, half, st);
+    if (i + 1 < rounds) __syncthreads();  // the slice is read (by its own wavefront, in the compiler's eyes too)
+  }
+
+  // ---- the partial results meet: weights of wavefront w carry 2^eoff[w]; the smallest offset belongs to the largest maximum
+  if (half == 0) s_eoff[wave][l32] = st.eoff;
+  __syncthreads();
+  float eoff = s_eoff[0][l32];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) eoff = fminf(eoff, s_eoff[w][l32]);
+  const float corr = __builtin_amdgcn_exp2f(eoff - st.eoff);
+  s_sum[wave][lane] = st.sum * corr;
+  v4f *part = reinterpret_cast<v4f *>(s_k);
+#pragma unroll
+  for (int a = 0; a < D / 32; ++a)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      v4f t;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) t[r] = st.oc[a][4 * g + r] * corr;
+      part[(4 * a + g) * 64 + lane] = t;
+    }
+  __syncthreads();
+  // item (a, g): four channels 32 a + 8 g + 4 half .. of every lane's query
+  float sum = 0.0f;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) sum += s_sum[w][l32] + s_sum[w][l32 + 32];
+  const float onorm = p.s / (sum * p.s_a), zf = (float)p.z_a;
+  int8_t *orow = p.a + (row0 + qrow) * p.lda + head * D;
+  for (int item = wave; item < D / 8; item += NW) {
+    const int8_t *at = s_mem + (item * 64 + lane) * 16;
+    v4f o = *reinterpret_cast<const v4f *>(at);
+#pragma unroll
+    for (int w = 1; w < NW; ++w) o += *reinterpret_cast<const v4f *>(at + w * SLICE);
+    float v[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[r] = __builtin_fmaf(o[r], onorm, zf);
+    if (q < p.tokens) *reinterpret_cast<uint32_t *>(orow + 32 * (item >> 2) + 8 * (item & 3) + 4 * half) = pack_codes(v);
+  }
+}
+
 template <int NT, int NW, int D, int G, bool CHUNKS>
 cwac_status launch_attention(const AttnParams &p, hipStream_t st) {
   const dim3 grid((unsigned)ceil_div((int64_t)p.pairs, G), (unsigned)ceil_div(p.tokens, 32 * NW));
@@ -695,6 +794,17 @@ cwac_status launch_attention(const AttnParams &p, hipStream_t st) {
 
 template <int D>
 cwac_status launch_attention_d(const AttnParams &p, hipStream_t st) {
+  // The keys split over a workgroup's wavefronts while there is at most one such workgroup to a compute unit (us, above / split:
+  // 3 x 12 x 197 tokens, 252 of them, 6.6 / 5.3; 4 x 12 x 197, 336, 6.7 / 7.3; 12 x 577, 228, 12.9 / 8.4; 24 x 577, 456, 13.4 / 12.9) and
+  // more than three key tiles (12 x 50: 3.6 / 4.2).
+  if (p.tokens > 96 && (int64_t)p.pairs * ceil_div(p.tokens, 32) <= 256) {
+    const dim3 grid(p.pairs, (unsigned)ceil_div(p.tokens, 32));
+    if (p.bias)
+      attention_split_kernel<D, true><<<grid, 64 * kSplitWaves, 0, st>>>(p);
+    else
+      attention_split_kernel<D, false><<<grid, 64 * kSplitWaves, 0, st>>>(p);
+    return launch_status();
+  }
   switch ((p.tokens + 31) / 32) {
     // 256 threads per workgroup for short sequences
     case 1: return launch_attention<1, 1, D, 4, false>(p, st);

@@ -308,7 +308,10 @@ def test_attention_one_dominant_key_picks_its_value(tokens):
 @pytest.mark.parametrize("batch,tokens,heads,head_dim", [
     (1, 16, 5, 64), (3, 17, 3, 32), (1, 32, 1, 32), (5, 48, 1, 64), (1, 80, 2, 32), (1, 112, 2, 64), (1, 144, 3, 32),
     (1, 160, 1, 64), (2, 176, 1, 32), (1, 208, 2, 64), (1, 209, 1, 64), (1, 256, 1, 64), (1, 257, 2, 32),
-    (1, 272, 1, 64), (1, 273, 1, 32), (1, 384, 1, 64), (1, 385, 2, 64)])
+    (1, 272, 1, 64), (1, 273, 1, 32), (1, 384, 1, 64), (1, 385, 2, 64), (1, 96, 2, 64), (1, 97, 1, 64), (1, 2048, 4, 32),
+    # enough heads for a workgroup to hold one each: every key tile count again, and chunks of a long sequence
+    (26, 80, 4, 32), (65, 112, 1, 64), (18, 144, 3, 32), (52, 160, 1, 64), (22, 176, 2, 32), (10, 208, 4, 64), (37, 209, 1, 64),
+    (37, 224, 1, 32), (33, 256, 1, 64), (15, 257, 2, 32), (29, 272, 1, 64), (29, 273, 1, 32), (22, 384, 1, 64), (5, 385, 4, 64)])
 @pytest.mark.parametrize("rising", [False, True])
 def test_attention_tile_edges_and_rising_maxima(batch, tokens, heads, head_dim, rising):
     """The last key tile holding at most or more than 16 keys, one tile or two left in the last pair, heads that do
@@ -334,11 +337,12 @@ def test_attention_tile_edges_and_rising_maxima(batch, tokens, heads, head_dim, 
     _codes_within(full[:-1].cpu().numpy(), v, delta)
 
 
+@pytest.mark.parametrize("heads", [2, 64])  # keys split over a workgroup's wavefronts, and a workgroup per head
 @pytest.mark.parametrize("tokens,low", [(49, -65504.0), (144, -np.inf), (197, -65504.0), (300, -np.inf)])
-def test_attention_bias_that_masks_whole_key_groups(tokens, low):
+def test_attention_bias_that_masks_whole_key_groups(tokens, low, heads):
     """A bias of the lowest binary16 value, or minus infinity, on every key but the last eleven: the groups of
     keys before them have no weight, and no NaN."""
-    heads, d = 2, 32
+    d = 32
     rng = np.random.default_rng(tokens)
     r = np.clip(np.rint(rng.standard_normal((tokens, 3 * heads * d)) * 30), -128, 127).astype(np.int8)
     bias16 = np.zeros((heads, tokens, 32 * ((tokens + 31) // 32)), dtype=np.float16)
