@@ -10,8 +10,7 @@
 //   quantizer  code = clip(rne(fma(y, 1 / s, z)), -128, 127)                            (Eq. 1)
 //   attention  S = (K - z)(Q - z)^T exactly (integers below 2^24 in the fp32 MFMA accumulators);
 //              P = 1024 p = exp2(fma(S, s^2 / sqrt(d) * log2 e, 10 - that * max S));  O = (sum_j RN16(P_j) (V_j - z)) * s / sum_j P_j,
-//              keys taken in groups of 64 with a running maximum (earlier partial sums rescaled when it rises by more
-//              than a factor of 32 in the weights)
+//              keys taken in groups of 64 with a running maximum (earlier partial sums rescaled whenever it rises)
 //   GELU table entry(c) = clip(rne(GELU(s_in (c - z_in)) / s_out + z_out)) evaluated in fp64 (erf form)
 #include <hip/hip_runtime.h>
 
@@ -451,10 +450,6 @@ struct AttnState {
   v16f oc[D / 32];
 };
 
-// A raised maximum rescales what has been summed only if it grew by more than this many powers of two: the
-// weights then stay below 1024 * 2^kLazy = 32768, inside binary16.
-constexpr float kLazy = 5.0f;
-
 // A query's bias for a pair of key tiles, read one pair ahead (so the loads travel under the pair before).
 // Rows are padded to whole key tiles; a second tile beyond the last one reads the last one again.
 struct AttnBias {
@@ -472,7 +467,13 @@ struct AttnBias {
 
 // Scores, softmax weights and the second product for CNT key tiles from LDS tile t0 on, whose first key is
 // key0 + 32 t0 of the sequence.  HALF: only the first 16 keys of the (single) tile can be real.
-template <int CNT, int D, int VS, bool BIAS, bool HALF = false>
+// The weights always refer to the exact running maximum: the largest one is then 1024 and binary16 does not
+// round it.  Rescaling only after a rise by more than 2^5 took 1-5 % less time, but its dominant weights are rounded
+// while their sum is not: 128 x 197 tokens of peaked scores had 1.8 times the codes off against 64 bits (2.5e-3,
+// here 1.4e-3).  STRAIGHT: rescale in every group, by 1 where nothing rose.  With the chunked kernel's free registers
+// that is ahead of the branch (4 x 577 tokens 14.1 -> 13.4 us); the whole-sequence forms of 6 and 7 tiles spill for it
+// (128 x 197: 39 -> 68 us).
+template <int CNT, int D, int VS, bool BIAS, bool STRAIGHT, bool HALF = false>
 __device__ __forceinline__ void attention_key_group(int t0, bool first, const int8_t *s_k, const int8_t *s_v,
                                                     const h8 (&fq)[D / 16], const AttnBias &bias, int left,
                                                     float lscale, int l32, int half, AttnState<D> &st) {
@@ -524,7 +525,8 @@ __device__ __forceinline__ void attention_key_group(int t0, bool first, const in
   if (first) {
     st.mx = gmx;
     st.eoff = __builtin_fmaf(-gmx, dscale, 10.0f);
-  } else if ((gmx - st.mx) * dscale > kLazy) {  // the same decision in both lanes of a query
+  } else if (STRAIGHT || gmx > st.mx) {  // the same decision in both lanes of a query
+    if (STRAIGHT) gmx = fmaxf(gmx, st.mx);
     const float eoff = __builtin_fmaf(-gmx, dscale, 10.0f);
     const float corr = __builtin_amdgcn_exp2f(eoff - st.eoff);  // of the offsets as they are used
     st.sum *= corr;
@@ -571,11 +573,11 @@ __device__ __forceinline__ void attention_chunk(int key0, int tokens, const int8
     const AttnBias now = bias;
     if (BIAS && (CHUNKS || t0 + 2 < NT)) bias.load(bias_row, key0 + 32 * t0 + 64, tokens, half);
     if (t0 + 1 < NT && (!CHUNKS || rest > 32))
-      attention_key_group<2, D, VS, BIAS>(t0, f, s_k, s_v, fq, now, rest, lscale, l32, half, st);
+      attention_key_group<2, D, VS, BIAS, CHUNKS>(t0, f, s_k, s_v, fq, now, rest, lscale, l32, half, st);
     else if (rest > 16)
-      attention_key_group<1, D, VS, BIAS>(t0, f, s_k, s_v, fq, now, rest, lscale, l32, half, st);
+      attention_key_group<1, D, VS, BIAS, CHUNKS>(t0, f, s_k, s_v, fq, now, rest, lscale, l32, half, st);
     else
-      attention_key_group<1, D, VS, BIAS, true>(t0, f, s_k, s_v, fq, now, rest, lscale, l32, half, st);
+      attention_key_group<1, D, VS, BIAS, CHUNKS, true>(t0, f, s_k, s_v, fq, now, rest, lscale, l32, half, st);
     __builtin_amdgcn_sched_barrier(0);  // one group's score tiles live at a time
   }
 }
@@ -741,7 +743,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) void attention_split_kernel(const
       if (BIAS) bias.load(bias_row, 32 * (tile + NW), p.tokens, half);
     }
     if (tile < tiles)
-      attention_key_group<1, D, v_stride(1), BIAS>(0, i == 0, s_k, s_v, fq, now, p.tokens - 32 * tile, lscale, l32, half, st);
+      attention_key_group<1, D, v_stride(1), BIAS, false>(0, i == 0, s_k, s_v, fq, now, p.tokens - 32 * tile, lscale, l32, half, st);
     if (i + 1 < rounds) __syncthreads();  // the slice is read (by its own wavefront, in the compiler's eyes too)
   }
 
