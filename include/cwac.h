@@ -582,8 +582,8 @@ enum {
   CWAC_SHAPE_128_PAIR = 4,    /* 128 tokens x 256 channels, two workgroups per compute unit (K steps of 64); where its
                                  tiles are at most one per compute unit, k >= 3072 and k % 128 == 0: one workgroup per
                                  compute unit with three stages of 128 */
-  CWAC_SHAPE_128_128 = 5,     /* 128 x 128, four wavefronts of 64 x 64; K steps of 64 or 128 and two or three stages by
-                                 the number of tiles, k and the output's width */
+  CWAC_SHAPE_128_128 = 5,     /* 128 x 128, four wavefronts of 64 x 64 (eight that share a stage's K with three stages); K
+                                 steps of 64 or 128 and two or three stages by the number of tiles, k and the output's width */
   CWAC_SHAPE_256_PERSIST = 6  /* CWAC_SHAPE_256_8W's tile on persistent workgroups, one per compute unit, the
                                  next tile's first loads in flight under a tile's epilogue (linear layers, every
                                  epilogue but the fused statistics; convolutions take CWAC_SHAPE_256_8W) */

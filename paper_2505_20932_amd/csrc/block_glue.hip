@@ -351,8 +351,8 @@ __global__ __launch_bounds__(256) void table_lookup_kernel(const int8_t *in, int
 // of seven wavefronts to a compute unit), score tiles in pairs, a bias read a pair ahead, and a fill that moves
 // 4 keys x D / 8 channels per thread: V is transposed in registers (8-byte LDS writes instead of 2-byte ones).
 // Against one workgroup to a compute unit, 2-byte transposing writes and 224-query blocks of long sequences:
-// 128 images x 12 heads x 197 tokens 44.4 -> 34.8 us, 8 x 12 x 577 32.1 -> 20.9, 148 x 16 x 49 with a bias
-// 9.8 -> 8.6, one image 7.2 -> 6.5.  Chunks of 64 or 192 keys, three, five or seven wavefronts and shorter
+// 128 images x 12 heads x 197 tokens 45.5 -> 38.0 us, 8 x 12 x 577 32.1 -> 20.9, 148 x 16 x 49 with a bias
+// 9.5 -> 8.5, one image 7.2 -> 6.6.  Chunks of 64 or 192 keys, three, five or seven wavefronts and shorter
 // chunks for 197 tokens were 5 to 150 % slower.
 // ------------------------------------------------------------------------------------------
 constexpr int kHeadDim = 64;     // widest head; 32 is the other width
@@ -691,7 +691,7 @@ __global__ __launch_bounds__(64 * NW * G, D == 64 && BIAS ? 2 : (CHUNKS || (BIAS
 // takes tiles wave, wave + 8, ... - one at 197 tokens - with K and V of a tile in its own slice of LDS, and the eight
 // partial results meet once: each wavefront rescales to the largest maximum and all threads add up, in wavefront
 // order, normalize and store.  us, a workgroup per 224 queries (128 of a long sequence) of a head / this: one image of 12 heads and 197
-// tokens 6.6 / 5.0, of 577 tokens 12.9 / 8.4, of 16 heads and 257 tokens 7.9 / 5.9, window of 16 x 32 and 144 tokens 5.5 / 4.2.
+// tokens 6.6 / 5.0, of 577 tokens 12.9 / 8.6, of 16 heads and 257 tokens 7.9 / 5.9, window of 16 x 32 and 144 tokens 5.5 / 4.2.
 constexpr int kSplitWaves = 8;
 template <int D, bool BIAS>
 __global__ __launch_bounds__(64 * kSplitWaves) void attention_split_kernel(const AttnParams p) {
