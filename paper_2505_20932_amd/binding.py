@@ -161,7 +161,7 @@ def lib() -> C.CDLL:
             fn = getattr(l, name)
             fn.restype, fn.argtypes = res, args
         from . import _fast_calls as calls
-        calls.bind(cwac_qparams, {name: C.cast(getattr(l, name), vp).value for name in sig})
+        calls.bind(cwac_qparams, {name: C.cast(getattr(l, name), vp).value for name in sig}, _check)
         _lib, _calls = l, calls
     return _lib
 

@@ -8,6 +8,8 @@
 // Every function returns True when the call was made and returned CWAC_OK, and False otherwise: an argument that is
 // not exactly what the call documents, or an error status (nothing was launched then).  The caller goes on with
 // the ctypes form, which makes the checks again and raises.  So nothing is refused or accepted here that was not before.
+// CWAC_E_LAUNCH alone is raised from here: the runtime's error is taken with the status, and a second call could pass.
+#define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
 #include <ATen/core/TensorBase.h>
@@ -28,7 +30,7 @@ struct Entries {
   decltype(&::qconv2d_cwac_forward) conv2d;
   decltype(&::qlinear_w4a16_cwac_forward) w4a16;
 } g;
-PyObject *g_qparams_type = nullptr;
+PyObject *g_qparams_type = nullptr, *g_check = nullptr;  // the binding's structure type and its check of a status
 
 // What a call is given, checked one by one; `ok` stays true while everything is what the call documents.
 struct Args {
@@ -99,24 +101,37 @@ int64_t pitch(const at::TensorBase &t) {
 }
 bool same_shape(const at::TensorBase &a, const at::TensorBase &b) { return a.size(0) == b.size(0) && a.size(1) == b.size(1); }
 
-// Runs `call` with Python's lock released; False for an error status, for arguments that did not fit and for
-// tensors without storage (torch throws).
+// `f` for the entry point `name`: its result, False for tensors without storage (torch throws), an exception
+// for a launch that failed.
+struct LaunchFailed {};
 template <typename F>
-PyObject *guarded(F &&f) {
+PyObject *guarded(const char *name, F &&f) {
   bool done = false;
   try {
     done = f();
+  } catch (const LaunchFailed &) {
+    PyErr_Clear();
+    return PyObject_CallFunction(g_check, "is", (int)CWAC_E_LAUNCH, name);  // raises
   } catch (...) {
     done = false;
   }
   if (PyErr_Occurred()) PyErr_Clear();
   return PyBool_FromLong(done);
 }
+
+// Runs `call` with Python's lock released.
+struct Unlock {
+  PyThreadState *state = PyEval_SaveThread();
+  ~Unlock() { PyEval_RestoreThread(state); }
+};
 template <typename F>
 bool unlocked(F &&call) {
-  cwac_status st;
-  Py_BEGIN_ALLOW_THREADS st = call();
-  Py_END_ALLOW_THREADS return st == CWAC_OK;
+  const cwac_status st = [&] {
+    Unlock u;
+    return call();
+  }();
+  if (st == CWAC_E_LAUNCH) throw LaunchFailed();
+  return st == CWAC_OK;
 }
 
 constexpr auto kI8 = at::kChar;
@@ -124,7 +139,7 @@ constexpr auto kF32 = at::kFloat;
 
 // (x, s, z, q, stream)
 PyObject *py_quantize_act(PyObject *, PyObject *const *a, Py_ssize_t n) {
-  return guarded([&] {
+  return guarded("cwac_quantize_act", [&] {
     Args v;
     if (n != 5) return false;
     const at::TensorBase *x = v.matrix(a[0], kF32), *q = v.matrix(a[3], kI8);
@@ -142,7 +157,7 @@ PyObject *py_quantize_act(PyObject *, PyObject *const *a, Py_ssize_t n) {
 
 // (x, scale, q, stream)
 PyObject *py_quantize_rows_sym(PyObject *, PyObject *const *a, Py_ssize_t n) {
-  return guarded([&] {
+  return guarded("cwac_quantize_rows_sym", [&] {
     Args v;
     if (n != 4) return false;
     const at::TensorBase *x = v.matrix(a[0], kF32), *scale = v.typed(a[1], kF32), *q = v.matrix(a[2], kI8);
@@ -183,7 +198,7 @@ at::ScalarType out_type(long long kind) {
 
 // (x_q, w_q, qp, mult, offset, fbias, s_x_row, out_kind, out, stream)
 PyObject *py_forward(PyObject *, PyObject *const *a, Py_ssize_t n) {
-  return guarded([&] {
+  return guarded("qlinear_cwac_forward", [&] {
     Args v;
     if (n != 10) return false;
     const int32_t kind = (int32_t)v.integer(a[7]);
@@ -203,7 +218,7 @@ PyObject *py_forward(PyObject *, PyObject *const *a, Py_ssize_t n) {
 
 // (x_q, w_q, qp, mult, offset, table, out, stream)
 PyObject *py_forward_table(PyObject *, PyObject *const *a, Py_ssize_t n) {
-  return guarded([&] {
+  return guarded("qlinear_cwac_forward_table", [&] {
     Args v;
     Linear l;
     if (n != 8 || !l.take(v, a[0], a[1], a[6], kI8)) return false;
@@ -223,7 +238,7 @@ PyObject *py_forward_table(PyObject *, PyObject *const *a, Py_ssize_t n) {
 
 // (x_q, w_q, qp, m0, shift, offset, out, stream)
 PyObject *py_forward_fixed_point(PyObject *, PyObject *const *a, Py_ssize_t n) {
-  return guarded([&] {
+  return guarded("qlinear_cwac_forward_fixed_point", [&] {
     Args v;
     Linear l;
     if (n != 8 || !l.take(v, a[0], a[1], a[6], kI8)) return false;
@@ -242,7 +257,7 @@ PyObject *py_forward_fixed_point(PyObject *, PyObject *const *a, Py_ssize_t n) {
 
 // (x_q, w_q, stride, pad, qp, mult, offset, fbias, out_kind, out, stream)
 PyObject *py_conv2d(PyObject *, PyObject *const *a, Py_ssize_t n) {
-  return guarded([&] {
+  return guarded("qconv2d_cwac_forward", [&] {
     Args v;
     if (n != 11) return false;
     const at::TensorBase *x = v.typed(a[0], kI8), *w = v.typed(a[1], kI8);
@@ -274,7 +289,7 @@ PyObject *py_conv2d(PyObject *, PyObject *const *a, Py_ssize_t n) {
 
 // (x, packed_w, packed_sz, n, mult, fbias, out, stream)
 PyObject *py_w4a16(PyObject *, PyObject *const *a, Py_ssize_t n) {
-  return guarded([&] {
+  return guarded("qlinear_w4a16_cwac_forward", [&] {
     Args v;
     if (n != 8) return false;
     const at::TensorBase *x = v.matrix(a[0], at::kHalf), *out = v.tensor(a[6]);
@@ -297,9 +312,9 @@ PyObject *py_w4a16(PyObject *, PyObject *const *a, Py_ssize_t n) {
   });
 }
 
-// (the type of cwac_qparams, {entry point: address})
+// (the type of cwac_qparams, {entry point: address}, the check of a status)
 PyObject *py_bind(PyObject *, PyObject *const *a, Py_ssize_t n) {
-  if (n != 2 || !PyDict_Check(a[1])) return PyErr_Format(PyExc_TypeError, "bind(type, addresses)");
+  if (n != 3 || !PyDict_Check(a[1])) return PyErr_Format(PyExc_TypeError, "bind(type, addresses, check)");
   const struct {
     const char *name;
     void **slot;
@@ -317,6 +332,8 @@ PyObject *py_bind(PyObject *, PyObject *const *a, Py_ssize_t n) {
   }
   Py_INCREF(a[0]);
   Py_XSETREF(g_qparams_type, a[0]);
+  Py_INCREF(a[2]);
+  Py_XSETREF(g_check, a[2]);
   Py_RETURN_NONE;
 }
 

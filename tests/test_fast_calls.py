@@ -1,5 +1,6 @@
 """The binding's native calls: taken for what a call documents, and only for that; everything else goes on to the ctypes
 form and is refused or accepted as that one does."""
+import ctypes
 import threading
 
 import numpy as np
@@ -24,7 +25,7 @@ def test_what_does_not_fit_is_left_to_the_ctypes_form():
         with pytest.raises(AssertionError):
             call()
     with pytest.raises(KeyError):
-        calls.bind(B.cwac_qparams, {})
+        calls.bind(B.cwac_qparams, {}, B._check)
     assert B._fast_calls() is calls
 
 
@@ -100,6 +101,26 @@ def test_misfits_are_refused_as_before():
         P.cwac_quantize_act(torch.zeros(4, 8, device=DEV), -1.0, 0, torch.zeros(4, 8, dtype=torch.int8, device=DEV))
     q = torch.zeros(4, 8, dtype=torch.int8, device=DEV)
     P.cwac_quantize_act(torch.ones(4, 8, device=DEV), np.float32(0.5), np.int64(1), q)                 # numbers of other types
+    assert (q == 3).all()
+
+
+@pytest.mark.gpu
+def test_a_failed_launch_raises_at_once():
+    """The status of a refused launch comes with the runtime's error, which a second call would not see."""
+    calls, made = B._fast_calls(), []
+    x, q = torch.ones(4, 8, device=DEV), torch.zeros(4, 8, dtype=torch.int8, device=DEV)
+    refuse = ctypes.CFUNCTYPE(ctypes.c_int32, *B.lib().cwac_quantize_act.argtypes)(lambda *a: made.append(1) or -6)
+    names = ("cwac_quantize_act", "cwac_quantize_rows_sym", "qlinear_cwac_forward", "qlinear_cwac_forward_table",
+             "qlinear_cwac_forward_fixed_point", "qconv2d_cwac_forward", "qlinear_w4a16_cwac_forward")
+    real = {n: ctypes.cast(getattr(B.lib(), n), ctypes.c_void_p).value for n in names}
+    calls.bind(B.cwac_qparams, dict(real, cwac_quantize_act=ctypes.cast(refuse, ctypes.c_void_p).value), B._check)
+    try:
+        with pytest.raises(B.CwacError, match="cwac_quantize_act"):
+            P.cwac_quantize_act(x, 0.5, 1, q)
+    finally:
+        calls.bind(B.cwac_qparams, real, B._check)
+    assert len(made) == 1
+    P.cwac_quantize_act(x, 0.5, 1, q)
     assert (q == 3).all()
 
 
