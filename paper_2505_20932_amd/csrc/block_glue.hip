@@ -34,9 +34,9 @@ template <int CTRL>
 __device__ __forceinline__ float dpp(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
 }
-template <int LPR>
+template <int LPR, bool PAIRED = false>
 __device__ __forceinline__ float group_sum(float v) {
-  v += dpp<0xb1>(v);   // quad_perm 1,0,3,2
+  if constexpr (!PAIRED) v += dpp<0xb1>(v);  // quad_perm 1,0,3,2 (PAIRED: neighbours hold their common sum already)
   v += dpp<0x4e>(v);   // quad_perm 2,3,0,1
   v += dpp<0x141>(v);  // row_half_mirror: the other quad of 8
   v += dpp<0x140>(v);  // row_mirror: the other half of 16
@@ -86,13 +86,19 @@ __device__ __forceinline__ uint32_t pack_codes(const float (&v)[4]) {
 // per lane), two-pass mean / variance with the sums taken over the lanes' registers by DPP and half-wave
 // exchanges (no LDS).  HBM bytes per element: 2 (h) [+ 1 (codes) + 2 (h1)] + 1 (x_q).
 //
-// Two forms.  Many rows: V = 8, LPR = 16, 32 or 64 - the host picks the pair with the fewest idle lanes, e.g.
-// 32 x 3 for C = 768 - bound by HBM and, close behind, by the ~16 vector instructions per element; gamma and
-// beta pass through LDS, staged while the row's loads are in flight.  Few rows (few wavefronts to a
-// compute unit): the serial chain of one row is what takes the time, so a wavefront takes one row with V = 4,
-// half the elements per lane, and reads gamma and beta straight into registers.
-// Residual + norm, microseconds, with shuffles through LDS, an integer rounding chain and a row loop / now: 25216 x 768
-// 20.4 / 18.5 (6.3 TB/s), 7252 x 512 6.1 / 5.5, 4616 x 768 6.5 / 5.4, 197 x 768 3.6 / 2.3.
+// The order of a row's sums follows from C alone, never from the number of rows: a token's codes do not depend on
+// the batch that it comes in.  It is the order of vectors of 8 channels on 16, 32 or 64 lanes, whichever pair LPR x NV has
+// the fewest idle lanes (32 x 3 for C = 768) - or, where it leaves none idle and that one would, of vectors of 4 on 64 lanes
+// (C = 1280 and 1792).
+//
+// Many rows: workgroups of 256 threads, bound by HBM and, close behind, by the ~16 vector instructions per element;
+// gamma and beta pass through LDS, staged while the row's loads are in flight.  Few rows (few wavefronts to a compute
+// unit): the serial chain of one row is what takes the time.  So a workgroup is one wavefront, gamma and beta go straight
+// into registers, and a vector of 8 is split over a PAIR of lanes: either takes half the elements, and the chain of a sum
+// goes from the first to the second lane of the pair with every vector.
+// Residual + norm, microseconds, with shuffles through LDS, an integer rounding chain and a row loop / with a wavefront per
+// row of 4 channels per lane for few rows, whose sums had an order of their own / now: 197 x 768 4.2 / 3.1 / 3.2, 2308 x 768
+// 5.7 / 5.5 / 4.8, 7252 x 512 7.1 / 7.4 / 6.8, 4616 x 768 7.9 / 7.1 / 6.6, 25216 x 768 27.2 / 25.4 / 25.5.
 // ------------------------------------------------------------------------------------------
 struct LnParams {
   const _Float16 *h;
@@ -129,10 +135,30 @@ struct LnVec<4> {
   static __device__ __forceinline__ uint32_t pack(const uint32_t (&w)[1]) { return w[0]; }
 };
 
+// The sum of a row: `add` adds an element to a chain.
+template <int LPR, int NV, int V, bool PAIRS, typename F>
+__device__ __forceinline__ float row_sum(F &&add) {
+  float s = 0.0f;
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+#pragma unroll
+    for (int e = 0; e < V; ++e) s = add(s, j, e);
+    if constexpr (PAIRS) {  // what counts: the first lane's four, the second lane's on top of them, then both go on from there
+      s = dpp<0xa0>(s);     // quad_perm 0,0,2,2
+#pragma unroll
+      for (int e = 0; e < V; ++e) s = add(s, j, e);
+      s = dpp<0xf5>(s);  // quad_perm 1,1,3,3
+    }
+  }
+  return group_sum<LPR, PAIRS>(s);
+}
+
 // FULL: every lane's every vector is inside the row (C = V * LPR * NV): no masks.
-template <int LPR, int NV, int V, int THREADS, bool FULL>
+template <int LPR, int NV, int V, int THREADS, bool FULL, bool PAIRS = false>
 __global__ __launch_bounds__(THREADS) void residual_ln_quant_kernel(const LnParams p) {
-  constexpr bool kLds = V == 8;  // gamma and beta through LDS
+  constexpr bool kLds = THREADS > 64;  // gamma and beta through LDS
+  static_assert(!kLds || V == 8, "the two halves of a vector of 8 lie apart in LDS");
+  static_assert(!PAIRS || (V == 4 && LPR >= 32), "half a vector of 8 to a lane, on twice its lanes");
   const int lane = threadIdx.x & (LPR - 1);  // position inside the row's group of LPR lanes
   const int nvec = p.c / V;
   const int64_t row = ((int64_t)blockIdx.x * THREADS + threadIdx.x) / LPR;
@@ -158,7 +184,7 @@ __global__ __launch_bounds__(THREADS) void residual_ln_quant_kernel(const LnPara
   // gamma and beta in LDS: the first and the second four channels of every vector side by side, so that the
   // lanes of a 16-byte read cover all banks
   __shared__ __attribute__((aligned(16))) float s_gb[kLds ? 4096 : 4];
-  float4 gr[kLds ? 1 : NV], br[kLds ? 1 : NV];
+  float4 gr[kLds ? 1 : NV][V / 4], br[kLds ? 1 : NV][V / 4];
   if (p.x_q) {
     if constexpr (kLds) {
       for (int i = threadIdx.x; i < p.c / 4; i += THREADS) {
@@ -171,8 +197,11 @@ __global__ __launch_bounds__(THREADS) void residual_ln_quant_kernel(const LnPara
 #pragma unroll
       for (int j = 0; j < NV; ++j) {
         const int v = (FULL || lane + LPR * j < nvec) ? lane + LPR * j : 0;
-        gr[j] = *reinterpret_cast<const float4 *>(p.gamma + 4 * v);
-        br[j] = *reinterpret_cast<const float4 *>(p.beta + 4 * v);
+#pragma unroll
+        for (int q = 0; q < V / 4; ++q) {
+          gr[j][q] = *reinterpret_cast<const float4 *>(p.gamma + V * v + 4 * q);
+          br[j][q] = *reinterpret_cast<const float4 *>(p.beta + V * v + 4 * q);
+        }
       }
     }
   }
@@ -201,24 +230,15 @@ __global__ __launch_bounds__(THREADS) void residual_ln_quant_kernel(const LnPara
     }
   }
   if (!p.x_q) return;
-  float s = 0.0f;
-#pragma unroll
-  for (int j = 0; j < NV; ++j)
-#pragma unroll
-    for (int e = 0; e < V; ++e) s += x[j][e];
-  const float mean = group_sum<LPR>(s) * p.inv_c;
-  float ss = 0.0f;
+  const float mean = row_sum<LPR, NV, V, PAIRS>([&](float s, int j, int e) { return s + x[j][e]; }) * p.inv_c;
 #pragma unroll
   for (int j = 0; j < NV; ++j) {
     const bool ok = FULL || lane + LPR * j < nvec;
 #pragma unroll
-    for (int e = 0; e < V; ++e) {
-      const float d = ok ? x[j][e] - mean : 0.0f;
-      x[j][e] = d;
-      ss = __builtin_fmaf(d, d, ss);
-    }
+    for (int e = 0; e < V; ++e) x[j][e] = ok ? x[j][e] - mean : 0.0f;
   }
-  const float var = group_sum<LPR>(ss) * p.inv_c;
+  const float var =
+      row_sum<LPR, NV, V, PAIRS>([&](float s, int j, int e) { return __builtin_fmaf(x[j][e], x[j][e], s); }) * p.inv_c;
   const float rstd = __builtin_amdgcn_rsqf(var + p.eps);  // 1 ulp
   const float zf = (float)p.z_x, inv_s = p.inv_s_x;
 #pragma unroll
@@ -233,7 +253,7 @@ __global__ __launch_bounds__(THREADS) void residual_ln_quant_kernel(const LnPara
         g4 = *reinterpret_cast<const float4 *>(s_gb + 1024 * q + 4 * vs);
         b4 = *reinterpret_cast<const float4 *>(s_gb + 2048 + 1024 * q + 4 * vs);
       } else {
-        g4 = gr[j], b4 = br[j];
+        g4 = gr[j][q], b4 = br[j][q];
       }
       const float g[4] = {g4.x, g4.y, g4.z, g4.w}, b[4] = {b4.x, b4.y, b4.z, b4.w};
       float y[4];
@@ -242,6 +262,17 @@ __global__ __launch_bounds__(THREADS) void residual_ln_quant_kernel(const LnPara
       w[q] = pack_codes(y);
     }
     if (live && (FULL || v < nvec)) *reinterpret_cast<typename LnVec<V>::Codes *>(p.x_q + at * p.ldxq + V * v) = LnVec<V>::pack(w);
+  }
+}
+
+// A wavefront or 256 threads to a workgroup.
+template <int LPR, int NV, bool FULL>
+void launch_ln_form(const LnParams &p, bool wave, hipStream_t st) {
+  if (wave) {
+    constexpr int V = LPR == 64 ? 8 : 4, L = LPR * 8 / V;  // (no pairs of lanes for the widest rows)
+    residual_ln_quant_kernel<L, NV, V, 64, FULL, V == 4><<<dim3((unsigned)ceil_div(p.m, 64 / L)), 64, 0, st>>>(p);
+  } else {
+    residual_ln_quant_kernel<LPR, NV, 8, 256, FULL><<<dim3((unsigned)ceil_div(p.m, 256 / LPR)), 256, 0, st>>>(p);
   }
 }
 
@@ -258,33 +289,25 @@ cwac_status launch_ln(const LnParams &p, hipStream_t st) {
     const int cnv = (nvec + cand - 1) / cand;
     if (cnv <= 4 && cnv * cand < nv * lpr) lpr = cand, nv = cnv;
   }
-  // A wavefront per row (residual + norm, microseconds, row groups of 8 channels per lane / this): 197 x 768 3.0 / 2.3,
-  // 788 x 768 3.2 / 2.5, 2308 x 768 4.2 / 3.7, 197 x 1280 3.4 / 2.7; level at 3152 x 768 (4.4 / 4.3) and behind at
-  // 7252 x 256 (3.4 / 4.1) and 2000 x 2048 (6.0 / 6.4).  Also where it leaves no idle lane and the other would:
-  // 12608 x 1280 17.4 / 16.4.
-  if ((m <= 2304 && m * c <= 2400000) || (c % 256 == 0 && nvec != lpr * nv)) {
+  if (nvec != lpr * nv && c % 256 == 0) {  // no idle lane with V = 4: C = 1280 (12608 rows 17.4 -> 16.4 us) and 1792
     const dim3 grid((unsigned)m);
-#define CWAC_LN_CASE(N)                                                  \
-  case N:                                                                \
-    if (c == 256 * N)                                                    \
-      residual_ln_quant_kernel<64, N, 4, 64, true><<<grid, 64, 0, st>>>(p);  \
-    else                                                                 \
-      residual_ln_quant_kernel<64, N, 4, 64, false><<<grid, 64, 0, st>>>(p); \
-    break;
-    switch ((c + 255) / 256) {
-      CWAC_LN_CASE(1) CWAC_LN_CASE(2) CWAC_LN_CASE(3) CWAC_LN_CASE(4) CWAC_LN_CASE(5) CWAC_LN_CASE(6) CWAC_LN_CASE(7)
-      CWAC_LN_CASE(8)
-    }
-#undef CWAC_LN_CASE
+    if (c == 1280)
+      residual_ln_quant_kernel<64, 5, 4, 64, true><<<grid, 64, 0, st>>>(p);
+    else
+      residual_ln_quant_kernel<64, 7, 4, 64, true><<<grid, 64, 0, st>>>(p);
     return launch_status();
   }
-  const dim3 grid((unsigned)ceil_div(m, 256 / lpr));
-#define CWAC_LN_CASE(L, N)                                                                     \
-  if (lpr == L && nv == N) {                                                                   \
-    if (nvec == L * N)                                                                         \
-      residual_ln_quant_kernel<L, N, 8, 256, true><<<grid, 256, 0, st>>>(p);                   \
-    else                                                                                       \
-      residual_ln_quant_kernel<L, N, 8, 256, false><<<grid, 256, 0, st>>>(p);                  \
+  // One wavefront to a workgroup (microseconds, 256 threads / this): 197 x 384 3.7 / 3.2, 2308 x 768 5.5 / 4.8, 7252 x 768
+  // 10.5 / 10.0, 12608 x 768 15.7 / 14.7, 12608 x 384 9.8 / 9.3; level at 7252 x 192 and behind at 25216 x 192 (10.0 / 11.4) and
+  // 25216 x 640 (20.9 / 21.5).  Rows of 64 lanes, where a lane keeps its 8 channels: 197 x 512 3.2 / 2.9, 25216 x 512 18.5 / 17.5,
+  // 4616 x 1024 9.4 / 8.8, 7252 x 2048 20.7 / 20.4; level at 12608 x 1024 (17.9) and behind at 25216 x 2048 (54.7 / 60.0).
+  const bool wave = lpr == 64 ? m <= 8192 || c <= 512 : m <= (c >= 256 ? 16384 : 2304);
+#define CWAC_LN_CASE(L, N)                                                                          \
+  if (lpr == L && nv == N) {                                                                        \
+    if (nvec == L * N)                                                                              \
+      launch_ln_form<L, N, true>(p, wave, st);                                                      \
+    else                                                                                            \
+      launch_ln_form<L, N, false>(p, wave, st);                                                     \
   }
   // clang-format off
   CWAC_LN_CASE(64, 1) else CWAC_LN_CASE(64, 2) else CWAC_LN_CASE(64, 3) else CWAC_LN_CASE(64, 4)

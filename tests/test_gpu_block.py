@@ -82,9 +82,10 @@ def test_residual_ln_quant(m, c, with_residual):
 
 
 @pytest.mark.parametrize("m,c", [(2304, 1040), (2308, 1040), (2305, 264), (700, 776), (2310, 1280), (2500, 1032),
-                                 (3000, 56), (2400, 136), (130, 1536), (1, 2048), (2401, 520), (2311, 2040)])
+                                 (3000, 56), (2400, 136), (130, 1536), (1, 2048), (2401, 520), (2311, 2040),
+                                 (3, 384), (16385, 264), (16390, 384), (8195, 520), (8193, 1016), (8200, 2048), (16387, 776)])
 def test_residual_ln_quant_row_and_group_forms(m, c):
-    """Either side of the bounds between a wavefront per row and groups of lanes, each number of vectors per lane,
+    """Either side of the bounds between one wavefront and 256 threads to a workgroup, each number of vectors per lane,
     rows that fill their lanes and rows that do not; in place."""
     print(f"residual + layer norm + quantizer {m} x {c}", flush=True)
     h, r, gamma, beta = _ln_case(m + c, m, c)
@@ -98,6 +99,22 @@ def test_residual_ln_quant_row_and_group_forms(m, c):
     assert (got16 == want16).mean() > 0.999 and np.abs(got16.astype(float) - want16.astype(float)).max() < 0.04
     _, v = blk.quantize(blk.layernorm(got16.astype(np.float64), gamma, beta, 1e-6), 0.03, 4)
     assert _codes_within(xq[:-1].cpu().numpy(), v, 64 * U32 * (np.abs(v) + 128) + 1e-4) > 0.99
+
+
+@pytest.mark.parametrize("c", [64, 128, 136, 192, 256, 264, 384, 520, 512, 640, 768, 776, 1024, 1280, 1536, 1792, 2048])
+def test_residual_ln_quant_of_a_token_does_not_depend_on_the_batch(c):
+    """Rows alone, in a batch that fills the chip and in one between them: the same bits, whichever form runs."""
+    print(f"residual + layer norm + quantizer {c} channels, batches", flush=True)
+    h, r, gamma, beta = _ln_case(31 + c, 5000, c)
+    hd, rd, gd, bd = (_dev(np.tile(h, (4, 1))), _dev(np.tile(r, (4, 1))), _dev(gamma), _dev(beta))
+    def run(m):
+        h_out, xq = torch.empty(m, c, dtype=torch.float16, device=DEV), torch.empty(m, c, dtype=torch.int8, device=DEV)
+        P.vit_residual_ln_quant(hd[:m], rd[:m], 0.01, 3, h_out, gd, bd, 1e-6, 0.02, -5, xq)
+        return h_out.view(torch.int16), xq
+    h_all, x_all = run(20000)
+    for m in (1, 197, 2000, 2305, 5000, 9000):
+        h_m, x_m = run(m)
+        assert torch.equal(h_m, h_all[:m]) and torch.equal(x_m, x_all[:m]), m
 
 
 def test_residual_only_and_quantizer_saturation():
