@@ -462,7 +462,8 @@ cwac_status qlinear_w4a16_cwac_forward(const uint16_t *x, int64_t ldx, const voi
  *   r != NULL:    t = h + s_r * (r - z_r) in fp32; h_out (nullable) receives RN16(t), and the
  *                 layer norm reads that rounded value
  *   x_q != NULL:  x_q = Q(LN(t; gamma, beta, eps); s_x, z_x); LN over the c channels of a row,
- *                 biased variance, fp32, two passes over the register-resident row
+ *                 biased variance, fp32, two passes over the register-resident row; a row's codes do not
+ *                 depend on the other rows or on their number
  *   h, h_out   binary16 [m, c], pitches ldh, ldho (elements); 16-byte aligned, pitch % 8 == 0
  *   r, x_q     int8 [m, c], pitches ldr, ldxq; 8-byte aligned, pitch % 8 == 0
  *   gamma, beta  fp32 [c], 16-byte aligned (required with x_q)
@@ -502,7 +503,8 @@ cwac_status vit_table_lookup(const int8_t *in, int64_t ld_in, const int8_t *tabl
  *          -inf would get NaN weights)
  * "image" is whatever attends within itself: an image of a ViT, a window of a windowed model.
  * Scores are exact (integers in fp32 accumulators), the softmax is fp32, the weights meet the
- * values as binary16 (relative error 2^-11 per term), accumulation in fp32. */
+ * values as binary16 (relative error 2^-11 per term), accumulation in fp32.  The codes of an image do not
+ * depend on the other images of the batch or on their number. */
 cwac_status vit_attention_int8(const int8_t *r_qkv, int64_t ld, float s, int32_t z, int32_t batch,
                                int32_t tokens, int32_t heads, int32_t head_dim, const uint16_t *bias,
                                int64_t ldb, float s_a, int32_t z_a, int8_t *a_q, int64_t lda, void *stream);

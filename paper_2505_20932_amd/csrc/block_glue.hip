@@ -10,7 +10,8 @@
 //   quantizer  code = clip(rne(fma(y, 1 / s, z)), -128, 127)                            (Eq. 1)
 //   attention  S = (K - z)(Q - z)^T exactly (integers below 2^24 in the fp32 MFMA accumulators);
 //              P = 1024 p = exp2(fma(S, s^2 / sqrt(d) * log2 e, 10 - that * max S));  O = (sum_j RN16(P_j) (V_j - z)) * s / sum_j P_j,
-//              keys taken in groups of 64 with a running maximum (earlier partial sums rescaled whenever it rises)
+//              keys taken in groups of 64 with a running maximum (earlier partial sums rescaled whenever it rises); the order of
+//              all sums follows from the number of tokens alone
 //   GELU table entry(c) = clip(rne(GELU(s_in (c - z_in)) / s_out + z_out)) evaluated in fp64 (erf form)
 #include <hip/hip_runtime.h>
 
@@ -488,20 +489,13 @@ struct AttnBias {
   }
 };
 
-// Scores, softmax weights and the second product for CNT key tiles from LDS tile t0 on, whose first key is
-// key0 + 32 t0 of the sequence.  HALF: only the first 16 keys of the (single) tile can be real.
-// The weights always refer to the exact running maximum: the largest one is then 1024 and binary16 does not
-// round it.  Rescaling only after a rise by more than 2^5 took 1-5 % less time, but its dominant weights are rounded
-// while their sum is not: 128 x 197 tokens of peaked scores had 1.8 times the codes off against 64 bits (2.5e-3,
-// here 1.4e-3).  STRAIGHT: rescale in every group, by 1 where nothing rose.  With the chunked kernel's free registers
-// that is ahead of the branch (4 x 577 tokens 14.1 -> 13.4 us); the whole-sequence forms of 6 and 7 tiles spill for it
-// (128 x 197: 39 -> 68 us).
-template <int CNT, int D, int VS, bool BIAS, bool STRAIGHT, bool HALF = false>
-__device__ __forceinline__ void attention_key_group(int t0, bool first, const int8_t *s_k, const int8_t *s_v,
-                                                    const h8 (&fq)[D / 16], const AttnBias &bias, int left,
-                                                    float lscale, int l32, int half, AttnState<D> &st) {
+// Scores of CNT key tiles from LDS tile t0 on - with a bias already as logits in the log2 domain -, minus infinity for keys
+// beyond the `left` that are left of the sequence, and their maximum (in both lanes of a query).  HALF: only the first
+// 16 keys of the (single) tile can be real.
+template <int CNT, int D, bool BIAS, bool HALF>
+__device__ __forceinline__ float attention_scores(int t0, const int8_t *s_k, const h8 (&fq)[D / 16], const AttnBias &bias, int left,
+                                                  float lscale, int l32, int half, v16f (&sc)[CNT]) {
   constexpr int R = HALF ? 8 : 16;  // score registers of a tile that can hold real keys
-  v16f sc[CNT];
 #pragma unroll
   for (int t = 0; t < CNT; ++t) {
 #pragma unroll
@@ -526,7 +520,6 @@ __device__ __forceinline__ void attention_key_group(int t0, bool first, const in
           sc[t][4 * g + r] = __builtin_fmaf(bf[r], 1.44269504088896340736f, sc[t][4 * g + r] * lscale);
       }
   }
-  const float dscale = BIAS ? 1.0f : lscale;  // what turns a score difference into a log2 difference
   float gmx = -1e30f;  // finite, so that a group whose keys are all masked by the bias has zero weights
 #pragma unroll
   for (int t = 0; t < CNT; ++t) {
@@ -538,12 +531,28 @@ __device__ __forceinline__ void attention_key_group(int t0, bool first, const in
 #pragma unroll
     for (int i = 0; i < R; ++i) gmx = fmaxf(gmx, sc[t][i]);
   }
-  {
-    const uint32_t mine = __builtin_bit_cast(uint32_t, gmx);
-    const auto both = __builtin_amdgcn_permlane32_swap(mine, mine, false, false);
-    const uint32_t low = both[0], high = both[1];
-    gmx = fmaxf(__builtin_bit_cast(float, low), __builtin_bit_cast(float, high));
-  }
+  const uint32_t mine = __builtin_bit_cast(uint32_t, gmx);
+  const auto both = __builtin_amdgcn_permlane32_swap(mine, mine, false, false);
+  const uint32_t low = both[0], high = both[1];
+  return fmaxf(__builtin_bit_cast(float, low), __builtin_bit_cast(float, high));
+}
+
+// Scores, softmax weights and the second product for CNT key tiles from LDS tile t0 on, whose first key is
+// key0 + 32 t0 of the sequence.
+// The weights always refer to the exact running maximum: the largest one is then 1024 and binary16 does not
+// round it.  Rescaling only after a rise by more than 2^5 took 1-5 % less time, but its dominant weights are rounded
+// while their sum is not: 128 x 197 tokens of peaked scores had 1.8 times the codes off against 64 bits (2.5e-3,
+// here 1.4e-3).  STRAIGHT: rescale in every group, by 1 where nothing rose.  With the chunked kernel's free registers
+// that is ahead of the branch (4 x 577 tokens 14.1 -> 13.4 us); the whole-sequence forms of 6 and 7 tiles spill for it
+// (128 x 197: 39 -> 68 us).
+template <int CNT, int D, int VS, bool BIAS, bool STRAIGHT, bool HALF = false>
+__device__ __forceinline__ void attention_key_group(int t0, bool first, const int8_t *s_k, const int8_t *s_v,
+                                                    const h8 (&fq)[D / 16], const AttnBias &bias, int left,
+                                                    float lscale, int l32, int half, AttnState<D> &st) {
+  constexpr int R = HALF ? 8 : 16;
+  v16f sc[CNT];
+  float gmx = attention_scores<CNT, D, BIAS, HALF>(t0, s_k, fq, bias, left, lscale, l32, half, sc);
+  const float dscale = BIAS ? 1.0f : lscale;  // what turns a score difference into a log2 difference
   // 1024 p = exp2(S * lscale + (10 - mx * lscale)), one fused multiply-add per exponent
   if (first) {
     st.mx = gmx;
@@ -605,31 +614,26 @@ __device__ __forceinline__ void attention_chunk(int key0, int tokens, const int8
   }
 }
 
-// Normalizes, quantizes and stores one query's output row.  O^T: register 4 g + r of tile a is channel
-// 32 a + 8 g + 4 half + r of this lane's query; `sum` is the lane-local sum of weights.
-template <int D>
-__device__ __forceinline__ void attention_store_row(const AttnParams &p, float sum, const v16f (&oc)[D / 32], int8_t *orow,
-                                                    int half, bool store) {
-  sum += __shfl_xor(sum, 32, 64);
+// Normalizes, quantizes and stores 32 channels of one query's output.  O^T: register 8 g .. of the tile is channel
+// 8 g + 4 half + r of this lane's query; `sum` is the sum of its weights.
+__device__ __forceinline__ void attention_store_tile(const AttnParams &p, float sum, const v16f &oc, int8_t *orow, int half,
+                                                     bool store) {
   // sum and the accumulators both carry the factor 1024; the code is rne(O * s / (sum * s_a) + z_a)
   const float onorm = p.s / (sum * p.s_a), zf = (float)p.z_a;
+  uint32_t packed[4];
 #pragma unroll
-  for (int a = 0; a < D / 32; ++a) {
-    uint32_t packed[4];
+  for (int g = 0; g < 4; ++g) {
+    float v[4];
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      float v[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) v[r] = __builtin_fmaf(oc[a][4 * g + r], onorm, zf);
-      packed[g] = pack_codes(v);
-    }
-    // lower half-wave holds channels 8g .. 8g+3, upper 8g+4 .. 8g+7: after the two swaps the lower
-    // lane owns channels 0 .. 15 of this 32-channel tile and the upper lane 16 .. 31
-    const auto s02 = __builtin_amdgcn_permlane32_swap(packed[0], packed[2], false, false);
-    const auto s13 = __builtin_amdgcn_permlane32_swap(packed[1], packed[3], false, false);
-    const v4i o = {(int)s02[0], (int)s02[1], (int)s13[0], (int)s13[1]};
-    if (store) *reinterpret_cast<v4i *>(orow + 32 * a + 16 * half) = o;
+    for (int r = 0; r < 4; ++r) v[r] = __builtin_fmaf(oc[4 * g + r], onorm, zf);
+    packed[g] = pack_codes(v);
   }
+  // lower half-wave holds channels 8g .. 8g+3, upper 8g+4 .. 8g+7: after the two swaps the lower
+  // lane owns channels 0 .. 15 of this 32-channel tile and the upper lane 16 .. 31
+  const auto s02 = __builtin_amdgcn_permlane32_swap(packed[0], packed[2], false, false);
+  const auto s13 = __builtin_amdgcn_permlane32_swap(packed[1], packed[3], false, false);
+  const v4i o = {(int)s02[0], (int)s02[1], (int)s13[0], (int)s13[1]};
+  if (store) *reinterpret_cast<v4i *>(orow + 16 * half) = o;
 }
 
 // G heads per workgroup (short sequences: a head of two wavefronts alone would leave the compute unit to
@@ -705,23 +709,34 @@ __global__ __launch_bounds__(64 * NW * G, D == 64 && BIAS ? 2 : (CHUNKS || (BIAS
       __syncthreads();
     }
   }
-  if (wave_live)
-    attention_store_row<D>(p, st.sum, st.oc, p.a + (row0 + qrow) * p.lda + head * D, half, q < p.tokens && live);
+  if (wave_live) {
+    const float sum = st.sum + __shfl_xor(st.sum, 32, 64);
+#pragma unroll
+    for (int a = 0; a < D / 32; ++a)
+      attention_store_tile(p, sum, st.oc[a], p.a + (row0 + qrow) * p.lda + head * D + 32 * a, half, q < p.tokens && live);
+  }
 }
 
 // Few heads (an image or two): a workgroup per (image, head, block of 32 queries) whose eight wavefronts split the keys.  What
 // takes the time there is the chain of one wavefront through all key tiles on a few compute units; here a wavefront
-// takes tiles wave, wave + 8, ... - one at 197 tokens - with K and V of a tile in its own slice of LDS, and the eight
-// partial results meet once: each wavefront rescales to the largest maximum and all threads add up, in wavefront
-// order, normalize and store.  us, a workgroup per 224 queries (128 of a long sequence) of a head / this: one image of 12 heads and 197
-// tokens 6.6 / 5.0, of 577 tokens 12.9 / 8.6, of 16 heads and 257 tokens 7.9 / 5.9, window of 16 x 32 and 144 tokens 5.5 / 4.2.
+// takes tiles wave, wave + 8, ... - one at 197 tokens - with K and V of a tile in its own slice of LDS.  The result is
+// that of the kernel above bit for bit, so that an image's codes do not depend on how many images are with it:
+// the tiles' maxima are exchanged, every weight refers to the running maximum of its pair of tiles as there, and the weights
+// go through LDS to one wavefront per 32 channels, which adds the second products up in the order of the keys,
+// and to one that adds up the weights.
+// us per call of a replayed graph, the kernel above / this: one image of 12 heads and 197 tokens 7.5 / 5.6, of 577 tokens
+// 13.4 / 10.0, of 16 heads and 257 tokens with a bias 10.2 / 7.7, windows of 16 heads of 32 and 144 tokens with a bias 6.0 / 4.8.  Eight
+// partial results merged at the end, which another number of images does not reproduce: 5.4, 9.1, 6.8, 4.7.  With the chains'
+// operands read tile by tile: 6.1, 10.9, 7.9, 5.0.
 constexpr int kSplitWaves = 8;
 template <int D, bool BIAS>
 __global__ __launch_bounds__(64 * kSplitWaves) void attention_split_kernel(const AttnParams p) {
-  constexpr int NW = kSplitWaves, KB = 32 * k_stride(D), SLICE = KB + D * v_stride(1);
-  static_assert(SLICE >= D * 128, "a wavefront's partial outputs lie over its slice");
+  constexpr int NW = kSplitWaves, VS = v_stride(1);
+  constexpr int KB = 32 * k_stride(D) > 4096 ? 32 * k_stride(D) : 4096;  // K of a tile, then its weights as summands
+  constexpr int SLICE = KB + D * VS;
   __shared__ __attribute__((aligned(16))) int8_t s_mem[NW * SLICE];
-  __shared__ float s_eoff[NW][32], s_sum[NW][64];
+  __shared__ __attribute__((aligned(16))) h8 s_p[NW][2][64];  // weights as operands of the second product
+  __shared__ float s_max[NW][32], s_sum[32];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int l32 = lane & 31, half = lane >> 5;
   int8_t *s_k = s_mem + wave * SLICE, *s_v = s_k + KB;
@@ -749,62 +764,121 @@ __global__ __launch_bounds__(64 * kSplitWaves) void attention_split_kernel(const
 #pragma unroll
   for (int s = 0; s < D / 16; ++s) fq[s] = codes_to_h8(qraw[s], zbias);
   const float lscale = p.s * p.s * (D == 64 ? 0.125f : 0.17677669529663687f) * 1.44269504088896340736f;
-  AttnState<D> st;
-  st.mx = 0.0f, st.eoff = INFINITY, st.sum = 0.0f;  // no keys: rescaled by exp2(-inf)
+  const float dscale = BIAS ? 1.0f : lscale;
+  float run = 0.0f, prev = 0.0f;  // running maximum; exponent offset that the sums refer to
+  float sum = 0.0f;               // wavefront D / 32
+  v16f oc;                        // wavefronts below: 32 channels each
 #pragma unroll
-  for (int a = 0; a < D / 32; ++a)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) st.oc[a][i] = 0.0f;
+  for (int i = 0; i < 16; ++i) oc[i] = 0.0f;
   const int rounds = (tiles + NW - 1) / NW;
   for (int i = 0; i < rounds; ++i) {  // uniform over the workgroup
     const int tile = wave + NW * i;
-    if (tile < tiles) fill.store(s_k, s_v, zbias, lane);
+    const bool mine = tile < tiles;
+    v16f sc[1];
+    float tmax = -1e30f;
+    if (mine) {
+      fill.store(s_k, s_v, zbias, lane);
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      const AttnBias now = bias;
+      if (tile + NW < tiles) {
+        fill.load(qbase, p.ld, c, 32 * (tile + NW), p.tokens, lane);
+        if (BIAS) bias.load(bias_row, 32 * (tile + NW), p.tokens, half);
+      }
+      tmax = attention_scores<1, D, BIAS, false>(0, s_k, fq, now, p.tokens - 32 * tile, lscale, l32, half, sc);
+    }
+    if (half == 0) s_max[wave][l32] = tmax;
     __syncthreads();
-    const AttnBias now = bias;
-    if (tile + NW < tiles) {
-      fill.load(qbase, p.ld, c, 32 * (tile + NW), p.tokens, lane);
-      if (BIAS) bias.load(bias_row, 32 * (tile + NW), p.tokens, half);
+    float eoff[NW / 2], mine_off = 0.0f;  // of the round's pairs of tiles, and of this wavefront's
+#pragma unroll
+    for (int g = 0; g < NW / 2; ++g) {
+      const float gmx = fmaxf(s_max[2 * g][l32], s_max[2 * g + 1][l32]);
+      run = i == 0 && g == 0 ? gmx : fmaxf(run, gmx);
+      eoff[g] = __builtin_fmaf(-run, dscale, 10.0f);
+      if (wave >> 1 == g) mine_off = eoff[g];
     }
-    if (tile < tiles)
-      attention_key_group<1, D, v_stride(1), BIAS, false>(0, i == 0, s_k, s_v, fq, now, p.tokens - 32 * tile, lscale, l32, half, st);
-    if (i + 1 < rounds) __syncthreads();  // the slice is read (by its own wavefront, in the compiler's eyes too)
-  }
-
-  // ---- the partial results meet: weights of wavefront w carry 2^eoff[w]; the smallest offset belongs to the largest maximum
-  if (half == 0) s_eoff[wave][l32] = st.eoff;
-  __syncthreads();
-  float eoff = s_eoff[0][l32];
+    if (mine) {
+      v4f *s_w = reinterpret_cast<v4f *>(s_k) + lane;  // K of the tile has been read
 #pragma unroll
-  for (int w = 1; w < NW; ++w) eoff = fminf(eoff, s_eoff[w][l32]);
-  const float corr = __builtin_amdgcn_exp2f(eoff - st.eoff);
-  s_sum[wave][lane] = st.sum * corr;
-  v4f *part = reinterpret_cast<v4f *>(s_k);
+      for (int u = 0; u < 2; ++u) {
+        h8 fp;
+        float w[8];
 #pragma unroll
-  for (int a = 0; a < D / 32; ++a)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      v4f t;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) t[r] = st.oc[a][4 * g + r] * corr;
-      part[(4 * a + g) * 64 + lane] = t;
+        for (int e = 0; e < 8; ++e) {
+          const float x = sc[0][8 * u + e];
+          w[e] = __builtin_amdgcn_exp2f(BIAS ? x + mine_off : __builtin_fmaf(x, lscale, mine_off));
+          fp[e] = (_Float16)w[e];
+        }
+        s_p[wave][u][lane] = fp;
+        s_w[(2 * u) * 64] = v4f{w[0], w[1], w[2], w[3]};
+        s_w[(2 * u + 1) * 64] = v4f{w[4], w[5], w[6], w[7]};
+      }
     }
-  __syncthreads();
-  // item (a, g): four channels 32 a + 8 g + 4 half .. of every lane's query
-  float sum = 0.0f;
+    __syncthreads();
+    // The chains through the round's tiles, everything they need read first.  Tiles beyond the last are read (whatever is
+    // there) and left out.
+    const int here = tiles - NW * i < NW ? tiles - NW * i : NW;
+    if (wave < D / 32) {
+      h8 fv[NW][2], fp[NW][2];
 #pragma unroll
-  for (int w = 0; w < NW; ++w) sum += s_sum[w][l32] + s_sum[w][l32 + 32];
-  const float onorm = p.s / (sum * p.s_a), zf = (float)p.z_a;
-  int8_t *orow = p.a + (row0 + qrow) * p.lda + head * D;
-  for (int item = wave; item < D / 8; item += NW) {
-    const int8_t *at = s_mem + (item * 64 + lane) * 16;
-    v4f o = *reinterpret_cast<const v4f *>(at);
+      for (int t = 0; t < NW; ++t)
 #pragma unroll
-    for (int w = 1; w < NW; ++w) o += *reinterpret_cast<const v4f *>(at + w * SLICE);
-    float v[4];
+        for (int u = 0; u < 2; ++u) {
+          fv[t][u] = *reinterpret_cast<const h8 *>(s_mem + t * SLICE + KB + (32 * wave + l32) * VS + (16 * u + 8 * half) * 2);
+          fp[t][u] = s_p[t][u][lane];
+        }
 #pragma unroll
-    for (int r = 0; r < 4; ++r) v[r] = __builtin_fmaf(o[r], onorm, zf);
-    if (q < p.tokens) *reinterpret_cast<uint32_t *>(orow + 32 * (item >> 2) + 8 * (item & 3) + 4 * half) = pack_codes(v);
+      for (int t = 0; t < NW; ++t)  // (in registers here: the compiler would move each load down to its use)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) asm volatile("" : "+v"(fv[t][u]), "+v"(fp[t][u]));
+#pragma unroll
+      for (int t = 0; t < NW; ++t) {
+        if (t >= here) break;
+        if (t % 2 == 0) {
+          const float corr = __builtin_amdgcn_exp2f(eoff[t / 2] - prev);  // of the offsets as they are used
+          if (i > 0 || t > 0) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) oc[r] *= corr;
+          }
+          prev = eoff[t / 2];
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) oc = __builtin_amdgcn_mfma_f32_32x32x16_f16(fv[t][u], fp[t][u], oc, 0, 0, 0);
+      }
+    } else if (wave == D / 32) {
+      v4f w[NW][4];
+#pragma unroll
+      for (int t = 0; t < NW; ++t)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) w[t][g] = reinterpret_cast<const v4f *>(s_mem + t * SLICE)[g * 64 + lane];
+#pragma unroll
+      for (int t = 0; t < NW; ++t)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) asm volatile("" : "+v"(w[t][g]));
+#pragma unroll
+      for (int t = 0; t < NW; ++t) {
+        if (t >= here) break;
+        if (t % 2 == 0) {
+          const float corr = __builtin_amdgcn_exp2f(eoff[t / 2] - prev);
+          if (i > 0 || t > 0) sum *= corr;
+          prev = eoff[t / 2];
+        }
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) sum += w[t][g][r];
+      }
+    }
+    if (i + 1 < rounds) __syncthreads();  // the slices are read
   }
+  if (wave == D / 32) {
+    sum += __shfl_xor(sum, 32, 64);
+    if (half == 0) s_sum[l32] = sum;
+  }
+  __syncthreads();
+  if (wave < D / 32)
+    attention_store_tile(p, s_sum[l32], oc, p.a + (row0 + qrow) * p.lda + head * D + 32 * wave, half, q < p.tokens);
 }
 
 template <int NT, int NW, int D, int G, bool CHUNKS>
@@ -819,10 +893,10 @@ cwac_status launch_attention(const AttnParams &p, hipStream_t st) {
 
 template <int D>
 cwac_status launch_attention_d(const AttnParams &p, hipStream_t st) {
-  // The keys split over a workgroup's wavefronts while there is at most one such workgroup to a compute unit (us, above / split:
-  // 3 x 12 x 197 tokens, 252 of them, 6.6 / 5.3; 4 x 12 x 197, 336, 6.7 / 7.3; 12 x 577, 228, 12.9 / 8.4; 24 x 577, 456, 13.4 / 12.9) and
-  // more than three key tiles (12 x 50: 3.6 / 4.2).
-  if (p.tokens > 96 && (int64_t)p.pairs * ceil_div(p.tokens, 32) <= 256) {
+  // The keys split over a workgroup's wavefronts while there is at most one such workgroup to a compute unit - its LDS leaves
+  // room for one (us, above / split: 3 x 12 x 197 tokens, 252 of them, 7.6 / 5.9; 8 x 3 x 257, 216, 8.4 / 7.1; 12 x 577, 228, 13.4 / 10.0)
+  // - and more than four key tiles (12 x 144, five: 5.9 / 5.3; 12 x 128, four: 4.6 / 4.9).
+  if (p.tokens > 128 && (int64_t)p.pairs * ceil_div(p.tokens, 32) <= 256) {
     const dim3 grid(p.pairs, (unsigned)ceil_div(p.tokens, 32));
     if (p.bias)
       attention_split_kernel<D, true><<<grid, 64 * kSplitWaves, 0, st>>>(p);

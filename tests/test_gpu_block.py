@@ -333,7 +333,7 @@ def test_attention_one_dominant_key_picks_its_value(tokens):
 def test_attention_tile_edges_and_rising_maxima(batch, tokens, heads, head_dim, rising):
     """The last key tile holding at most or more than 16 keys, one tile or two left in the last pair, heads that do
     not fill a workgroup, chunks of a long sequence ending at or one past a tile.  `rising`: later keys score
-    higher, by steps above and below the bound that has earlier sums rescaled."""
+    higher, so that earlier sums are rescaled again and again."""
     print(f"attention {batch} x {tokens} tokens x {heads} heads of {head_dim}, rising {rising}", flush=True)
     rng = np.random.default_rng(tokens * 3 + head_dim + rising)
     c = head_dim * heads
@@ -383,6 +383,37 @@ def test_attention_row_subset_of_a_batch_matches_single_image():
     a3 = _attention(r, 0.05, 1, 3, tokens, heads, 0.03, -2)
     a1 = _attention(r[tokens:2 * tokens], 0.05, 1, 1, tokens, heads, 0.03, -2)
     np.testing.assert_array_equal(a3[tokens:2 * tokens], a1)
+
+
+@pytest.mark.parametrize("tokens", [97, 112, 128, 144, 176, 197, 224, 225, 257, 273, 300, 577, 1000])
+@pytest.mark.parametrize("head_dim", [64, 32])
+@pytest.mark.parametrize("with_bias", [False, True])
+def test_attention_of_an_image_does_not_depend_on_the_batch(tokens, head_dim, with_bias):
+    """Few heads of more than 128 tokens have their keys split over a workgroup's wavefronts, many do not: the same bits.
+    Keys that score higher towards the end, so that the running maximum rises over and over."""
+    heads = 3
+    few = max(1, 256 // (heads * ((tokens + 31) // 32)))
+    many = few + 2
+    assert few * heads * ((tokens + 31) // 32) <= 256 < many * heads * ((tokens + 31) // 32)
+    print(f"attention {few} and {many} x {tokens} tokens x {heads} heads of {head_dim}, bias {with_bias}", flush=True)
+    rng = np.random.default_rng(tokens + head_dim)
+    c = heads * head_dim
+    r = np.clip(np.rint(rng.standard_normal((many * tokens, 3 * c)) * 30 - 6), -128, 127)
+    r[:, c:2 * c] += np.tile(np.linspace(-40, 40, tokens), many)[:, None] * np.sign(r[:1, :c].mean() + 1e-9)
+    r = _dev(np.clip(np.rint(r), -128, 127).astype(np.int8))
+    bias = None
+    if with_bias:
+        bias = _dev((rng.standard_normal((heads, tokens, 32 * ((tokens + 31) // 32))) * 2).astype(np.float16))
+    def run(first, n):
+        a = torch.full((n * tokens + 1, c), 99, dtype=torch.int8, device=DEV)
+        P.vit_attention_int8(r[first * tokens:(first + n) * tokens], 0.04, -6, n, tokens, heads, 0.02, 3, a[:-1], head_dim=head_dim,
+                             bias=bias)
+        assert (a[-1] == 99).all()
+        return a[:-1]
+    together = run(0, many)
+    assert together.unique().numel() > 60
+    assert torch.equal(run(0, few), together[:few * tokens])
+    assert torch.equal(run(many - 1, 1), together[(many - 1) * tokens:])
 
 
 # ------------------------------------------------------------------ the whole block
@@ -467,6 +498,23 @@ def _run_block(orc, seed, batch, tokens, heads, hidden, rows, head_dim=64, attn_
 def test_block_chain_small(orc):
     print("block: 3 images x 197 tokens, 3 heads, MLP 768", flush=True)
     _run_block(orc, 3, 3, 197, 3, 768, np.arange(3 * 197))
+
+
+def test_block_of_an_image_does_not_depend_on_the_batch():
+    """All five kernels of a block: one image, three (whose keys are split) and twelve, the same residual stream."""
+    import vit_block_fixture as vit_block
+    tokens, heads, hidden = 197, 12, 3072
+    b = vit_block.build_block(7, 12, tokens, heads, hidden, device=DEV)
+    h = vit_block.residual_stream(7, 12 * tokens, b.c, DEV)
+    ws = torch.empty(P.vit_block_workspace(12, tokens, heads, hidden), dtype=torch.int8, device=DEV)
+    out = {}
+    for images in (12, 3, 1):
+        b.params.batch = images
+        out[images] = torch.empty_like(h[:images * tokens])
+        P.vit_block_w8a8_forward(b.params, h[:images * tokens], out[images], ws)
+    torch.cuda.synchronize()
+    for images in (3, 1):
+        assert torch.equal(out[images].view(torch.int16), out[12][:images * tokens].view(torch.int16)), images
 
 
 def test_block_chain_other_shapes(orc):
