@@ -640,8 +640,10 @@ __device__ __forceinline__ void attention_store_tile(const AttnParams &p, float 
 // workgroup turnover), NW wavefronts (32 queries each) per head; the wavefronts of a head work only on that
 // head's slice of LDS.  CHUNKS: the sequence passes through LDS in chunks of 32 NT keys, the next chunk's
 // codes travelling in registers; otherwise it fits one.  gridDim.y counts blocks of 32 NW queries.
+// Launch bounds: four wavefronts to a SIMD where the form fits 128 registers.  The biased 32-wide form of 6 tiles, like that of 7,
+// does not: held to 128 it spilled 10 of them (3 x 16 x 192 tokens 9.0 us, now 7.4; 128 x 16 x 192 60 / 52).
 template <int NT, int NW, int D, int G, bool BIAS, bool CHUNKS>
-__global__ __launch_bounds__(64 * NW * G, D == 64 && BIAS ? 2 : (CHUNKS || (BIAS && NT > 6) ? 3 : 4)) void attention_int8_kernel(const AttnParams p) {
+__global__ __launch_bounds__(64 * NW * G, D == 64 && BIAS ? 2 : (CHUNKS || (BIAS && NT > 5) ? 3 : 4)) void attention_int8_kernel(const AttnParams p) {
   constexpr int TP = 32 * NT;
   __shared__ __attribute__((aligned(16))) int8_t s_k_all[G * TP * k_stride(D)];
   __shared__ __attribute__((aligned(16))) int8_t s_v_all[G * D * v_stride(NT)];
