@@ -17,6 +17,7 @@
 
 #include <math.h>
 
+#include "attention_rules.h"
 #include "cwac_internal.h"
 
 namespace cwac {
@@ -376,7 +377,7 @@ __global__ __launch_bounds__(256) void table_lookup_kernel(const int8_t *in, int
 // 4 keys x D / 8 channels per thread: V is transposed in registers (8-byte LDS writes instead of 2-byte ones).
 // Against one workgroup to a compute unit, 2-byte transposing writes and 224-query blocks of long sequences:
 // 128 images x 12 heads x 197 tokens 45.5 -> 38.0 us, 8 x 12 x 577 32.1 -> 20.9, 148 x 16 x 49 with a bias
-// 9.5 -> 8.5, one image 7.2 -> 6.6.  Chunks of 64 or 192 keys, three, five or seven wavefronts and shorter
+// 9.5 -> 8.5, one image 7.2 -> 6.6 (blocks of 224 or 256 queries where attention_form says so).  Chunks of 64 or 192 keys, three, five or seven wavefronts and shorter
 // chunks for 197 tokens were 5 to 150 % slower.
 // ------------------------------------------------------------------------------------------
 constexpr int kHeadDim = 64;     // widest head; 32 is the other width
@@ -895,18 +896,15 @@ cwac_status launch_attention(const AttnParams &p, hipStream_t st) {
 
 template <int D>
 cwac_status launch_attention_d(const AttnParams &p, hipStream_t st) {
-  // The keys split over a workgroup's wavefronts while there is at most one such workgroup to a compute unit - its LDS leaves
-  // room for one (us, above / split: 3 x 12 x 197 tokens, 252 of them, 7.6 / 5.9; 8 x 3 x 257, 216, 8.4 / 7.1; 12 x 577, 228, 13.4 / 10.0)
-  // - and more than four key tiles (12 x 144, five: 5.9 / 5.3; 12 x 128, four: 4.6 / 4.9).
-  if (p.tokens > 128 && (int64_t)p.pairs * ceil_div(p.tokens, 32) <= 256) {
-    const dim3 grid(p.pairs, (unsigned)ceil_div(p.tokens, 32));
-    if (p.bias)
-      attention_split_kernel<D, true><<<grid, 64 * kSplitWaves, 0, st>>>(p);
-    else
-      attention_split_kernel<D, false><<<grid, 64 * kSplitWaves, 0, st>>>(p);
-    return launch_status();
-  }
-  switch ((p.tokens + 31) / 32) {
+  switch (attention_form(p.tokens, p.pairs, D, p.bias != nullptr)) {
+    case kAttnSplit: {
+      const dim3 grid(p.pairs, (unsigned)ceil_div(p.tokens, 32));
+      if (p.bias)
+        attention_split_kernel<D, true><<<grid, 64 * kSplitWaves, 0, st>>>(p);
+      else
+        attention_split_kernel<D, false><<<grid, 64 * kSplitWaves, 0, st>>>(p);
+      return launch_status();
+    }
     // 256 threads per workgroup for short sequences
     case 1: return launch_attention<1, 1, D, 4, false>(p, st);
     case 2: return launch_attention<2, 2, D, 2, false>(p, st);
@@ -915,7 +913,13 @@ cwac_status launch_attention_d(const AttnParams &p, hipStream_t st) {
     case 5: return launch_attention<5, 5, D, 1, false>(p, st);
     case 6: return launch_attention<6, 6, D, 1, false>(p, st);
     case 7: return launch_attention<7, 7, D, 1, false>(p, st);
-    default: return launch_attention<4, 4, D, 1, true>(p, st);
+    case kAttnChunks: return launch_attention<4, 4, D, 1, true>(p, st);
+    default: {  // kAttnChunksWide: without a bias
+      constexpr int NW = attention_wide_waves(D);
+      const dim3 grid(p.pairs, (unsigned)ceil_div(p.tokens, 32 * NW));
+      attention_int8_kernel<4, NW, D, 1, false, true><<<grid, 64 * NW, 0, st>>>(p);
+      return launch_status();
+    }
   }
 }
 

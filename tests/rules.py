@@ -8,6 +8,7 @@ _ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 _CSRC = os.path.join(_ROOT, "paper_2505_20932_amd", "csrc")
 
 _SHIM = r"""
+#include "attention_rules.h"
 #include "fast_rules.h"
 #include "splitk_rules.h"
 #include "w4_rules.h"
@@ -26,6 +27,7 @@ extern "C" void split_shape(int tile, int *out) {
   const SplitkTile &t = kSplitk[tile];
   out[0] = t.tn, out[1] = t.tm, out[2] = t.w, out[3] = t.d;
 }
+extern "C" int attention(int tokens, long long pairs, int head_dim, int bias) { return attention_form(tokens, pairs, head_dim, bias); }
 extern "C" int w4_tiles() { return kW4StreamTiles; }
 extern "C" void w4_shape(int tile, int *out) {
   const W4StreamTile &t = kW4Stream[tile];
@@ -65,6 +67,14 @@ def w4_tile16(m, n, k):
 def fast_shape(m, n, k, out_bytes):
     """CWAC_SHAPE_* the direct-to-LDS kernel picks for a linear layer of at least 256 channels."""
     return lib().fast_shape(m, n, k, out_bytes)
+
+
+ATTN_SPLIT, ATTN_CHUNKS, ATTN_CHUNKS_WIDE = 0, 8, 9
+
+
+def attention_form(batch, heads, tokens, head_dim, bias):
+    """ATTN_*, or 1 .. 7: the number of key tiles that a workgroup holds."""
+    return lib().attention(tokens, C.c_longlong(batch * heads), head_dim, bool(bias))
 
 
 def split_tile(m, n, k):

@@ -131,3 +131,26 @@ def test_gpu_shapes_reach_both_tile_widths_of_a_decoding_step():
     # a wavefront's share of the groups exceeds its two slots by a round at least, in shares of two lengths
     assert any(min(shares(k // 128, 8)) >= 3 and len(shares(k // 128, 8)) == 2 and m > 8 for m, n, k in TILES16)
     assert any(min(shares(k // 128, 8)) >= 2 and len(shares(k // 128, 8)) == 2 and m <= 8 for m, n, k in TILES16)
+
+
+# microseconds per call of a replayed graph: blocks of 128 queries, wide blocks
+@pytest.mark.parametrize("batch,heads,tokens,head_dim,narrow,wide",
+                         [(8, 12, 257, 64, 11.9, 10.9), (8, 12, 289, 64, 13.0, 11.8), (8, 12, 400, 64, 16.6, 14.3), (4, 12, 785, 64, 26.1, 22.5),
+                          (4, 12, 1025, 64, 33.1, 28.7), (1, 12, 4096, 64, 110.1, 94.5), (8, 12, 1025, 64, 58.2, 53.5),
+                          (8, 12, 577, 64, 21.1, 32.2), (8, 12, 785, 64, 36.1, 42.2), (32, 12, 400, 64, 39.8, 40.7), (128, 12, 257, 64, 78.7, 103.4),
+                          (3, 12, 257, 64, 8.5, 10.1), (2, 12, 1025, 64, 22.6, 27.6), (32, 16, 400, 32, 39.0, 32.9), (1, 16, 4096, 32, 76.4, 67.9),
+                          (32, 16, 785, 32, 120.9, 97.0), (128, 16, 400, 32, 141.4, 118.4), (128, 16, 257, 32, 73.0, 71.8),
+                          (8, 16, 577, 32, 20.0, 20.2), (32, 16, 257, 32, 21.7, 22.6)])
+def test_long_attention_takes_the_query_blocks_that_measured_faster(batch, heads, tokens, head_dim, narrow, wide):
+    want = rules.ATTN_CHUNKS_WIDE if wide < narrow else rules.ATTN_CHUNKS
+    assert rules.attention_form(batch, heads, tokens, head_dim, False) == want
+    assert rules.attention_form(batch, heads, tokens, head_dim, True) == rules.ATTN_CHUNKS
+
+
+# ... a workgroup per head (or 128 queries), the keys split over a workgroup's wavefronts
+@pytest.mark.parametrize("batch,heads,tokens,head_dim,bias,whole,split",
+                         [(3, 12, 197, 64, False, 7.6, 5.9), (8, 3, 257, 64, False, 8.4, 7.1), (1, 12, 577, 64, False, 13.4, 10.0),
+                          (1, 12, 144, 64, False, 5.9, 5.3), (1, 12, 128, 64, False, 4.6, 4.9), (1, 16, 257, 64, True, 10.2, 7.7),
+                          (1, 16, 144, 32, True, 6.0, 4.8)])
+def test_attention_of_few_heads_takes_the_form_that_measured_faster(batch, heads, tokens, head_dim, bias, whole, split):
+    assert (rules.attention_form(batch, heads, tokens, head_dim, bias) == rules.ATTN_SPLIT) == (split < whole)

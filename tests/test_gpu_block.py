@@ -385,6 +385,24 @@ def test_attention_row_subset_of_a_batch_matches_single_image():
     np.testing.assert_array_equal(a3[tokens:2 * tokens], a1)
 
 
+@pytest.mark.parametrize("batch,heads,tokens,head_dim", [(8, 12, 257, 64), (8, 12, 400, 64), (3, 12, 1025, 64), (4, 16, 577, 32),
+                                                         (8, 16, 257, 32), (35, 16, 385, 32), (29, 16, 225, 32), (8, 16, 449, 32)])
+def test_attention_in_wide_query_blocks_has_the_same_bits(batch, heads, tokens, head_dim):
+    """Blocks of 224 or 256 queries, ragged and whole, against two of the images alone (blocks of 128, or split keys)."""
+    print(f"attention in wide blocks {batch} x {tokens} tokens x {heads} heads of {head_dim}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(tokens)
+    c = heads * head_dim
+    r = (torch.randn(batch * tokens, 3 * c, device=DEV, generator=g) * 30 - 6).round().clamp(-128, 127).to(torch.int8)
+    def run(first, n):
+        a = torch.full((n * tokens + 1, c), 99, dtype=torch.int8, device=DEV)
+        P.vit_attention_int8(r[first * tokens:(first + n) * tokens], 0.04, -6, n, tokens, heads, 0.02, 3, a[:-1], head_dim=head_dim)
+        assert (a[-1] == 99).all()
+        return a[:-1]
+    together = run(0, batch)
+    for first in range(0, batch - 1, 2):
+        assert torch.equal(run(first, 2), together[first * tokens:(first + 2) * tokens]), first
+
+
 @pytest.mark.parametrize("tokens", [97, 112, 128, 144, 176, 197, 224, 225, 257, 273, 300, 577, 1000])
 @pytest.mark.parametrize("head_dim", [64, 32])
 @pytest.mark.parametrize("with_bias", [False, True])
