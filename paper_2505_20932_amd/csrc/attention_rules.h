@@ -19,7 +19,7 @@ inline int attention_form(int tokens, int64_t pairs, int head_dim, bool bias) {
   const int tiles = (tokens + 31) / 32;
   // The keys split over a workgroup's wavefronts while there is at most one such workgroup to a compute unit - its LDS leaves
   // room for one (us, a workgroup per head or 128 queries / split: 3 x 12 x 197 tokens, 252 of them, 7.6 / 5.9; 8 x 3 x 257, 216,
-  // 8.4 / 7.1; 12 x 577, 228, 13.4 / 10.0) - and more than four key tiles (12 x 144, five: 5.9 / 5.3; 12 x 128, four: 4.6 / 4.9).
+  // 8.4 / 6.8; 12 x 577, 228, 13.4 / 9.2) - and more than four key tiles (12 x 144, five: 5.9 / 5.3; 12 x 128, four: 4.6 / 4.9).
   if (tiles > 4 && pairs * tiles <= 256) return kAttnSplit;
   if (tiles <= 7) return tiles;
   // Every workgroup reads and converts all keys of its head, so one wide block beats two blocks of 128 on the same compute unit;

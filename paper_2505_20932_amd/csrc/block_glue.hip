@@ -720,21 +720,23 @@ __global__ __launch_bounds__(64 * NW * G, D == 64 && BIAS ? 2 : (CHUNKS || (BIAS
   }
 }
 
-// Few heads (an image or two): a workgroup per (image, head, block of 32 queries) whose eight wavefronts split the keys.  What
-// takes the time there is the chain of one wavefront through all key tiles on a few compute units; here a wavefront
-// takes tiles wave, wave + 8, ... - one at 197 tokens - with K and V of a tile in its own slice of LDS.  The result is
+// Few heads (an image or two): a workgroup per (image, head, block of 32 queries) whose wavefronts split the keys.  What
+// takes the time there is the chain of one wavefront through all key tiles on a few compute units; here wavefronts 0 .. 7
+// take tiles wave, wave + 8, ... - one at 197 tokens - with K and V of a tile in their own slices of LDS.  The result is
 // that of the kernel above bit for bit, so that an image's codes do not depend on how many images are with it:
 // the tiles' maxima are exchanged, every weight refers to the running maximum of its pair of tiles as there, and the weights
 // go through LDS to one wavefront per 32 channels, which adds the second products up in the order of the keys,
-// and to one that adds up the weights.
-// us per call of a replayed graph, the kernel above / this: one image of 12 heads and 197 tokens 7.5 / 5.6, of 577 tokens
-// 13.4 / 10.0, of 16 heads and 257 tokens with a bias 10.2 / 7.7, windows of 16 heads of 32 and 144 tokens with a bias 6.0 / 4.8.  Eight
-// partial results merged at the end, which another number of images does not reproduce: 5.4, 9.1, 6.8, 4.7.  With the chains'
-// operands read tile by tile: 6.1, 10.9, 7.9, 5.0.
+// and to one that adds up the weights.  These three hold a round's operands in registers, so that their chains run under
+// the scores of the next round.
+// us per call of a replayed graph, the kernel above / eight partial results merged at the end, which another number of images
+// does not reproduce / this: one image of 12 heads and 197 tokens 7.5 / 5.4 / 5.7, of 577 tokens 13.4 / 9.0 / 9.2, of 16 heads
+// and 257 tokens with a bias 10.2 / 6.9 / 7.3, windows of 16 heads of 32 and 144 tokens with a bias 6.0 / 4.7 / 4.8.  With the chains on
+// wavefronts 0 to 2: 5.6, 10.0, 7.7, 4.8; with their operands read tile by tile, too: 6.1, 10.9, 7.9, 5.0.
 constexpr int kSplitWaves = 8;
+constexpr int split_threads(int d) { return 64 * (kSplitWaves + d / 32 + 1); }
 template <int D, bool BIAS>
-__global__ __launch_bounds__(64 * kSplitWaves) void attention_split_kernel(const AttnParams p) {
-  constexpr int NW = kSplitWaves, VS = v_stride(1);
+__global__ __launch_bounds__(split_threads(D)) void attention_split_kernel(const AttnParams p) {
+  constexpr int NW = kSplitWaves, NO = D / 32, VS = v_stride(1);
   constexpr int KB = 32 * k_stride(D) > 4096 ? 32 * k_stride(D) : 4096;  // K of a tile, then its weights as summands
   constexpr int SLICE = KB + D * VS;
   __shared__ __attribute__((aligned(16))) int8_t s_mem[NW * SLICE];
@@ -742,99 +744,126 @@ __global__ __launch_bounds__(64 * kSplitWaves) void attention_split_kernel(const
   __shared__ float s_max[NW][32], s_sum[32];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int l32 = lane & 31, half = lane >> 5;
-  int8_t *s_k = s_mem + wave * SLICE, *s_v = s_k + KB;
   const uint32_t pair = blockIdx.x, image = pair / (uint32_t)p.heads;
   const int head = (int)(pair - image * p.heads);
   const int64_t row0 = (int64_t)image * p.tokens;
   const int c = p.heads * D;
-  const int8_t *qbase = p.r + row0 * p.ld + head * D;
-  const _Float16 zb = (_Float16)(float)(1152 + p.z);
-  const h2 zbias = {zb, zb};
   const int q = (int)blockIdx.y * 32 + l32, qrow = q < p.tokens ? q : p.tokens - 1;
-  const uint16_t *bias_row = BIAS ? p.bias + ((int64_t)head * p.tokens + qrow) * p.ldb : nullptr;
-  const int tiles = (p.tokens + 31) / 32;
-  AttnFill<1, 1, D> fill;
-  AttnBias bias;
-  if (wave < tiles) {
-    fill.load(qbase, p.ld, c, 32 * wave, p.tokens, lane);
-    if (BIAS) bias.load(bias_row, 32 * wave, p.tokens, half);
-  }
-  uint2 qraw[D / 16];
-  h8 fq[D / 16];
-#pragma unroll
-  for (int s = 0; s < D / 16; ++s)
-    qraw[s] = *reinterpret_cast<const uint2 *>(qbase + (uint32_t)(qrow * (int)p.ld + 16 * s + 8 * half));
-#pragma unroll
-  for (int s = 0; s < D / 16; ++s) fq[s] = codes_to_h8(qraw[s], zbias);
+  const int tiles = (p.tokens + 31) / 32, rounds = (tiles + NW - 1) / NW;
   const float lscale = p.s * p.s * (D == 64 ? 0.125f : 0.17677669529663687f) * 1.44269504088896340736f;
   const float dscale = BIAS ? 1.0f : lscale;
-  float run = 0.0f, prev = 0.0f;  // running maximum; exponent offset that the sums refer to
-  float sum = 0.0f;               // wavefront D / 32
-  v16f oc;                        // wavefronts below: 32 channels each
-#pragma unroll
-  for (int i = 0; i < 16; ++i) oc[i] = 0.0f;
-  const int rounds = (tiles + NW - 1) / NW;
-  for (int i = 0; i < rounds; ++i) {  // uniform over the workgroup
-    const int tile = wave + NW * i;
-    const bool mine = tile < tiles;
-    v16f sc[1];
-    float tmax = -1e30f;
-    if (mine) {
-      fill.store(s_k, s_v, zbias, lane);
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      const AttnBias now = bias;
-      if (tile + NW < tiles) {
-        fill.load(qbase, p.ld, c, 32 * (tile + NW), p.tokens, lane);
-        if (BIAS) bias.load(bias_row, 32 * (tile + NW), p.tokens, half);
-      }
-      tmax = attention_scores<1, D, BIAS, false>(0, s_k, fq, now, p.tokens - 32 * tile, lscale, l32, half, sc);
-    }
-    if (half == 0) s_max[wave][l32] = tmax;
-    __syncthreads();
-    float eoff[NW / 2], mine_off = 0.0f;  // of the round's pairs of tiles, and of this wavefront's
+  float run = 0.0f;  // running maximum
+  // exponent offsets of the four pairs of tiles of round i, from the tiles' maxima
+  auto offsets = [&](int i, float(&eoff)[NW / 2]) {
 #pragma unroll
     for (int g = 0; g < NW / 2; ++g) {
       const float gmx = fmaxf(s_max[2 * g][l32], s_max[2 * g + 1][l32]);
       run = i == 0 && g == 0 ? gmx : fmaxf(run, gmx);
       eoff[g] = __builtin_fmaf(-run, dscale, 10.0f);
-      if (wave >> 1 == g) mine_off = eoff[g];
     }
-    if (mine) {
-      v4f *s_w = reinterpret_cast<v4f *>(s_k) + lane;  // K of the tile has been read
+  };
+
+  // Three barriers to a round: the maxima (and V) are there; the weights are there; both are read.
+  if (wave < NW) {  // ---- scores and weights of a tile
+    int8_t *s_k = s_mem + wave * SLICE, *s_v = s_k + KB;
+    const int8_t *qbase = p.r + row0 * p.ld + head * D;
+    const _Float16 zb = (_Float16)(float)(1152 + p.z);
+    const h2 zbias = {zb, zb};
+    const uint16_t *bias_row = BIAS ? p.bias + ((int64_t)head * p.tokens + qrow) * p.ldb : nullptr;
+    AttnFill<1, 1, D> fill;
+    AttnBias bias;
+    if (wave < tiles) {
+      fill.load(qbase, p.ld, c, 32 * wave, p.tokens, lane);
+      if (BIAS) bias.load(bias_row, 32 * wave, p.tokens, half);
+    }
+    uint2 qraw[D / 16];
+    h8 fq[D / 16];
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        h8 fp;
-        float w[8];
+    for (int s = 0; s < D / 16; ++s)
+      qraw[s] = *reinterpret_cast<const uint2 *>(qbase + (uint32_t)(qrow * (int)p.ld + 16 * s + 8 * half));
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float x = sc[0][8 * u + e];
-          w[e] = __builtin_amdgcn_exp2f(BIAS ? x + mine_off : __builtin_fmaf(x, lscale, mine_off));
-          fp[e] = (_Float16)w[e];
+    for (int s = 0; s < D / 16; ++s) fq[s] = codes_to_h8(qraw[s], zbias);
+    for (int i = 0; i < rounds; ++i) {
+      const int tile = wave + NW * i;
+      const bool mine = tile < tiles;
+      v16f sc[1];
+      float tmax = -1e30f;
+      if (mine) {
+        fill.store(s_k, s_v, zbias, lane);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const AttnBias now = bias;
+        if (tile + NW < tiles) {
+          fill.load(qbase, p.ld, c, 32 * (tile + NW), p.tokens, lane);
+          if (BIAS) bias.load(bias_row, 32 * (tile + NW), p.tokens, half);
         }
-        s_p[wave][u][lane] = fp;
-        s_w[(2 * u) * 64] = v4f{w[0], w[1], w[2], w[3]};
-        s_w[(2 * u + 1) * 64] = v4f{w[4], w[5], w[6], w[7]};
+        tmax = attention_scores<1, D, BIAS, false>(0, s_k, fq, now, p.tokens - 32 * tile, lscale, l32, half, sc);
       }
+      if (half == 0) s_max[wave][l32] = tmax;
+      __syncthreads();
+      float eoff[NW / 2], off = 0.0f;
+      offsets(i, eoff);
+#pragma unroll
+      for (int g = 0; g < NW / 2; ++g)
+        if (wave >> 1 == g) off = eoff[g];
+      if (mine) {
+        v4f *s_w = reinterpret_cast<v4f *>(s_k) + lane;  // K of the tile has been read
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          h8 fp;
+          float w[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const float x = sc[0][8 * u + e];
+            w[e] = __builtin_amdgcn_exp2f(BIAS ? x + off : __builtin_fmaf(x, lscale, off));
+            fp[e] = (_Float16)w[e];
+          }
+          s_p[wave][u][lane] = fp;
+          s_w[(2 * u) * 64] = v4f{w[0], w[1], w[2], w[3]};
+          s_w[(2 * u + 1) * 64] = v4f{w[4], w[5], w[6], w[7]};
+        }
+      }
+      __syncthreads();
+      if (i + 1 < rounds) __syncthreads();
     }
     __syncthreads();
-    // The chains through the round's tiles, everything they need read first.  Tiles beyond the last are read (whatever is
-    // there) and left out.
-    const int here = tiles - NW * i < NW ? tiles - NW * i : NW;
-    if (wave < D / 32) {
+    return;
+  }
+
+  // ---- the chains through the tiles, everything that a round needs in registers first (asm: the compiler would move each
+  // load down to its use).  Tiles beyond the last are read, whatever is there, and left out.
+  float prev = 0.0f;  // exponent offset that the sums refer to
+  if (wave < NW + NO) {
+    const int a = wave - NW;
+    v16f oc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) oc[r] = 0.0f;
+    for (int i = 0; i < rounds; ++i) {
+      const int here = tiles - NW * i < NW ? tiles - NW * i : NW;
+      float eoff[NW / 2];
       h8 fv[NW][2], fp[NW][2];
+      __syncthreads();
+      offsets(i, eoff);
 #pragma unroll
       for (int t = 0; t < NW; ++t)
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          fv[t][u] = *reinterpret_cast<const h8 *>(s_mem + t * SLICE + KB + (32 * wave + l32) * VS + (16 * u + 8 * half) * 2);
-          fp[t][u] = s_p[t][u][lane];
-        }
+        for (int u = 0; u < 2; ++u)
+          fv[t][u] = *reinterpret_cast<const h8 *>(s_mem + t * SLICE + KB + (32 * a + l32) * VS + (16 * u + 8 * half) * 2);
 #pragma unroll
-      for (int t = 0; t < NW; ++t)  // (in registers here: the compiler would move each load down to its use)
+      for (int t = 0; t < NW; ++t)
 #pragma unroll
-        for (int u = 0; u < 2; ++u) asm volatile("" : "+v"(fv[t][u]), "+v"(fp[t][u]));
+        for (int u = 0; u < 2; ++u) asm volatile("" : "+v"(fv[t][u]));
+      __syncthreads();
+#pragma unroll
+      for (int t = 0; t < NW; ++t)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) fp[t][u] = s_p[t][u][lane];
+#pragma unroll
+      for (int t = 0; t < NW; ++t)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) asm volatile("" : "+v"(fp[t][u]));
+      if (i + 1 < rounds) __syncthreads();
 #pragma unroll
       for (int t = 0; t < NW; ++t) {
         if (t >= here) break;
@@ -849,8 +878,18 @@ __global__ __launch_bounds__(64 * kSplitWaves) void attention_split_kernel(const
 #pragma unroll
         for (int u = 0; u < 2; ++u) oc = __builtin_amdgcn_mfma_f32_32x32x16_f16(fv[t][u], fp[t][u], oc, 0, 0, 0);
       }
-    } else if (wave == D / 32) {
+    }
+    __syncthreads();
+    attention_store_tile(p, s_sum[l32], oc, p.a + (row0 + qrow) * p.lda + head * D + 32 * a, half, q < p.tokens);
+  } else {
+    float sum = 0.0f;
+    for (int i = 0; i < rounds; ++i) {
+      const int here = tiles - NW * i < NW ? tiles - NW * i : NW;
+      float eoff[NW / 2];
       v4f w[NW][4];
+      __syncthreads();
+      offsets(i, eoff);
+      __syncthreads();
 #pragma unroll
       for (int t = 0; t < NW; ++t)
 #pragma unroll
@@ -859,6 +898,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) void attention_split_kernel(const
       for (int t = 0; t < NW; ++t)
 #pragma unroll
         for (int g = 0; g < 4; ++g) asm volatile("" : "+v"(w[t][g]));
+      if (i + 1 < rounds) __syncthreads();
 #pragma unroll
       for (int t = 0; t < NW; ++t) {
         if (t >= here) break;
@@ -873,15 +913,10 @@ __global__ __launch_bounds__(64 * kSplitWaves) void attention_split_kernel(const
           for (int r = 0; r < 4; ++r) sum += w[t][g][r];
       }
     }
-    if (i + 1 < rounds) __syncthreads();  // the slices are read
-  }
-  if (wave == D / 32) {
     sum += __shfl_xor(sum, 32, 64);
     if (half == 0) s_sum[l32] = sum;
+    __syncthreads();
   }
-  __syncthreads();
-  if (wave < D / 32)
-    attention_store_tile(p, s_sum[l32], oc, p.a + (row0 + qrow) * p.lda + head * D + 32 * wave, half, q < p.tokens);
 }
 
 template <int NT, int NW, int D, int G, bool CHUNKS>
@@ -900,9 +935,9 @@ cwac_status launch_attention_d(const AttnParams &p, hipStream_t st) {
     case kAttnSplit: {
       const dim3 grid(p.pairs, (unsigned)ceil_div(p.tokens, 32));
       if (p.bias)
-        attention_split_kernel<D, true><<<grid, 64 * kSplitWaves, 0, st>>>(p);
+        attention_split_kernel<D, true><<<grid, split_threads(D), 0, st>>>(p);
       else
-        attention_split_kernel<D, false><<<grid, 64 * kSplitWaves, 0, st>>>(p);
+        attention_split_kernel<D, false><<<grid, split_threads(D), 0, st>>>(p);
       return launch_status();
     }
     // 256 threads per workgroup for short sequences
