@@ -5,6 +5,7 @@
 #include <math.h>
 
 #include "cwac_internal.h"
+#include "quantize_rules.h"
 
 namespace cwac {
 namespace {
@@ -455,10 +456,21 @@ extern "C" cwac_status cwac_quantize_rows_sym_bits(const float *x, int64_t ldx, 
                   aligned(q, 4);
   const float qmax = (float)((1 << (bits - 1)) - 1);
   hipStream_t st = as_stream(stream);
-  if (vec && k <= 16384 && (k <= 4096 || rows <= (1 << 21)))  // a grid counts fewer than 2^32 threads
-    return launch_rows_reg(x, ldx, (int)rows, k, qmax, scale, q, ldq, st);
-  quantize_rows_sym_kernel<<<(unsigned)rows, kThreads, 0, st>>>(x, ldx, k, vec, qmax, scale, q, ldq);
-  return launch_status();
+  const int64_t most = quantize_rows_per_launch(k, vec);
+  for (int64_t row = 0; row < rows; row += most) {
+    const int n = (int)(rows - row < most ? rows - row : most);
+    const float *xr = x + row * ldx;
+    int8_t *qr = q + row * ldq;
+    cwac_status status;
+    if (vec && k <= 16384) {
+      status = launch_rows_reg(xr, ldx, n, k, qmax, scale + row, qr, ldq, st);
+    } else {
+      quantize_rows_sym_kernel<<<(unsigned)n, kThreads, 0, st>>>(xr, ldx, k, vec, qmax, scale + row, qr, ldq);
+      status = launch_status();
+    }
+    if (status != CWAC_OK) return status;
+  }
+  return CWAC_OK;
 }
 
 extern "C" cwac_status cwac_quantize_rows_sym(const float *x, int64_t ldx, int64_t rows,

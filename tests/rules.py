@@ -10,6 +10,7 @@ _CSRC = os.path.join(_ROOT, "paper_2505_20932_amd", "csrc")
 _SHIM = r"""
 #include "attention_rules.h"
 #include "fast_rules.h"
+#include "quantize_rules.h"
 #include "splitk_rules.h"
 #include "w4_rules.h"
 using namespace cwac;
@@ -28,6 +29,8 @@ extern "C" void split_shape(int tile, int *out) {
   out[0] = t.tn, out[1] = t.tm, out[2] = t.w, out[3] = t.d;
 }
 extern "C" int attention(int tokens, long long pairs, int head_dim, int bias) { return attention_form(tokens, pairs, head_dim, bias); }
+extern "C" int row_threads(int k, int vec) { return quantize_row_threads(k, vec); }
+extern "C" long long rows_per_launch(int k, int vec) { return quantize_rows_per_launch(k, vec); }
 extern "C" int w4_tiles() { return kW4StreamTiles; }
 extern "C" void w4_shape(int tile, int *out) {
   const W4StreamTile &t = kW4Stream[tile];
@@ -75,6 +78,12 @@ ATTN_SPLIT, ATTN_CHUNKS, ATTN_CHUNKS_WIDE = 0, 8, 9
 def attention_form(batch, heads, tokens, head_dim, bias):
     """ATTN_*, or 1 .. 7: the number of key tiles that a workgroup holds."""
     return lib().attention(tokens, C.c_longlong(batch * heads), head_dim, bool(bias))
+
+
+def quantize_grid(k, vec):
+    """(rows of one launch of the row quantizer, threads per row)."""
+    lib().rows_per_launch.restype = C.c_longlong
+    return lib().rows_per_launch(k, vec), lib().row_threads(k, vec)
 
 
 def split_tile(m, n, k):

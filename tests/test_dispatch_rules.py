@@ -154,3 +154,10 @@ def test_long_attention_takes_the_query_blocks_that_measured_faster(batch, heads
                           (1, 16, 144, 32, True, 6.0, 4.8)])
 def test_attention_of_few_heads_takes_the_form_that_measured_faster(batch, heads, tokens, head_dim, bias, whole, split):
     assert (rules.attention_form(batch, heads, tokens, head_dim, bias) == rules.ATTN_SPLIT) == (split < whole)
+
+
+def test_row_quantizer_launches_fewer_than_2_to_the_32_threads():
+    for k in (1, 3, 4, 256, 512, 516, 1024, 1028, 4096, 4100, 16384, 16388, 100000):
+        for vec in (0, 1):
+            rows, threads = rules.quantize_grid(k, vec)
+            assert rows > 0 and (rows + 3) * threads < 2 ** 32, (k, vec)

@@ -121,3 +121,21 @@ def test_row_quantizer_special_rows():
     wq, ws = rows_want(x)
     np.testing.assert_array_equal(s, ws)
     np.testing.assert_array_equal(q, wq)
+
+
+@pytest.mark.parametrize("m,k,edge", [(2 ** 25 + 5, 4, 2 ** 25), (2 ** 23 + 3, 1, 2 ** 23), (2 ** 24 + 2, 3, 2 ** 24)])
+def test_row_quantizer_of_more_rows_than_one_launch_holds(m, k, edge):
+    """Rows around the end of a launch, the first and the last, against Eq. 1; and every scale."""
+    print(f"row quantizer {m} x {k}", flush=True)
+    x = torch.randn(m, k, device=DEV, generator=torch.Generator(device=DEV).manual_seed(k))
+    q, s = torch.full((m + 1, k), 77, dtype=torch.int8, device=DEV), torch.full((m + 1,), -7.0, device=DEV)
+    P.cwac_quantize_rows_sym(x, s[:m], q[:m])
+    torch.cuda.synchronize()
+    assert (q[m] == 77).all() and s[m] == -7.0
+    for at in (0, edge - 600, m - 1000):
+        rows = slice(at, min(at + 1000, m))
+        wq, ws = rows_want(x[rows].cpu().numpy())
+        np.testing.assert_array_equal(q[rows].cpu().numpy(), wq)
+        np.testing.assert_array_equal(s[rows].cpu().numpy(), ws)
+    want = (x.abs().amax(1) / 127.0).clamp_min(float(TINY) * 256)  # (a row of zeros has the smallest scale)
+    assert torch.allclose(s[:m], want, rtol=1e-6, atol=0)
