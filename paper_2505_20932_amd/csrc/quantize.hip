@@ -337,8 +337,7 @@ cwac_status rows_reg(const float *x, int64_t ldx, int rows, int k, float qmax, f
 cwac_status launch_rows_reg(const float *x, int64_t ldx, int rows, int k, float qmax, float *scale, int8_t *q, int64_t ldq,
                             hipStream_t st) {
   const int vecs = (k + 255) / 256;  // per lane, were the row one wavefront's
-  // A wavefront per row to k = 1024, four to 4096, sixteen beyond.  Four instead of sixteen: 16 x 11008 3.8 us against 3.0, 4096 x
-  // 11008 35.0 against 32.4, level at 5000 x 5120; sixteen instead of four: 512 x 4096 4.3 against 3.1.
+  if (vecs <= 4 && quantize_row_threads(rows, k, true) == 256) return rows_reg<4, 1, 256>(x, ldx, rows, k, qmax, scale, q, ldq, st);
   if (vecs <= 1) return rows_reg<1, 1, 256>(x, ldx, rows, k, qmax, scale, q, ldq, st);
   if (vecs <= 2) return rows_reg<1, 2, 256>(x, ldx, rows, k, qmax, scale, q, ldq, st);
   if (vecs <= 4) return rows_reg<1, 4, 256>(x, ldx, rows, k, qmax, scale, q, ldq, st);
@@ -456,7 +455,7 @@ extern "C" cwac_status cwac_quantize_rows_sym_bits(const float *x, int64_t ldx, 
                   aligned(q, 4);
   const float qmax = (float)((1 << (bits - 1)) - 1);
   hipStream_t st = as_stream(stream);
-  const int64_t most = quantize_rows_per_launch(k, vec);
+  const int64_t most = quantize_rows_per_launch(rows, k, vec);
   for (int64_t row = 0; row < rows; row += most) {
     const int n = (int)(rows - row < most ? rows - row : most);
     const float *xr = x + row * ldx;

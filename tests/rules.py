@@ -29,8 +29,8 @@ extern "C" void split_shape(int tile, int *out) {
   out[0] = t.tn, out[1] = t.tm, out[2] = t.w, out[3] = t.d;
 }
 extern "C" int attention(int tokens, long long pairs, int head_dim, int bias) { return attention_form(tokens, pairs, head_dim, bias); }
-extern "C" int row_threads(int k, int vec) { return quantize_row_threads(k, vec); }
-extern "C" long long rows_per_launch(int k, int vec) { return quantize_rows_per_launch(k, vec); }
+extern "C" int row_threads(long long rows, int k, int vec) { return quantize_row_threads(rows, k, vec); }
+extern "C" long long rows_per_launch(long long rows, int k, int vec) { return quantize_rows_per_launch(rows, k, vec); }
 extern "C" int w4_tiles() { return kW4StreamTiles; }
 extern "C" void w4_shape(int tile, int *out) {
   const W4StreamTile &t = kW4Stream[tile];
@@ -80,10 +80,10 @@ def attention_form(batch, heads, tokens, head_dim, bias):
     return lib().attention(tokens, C.c_longlong(batch * heads), head_dim, bool(bias))
 
 
-def quantize_grid(k, vec):
+def quantize_grid(rows, k, vec):
     """(rows of one launch of the row quantizer, threads per row)."""
     lib().rows_per_launch.restype = C.c_longlong
-    return lib().rows_per_launch(k, vec), lib().row_threads(k, vec)
+    return lib().rows_per_launch(C.c_longlong(rows), k, vec), lib().row_threads(C.c_longlong(rows), k, vec)
 
 
 def split_tile(m, n, k):

@@ -159,5 +159,13 @@ def test_attention_of_few_heads_takes_the_form_that_measured_faster(batch, heads
 def test_row_quantizer_launches_fewer_than_2_to_the_32_threads():
     for k in (1, 3, 4, 256, 512, 516, 1024, 1028, 4096, 4100, 16384, 16388, 100000):
         for vec in (0, 1):
-            rows, threads = rules.quantize_grid(k, vec)
-            assert rows > 0 and (rows + 3) * threads < 2 ** 32, (k, vec)
+            for asked in (1, 511, 512, 2 ** 24, 2 ** 31 - 1):
+                rows, threads = rules.quantize_grid(asked, k, vec)
+                assert rows > 0 and (rows + 3) * threads < 2 ** 32, (asked, k, vec)
+
+
+# microseconds per call of a replayed graph: one wavefront to a row, four
+@pytest.mark.parametrize("rows,k,one,four", [(8, 1000, 3.19, 3.03), (64, 1024, 3.30, 3.11), (197, 896, 3.35, 3.16), (197, 640, 3.18, 3.15),
+                                             (512, 640, 3.24, 3.33), (1000, 1000, 3.80, 3.90), (4096, 772, 5.21, 6.73)])
+def test_row_quantizer_takes_the_wavefronts_that_measured_faster(rows, k, one, four):
+    assert (rules.quantize_grid(rows, k, 1)[1] == 256) == (four < one)

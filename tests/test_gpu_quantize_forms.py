@@ -46,7 +46,7 @@ def run_rows(x, bits=8, pad=0):
 
 @pytest.mark.parametrize("m,k,pad", [(1, 4, 0), (5, 256, 0), (7, 260, 4), (9, 512, 0), (3, 516, 8), (6, 1024, 0), (2, 1028, 0),
                                      (3, 2048, 0), (2, 2052, 4), (3, 4096, 0), (2, 4100, 0), (3, 8192, 0), (2, 8196, 4), (2, 11008, 0),
-                                     (2, 12292, 0), (2, 16384, 0), (2, 16388, 0), (3, 770, 0), (3, 768, 3)])
+                                     (2, 12292, 0), (2, 16384, 0), (2, 16388, 0), (3, 770, 0), (3, 768, 3), (511, 772, 0), (512, 516, 8), (513, 1024, 0)])
 def test_row_quantizer_every_form(m, k, pad):
     rng = np.random.default_rng(m + k + pad)
     x = (rng.standard_normal((m, k)) * np.exp(3 * rng.standard_normal((m, 1)))).astype(np.float32)
