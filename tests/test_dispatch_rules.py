@@ -41,7 +41,9 @@ def test_weight_only_mid_batch_takes_the_kernel_that_measured_faster(m, n, k, ti
                           (1310, 5600, 384, 4, 13.6, 10.4), (1863, 4064, 128, 1, 9.5, 6.8), (8031, 816, 128, 4, 12.6, 9.2),
                           (7107, 1072, 128, 1, 9.2, 6.4), (3106, 2656, 128, 1, 9.1, 8.2), (1517, 6256, 128, 4, 13.8, 11.8),
                           (12608, 2304, 384, 4, 34.5, 31.5), (25216, 1152, 512, 4, 39.9, 32.0), (12608, 2304, 768, 4, 44.7, 39.2),
-                          (50432, 2304, 768, 4, 134.9, 139.8), (25216, 1152, 1024, 4, 51.8, 46.9), (25216, 2304, 1024, 4, 87.7, 92.7),
+                          (50432, 2304, 768, 4, 134.9, 139.8), (25216, 2304, 768, 4, 76.8, 79.4), (20000, 2304, 768, 4, 62.7, 64.8),
+                          (16000, 3072, 768, 4, 65.4, 67.6), (7252, 4096, 1024, 4, 49.1, 50.6), (30000, 1024, 1024, 4, 49.4, 51.6), (20000, 1536, 384, 4, 35.9, 32.9),
+                          (7252, 4096, 512, 4, 37.9, 33.8), (25216, 1152, 1024, 4, 51.8, 46.9), (25216, 2304, 1024, 4, 87.7, 92.7),
                           (20000, 1536, 1536, 4, 61.5, 73.4), (2000, 3072, 768, 1, 13.6, 10.0), (3152, 3072, 768, 1, 14.3, 15.2), (12608, 768, 3072, 4, 39.4, 45.7)])
 def test_half_a_round_of_large_tiles_takes_the_tile_that_measured_faster(m, n, k, out_bytes, persistent, quarter):
     want = B.CWAC_SHAPE_128_128 if quarter < persistent else B.CWAC_SHAPE_256_PERSIST
