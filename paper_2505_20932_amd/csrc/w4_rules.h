@@ -64,6 +64,16 @@ inline bool w4_stream16_pays(int64_t m, int n, int k) {
 // 128-token tiles of the tiled kernel in a launch up to which it takes them (one per compute unit)
 constexpr int64_t kW4HalfTileUpTo = 256;
 
+// Pieces that the tiles of the last round are cut into (512-channel tiles of the tiled kernel, one per compute unit and round).
+// A thin last round in pieces (us, whole tiles / pieces): rest 8, 1400 x 12288 x 4096 190 / 164; rest 32, 3000 x 6144 x 2048
+// 98 / 82; rest 64, 3000 x 12288 x 4096 298 / 273; rest 96, 2048 x 11008 x 4096 189 / 174; rest 128, 2048 x 12288 x 4096 200 / 189.
+// Quarters rather than halves to 64: rest 8 164 / 169, rest 64 273 / 276; level at 68.  More than 128 tiles would need two
+// rounds of halves, 2 x 2/3 of a tile.
+inline int w4_pieces(int64_t tiles) {
+  const int64_t rest = tiles % 256;
+  return tiles <= 256 || rest == 0 || rest > 128 ? 1 : rest <= 64 ? 4 : 2;
+}
+
 // Whether the weight-streaming kernel takes the layer, with the tile above.  Up to 32 tokens always: the layer is its weight
 // stream, and a tile of the tiled kernel would compute 128 token rows for them.  Tiled -> streaming, 1 / 16 / 32 tokens:
 // 131072 x 4096 99 / 104 / 104 us -> 58 / 76 / 91, 151936 x 4096 173 / 177 / 178 -> 64 / 88 / 108.

@@ -1084,15 +1084,11 @@ cwac_status qlinear_w4a16_cwac_forward_ex(const uint16_t *x, int64_t ldx, const 
   if (w4_tile == 512 || (w4_tile == 0 && n >= 512)) {
     p.tiles_m = (int)ceil_div(m, 128);
     p.tiles_n = (int)ceil_div(n, 512);
-    const int64_t tiles = (int64_t)p.tiles_m * p.tiles_n, rest = tiles % 256;
-    // A thin last round in pieces (us, whole tiles / pieces): rest 8, 1400 x 12288 x 4096 190 / 164; rest 32, 3000 x 6144 x
-    // 2048 98 / 82; rest 64, 3000 x 12288 x 4096 298 / 273; rest 96, 2048 x 11008 x 4096 189 / 174; rest 128, 2048 x 12288 x 4096
-    // 200 / 189.  Quarters rather than halves to 64: rest 8 164 / 169, rest 64 273 / 276; level at 68.  More than 128
-    // tiles would need two rounds of halves, 2 x 2/3 of a tile.
-    if (tiles > 256 && rest > 0 && rest <= 64)
+    const int pieces = w4_pieces((int64_t)p.tiles_m * p.tiles_n);
+    if (pieces == 4)
       return out_kind == CWAC_OUT_FP16 ? launch_w4<CWAC_OUT_FP16, 4, 1, 4>(p, as_stream(stream_handle))
                                        : launch_w4<CWAC_OUT_FP32, 4, 1, 4>(p, as_stream(stream_handle));
-    if (tiles > 256 && rest > 0 && rest <= 128)
+    if (pieces == 2)
       return out_kind == CWAC_OUT_FP16 ? launch_w4<CWAC_OUT_FP16, 4, 1, 2>(p, as_stream(stream_handle))
                                        : launch_w4<CWAC_OUT_FP32, 4, 1, 2>(p, as_stream(stream_handle));
     return out_kind == CWAC_OUT_FP16 ? launch_w4<CWAC_OUT_FP16, 4, 1>(p, as_stream(stream_handle))

@@ -31,6 +31,7 @@ extern "C" void split_shape(int tile, int *out) {
 extern "C" int attention(int tokens, long long pairs, int head_dim, int bias) { return attention_form(tokens, pairs, head_dim, bias); }
 extern "C" int row_threads(long long rows, int k, int vec) { return quantize_row_threads(rows, k, vec); }
 extern "C" long long rows_per_launch(long long rows, int k, int vec) { return quantize_rows_per_launch(rows, k, vec); }
+extern "C" int w4_cut(long long tiles) { return w4_pieces(tiles); }
 extern "C" int w4_tiles() { return kW4StreamTiles; }
 extern "C" void w4_shape(int tile, int *out) {
   const W4StreamTile &t = kW4Stream[tile];
@@ -95,6 +96,11 @@ def split_shape(tile):
     out = (C.c_int * 4)()
     lib().split_shape(tile, out)
     return tuple(out)
+
+
+def w4_pieces(m, n):
+    """Pieces to a tile of the last round of 512-channel tiles (1: whole)."""
+    return lib().w4_cut(C.c_longlong(-(-m // 128) * -(-n // 512)))
 
 
 def w4_shape(tile):

@@ -1,4 +1,6 @@
 """Dispatch rules on the CPU: which kernel and tile a layer's sizes pick."""
+import ctypes as C
+
 import pytest
 
 import rules
@@ -171,3 +173,43 @@ def test_row_quantizer_launches_fewer_than_2_to_the_32_threads():
                                              (512, 640, 3.24, 3.33), (1000, 1000, 3.80, 3.90), (4096, 772, 5.21, 6.73)])
 def test_row_quantizer_takes_the_wavefronts_that_measured_faster(rows, k, one, four):
     assert (rules.quantize_grid(rows, k, 1)[1] == 256) == (four < one)
+
+
+# microseconds measured with cold weights: the last round of 512-channel tiles whole, in halves, in quarters of a tile
+@pytest.mark.parametrize("m,n,whole,halves,quarters", [(1400, 12288, 190, 169, 164), (3000, 12288, 298, 276, 273), (2048, 11008, 189, 174, 999),
+                                                       (2048, 12288, 200, 189, 999)])
+def test_weight_only_prefill_cuts_the_last_round_as_measured_fastest(m, n, whole, halves, quarters):
+    assert rules.w4_pieces(m, n) == min((whole, 1), (halves, 2), (quarters, 4))[1]
+
+
+def test_weight_only_prefill_keeps_whole_tiles_in_full_rounds():
+    assert [rules.lib().w4_cut(C.c_longlong(t)) for t in (1, 128, 255, 256, 257, 320, 321, 384, 385, 511, 512, 513)] == \
+        [1, 1, 1, 1, 4, 4, 2, 2, 1, 1, 1, 4]
+
+
+def tile_of_block(pid, tiles_m, tiles_n):
+    """The kernels' order of tiles (qlinear_common.h): a contiguous range to each of 8 dies, in bands of 8 tile rows."""
+    per, rem = divmod(tiles_m * tiles_n, 8)
+    at = pid % 8 * per + min(pid % 8, rem) + pid // 8
+    band = 8 * tiles_n
+    rows = min(tiles_m - at // band * 8, 8)
+    return at // band * 8 + at % band % rows, at % band // rows
+
+
+def test_gpu_shapes_reach_every_piece_of_the_cut_last_round():
+    """Halves and quarters; among the cut tiles the last rows' (whole, partial and empty pieces) and the last channels'."""
+    from test_gpu_w4_mid_batch import HALVES, QUARTERS
+    seen = set()
+    for pieces, shapes in ((4, QUARTERS), (2, HALVES)):
+        for m, n, k in shapes:
+            assert rules.w4_tile(m, n, k) == -1 and rules.w4_pieces(m, n) == pieces
+            tiles_m, tiles_n = -(-m // 128), -(-n // 512)
+            tiles = tiles_m * tiles_n
+            cut = [tile_of_block(i, tiles_m, tiles_n) for i in range(tiles - tiles % 256, tiles)]
+            for tm, tn in cut:
+                for piece in range(pieces):
+                    rows = m - tm * 128 - piece * (128 // pieces)
+                    seen.add((pieces, "empty" if rows <= 0 else "partial" if rows < 128 // pieces else "whole"))
+                if tn == tiles_n - 1 and n % 512:
+                    seen.add((pieces, "shifted"))
+    assert seen == {(p, what) for p in (2, 4) for what in ("whole", "partial", "empty", "shifted")}

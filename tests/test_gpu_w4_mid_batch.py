@@ -1,6 +1,6 @@
-"""GPU parity of the weight-streaming INT4 kernel: each of its tiles (channels x tokens) at its ragged edges - a last token
+"""GPU parity of the weight-only INT4 kernels: each tile of the streaming one (channels x tokens) at its ragged edges - a last token
 block of one row, an odd number of 32-channel blocks, fewer K units than wavefronts - and with K of several rounds of
-its ring, on operands whose every partial sum is exactly representable, against the oracle bit for bit."""
+its ring - and the tiled one's cut last round, on operands whose every partial sum is exactly representable, against the oracle bit for bit."""
 import numpy as np
 import pytest
 import torch
@@ -29,7 +29,13 @@ TILES16 = [(1, 256, 128), (8, 288, 896), (9, 288, 1152), (16, 320, 3200), (3, 40
 WIDE_MAIN_LOOP = [(5, 12320, 4224), (13, 4128, 4224), (8, 12320, 1024)]
 
 
-@pytest.mark.parametrize("m,n,k", SHORT + MAIN_LOOP + TILES16 + WIDE_MAIN_LOOP)
+# the tiled kernel's last round in quarters and in halves of a tile: a last tile of 20, 85 and 120 rows, whose later pieces are
+# empty or partial, and one of 10 rows; a last tile of channels that overlaps its neighbour; 8, 64, 85 and 96 tiles in the round
+QUARTERS = [(1300, 11808, 128), (1365, 11808, 256), (2500, 8192, 256)]
+HALVES = [(1290, 15392, 128), (2040, 11008, 256)]
+
+
+@pytest.mark.parametrize("m,n,k", SHORT + MAIN_LOOP + TILES16 + WIDE_MAIN_LOOP + QUARTERS + HALVES)
 def test_mid_batch_exact_operands(w4, m, n, k):  # noqa: F811
     print(f"w4a16 mid batch {m} x {n} x {k}", flush=True)
     x16, codes, scales, zeros = _exact_case(700 + m + n + k, m, n, k)
