@@ -213,3 +213,10 @@ def test_gpu_shapes_reach_every_piece_of_the_cut_last_round():
                 if tn == tiles_n - 1 and n % 512:
                     seen.add((pieces, "shifted"))
     assert seen == {(p, what) for p in (2, 4) for what in ("whole", "partial", "empty", "shifted")}
+
+
+def test_gpu_shapes_reach_every_attention_form():
+    from test_gpu_block import FORMS
+    seen = {(rules.attention_form(batch, heads, tokens, d, bias), d, bias) for batch, heads, tokens, d, bias in FORMS}
+    assert seen == {(form, d, bias) for form in range(10) for d in (64, 32) for bias in (False, True)
+                    if not (bias and form == rules.ATTN_CHUNKS_WIDE)}

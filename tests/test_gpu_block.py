@@ -207,6 +207,43 @@ def test_attention_random_codes(batch, tokens, heads):
     print(f"  pinned to one code: {pinned:.3f}, equal to the oracle's code: {(got == want).mean():.4f}", flush=True)
 
 
+# every form of the kernel that a call can take, for either head width, without and with a bias (wide blocks: without):
+# 1 to 7 key tiles to a workgroup, keys in three and in five chunks, keys split over wavefronts in one round and in three
+FORMS = [(batch, heads, tokens, d, bias) for d in (64, 32) for bias in (False, True)
+         for batch, heads, tokens in ((5, 3, 20), (6, 4, 49), (3, 2, 90), (3, 2, 113), (18, 3, 144), (15, 3, 190), (13, 3, 213),
+                                      (2, 16, 260), (1, 16, 577), (2, 3, 197), (1, 2, 577))]
+FORMS += [(8, 12, 257, 64, False), (8, 16, 257, 32, False), (1, 64, 513, 64, False), (1, 64, 385, 32, False)]
+
+
+@pytest.mark.parametrize("batch,heads,tokens,head_dim,with_bias", FORMS)
+def test_attention_every_form(batch, heads, tokens, head_dim, with_bias):
+    """Random codes, a random bias with masked entries of its own for every head, query and key."""
+    print(f"attention {batch} x {tokens} tokens x {heads} heads of {head_dim}, bias {with_bias}", flush=True)
+    rng = np.random.default_rng(batch + 10 * tokens + heads + head_dim + 7 * with_bias)
+    c = head_dim * heads
+    r = np.clip(np.rint(rng.standard_normal((batch * tokens, 3 * c)) * 30 + 4), -128, 127).astype(np.int8)
+    s, z = np.float32(0.04), 4
+    bias = bias16 = None
+    if with_bias:
+        bias16 = np.full((heads, tokens, 32 * ((tokens + 31) // 32)), 123.0, dtype=np.float16)
+        bias16[:, :, :tokens] = (rng.standard_normal((heads, tokens, tokens)) * 2).astype(np.float16)
+        masked = rng.random((heads, tokens, tokens)) < 0.05
+        masked[:, np.arange(tokens), np.arange(tokens)] = False
+        bias16[:, :, :tokens][masked] = np.float16(-100.0)
+        bias = bias16[:, :, :tokens].astype(np.float64)
+    o, mag = blk.attention_codes(r, s, z, batch, tokens, heads, bias)
+    s_a, z_a = _out_params(o)
+    full = torch.full((batch * tokens + 1, c), 99, dtype=torch.int8, device=DEV)
+    P.vit_attention_int8(_dev(r), float(s), z, batch, tokens, heads, s_a, z_a, full[:-1], head_dim=head_dim,
+                         bias=None if bias16 is None else _dev(bias16))
+    torch.cuda.synchronize()
+    assert (full[-1] == 99).all()
+    got = full[:-1].cpu().numpy()
+    want, v = blk.quantize(o, np.float32(s_a), z_a)
+    _codes_within(got, v, (2.0 ** -11 + 1024 * U32) * mag / s_a + 64 * U32 * (np.abs(v) + 128) + 1e-4)
+    assert (got == want).mean() > 0.9, float((got == want).mean())
+
+
 @pytest.mark.parametrize("batch,tokens,heads,head_dim", [(6, 49, 4, 32), (2, 197, 2, 64), (3, 64, 1, 32),
                                                          (5, 20, 3, 64), (1, 224, 1, 32)])
 def test_attention_with_logit_bias(batch, tokens, heads, head_dim):
@@ -246,8 +283,8 @@ def test_attention_with_logit_bias(batch, tokens, heads, head_dim):
     (2, 225, 2, 64, False), (1, 448, 1, 64, False), (1, 449, 2, 32, False), (2, 577, 3, 64, False),
     (1, 1000, 2, 64, True), (1, 577, 2, 32, True), (1, 300, 1, 64, True), (1, 4096, 1, 64, False)])
 def test_attention_long_sequences(batch, tokens, heads, head_dim, with_bias):
-    """More than 224 tokens: the keys pass through the workgroup in chunks and the queries split into blocks
-    of 224 - chunk counts 2 .. 19, last chunks of 1 token up to a full one, last query blocks ragged."""
+    """More than 224 tokens, few heads: 1 to 16 rounds of eight key tiles, last tiles of 1 token up to a full one,
+    last query blocks ragged."""
     print(f"attention {batch} x {tokens} tokens x {heads} heads of {head_dim}, bias {with_bias}", flush=True)
     rng = np.random.default_rng(batch * 7 + tokens + heads + head_dim)
     c = head_dim * heads
