@@ -6,11 +6,13 @@ is no fallback: a missing library or an error status raises.
 Calls go through ctypes.  The most frequent ones - quantizers and forwards, several
 per layer and token - are first offered to a small extension module
 (csrc/fast_calls.cpp) that makes the same call in a tenth of the host time; whatever
-does not fit it exactly, errors included, takes the ctypes form."""
+does not fit it exactly, errors included, takes the ctypes form.  So does everything where
+the module cannot be imported."""
 from __future__ import annotations
 
 import ctypes as C
 import os
+import warnings
 from typing import Optional
 
 import torch  # imported first so that the library binds to torch's HIP runtime
@@ -82,6 +84,23 @@ _lib = None
 _calls = None  # the extension module, bound to the library's entry points
 
 
+class _NoFastCalls:
+    """In the extension module's place where it cannot be imported: declines every call."""
+
+    def __getattr__(self, name):
+        return lambda *args: False
+
+
+def _import_fast_calls(entries):
+    try:
+        from . import _fast_calls as calls
+    except ImportError as e:  # not built, or built for another Python or torch: ctypes serves every call
+        warnings.warn(f"calls go through ctypes, which takes several microseconds more each: {e}", RuntimeWarning)
+        return _NoFastCalls()
+    calls.bind(cwac_qparams, entries, _check)
+    return calls
+
+
 def _fast_calls():
     if _calls is None:
         lib()
@@ -92,10 +111,9 @@ def lib() -> C.CDLL:
     """Loads the HIP library built in-tree (see build.py); raises if it is absent."""
     global _lib, _calls
     if _lib is None:
-        for path in (LIB_PATH, os.path.join(_PKG, "_fast_calls.so")):
-            if not os.path.exists(path):
-                raise CwacError(f"{path} is missing: build it with "
-                                "`python -m paper_2505_20932_amd.build` (no fallback path exists)")
+        if not os.path.exists(LIB_PATH):
+            raise CwacError(f"{LIB_PATH} is missing: build it with "
+                            "`python -m paper_2505_20932_amd.build` (no fallback path exists)")
         l = C.CDLL(LIB_PATH)
         vp, i64, i32, f32, f64, sz = C.c_void_p, C.c_int64, C.c_int32, C.c_float, C.c_double, C.c_size_t
         qpp = C.POINTER(cwac_qparams)
@@ -160,9 +178,7 @@ def lib() -> C.CDLL:
         for name, (res, args) in sig.items():
             fn = getattr(l, name)
             fn.restype, fn.argtypes = res, args
-        from . import _fast_calls as calls
-        calls.bind(cwac_qparams, {name: C.cast(getattr(l, name), vp).value for name in sig}, _check)
-        _lib, _calls = l, calls
+        _lib, _calls = l, _import_fast_calls({name: C.cast(getattr(l, name), vp).value for name in sig})
     return _lib
 
 

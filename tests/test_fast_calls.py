@@ -29,6 +29,22 @@ def test_what_does_not_fit_is_left_to_the_ctypes_form():
     assert B._fast_calls() is calls
 
 
+def test_without_the_extension_module_the_ctypes_form_serves_every_call(monkeypatch):
+    """Not built, or built for another Python or torch: the import fails, and the library is usable all the same."""
+    import sys
+    monkeypatch.delattr(P, "_fast_calls", raising=False)
+    monkeypatch.setitem(sys.modules, "paper_2505_20932_amd._fast_calls", None)
+    monkeypatch.setattr(B, "_lib", None)
+    monkeypatch.setattr(B, "_calls", None)
+    with pytest.warns(RuntimeWarning, match="ctypes"):
+        B.lib()
+    assert B.cwac_forward_kernel_for(197, 768, 768, 768, 768) == B.CWAC_KERNEL_SPLIT_K
+    x, q = torch.zeros(4, 32), torch.zeros(4, 32, dtype=torch.int8)
+    assert B._fast_calls().quantize_act(x, 0.1, 0, q, None) is False
+    with pytest.raises(AssertionError):                                # the ctypes form's own refusal
+        P.cwac_quantize_act(x, 0.1, 0, q)
+
+
 def layer(seed=0, m=5, n=48, k=64):
     g = torch.Generator(device=DEV).manual_seed(seed)
     x = torch.randint(-128, 128, (m, k), dtype=torch.int8, device=DEV, generator=g)
