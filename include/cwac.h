@@ -610,7 +610,9 @@ typedef struct cwac_tuning {
 
 /* Which kernel qlinear_cwac_forward(_ex) would run for these sizes and this tuning (host
  * arithmetic only; nothing is launched, no pointer is involved): CWAC_KERNEL_DIRECT_LDS,
- * CWAC_KERNEL_SPLIT_K or CWAC_KERNEL_GENERIC_64 / _128 / _256; a negative cwac_status for sizes the forward rejects. */
+ * CWAC_KERNEL_SPLIT_K or CWAC_KERNEL_GENERIC_64 / _128 / _256; a negative cwac_status for sizes the forward rejects.
+ * It answers for the plain forward.  By itself qlinear_cwac_forward_table may take another kernel where the answer is
+ * CWAC_KERNEL_GENERIC_64 (one that looks up in its epilogue); told to use that tile it does, and looks up in a second pass. */
 int32_t cwac_forward_kernel_for(int64_t m, int32_t n, int32_t k, int64_t ldx, int64_t ldw,
                                 int32_t out_kind, const cwac_tuning *tuning);
 
