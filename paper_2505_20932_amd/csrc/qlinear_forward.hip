@@ -351,17 +351,12 @@ extern "C" cwac_status qlinear_cwac_forward_table_ex(const int8_t *x_q, int64_t 
     return CWAC_E_ALIGN;
   // Where the plain forward would take the direct-to-LDS kernel, the table is applied in that kernel's
   // epilogue (layers of 256 channels and more), and likewise in the small-problem kernel's; elsewhere - and where the caller
-  // forces a register-staged tile - the forward is followed by a lookup pass in place.  That pass costs 2 to 2.5 us, so
-  // by itself a layer leaves the register-staged tiles earlier (microseconds, register-staged tile and lookup / split-K /
-  // direct-to-LDS): 394 x 1536 x 384 6.6 / 4.7 / 5.3, 197 x 5120 x 1280 11.7 / 8.8 / -, 591 x 1536 x 384 (3.6 rounds of 32 x 32
-  // tiles) 7.3 / 5.2 / 5.4, 788 x 1536 x 384 (4.7) 7.8 / 6.6 / 5.5, 592 x 2048 x 512 (4.8) 8.6 / 7.0 / 5.8.
+  // forces a register-staged tile - the forward is followed by a lookup pass in place; for that pass's sake, a layer leaves the
+  // 64 x 64 tile earlier than the plain forward does, where nobody forces a kernel (table_form).
   int choice = choose_forward(m, n, k, ldx, ldw, tune);
   if (tune.kernel == CWAC_KERNEL_AUTO && choice == CWAC_KERNEL_GENERIC_64 && fast_pitch_ok(ldx, ldw)) {
-    const int64_t t32 = tiles_of(m, n, 32, 32);
-    if (t32 > 1024 && m >= 128 && n >= kFastTile && (k % 64) == 0)
-      choice = CWAC_KERNEL_DIRECT_LDS;
-    else if (t32 <= 1536)
-      choice = CWAC_KERNEL_SPLIT_K;
+    const int form = table_form(m, n, k);
+    if (form != 0) choice = form == 2 ? CWAC_KERNEL_DIRECT_LDS : CWAC_KERNEL_SPLIT_K;
   }
   const bool fused = n >= kFastTile && choice == CWAC_KERNEL_DIRECT_LDS;
   FwdParams p = {};

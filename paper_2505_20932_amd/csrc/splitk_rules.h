@@ -48,4 +48,19 @@ inline int splitk_tile(int64_t m, int n, int k) {
   return rounds <= (most < cap ? most : cap) ? 3 : 0;
 }
 
+// A layer with a code table behind its int8 output, where the plain forward takes the 64 x 64 register-staged tile: 0 that tile and
+// a lookup pass, 1 this kernel, 2 the direct-to-LDS kernel, both of which look up in their epilogue.  The pass costs 2 to 2.5 us, so
+// such a layer leaves the tile earlier (microseconds, register-staged tile and lookup / split-K / direct-to-LDS):
+// 394 x 1536 x 384 6.6 / 4.7 / 5.3, 591 x 1536 x 384 (3.6 rounds of 32 x 32 tiles) 7.3 / 5.2 / 5.4, 788 x 1536 x 384 (4.7) 7.8 / 6.6 /
+// 5.5, 592 x 2048 x 512 (4.8) 8.6 / 7.0 / 5.8.  Four rounds, more from K = 640 to where the 128 x 128 tiles get a deep ring
+// (quarter_ring): 160 x 6656 x 768 (4.1) 10.0 / 7.6 / 8.3, 250 x 5120 x 768 (5.0) 10.1 / 8.5 / 8.3, 250 x 5120 x 1024 (5.0) 11.2 / 8.9 /
+// 9.3, 224 x 6656 x 1024 (5.7) 11.3 / 9.6 / 9.3, 197 x 5120 x 1280 (4.4) 12.2 / 9.7 / 10.8, 250 x 6144 x 1280 (6.0) 12.5 / 10.8 / 10.9,
+// 224 x 6144 x 1536 (5.3) 13.5 / 11.0 / 10.2.
+inline int table_form(int64_t m, int n, int k) {
+  const int64_t t32 = tiles_of(m, n, 32, 32);
+  const double rounds = k >= 640 && k < 1536 ? 4.0 + (double)(k - 640) / 320.0 : 4.0;
+  if ((double)t32 > 256.0 * rounds && m >= 128 && n >= 256 && (k % 64) == 0) return 2;
+  return t32 <= 1536 ? 1 : 0;
+}
+
 }  // namespace cwac

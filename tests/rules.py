@@ -24,6 +24,7 @@ extern "C" int w4_tile16(long long m, int n, int k) { return w4_stream16_pays(m,
 extern "C" int fast_shape(long long m, int n, int k, int out_bytes) { return fast_linear_shape(m, n, k, out_bytes); }
 // the small-problem kernel's tile, 0 where the tile kernels take the layer
 extern "C" int split_tile(long long m, int n, int k) { return splitk_tile(m, n, k); }
+extern "C" int table(long long m, int n, int k) { return table_form(m, n, k); }
 extern "C" void split_shape(int tile, int *out) {
   const SplitkTile &t = kSplitk[tile];
   out[0] = t.tn, out[1] = t.tm, out[2] = t.w, out[3] = t.d;
@@ -89,6 +90,11 @@ def quantize_grid(rows, k, vec):
 
 def split_tile(m, n, k):
     return lib().split_tile(m, n, k)
+
+
+def table_form(m, n, k):
+    """What a layer with a code table takes instead of the 64 x 64 tile: 0 nothing, 1 split-K, 2 direct-to-LDS."""
+    return lib().table(C.c_longlong(m), n, k)
 
 
 def split_shape(tile):

@@ -220,3 +220,12 @@ def test_gpu_shapes_reach_every_attention_form():
     seen = {(rules.attention_form(batch, heads, tokens, d, bias), d, bias) for batch, heads, tokens, d, bias in FORMS}
     assert seen == {(form, d, bias) for form in range(10) for d in (64, 32) for bias in (False, True)
                     if not (bias and form == rules.ATTN_CHUNKS_WIDE)}
+
+
+# microseconds measured with cold weights: the 64 x 64 tile kernel and a lookup pass, the split-K kernel, 128-token direct-to-LDS tiles
+@pytest.mark.parametrize("m,n,k,tile,split,lds", [(591, 1536, 384, 7.3, 5.2, 5.4), (788, 1536, 384, 7.8, 6.6, 5.5), (592, 2048, 512, 8.6, 7.0, 5.8),
+                                                  (160, 6656, 768, 10.0, 7.6, 8.3), (250, 5120, 768, 10.1, 8.5, 8.3), (250, 5120, 1024, 11.2, 8.9, 9.3),
+                                                  (224, 6656, 1024, 11.3, 9.6, 9.3), (197, 5120, 1280, 12.2, 9.7, 10.8), (250, 6144, 1280, 12.5, 10.8, 10.9),
+                                                  (224, 6144, 1536, 13.5, 11.0, 10.2), (255, 8192, 256, 8.3, 8.6, 5.7)])
+def test_a_code_table_moves_a_layer_off_the_register_staged_tile_as_measured(m, n, k, tile, split, lds):
+    assert rules.table_form(m, n, k) == min((tile, 0), (split, 1), (lds, 2))[1]

@@ -91,11 +91,12 @@ def test_conv_ring_bit_exact(orc, shape):
     np.testing.assert_array_equal(out.cpu().numpy(), orc.folded_forward(acc, off, mult, 3))
 
 
-# layers whose plain forward takes a register-staged tile: the code table in the split-K kernel (up to four rounds of 32 x 32
-# tiles, or fewer than 128 tokens), in 128 x 128 tiles (beyond; one row of tiles, two that overlap in all rows but one, ragged
+# layers whose plain forward takes a register-staged tile: the code table in the split-K kernel (four rounds of 32 x 32 tiles, for
+# some K up to six, or fewer than 128 tokens), in 128 x 128 tiles (beyond; one row of tiles, two that overlap in all rows but one, ragged
 # channels, both K steps and ring depths), and as a pass of its own (K no multiple of 64)
 @pytest.mark.parametrize("m,n,k", [(394, 1536, 384), (591, 1536, 384), (700, 1520, 384), (592, 2048, 512), (100, 11008, 48), (700, 1520, 400),
-                                   (128, 8208, 128), (129, 6672, 192), (255, 4144, 384), (128, 12288, 1536), (129, 6672, 3072)])
+                                   (128, 8208, 128), (129, 6672, 192), (255, 4144, 384), (128, 12288, 1536), (129, 6672, 3072),
+                                   (197, 5120, 1280), (131, 5120, 704), (250, 6144, 1280), (224, 6656, 1024)])
 def test_code_table_of_layers_between_the_kernels(orc, m, n, k):
     print(f"code table {m} x {n} x {k}", flush=True)
     rng = np.random.default_rng(m + n + k)
