@@ -245,9 +245,10 @@ static int choose_forward(int64_t m, int n, int k, int64_t ldx, int64_t ldw, con
   const bool split_ok = fast_pitch_ok(ldx, ldw);
   const bool split = split_ok && (tile == 64 || m <= 32) && splitk_tile(m, n, k) != 0;
   // 80 to 95 tiles of 128 x 128 still pay against the 64 x 64 register-staged one (microseconds, 64 x 64 / 128 x 128:
-  // 788 x 1536 x 512 6.6 / 6.0, 256 x 5504 x 2048 13.2 / 11.7, 640 x 2048 x 512 6.6 / 6.3; fewer are not sure to:
-  // 700 x 1536 x 512, 72: 6.5 / 5.6, but 2000 x 512 x 512, 64: 6.0 / 6.5, 450 x 2304 x 768, 72: 7.2 / 7.3)
-  if (fast_ok && n >= kFastTile && !split && (k % 128) == 0 && tiles_of(m, n, 128, 128) >= 80) fast = true;
+  // 788 x 1536 x 512 6.6 / 6.0, 256 x 5504 x 2048 13.2 / 11.7, 640 x 2048 x 512 6.6 / 6.3; 11 such layers, K = 128 to 2048: 0 to 23 %, but for
+  // int8 outputs at K = 1280, -1 to -2 %) where the rows of the output can be stored whole (1280 x 1000 x 768 int8 7.6 / 8.1); fewer are
+  // not sure to: 700 x 1536 x 512, 72: 6.5 / 5.6, but 2000 x 512 x 512, 64: 6.0 / 6.5, 450 x 2304 x 768, 72: 7.2 / 7.3
+  if (fast_ok && n >= kFastTile && !split && (k % 128) == 0 && (n % 16) == 0 && tiles_of(m, n, 128, 128) >= 80) fast = true;
   // the caller's override (results are identical)
   if (tune.kernel == CWAC_KERNEL_DIRECT_LDS) {
     fast = fast_ok;

@@ -112,7 +112,7 @@ def test_random_shapes_lie_on_both_sides_of_the_weight_streaming_kernels_limit()
                                                   (256, 3072, 768, 7.14, 5.92, 7.5), (788, 1280, 1280, 9.9, 8.2, 9.7),
                                                   (256, 5504, 2048, 13.19, 12.3, 11.73), (577, 2048, 2048, 13.2, 11.2, 11.7),
                                                   (2000, 512, 512, 6.0, 7.1, 6.5), (300, 2304, 768, 7.2, 6.0, 7.4),
-                                                  (450, 2304, 768, 7.2, 7.6, 7.3)])
+                                                  (450, 2304, 768, 7.2, 7.6, 7.3), (1280, 1000, 768, 7.62, 8.15, 8.11), (1280, 1024, 768, 7.68, 8.13, 7.55)])
 def test_layers_between_the_kernels_take_the_one_that_measured_fastest(m, n, k, tile, split, lds):
     want = min((tile, B.CWAC_KERNEL_GENERIC_64), (split, B.CWAC_KERNEL_SPLIT_K), (lds, B.CWAC_KERNEL_DIRECT_LDS))[1]
     assert B.cwac_forward_kernel_for(m, n, k, k, k) == want
