@@ -494,13 +494,13 @@ cwac_status vit_table_lookup(const int8_t *in, int64_t ld_in, const int8_t *tabl
  *   a_q    int8 [batch * tokens, c] = Q(softmax(q k^T / sqrt(d)) v; s_a, z_a) per image and head;
  *          pitch lda (lda % 16 == 0, base 16-byte aligned)
  *   1 <= tokens <= 4096 (up to 224 tokens one workgroup holds a head's keys and values; beyond, the keys
- *   pass through it in chunks of 128 with a running softmax), heads <= 64
+ *   pass through it in chunks of 128 with a running softmax; few heads of more than 128 tokens: the keys are
+ *   split over a workgroup's wavefronts), heads <= 64
  *   bias   NULL, or device binary16 [heads, tokens, ldb] added to the logits q k^T / sqrt(d) before the
  *          softmax (the relative position bias - or a mask of large negative values - of a windowed
  *          model; shared by all images); ldb % 4 == 0 and ldb >= tokens rounded up to a multiple of 32
- *          (the padding is read, not used); 8-byte aligned.  Every entry must be FINITE: mask with a
- *          large negative value such as -100, not with -inf (a query whose leading keys are all
- *          -inf would get NaN weights)
+ *          (the padding is read, not used); 8-byte aligned.  Masks: a large negative value or -inf, as
+ *          long as every query keeps a key with a finite entry; neither +inf nor NaN
  * "image" is whatever attends within itself: an image of a ViT, a window of a windowed model.
  * Scores are exact (integers in fp32 accumulators), the softmax is fp32, the weights meet the
  * values as binary16 (relative error 2^-11 per term), accumulation in fp32.  The codes of an image do not
