@@ -68,12 +68,14 @@ inline int fast_linear_shape(int64_t m, int n, int k, int out_bytes) {
   //    With 4-byte outputs and a short K loop the tile's store burst weighs as much as its K loop: there the 128 x 128
   //    tile (three workgroups per compute unit, four times as many tiles, stores spread out) finishes sooner.  fp32, two sets of
   //    54 and 110 layers from 160 to 2364 tiles, each on its own machine, persistent / 128 x 128: K = 384 and 512 1.00 to 1.25
-  //    (12608 x 2304 x 384 34.5 / 31.5, 25216 x 1152 x 512 39.9 / 32.0) but for 200 tiles (0.94 to 0.96); K = 640 to 768 to two
-  //    rounds 1.00 to 1.26 (12608 x 2304 x 768 44.7 / 39.2), beyond them from 0.96 up on the second machine (25216 x 2304 x 768,
+  //    (12608 x 2304 x 384 34.5 / 31.5, 25216 x 1152 x 512 39.9 / 32.0); K = 640 to 768 to two rounds 1.00 to 1.26 (12608 x 2304 x 768
+  //    44.7 / 39.2), beyond them from 0.96 up on the second machine (25216 x 2304 x 768,
   //    3.5 rounds: 76.8 / 79.4; 20000 x 2304 x 768, 2.8: 62.7 / 64.8); K = 1024 ahead where the last 256 channels are at most half
   //    used (25216 x 1152 51.8 / 46.9), else 0.96 to 1.00 (7252 x 4096 49.1 / 50.6, 30000 x 1024 49.4 / 51.6), beyond two rounds 0.86 to
   //    1.05; K = 1536 0.77 to 1.02.  In any case to K = 1024 where the last round leaves a good part of the chip idle (33000 x 1152 x
-  //    1024: 68.8 / 60.5).
+  //    1024: 68.8 / 60.5).  All of that but for one round of tiles whose 128 x 128 ones just miss one of their own (three to a compute
+  //    unit, 768): 12608 x 1024 x 1024, 800 of them, 24.2 / 26.1, 3152 x 4096 x 512, 832, 20.0 / 20.9, 9000 x 1536 x 384, 864, 18.9 / 19.7;
+  //    level at 4616 x 3072 x 768, 912 (ragged channels stay: 12608 x 1000 x 768, 792, 1.06).
   //  * 128 to 255 tokens: 128-token tiles, the only ones that the rows fill.
   if (fast_prefers_quarter_tile(m, n)) return CWAC_SHAPE_128_128;
   if ((k % 128) != 0) return CWAC_SHAPE_128_PAIR;
@@ -85,7 +87,9 @@ inline int fast_linear_shape(int64_t m, int n, int k, int out_bytes) {
   }
   const double fill = (double)t256 / (double)(256 * ((t256 + 255) / 256));  // busy share of the rounds
   const bool half_used = tiles_of(1, n, 1, 128) % 2 != 0;
-  if (out_bytes > 1 && k <= 1024 && (fill < 0.85 || k <= 512 || (t256 <= 512 && (k <= 768 || half_used)))) return CWAC_SHAPE_128_128;
+  const int64_t t_q = tiles_of(m, n, 128, 128);
+  const bool just_missed = t256 < 256 && (n % 128) == 0 && t_q > 768 && t_q <= 880;
+  if (out_bytes > 1 && k <= 1024 && !just_missed && (fill < 0.85 || k <= 512 || (t256 <= 512 && (k <= 768 || half_used)))) return CWAC_SHAPE_128_128;
   return CWAC_SHAPE_256_PERSIST;
 }
 

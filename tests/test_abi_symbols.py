@@ -339,7 +339,7 @@ def test_kernel_query_names_the_small_problem_kernel(lib):
         assert ask(m, n, k, k, k, tuning=tun(kernel=g64)) == g64
         assert ask(m, n, k, big, k) == ask(m, n, k, k, big) == g64                          # pitches beyond its 32-bit offsets
         assert ask(m, n, k, big, k, tuning=tun(kernel=split)) == g64                        # ... forced, too
-    assert ask(200, 11008, 4096, 4096, 4096) == g64                                         # (of the split-K kernel)
+    assert ask(200, 11008, 4096, 4096, 4096) == g64                                         # ahead of the split-K kernel
     assert ask(200, 11008, 4096, 4096, 4096, tuning=tun(kernel=split)) == split
     assert ask(16384, 4096, 4096, 4096, 4096, tuning=tun(kernel=split)) == split
     assert ask(16384, 4096, 4096, big, 4096, tuning=tun(kernel=split)) == binding.CWAC_KERNEL_GENERIC_256

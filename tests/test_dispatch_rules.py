@@ -45,7 +45,8 @@ def test_weight_only_mid_batch_takes_the_kernel_that_measured_faster(m, n, k, ti
                           (12608, 2304, 384, 4, 34.5, 31.5), (25216, 1152, 512, 4, 39.9, 32.0), (12608, 2304, 768, 4, 44.7, 39.2),
                           (50432, 2304, 768, 4, 134.9, 139.8), (25216, 2304, 768, 4, 76.8, 79.4), (20000, 2304, 768, 4, 62.7, 64.8),
                           (16000, 3072, 768, 4, 65.4, 67.6), (7252, 4096, 1024, 4, 49.1, 50.6), (30000, 1024, 1024, 4, 49.4, 51.6), (20000, 1536, 384, 4, 35.9, 32.9),
-                          (7252, 4096, 512, 4, 37.9, 33.8), (25216, 1152, 1024, 4, 51.8, 46.9), (25216, 2304, 1024, 4, 87.7, 92.7),
+                          (7252, 4096, 512, 4, 37.9, 33.8), (12608, 1024, 1024, 4, 24.2, 26.1), (3152, 4096, 512, 4, 20.0, 20.9), (9000, 1536, 384, 4, 18.9, 19.7),
+                          (5000, 2560, 896, 4, 22.8, 24.5), (9000, 1152, 512, 4, 17.9, 16.2), (12608, 1000, 768, 4, 39.5, 37.1), (3152, 3840, 640, 4, 20.0, 17.7), (25216, 1152, 1024, 4, 51.8, 46.9), (25216, 2304, 1024, 4, 87.7, 92.7),
                           (20000, 1536, 1536, 4, 61.5, 73.4), (2000, 3072, 768, 1, 13.6, 10.0), (3152, 3072, 768, 1, 14.3, 15.2), (12608, 768, 3072, 4, 39.4, 45.7)])
 def test_half_a_round_of_large_tiles_takes_the_tile_that_measured_faster(m, n, k, out_bytes, persistent, quarter):
     want = B.CWAC_SHAPE_128_128 if quarter < persistent else B.CWAC_SHAPE_256_PERSIST
