@@ -53,12 +53,14 @@ inline int w4_stream_tile(int64_t m, int n, int k) {
 
 // Whether up to 16 tokens run in tiles of 16 channels instead (w4a16_stream16_kernel).  With m x n, the channels that the fullest of
 // 256 compute units gets are what counts: fewer with 16-channel tiles up to n = 4096 (16 against 32) and from 8224 to 12288
-// (48 against 64).  Gain over the 32-channel tiles, k = 128 .. 8192: n <= 4096 11 to 56 %, 9216 .. 12288 with up to 8 tokens 0 to
-// 24 %; with up to 8 tokens and n = 4128 .. 8192, where both give 32, -3 to 22 % to k = 4096, -8 to 5 % beyond.  Wider layers
-// lose up to 33 %, and 9 to 16 tokens wider than 4096 up to 40 %: their activations are read by twice the workgroups.
+// (48 against 64).  Gain over the 32-channel tiles, k = 128 .. 8192: n <= 4096 11 to 56 %, 8224 .. 12288 with up to 8 tokens 0 to
+// 24 %; with up to 8 tokens and n = 4128 .. 8192, where both give 32, 0 to 22 % to k = 1024, -1 to 6 % at 1536 and, but for the
+// narrowest, -5 to 4 % from 2048 on (us, 32 / 16 channels: 1 x 6144 x 2048 4.57 / 4.74, 4 x 8192 x 4096 6.05 / 6.39, 8 x 4128 x 4096
+// 5.94 / 5.76).  Wider layers lose up to 33 %, and 9 to 16 tokens wider than 4096 up to 40 %: their activations are read by twice the
+// workgroups.
 inline bool w4_stream16_pays(int64_t m, int n, int k) {
   if (n <= 4096) return m <= 16;
-  return m <= 8 && n <= 12288 && (n > 8192 || k <= 4096);
+  return m <= 8 && n <= 12288 && (n > 8192 || k <= (n <= 4608 ? 4096 : 1536));
 }
 
 // 128-token tiles of the tiled kernel in a launch up to which it takes them (one per compute unit)

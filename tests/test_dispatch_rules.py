@@ -123,7 +123,9 @@ def test_layers_between_the_kernels_take_the_one_that_measured_fastest(m, n, k, 
 @pytest.mark.parametrize("m,n,k,wide,narrow", [(1, 4096, 11008, 12.0, 8.1), (16, 4096, 4096, 7.0, 5.6), (12, 256, 8192, 8.5, 5.6),
                                                (8, 12288, 4096, 11.2, 9.2), (9, 12288, 4096, 10.9, 12.4), (16, 5120, 2048, 4.7, 5.7),
                                                (8, 5120, 8192, 9.8, 10.7), (4, 6144, 512, 3.5, 3.3), (1, 24576, 1024, 5.8, 7.0),
-                                               (8, 14336, 256, 3.5, 4.3), (4, 11008, 4096, 9.8, 8.2)])
+                                               (8, 14336, 256, 3.5, 4.3), (4, 11008, 4096, 9.8, 8.2), (1, 6144, 2048, 4.57, 4.74), (4, 8192, 4096, 6.05, 6.39),
+                                               (4, 5504, 2048, 4.62, 4.71), (8, 4128, 4096, 5.94, 5.76), (1, 4608, 4096, 5.85, 5.76), (8, 8192, 1024, 4.15, 3.91),
+                                               (4, 7168, 512, 3.60, 3.36), (8, 11008, 2048, 6.11, 5.35)])
 def test_weight_only_decode_takes_the_tile_that_measured_faster(m, n, k, wide, narrow):
     assert rules.w4_tile16(m, n, k) == (narrow < wide)
 
