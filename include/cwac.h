@@ -494,8 +494,8 @@ cwac_status vit_table_lookup(const int8_t *in, int64_t ld_in, const int8_t *tabl
  *   a_q    int8 [batch * tokens, c] = Q(softmax(q k^T / sqrt(d)) v; s_a, z_a) per image and head;
  *          pitch lda (lda % 16 == 0, base 16-byte aligned)
  *   1 <= tokens <= 4096 (up to 224 tokens one workgroup holds a head's keys and values; beyond, the keys
- *   pass through it in chunks of 128 with a running softmax; few heads of more than 128 tokens: the keys are
- *   split over a workgroup's wavefronts), heads <= 64
+ *   pass through it in chunks of 128 with a running softmax; few heads and more than about 100 tokens: the
+ *   keys are split over a workgroup's wavefronts), heads <= 64
  *   bias   NULL, or device binary16 [heads, tokens, ldb] added to the logits q k^T / sqrt(d) before the
  *          softmax (the relative position bias - or a mask of large negative values - of a windowed
  *          model; shared by all images); ldb % 4 == 0 and ldb >= tokens rounded up to a multiple of 32

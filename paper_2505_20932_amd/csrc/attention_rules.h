@@ -19,8 +19,9 @@ inline int attention_form(int tokens, int64_t pairs, int head_dim, bool bias) {
   const int tiles = (tokens + 31) / 32;
   // The keys split over a workgroup's wavefronts while there is at most one such workgroup to a compute unit - its LDS leaves
   // room for one (us, a workgroup per head or 128 queries / split: 3 x 12 x 197 tokens, 252 of them, 7.6 / 5.9; 8 x 3 x 257, 216,
-  // 8.4 / 6.8; 12 x 577, 228, 13.4 / 9.2) - and more than four key tiles (12 x 144, five: 5.9 / 5.3; 12 x 128, four: 4.6 / 4.9).
-  if (tiles > 4 && pairs * tiles <= 256) return kAttnSplit;
+  // 8.4 / 6.8; 12 x 577, 228, 13.4 / 9.2) - and more than four key tiles (12 x 144, five: 5.9 / 5.3; 12 x 128, four: 4.6 / 4.8), or four
+  // of 32-wide heads with a bias (4 x 128 4.8 / 4.5, 16 x 100 4.75 / 4.67; 64-wide 16 x 112 5.3 / 5.4, 32-wide without 16 x 128 3.9 / 4.2).
+  if ((tiles > 4 || (tiles == 4 && bias && head_dim == 32)) && pairs * tiles <= 256) return kAttnSplit;
   if (tiles <= 7) return tiles;
   // Every workgroup reads and converts all keys of its head, so one wide block beats two blocks of 128 on the same compute unit;
   // but two wide ones that do not fit it together follow one another.  What counts are the query tiles that the fullest

@@ -157,8 +157,9 @@ def test_long_attention_takes_the_query_blocks_that_measured_faster(batch, heads
 # ... a workgroup per head (or 128 queries), the keys split over a workgroup's wavefronts
 @pytest.mark.parametrize("batch,heads,tokens,head_dim,bias,whole,split",
                          [(3, 12, 197, 64, False, 7.6, 5.9), (8, 3, 257, 64, False, 8.4, 6.8), (1, 12, 577, 64, False, 13.4, 9.2),
-                          (1, 12, 144, 64, False, 5.9, 5.3), (1, 12, 128, 64, False, 4.6, 4.9), (1, 16, 257, 64, True, 10.2, 7.3),
-                          (1, 16, 144, 32, True, 6.0, 4.8)])
+                          (1, 12, 144, 64, False, 5.9, 5.3), (1, 12, 128, 64, False, 4.6, 4.8), (1, 16, 257, 64, True, 10.2, 7.3),
+                          (1, 16, 144, 32, True, 6.0, 4.8), (1, 4, 128, 32, True, 4.83, 4.53), (1, 16, 100, 32, True, 4.75, 4.67),
+                          (1, 16, 112, 64, True, 5.32, 5.41), (1, 16, 128, 32, False, 3.87, 4.19)])
 def test_attention_of_few_heads_takes_the_form_that_measured_faster(batch, heads, tokens, head_dim, bias, whole, split):
     assert (rules.attention_form(batch, heads, tokens, head_dim, bias) == rules.ATTN_SPLIT) == (split < whole)
 

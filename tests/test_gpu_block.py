@@ -212,7 +212,7 @@ def test_attention_random_codes(batch, tokens, heads):
 FORMS = [(batch, heads, tokens, d, bias) for d in (64, 32) for bias in (False, True)
          for batch, heads, tokens in ((5, 3, 20), (6, 4, 49), (3, 2, 90), (3, 2, 113), (18, 3, 144), (15, 3, 190), (13, 3, 213),
                                       (2, 16, 260), (1, 16, 577), (2, 3, 197), (1, 2, 577))]
-FORMS += [(8, 12, 257, 64, False), (8, 16, 257, 32, False), (1, 64, 513, 64, False), (1, 64, 385, 32, False)]
+FORMS += [(17, 4, 113, 32, True), (8, 12, 257, 64, False), (8, 16, 257, 32, False), (1, 64, 513, 64, False), (1, 64, 385, 32, False)]
 
 
 @pytest.mark.parametrize("batch,heads,tokens,head_dim,with_bias", FORMS)
@@ -444,7 +444,7 @@ def test_attention_in_wide_query_blocks_has_the_same_bits(batch, heads, tokens, 
 @pytest.mark.parametrize("head_dim", [64, 32])
 @pytest.mark.parametrize("with_bias", [False, True])
 def test_attention_of_an_image_does_not_depend_on_the_batch(tokens, head_dim, with_bias):
-    """Few heads of more than 128 tokens have their keys split over a workgroup's wavefronts, many do not: the same bits.
+    """Few heads of more than 128 tokens (with a bias 96, of 32-wide ones) have their keys split over a workgroup's wavefronts, many do not: the same bits.
     Keys that score higher towards the end, so that the running maximum rises over and over."""
     heads = 3
     few = max(1, 256 // (heads * ((tokens + 31) // 32)))
