@@ -377,8 +377,8 @@ __global__ __launch_bounds__(256) void table_lookup_kernel(const int8_t *in, int
 // 4 keys x D / 8 channels per thread: V is transposed in registers (8-byte LDS writes instead of 2-byte ones).
 // Against one workgroup to a compute unit, 2-byte transposing writes and 224-query blocks of long sequences:
 // 128 images x 12 heads x 197 tokens 45.5 -> 38.0 us, 8 x 12 x 577 32.1 -> 20.9, 148 x 16 x 49 with a bias
-// 9.5 -> 8.5, one image 7.2 -> 6.6 (blocks of 224 or 256 queries where attention_form says so).  Chunks of 64 or 192 keys, three, five or seven wavefronts and shorter
-// chunks for 197 tokens were 5 to 150 % slower.
+// 9.5 -> 8.5, one image 7.2 -> 6.6; blocks of 224 or 256 queries where attention_form says so.  Chunks of 64 or 192 keys, three,
+// five or seven wavefronts and shorter chunks for 197 tokens were 5 to 150 % slower.
 // ------------------------------------------------------------------------------------------
 constexpr int kHeadDim = 64;     // widest head; 32 is the other width
 constexpr int kMaxTokens = 4096; // longest sequence
